@@ -6,13 +6,14 @@
 //
 // Execution model.  A chain is a strict sequence of SHA-256 compressions
 // (h_j needs h_{j-1}), so all parallelism comes from the batch.  Two kernels:
-//   * k_chains: one lane owns one request and walks its chain (a wave
-//     advances 64 chains); for batches that fill every SIMD, ordered longest
-//     first (LPT) so that the lanes of a wave carry similar block counts and
-//     long chains start early;
-//   * k_chains_lp: three waves per 64 requests, two lanes per request for
-//     the rounds and a third wave for the message schedule, which shortens
-//     every chain; for batches of at most two workgroups per CU.
+//   * k_chains_lp: four waves per 64 requests, two lanes per request for
+//     the rounds on two of them and for the message schedule on the other
+//     two, which shortens every chain; for batches of at most two workgroups
+//     per CU;
+//   * k_chains_mixed: larger batches, ordered longest first: the longest
+//     requests on lane-pair workgroups, the others on one lane each (a wave
+//     advances 64 chains), so that the lanes of a wave carry similar block
+//     counts and long chains start early.
 //
 // Per block a lane issues two compressions: (IV; h_{j-1} || T_j[0..7]) and
 // (state; T_j[8..15] || padding of a 96-byte message).  Three cases leave
@@ -43,13 +44,6 @@
 
 #include "common.h"
 #include "sha256_cdna4.h"
-
-#ifndef KVGOV_LP_COVER
-#define KVGOV_LP_COVER 2  // lane-pair kernel: steps between a barrier and its first word
-#endif
-#ifndef KVGOV_LP_GROUPS
-#define KVGOV_LP_GROUPS 16, 32, 48, 64  // lane-pair kernel: schedule group bounds
-#endif
 
 namespace kvgov {
 
@@ -577,35 +571,13 @@ __device__ __forceinline__ void single_chain(const ChainArgs &a, int32_t i) {
 }
 
 // ---------------------------------------------------------------------------
-// helpers of the lane-pair kernel
-// ---------------------------------------------------------------------------
-
-// Block count and boundary block of a request, used to keep the waves of a
-// workgroup in lockstep: every wave decides trip counts and boundary
-// iterations over all requests of the workgroup.
-struct ReqPeek {
-  int64_t nf;
-  int64_t kr;  // iteration of the boundary block, else -1
-};
-
-template <int MODE>
-__device__ __forceinline__ ReqPeek req_peek(const ChainArgs &a, int32_t i) {
-  ReqPeek p{0, -1};
-  if (i < a.n) {
-    ChainReq q;
-    const int32_t r = a.order ? a.order[i] : i;
-    if (chain_setup<MODE>(a, r, q)) p = ReqPeek{q.nf, q.kr};
-  }
-  return p;
-}
-
-// ---------------------------------------------------------------------------
 // lane-pair chain kernel
 // ---------------------------------------------------------------------------
 //
 // A chain is latency-bound: the 64 rounds of a compression are a dependency
-// chain, and with one lane per request a round costs its wave 14
-// instructions (plus 10 per schedule word).  This kernel takes the message
+// chain, and a wave alone on its SIMD issues one instruction per ~4.16
+// cycles, so what a block costs is the number of instructions its rounds
+// waves issue, plus what they wait for.  This kernel takes the message
 // schedule off the rounds lanes and splits each round over two lanes.
 // Write A_t for the word a after round t and E_t for e (so b_t = A_{t-1},
 // c_t = A_{t-2}, d_t = A_{t-3}, and likewise f, g, h from E).  A round is
@@ -625,93 +597,102 @@ __device__ __forceinline__ ReqPeek req_peek(const ChainArgs &a, int32_t i) {
 //                                                  + A_{i-3}            |
 //   x0 = S + F + Z                                 E_{i+1}              | A_{i-1}
 // with per-lane rotation amounts, m = 0 (E) or ~0 (A), and kw = K + W on E
-// lanes and 1 on A lanes (a constant column of the LDS tables).  Choose with
+// lanes and 1 on A lanes (a row of their own in the LDS tables).  Choose with
 // ~(a ^ b) as selector is Maj(a, b, c).  Z depends only on words from
 // earlier steps, so it is formed one step ahead, and the DPP read is off the
 // dependency chain (x0 -> rotates -> xor3 -> add3, and x0 -> X -> choose).
-// A compression takes 66 steps: in steps 0 and 1 the A lane has nothing to
-// compute (its x0 is then set to the initial b, then a; it starts from c, d),
-// and in steps 64 and 65 only the A lane computes (A_63, A_64).
 //
-// Workgroup: 64 requests.  Waves 0 and 1 run the rounds of 32 requests each;
-// wave 2 ("schedule", one lane per request) writes K + W of both
-// compressions to LDS tables [round][request].  Per block j, C1 = (IV;
-// h_{j-1} || T[0..7]) and C2 = (state; T[8..15] || padding):
-//   phase 1  rounds: C1 rounds 0-11      schedule: reads h_{j-1}, C1's W[16..31]
-//   phase 2  rounds: C1 rounds 12-27     schedule: C1's W[32..47]
-//   phase 3  rounds: C1 rounds 28-43     schedule: C1's W[48..63]
-//   phase 4  rounds: C1 rounds 44-63 and all of C2, then h_j to LDS and the
-//            digest; schedule: the words of block j+1 that depend on tokens
-//            only (C1 rounds 8-15, all of C2), double buffered by parity
-// with a workgroup barrier after each phase; each barrier sits four rounds
-// before the words it releases are needed, so that their LDS reads overlap
-// those rounds.  The first compression's K + W of rounds 0..7 (the words of
-// h_{j-1}) are formed by the rounds lanes from the LDS copy of h_{j-1},
-// whose constant column holds 1 - K[t], so that the A lanes' sum is 1 there
-// as well.  Iterations where some request of the workgroup has a special
-// block run on the E lanes alone (rolled compressions) while the schedule
-// wave prepares the next block.  All three waves derive trip counts and
-// special iterations from all 64 requests, so they meet the same barriers.
-
-constexpr int kLpCols = kWave + 1;  // 64 requests + the constant column
-constexpr int kLpThreads = 3 * kWave;
+// The steps of a block.  C1 = (IV; h_{j-1} || T[0..7]), C2 = (state;
+// T[8..15] || padding).
+//   * C1's round 0 has a constant state: E_1 = K_0 + W_0 + constant, so C1
+//     starts at step 1.  The A lane has nothing to compute in steps 0 and 1;
+//     its x0 is set to the initial b, then a.
+//   * The A lane finishes C1 (A_63, A_64) in steps 64 and 65, and the E lane
+//     needs nothing of it for C2's rounds 0 and 1 but words that are two
+//     steps old, so those two steps are C2's steps 0 and 1 at the same time.
+//     The feed-forward of C1 (the state's words plus IV) is added to the
+//     ring on the E lanes before step 0 and on the A lanes after step 1; what
+//     a lane's Z takes from its partner's ring (or from its own, as x3) while
+//     the two differ by that addition is made up in kw: C2's kw rows 0, 1, 2
+//     hold + IV_3 + IV_7, + IV_2, + IV_1 for the E lanes, and rows 1 and 2
+//     of the A lanes' row 1 - IV_4 and 1 - IV_3.
+//   * C2 ends with the A lane's two steps of its own (64, 65).
+// So a block is 63 + 66 steps, 129 x 9 instructions, and some 90 more (LDS
+// reads, feed-forward, the message words of the next block, the store).
+//
+// The steps are two asm statements per block, with their LDS reads, waits and
+// barriers inside: every four K + W words are one ds_read_b128 (tables
+// [request][round], the row strides 4 words past a multiple of 16 banks),
+// issued at least four steps before their first use into a ring of four quads, the quad a read
+// overwrites having just been used.  Every instruction between two such points
+// is eight bytes long or paired with another of four, from an eight-byte
+// boundary on: a wave alone on its SIMD issues an instruction every 4.0
+// cycles while the eight-byte ones lie on eight-byte boundaries and every 5.0
+// cycles where they do not (the same 64 steps in a loop, 146 against 182
+// cycles per four steps, as one four-byte s_nop is put before them), and a
+// taken branch costs it 30 to 130 cycles.  With all of that a block takes
+// 5,330 cycles, of which the steps are 4,640 and the 30 LDS reads 340 (11.5
+// each); 4096 chains of 137 to 196 blocks take 0.472 ms.  Compiled code
+// around shorter asm runs, with a wait for a whole group's reads at
+// the head of each run, two-word reads, 132 steps and about 280 other
+// instructions a block took 7,350 cycles, 0.622 ms.
+//
+// Workgroup: 64 requests, four waves.  Waves 0 and 1 run the rounds of 32
+// requests each, waves 2 and 3 the message schedule, two lanes per request:
+// C1's words 16..63 (which depend on h_{j-1}) in six groups of eight, one
+// barrier each (a group takes the schedule waves about as long as the rounds
+// waves take for eight steps, so groups of sixteen made the rounds wait:
+// 0.542 against 0.530 ms), then the tables of block j + 1 that depend on
+// tokens only.  All four waves meet seven barriers per iteration; trip
+// counts are decided over all 64 requests.  A request that has ended keeps running on what its LDS
+// rows hold and stores nothing.
+//
+// The boundary block k > 0 is a 128-byte message, three compressions: the
+// iteration of that block takes (IV; sigma || h_{k-1}) and (.; T_k), and the
+// request takes one more iteration for the padding block, as C2 from the
+// saved state (its C1 is idle).  Only that request's chain is longer by one
+// iteration, so requests of one workgroup with different boundaries do not
+// add up.  (16,384 requests of ~60 blocks with uniform boundaries: 0.258 ms
+// with a third compression, for the whole workgroup, in every iteration that
+// holds some request's boundary block, two of three; 0.169 ms now.)
 
 struct LpLds {
-  uint32_t ha[8][kLpCols];      // message words 0..7 of the first compression;
-                                // constant column: 1 - K[t]
-  uint32_t hb[8][kLpCols];      // message words 8..15; constant column: 1 - K[8 + t]
-  uint32_t c1b[48][kLpCols];    // K + W of the first compression, rounds 16..63
-  uint32_t c2[2][64][kLpCols];  // K + W of the second compression, by block parity
-  uint32_t c3[64][2];           // K + W of a 128-byte message's padding block; [.][1] = 1
+  uint32_t msg[kWave][20];        // words 0..15 of the first message (for the schedule)
+  uint32_t kwm[kWave + 2][12];    // K + words 8..15 of it; then the A lanes', and a row
+                                  // that is written and never read
+  uint32_t c1[kWave + 1][52];     // K + W of the first compression, rounds 16..63
+  uint32_t c2[2][kWave + 1][68];  // K + W of the second compression, by iteration parity
 };
-constexpr int kLpRows = 8 + 8 + 48 + 128;  // rows with a constant column
-static_assert(sizeof(LpLds) == (size_t)kLpRows * kLpCols * 4 + 64 * 2 * 4,
-              "LpLds rows are contiguous");
+static_assert(sizeof(LpLds) % 16 == 0, "LpLds rows are read 16 bytes at a time");
 
-// K + W of the padding block of a 128-byte message (constant), from the
-// schedule's definition
-struct PadSchedule {
-  uint32_t kw[64];
-};
-constexpr uint32_t c_rotr(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
-constexpr PadSchedule make_pad128_schedule() {
-  PadSchedule p{};
-  uint32_t w[64] = {};
-  w[0] = 0x80000000u;
-  w[15] = 128 * 8;
-  for (int t = 16; t < 64; ++t) {
-    const uint32_t s0 = c_rotr(w[t - 15], 7) ^ c_rotr(w[t - 15], 18) ^ (w[t - 15] >> 3);
-    const uint32_t s1 = c_rotr(w[t - 2], 17) ^ c_rotr(w[t - 2], 19) ^ (w[t - 2] >> 10);
-    w[t] = s1 + w[t - 7] + s0 + w[t - 16];
-  }
-  for (int t = 0; t < 64; ++t) p.kw[t] = kSha.K[t] + w[t];
-  return p;
-}
-__constant__ PadSchedule kPad128Dev = make_pad128_schedule();
+typedef uint32_t lp_quad __attribute__((ext_vector_type(4)));
 
 struct LpLane {
   uint32_t r1, r2, r3;  // rotation amounts of the lane's big sigma
   uint32_t m;           // 0 on E lanes, ~0 on A lanes
 };
 
+constexpr uint32_t c_rotr(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
+
+constexpr uint64_t kALanes = 0xAAAAAAAAAAAAAAAAull;  // lane mask of the A lanes
+
 // the partner lane's x (adjacent lanes swap: DPP quad_perm [1,0,3,2])
 __device__ __forceinline__ uint32_t lp_partner(uint32_t x) {
-  return __builtin_amdgcn_update_dpp(0u, x, 0xB1, 0xF, 0xF, false);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);
 }
 
-// z of a compression's step 0: (x3 ^ m) + kw_0 + the partner's x1
-__device__ __forceinline__ uint32_t lp_z0(const uint32_t s[4], uint32_t kw0, const LpLane &c) {
-  uint32_t z = (s[3] ^ c.m) + kw0;
-  asm("" : "+v"(z));  // keeps the partner term one DPP add
-  return z + lp_partner(s[1]);
+// LDS byte address of a shared object, as the ds instructions take it
+__device__ __forceinline__ uint32_t lds_addr(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
 }
 
-// One step, or two in one block.  On entry z holds this step's Z; a step
-// forms x0' and the next step's Z from kwn (the next step's x3 is this
-// step's x2, and its partner's x1 is the partner's present x0).  Written as
-// asm so that no instruction waits on the one before it, except the first
-// on the previous step's x0.  The DPP source (x0) was written at least one
-// step earlier (nine instructions), so the DPP read needs no wait states.
+// One step.  On entry Z holds this step's Z; the step forms x0' (V) and the
+// next step's Z (ZN) from KWN (the next step's x3 is this step's x2, and its
+// partner's x1 is the partner's present x0).  Ordered so that no instruction
+// waits on the one before it, except the first on the previous step's x0.
+// The DPP source (X0) was written at least eight instructions earlier, so
+// the DPP read needs no wait states.
+#define KVGOV_LP_T "%[t1]", "%[t2]", "%[t3]", "%[xx]", "%[f]", "%[sg]"
 #define KVGOV_LP_STEP(X0, X1, X2, Z, V, ZN, KWN, T1, T2, T3, XX, F, S)               \
   "v_alignbit_b32 " T1 ", " X0 ", " X0 ", %[r1]\n\t"                              \
   "v_alignbit_b32 " T2 ", " X0 ", " X0 ", %[r2]\n\t"                              \
@@ -722,642 +703,608 @@ __device__ __forceinline__ uint32_t lp_z0(const uint32_t s[4], uint32_t kw0, con
   "v_xad_u32 " ZN ", " X2 ", %[m], " KWN "\n\t"                                   \
   "v_add3_u32 " V ", " S ", " F ", " Z "\n\t"                                     \
   "v_add_u32_dpp " ZN ", " X0 ", " ZN " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-
-__device__ __forceinline__ void lp_step(uint32_t s[4], uint32_t &z, uint32_t kwn,
-                                        const LpLane &c) {
-  uint32_t t1, t2, t3, x, f, sg, v, zn;
-  asm(KVGOV_LP_STEP("%[x0]", "%[x1]", "%[x2]", "%[z]", "%[v]", "%[zn]", "%[kwn]", "%[t1]",
-                    "%[t2]", "%[t3]", "%[x]", "%[f]", "%[sg]")
-      : [t1] "=&v"(t1), [t2] "=&v"(t2), [x] "=&v"(x), [t3] "=&v"(t3), [f] "=&v"(f),
-        [sg] "=&v"(sg), [zn] "=&v"(zn), [v] "=&v"(v)
-      : [x0] "v"(s[0]), [x1] "v"(s[1]), [x2] "v"(s[2]), [z] "v"(z), [m] "v"(c.m),
-        [r1] "v"(c.r1), [r2] "v"(c.r2), [r3] "v"(c.r3), [kwn] "v"(kwn));
-  s[3] = s[2];
-  s[2] = s[1];
-  s[1] = s[0];
-  s[0] = v;
-  z = zn;
-}
-
-__device__ __forceinline__ void lp_step2(uint32_t s[4], uint32_t &z, uint32_t kwn1,
-                                         uint32_t kwn2, const LpLane &c) {
-  uint32_t t1, t2, t3, x, f, sg, u1, u2, u3, y, g, sh, va, vb, za, zb;
-  asm(KVGOV_LP_STEP("%[x0]", "%[x1]", "%[x2]", "%[z]", "%[va]", "%[za]", "%[k1]", "%[t1]",
-                    "%[t2]", "%[t3]", "%[x]", "%[f]", "%[sg]")
-      KVGOV_LP_STEP("%[va]", "%[x0]", "%[x1]", "%[za]", "%[vb]", "%[zb]", "%[k2]", "%[u1]",
-                    "%[u2]", "%[u3]", "%[y]", "%[g]", "%[sh]")
-      : [t1] "=&v"(t1), [t2] "=&v"(t2), [x] "=&v"(x), [t3] "=&v"(t3), [f] "=&v"(f),
-        [sg] "=&v"(sg), [za] "=&v"(za), [va] "=&v"(va), [u1] "=&v"(u1), [u2] "=&v"(u2),
-        [y] "=&v"(y), [u3] "=&v"(u3), [g] "=&v"(g), [sh] "=&v"(sh), [zb] "=&v"(zb),
-        [vb] "=&v"(vb)
-      : [x0] "v"(s[0]), [x1] "v"(s[1]), [x2] "v"(s[2]), [z] "v"(z), [m] "v"(c.m),
-        [r1] "v"(c.r1), [r2] "v"(c.r2), [r3] "v"(c.r3), [k1] "v"(kwn1), [k2] "v"(kwn2));
-  s[3] = s[1];
-  s[2] = s[0];
-  s[1] = va;
-  s[0] = vb;
-  z = zb;
-}
-
-// Runs of 6, 14 or 16 steps as one asm statement: the compiler puts a wait
-// state between consecutive asm statements (it cannot see that their DPP
-// sources are old), which cost about a cycle per step with two-step
-// statements.  The four words x0..x3 live in a ring of four registers q0..q3
-// (step k reads x0 from q[-k mod 4] and writes x0' over the dead x3), Z
-// alternates between y0 and y1, and six temporaries are reused by every
-// step.  After a multiple of four steps the ring is back in place; after
-// 4k + 2 steps x0..x3 sit in q2, q3, q0, q1.
-#define KVGOV_LP_RING_T "%[t1]", "%[t2]", "%[t3]", "%[x]", "%[f]", "%[sg]"
+// the last step: no next Z
+#define KVGOV_LP_LAST(X0, X1, X2, Z, V, T1, T2, T3, XX, F, S)                        \
+  "v_alignbit_b32 " T1 ", " X0 ", " X0 ", %[r1]\n\t"                              \
+  "v_alignbit_b32 " T2 ", " X0 ", " X0 ", %[r2]\n\t"                              \
+  "v_bitop3_b32 " XX ", " X0 ", " X1 ", %[m] bitop3:0xd2\n\t"                     \
+  "v_alignbit_b32 " T3 ", " X0 ", " X0 ", %[r3]\n\t"                              \
+  "v_bitop3_b32 " F ", " XX ", " X1 ", " X2 " bitop3:0xca\n\t"                    \
+  "v_bitop3_b32 " S ", " T1 ", " T2 ", " T3 " bitop3:0x96\n\t"                    \
+  "v_add3_u32 " V ", " S ", " F ", " Z "\n\t"
 #define KVGOV_LP_STEP_(...) KVGOV_LP_STEP(__VA_ARGS__)
-#define KVGOV_LP_R0(K) KVGOV_LP_STEP_("%[q0]", "%[q1]", "%[q2]", "%[y0]", "%[q3]", "%[y1]", K, KVGOV_LP_RING_T)
-#define KVGOV_LP_R1(K) KVGOV_LP_STEP_("%[q3]", "%[q0]", "%[q1]", "%[y1]", "%[q2]", "%[y0]", K, KVGOV_LP_RING_T)
-#define KVGOV_LP_R2(K) KVGOV_LP_STEP_("%[q2]", "%[q3]", "%[q0]", "%[y0]", "%[q1]", "%[y1]", K, KVGOV_LP_RING_T)
-#define KVGOV_LP_R3(K) KVGOV_LP_STEP_("%[q1]", "%[q2]", "%[q3]", "%[y1]", "%[q0]", "%[y0]", K, KVGOV_LP_RING_T)
-#define KVGOV_LP_RING4(A, B, C, D) KVGOV_LP_R0(A) KVGOV_LP_R1(B) KVGOV_LP_R2(C) KVGOV_LP_R3(D)
-#define KVGOV_LP_RING_OUT                                                                    \
-  [q0] "+v"(s[0]), [q1] "+v"(s[1]), [q2] "+v"(s[2]), [q3] "+v"(s[3]), [y0] "+v"(z),         \
-      [y1] "=&v"(y1), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [x] "=&v"(x),          \
-      [f] "=&v"(f), [sg] "=&v"(sg)
-#define KVGOV_LP_RING_IN [m] "v"(c.m), [r1] "v"(c.r1), [r2] "v"(c.r2), [r3] "v"(c.r3)
-#define KVGOV_LP_K(i) [k##i] "v"(k[i - 1])
+#define KVGOV_LP_LAST_(...) KVGOV_LP_LAST(__VA_ARGS__)
 
-// k[i] is the kw taken by step i (the next step's)
-template <int N>
-__device__ __forceinline__ void lp_ring(uint32_t s[4], uint32_t &z, const uint32_t k[N],
-                                        const LpLane &c) {
-  static_assert(N == 6 || N == 14 || N == 16, "ring runs of 6, 14 or 16 steps");
-  uint32_t y1, t1, t2, t3, x, f, sg;
-  if constexpr (N == 16) {
-    asm(KVGOV_LP_RING4("%[k1]", "%[k2]", "%[k3]", "%[k4]")
-        KVGOV_LP_RING4("%[k5]", "%[k6]", "%[k7]", "%[k8]")
-        KVGOV_LP_RING4("%[k9]", "%[k10]", "%[k11]", "%[k12]")
-        KVGOV_LP_RING4("%[k13]", "%[k14]", "%[k15]", "%[k16]")
-        : KVGOV_LP_RING_OUT
-        : KVGOV_LP_RING_IN, KVGOV_LP_K(1), KVGOV_LP_K(2), KVGOV_LP_K(3), KVGOV_LP_K(4),
-          KVGOV_LP_K(5), KVGOV_LP_K(6), KVGOV_LP_K(7), KVGOV_LP_K(8), KVGOV_LP_K(9),
-          KVGOV_LP_K(10), KVGOV_LP_K(11), KVGOV_LP_K(12), KVGOV_LP_K(13), KVGOV_LP_K(14),
-          KVGOV_LP_K(15), KVGOV_LP_K(16));
-  } else if constexpr (N == 14) {
-    asm(KVGOV_LP_RING4("%[k1]", "%[k2]", "%[k3]", "%[k4]")
-        KVGOV_LP_RING4("%[k5]", "%[k6]", "%[k7]", "%[k8]")
-        KVGOV_LP_RING4("%[k9]", "%[k10]", "%[k11]", "%[k12]")
-        KVGOV_LP_R0("%[k13]") KVGOV_LP_R1("%[k14]")
-        : KVGOV_LP_RING_OUT
-        : KVGOV_LP_RING_IN, KVGOV_LP_K(1), KVGOV_LP_K(2), KVGOV_LP_K(3), KVGOV_LP_K(4),
-          KVGOV_LP_K(5), KVGOV_LP_K(6), KVGOV_LP_K(7), KVGOV_LP_K(8), KVGOV_LP_K(9),
-          KVGOV_LP_K(10), KVGOV_LP_K(11), KVGOV_LP_K(12), KVGOV_LP_K(13), KVGOV_LP_K(14));
-  } else {
-    asm(KVGOV_LP_RING4("%[k1]", "%[k2]", "%[k3]", "%[k4]")
-        KVGOV_LP_R0("%[k5]") KVGOV_LP_R1("%[k6]")
-        : KVGOV_LP_RING_OUT
-        : KVGOV_LP_RING_IN, KVGOV_LP_K(1), KVGOV_LP_K(2), KVGOV_LP_K(3), KVGOV_LP_K(4),
-          KVGOV_LP_K(5), KVGOV_LP_K(6));
-  }
-  if constexpr (N % 4 == 2) {
-    const uint32_t w0 = s[2], w1 = s[3], w2 = s[0], w3 = s[1];
-    s[0] = w0;
-    s[1] = w1;
-    s[2] = w2;
-    s[3] = w3;
-  }
+// The four words x0..x3 live in a ring of four registers q0..q3: the k-th
+// step of a run reads x0 from q[-k mod 4] and writes x0' over the dead x3;
+// Z alternates between y0 and y1.
+#define KVGOV_LP_R0(K) KVGOV_LP_STEP_("%[q0]", "%[q1]", "%[q2]", "%[y0]", "%[q3]", "%[y1]", K, KVGOV_LP_T)
+#define KVGOV_LP_R1(K) KVGOV_LP_STEP_("%[q3]", "%[q0]", "%[q1]", "%[y1]", "%[q2]", "%[y0]", K, KVGOV_LP_T)
+#define KVGOV_LP_R2(K) KVGOV_LP_STEP_("%[q2]", "%[q3]", "%[q0]", "%[y0]", "%[q1]", "%[y1]", K, KVGOV_LP_T)
+#define KVGOV_LP_R3(K) KVGOV_LP_STEP_("%[q1]", "%[q2]", "%[q3]", "%[y1]", "%[q0]", "%[y0]", K, KVGOV_LP_T)
+
+// K + W quads, in fixed registers so that their words have names: words
+// 4n .. 4n + 3 of a compression sit in quad n % 4.  Taking a quad's words
+// in four steps (step i takes the kw of step i + 1): in C1 step i is the
+// ring's R[(i - 1) % 4], in C2 R[i % 4].
+#define KVGOV_LP_P0 "v[96:99]"
+#define KVGOV_LP_P1 "v[100:103]"
+#define KVGOV_LP_P2 "v[104:107]"
+#define KVGOV_LP_P3 "v[108:111]"
+#define KVGOV_LP_C1_P0 KVGOV_LP_R2("v96") KVGOV_LP_R3("v97") KVGOV_LP_R0("v98") KVGOV_LP_R1("v99")
+#define KVGOV_LP_C1_P1 KVGOV_LP_R2("v100") KVGOV_LP_R3("v101") KVGOV_LP_R0("v102") KVGOV_LP_R1("v103")
+#define KVGOV_LP_C1_P2 KVGOV_LP_R2("v104") KVGOV_LP_R3("v105") KVGOV_LP_R0("v106") KVGOV_LP_R1("v107")
+#define KVGOV_LP_C1_P3 KVGOV_LP_R2("v108") KVGOV_LP_R3("v109") KVGOV_LP_R0("v110") KVGOV_LP_R1("v111")
+#define KVGOV_LP_C2_P0 KVGOV_LP_R3("v96") KVGOV_LP_R0("v97") KVGOV_LP_R1("v98") KVGOV_LP_R2("v99")
+#define KVGOV_LP_C2_P1 KVGOV_LP_R3("v100") KVGOV_LP_R0("v101") KVGOV_LP_R1("v102") KVGOV_LP_R2("v103")
+#define KVGOV_LP_C2_P2 KVGOV_LP_R3("v104") KVGOV_LP_R0("v105") KVGOV_LP_R1("v106") KVGOV_LP_R2("v107")
+#define KVGOV_LP_C2_P3 KVGOV_LP_R3("v108") KVGOV_LP_R0("v109") KVGOV_LP_R1("v110") KVGOV_LP_R2("v111")
+#define KVGOV_LP_RD(P, A, OFF) "ds_read_b128 " P ", %[" A "] offset:" #OFF "\n\t"
+#define KVGOV_LP_WAIT(N) "s_waitcnt lgkmcnt(" #N ")\n\ts_nop 0\n\t"
+#define KVGOV_LP_ALIGN ".p2align 3\n\t"
+#define KVGOV_LP_BAR "s_waitcnt lgkmcnt(0)\n\ts_barrier\n\t"
+#define KVGOV_LP_TEMPS                                                                     \
+  [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [xx] "=&v"(xx), [f] "=&v"(f), [sg] "=&v"(sg)
+#define KVGOV_LP_ROLE [m] "v"(c.m), [r1] "v"(c.r1), [r2] "v"(c.r2), [r3] "v"(c.r3)
+
+// C1, steps 1..63.  q = x0, x1, x2 of step 1 (q[3] is free), z its Z; kw[2..7]
+// the K + W of rounds 2..7; a0 the value the A lanes' x0 takes after step 1.
+// Reads words 8..15 at LDS address am and 16..63 at ac1, each group of these after
+// the barrier that releases it (words 16.., 24.., 32.., 48..), and C2's
+// words 0..11 at ac2 into p.  On return q[1], q[2], q[3], q[0] are x0..x3
+// after step 63 and z the Z of step 64.
+__device__ __forceinline__ void lp_c1(uint32_t q[4], uint32_t &z, const uint32_t kw[8], uint32_t a0,
+                                      const LpLane &c, uint32_t am, uint32_t ac1, uint32_t ac2,
+                                      lp_quad p[3]) {
+  uint32_t y1, t1, t2, t3, xx, f, sg;
+  asm volatile(
+      KVGOV_LP_ALIGN
+      KVGOV_LP_RD(KVGOV_LP_P2, "am", 0) KVGOV_LP_RD(KVGOV_LP_P3, "am", 16)
+      KVGOV_LP_R0("%[k2]")                                                       // step 1
+      "v_cndmask_b32_e64 %[q3], %[q3], %[a0], %[al]\n\t"
+      KVGOV_LP_R1("%[k3]") KVGOV_LP_R2("%[k4]") KVGOV_LP_R3("%[k5]")             // 2..4
+      KVGOV_LP_R0("%[k6]") KVGOV_LP_R1("%[k7]")                                  // 5, 6
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P2                                            // 7..10
+      KVGOV_LP_BAR                                                               // 16..23
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac1", 0) KVGOV_LP_RD(KVGOV_LP_P1, "ac1", 16)
+      KVGOV_LP_C1_P3                                                             // 11..14
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P0                                            // 15..18
+      KVGOV_LP_BAR                                                               // 24..31
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac1", 32) KVGOV_LP_RD(KVGOV_LP_P3, "ac1", 48)
+      KVGOV_LP_C1_P1                                                             // 19..22
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P2                                            // 23..26
+      KVGOV_LP_BAR                                                               // 32..39
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac1", 64) KVGOV_LP_RD(KVGOV_LP_P1, "ac1", 80)
+      KVGOV_LP_C1_P3                                                             // 27..30
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P0                                            // 31..34
+      KVGOV_LP_BAR                                                               // 40..47
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac1", 96) KVGOV_LP_RD(KVGOV_LP_P3, "ac1", 112)
+      KVGOV_LP_C1_P1                                                             // 35..38
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P2                                            // 39..42
+      KVGOV_LP_BAR                                                               // 48..55
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac1", 128) KVGOV_LP_RD(KVGOV_LP_P1, "ac1", 144)
+      KVGOV_LP_C1_P3                                                             // 43..46
+      KVGOV_LP_WAIT(1) KVGOV_LP_C1_P0                                            // 47..50
+      KVGOV_LP_BAR                                                               // 56..63
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac1", 160) KVGOV_LP_RD(KVGOV_LP_P3, "ac1", 176)
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac2", 0)
+      KVGOV_LP_C1_P1                                                             // 51..54
+      KVGOV_LP_RD(KVGOV_LP_P1, "ac2", 16)
+      KVGOV_LP_WAIT(3) KVGOV_LP_C1_P2                                            // 55..58
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac2", 32)
+      KVGOV_LP_WAIT(3) KVGOV_LP_C1_P3                                            // 59..62
+      KVGOV_LP_WAIT(0) KVGOV_LP_R2("v96")                                        // 63
+      : [q0] "+v"(q[0]), [q1] "+v"(q[1]), [q2] "+v"(q[2]), [q3] "=&v"(q[3]), [y0] "+v"(z),
+        [y1] "=&v"(y1), KVGOV_LP_TEMPS, "=&{v[96:99]}"(p[0]), "=&{v[100:103]}"(p[1]),
+        "=&{v[104:107]}"(p[2])
+      : KVGOV_LP_ROLE, [k2] "v"(kw[2]), [k3] "v"(kw[3]), [k4] "v"(kw[4]), [k5] "v"(kw[5]),
+        [k6] "v"(kw[6]), [k7] "v"(kw[7]), [a0] "v"(a0), [al] "s"(kALanes), [am] "v"(am),
+        [ac1] "v"(ac1), [ac2] "v"(ac2)
+      : "v108", "v109", "v110", "v111", "memory");
+  z = y1;
 }
 
-// N steps; kw holds the group's own kw (kw[0] is already in z), kw_after
-// the kw of the step after the group
-template <int N>
-__device__ __forceinline__ void lp_steps(uint32_t s[4], uint32_t &z, const uint32_t *kw,
-                                         uint32_t kw_after, const LpLane &c) {
-  if constexpr (N == 6 || N == 14 || N == 16) {
-    uint32_t k[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) k[i] = i + 1 < N ? kw[i + 1] : kw_after;
-    lp_ring<N>(s, z, k, c);
-  } else {
-#pragma unroll
-    for (int i = 0; i + 1 < N; i += 2)
-      lp_step2(s, z, kw[i + 1], i + 2 < N ? kw[i + 2] : kw_after, c);
-    if (N & 1) lp_step(s, z, kw_after, c);
-  }
+// C2, steps 0..65.  s = the state's words (see the feed-forward above; the
+// A lanes' still without it), z the Z of step 0, p the words 0..11.  fa =
+// what the A lanes add after step 1 (0 on E lanes).  On return q holds x0..x3
+// after step 63 and n0, n1 the A lanes' last two words; s holds the state
+// C2 started from, but for the A lanes' s[3] without fa's fourth word.
+__device__ __forceinline__ void lp_c2(uint32_t s[4], uint32_t z, const lp_quad p[3],
+                                      const uint32_t fa[3], const LpLane &c, uint32_t ac2,
+                                      uint32_t q[4], uint32_t &n0, uint32_t &n1) {
+  uint32_t y1, x2, t1, t2, t3, xx, f, sg;
+  lp_quad p0, p1, p2;
+  asm volatile(
+      KVGOV_LP_ALIGN
+      KVGOV_LP_RD(KVGOV_LP_P3, "ac2", 48)
+      // steps 0 and 1 (C1's 64 and 65 on the A lanes)
+      KVGOV_LP_STEP_("%[s0]", "%[s1]", "%[s2]", "%[y0]", "%[q3]", "%[y1]", "v97", KVGOV_LP_T)
+      KVGOV_LP_STEP_("%[q3]", "%[s0]", "%[s1]", "%[y1]", "%[q2]", "%[y0]", "v98", KVGOV_LP_T)
+      "v_add_u32_e64 %[x2], %[s0], %[f2]\n\t"
+      "v_add_u32_e64 %[q2], %[q2], %[f0]\n\t"
+      "v_add_u32_e64 %[q3], %[q3], %[f1]\n\t"
+      "v_cndmask_b32_e64 %[s3], %[s3], %[s1], %[al]\n\t"
+      "v_cndmask_b32_e64 %[s2], %[s2], %[x2], %[al]\n\t"
+      "v_cndmask_b32_e64 %[s1], %[s1], %[q3], %[al]\n\t"
+      "v_cndmask_b32_e64 %[s0], %[s0], %[q2], %[al]\n\t"
+      KVGOV_LP_STEP_("%[q2]", "%[q3]", "%[x2]", "%[y0]", "%[q1]", "%[y1]", "v99", KVGOV_LP_T)
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac2", 64)
+      KVGOV_LP_R3("v100") KVGOV_LP_R0("v101") KVGOV_LP_R1("v102") KVGOV_LP_R2("v103")  // 3..6
+      KVGOV_LP_RD(KVGOV_LP_P1, "ac2", 80)
+      KVGOV_LP_C2_P2                                                             // 7..10
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac2", 96)
+      KVGOV_LP_WAIT(2) KVGOV_LP_C2_P3                                            // 11..14
+      KVGOV_LP_RD(KVGOV_LP_P3, "ac2", 112) KVGOV_LP_C2_P0                        // 15..18
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac2", 128) KVGOV_LP_WAIT(2) KVGOV_LP_C2_P1
+      KVGOV_LP_RD(KVGOV_LP_P1, "ac2", 144) KVGOV_LP_C2_P2
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac2", 160) KVGOV_LP_WAIT(2) KVGOV_LP_C2_P3       // 27..30
+      KVGOV_LP_RD(KVGOV_LP_P3, "ac2", 176) KVGOV_LP_C2_P0
+      KVGOV_LP_RD(KVGOV_LP_P0, "ac2", 192) KVGOV_LP_WAIT(2) KVGOV_LP_C2_P1
+      KVGOV_LP_RD(KVGOV_LP_P1, "ac2", 208) KVGOV_LP_C2_P2
+      KVGOV_LP_RD(KVGOV_LP_P2, "ac2", 224) KVGOV_LP_WAIT(2) KVGOV_LP_C2_P3       // 43..46
+      KVGOV_LP_RD(KVGOV_LP_P3, "ac2", 240) KVGOV_LP_C2_P0                        // 47..50
+      KVGOV_LP_WAIT(1) KVGOV_LP_C2_P1 KVGOV_LP_C2_P2                             // 51..58
+      KVGOV_LP_WAIT(0) KVGOV_LP_C2_P3                                            // 59..62
+      KVGOV_LP_R3("1")                                                           // 63
+      KVGOV_LP_STEP_("%[q0]", "%[q1]", "%[q2]", "%[y0]", "%[n0]", "%[y1]", "1", KVGOV_LP_T)
+      KVGOV_LP_LAST_("%[n0]", "%[q0]", "%[q1]", "%[y1]", "%[n1]", KVGOV_LP_T)
+      : [s0] "+v"(s[0]), [s1] "+v"(s[1]), [s2] "+v"(s[2]), [s3] "+v"(s[3]), [y0] "+v"(z),
+        [y1] "=&v"(y1), [x2] "=&v"(x2), [q0] "=&v"(q[0]), [q1] "=&v"(q[1]), [q2] "=&v"(q[2]),
+        [q3] "=&v"(q[3]), [n0] "=&v"(n0), [n1] "=&v"(n1), KVGOV_LP_TEMPS,
+        "=&{v[96:99]}"(p0), "=&{v[100:103]}"(p1), "=&{v[104:107]}"(p2)
+      : KVGOV_LP_ROLE, [f0] "v"(fa[0]), [f1] "v"(fa[1]), [f2] "v"(fa[2]), [al] "s"(kALanes),
+        [ac2] "v"(ac2), "{v[96:99]}"(p[0]), "{v[100:103]}"(p[1]), "{v[104:107]}"(p[2])
+      : "v108", "v109", "v110", "v111", "memory");
 }
 
-// steps 0 and 1 of a compression: the A lane's results are replaced by the
-// initial b, then a
-__device__ __forceinline__ void lp_head(uint32_t s[4], uint32_t &z, uint32_t kw1, uint32_t kw2,
-                                        const LpLane &c, uint32_t b0, uint32_t a0,
-                                        bool a_lane) {
-  lp_step(s, z, kw1, c);
-  s[0] = a_lane ? b0 : s[0];
-  lp_step(s, z, kw2, c);
-  s[0] = a_lane ? a0 : s[0];
-}
+// Message schedule on a lane pair: lane p of the pair makes the words W[t],
+// t = 16 + 2k + p, of step k, so a wave makes two words of 32 requests in
+// about 15 instructions.  Both lanes keep a 16-word window in which lane p's
+// logical word i at step k is W[2k + p + i], stored at w[(2k + i) & 15]: the
+// four operands of W[t] (t - 16, t - 15, t - 7, t - 2: logical 0, 1, 9, 14)
+// are then the same registers on both lanes.  After the step each lane takes
+// its partner's new word with one DPP swap: lane 0 needs it as logical 15 of
+// the next window (W[17 + 2k]), lane 1 as logical 13 (W[16 + 2k]); lane 1's
+// logical 15 (W[18 + 2k], lane 0's next word) is set the same way one step
+// later, before it is first read (as logical 9, four steps on).
+// Word 2k of the row at LDS address `row` (already offset by p) receives
+// K[t] + W[t]; kt = the lane's K.  Four steps are one asm statement of
+// eight-byte instructions only (see KVGOV_LP_ALIGN): 14 per step, and no
+// wait state before the DPP read (two instructions after the write).
+#define KVGOV_LP_SCHED(W0, W1, W9, W14, W15, KT, OFF)                               \
+  "v_alignbit_b32 %[t1], " W1 ", " W1 ", 7\n\t"                                    \
+  "v_alignbit_b32 %[t2], " W1 ", " W1 ", 18\n\t"                                   \
+  "v_lshrrev_b32_e64 %[t3], 3, " W1 "\n\t"                                         \
+  "v_alignbit_b32 %[t4], " W14 ", " W14 ", 17\n\t"                                 \
+  "v_bitop3_b32 %[t1], %[t1], %[t2], %[t3] bitop3:0x96\n\t"                        \
+  "v_alignbit_b32 %[t5], " W14 ", " W14 ", 19\n\t"                                 \
+  "v_lshrrev_b32_e64 %[t6], 10, " W14 "\n\t"                                       \
+  "v_add3_u32 " W0 ", %[t1], " W0 ", " W9 "\n\t"                                   \
+  "v_bitop3_b32 %[t4], %[t4], %[t5], %[t6] bitop3:0x96\n\t"                        \
+  "v_add_u32_e64 " W0 ", " W0 ", %[t4]\n\t"                                        \
+  "v_add_u32_e64 %[t1], " W0 ", " KT "\n\t"                                        \
+  "ds_write_b32 %[row], %[t1] offset:" OFF "\n\t"                                  \
+  "v_mov_b32_dpp " W1 ", " W0 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t" \
+  "v_cndmask_b32_e64 " W15 ", " W15 ", " W1 ", %[ol]\n\t"
+// w[i0] <- the new word (logical 14 of the next window), w[i1] <- the
+// partner's (logical 15; on lane 1 replaced before it is read), w[i15] on
+// lane 1 <- the partner's (logical 13)
 
-// steps 64 and 65: the A lane computes A_63 and A_64; the E lane's words
-// were final after step 63 (e..h), the A lane's after step 65 (a..d)
-__device__ __forceinline__ void lp_tail(uint32_t s[4], uint32_t &z, const LpLane &c,
-                                        bool a_lane) {
-  uint32_t e[4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x) e[x] = s[x];
-  lp_step2(s, z, 1u, 1u, c);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) s[x] = a_lane ? s[x] : e[x];
-}
-
-__device__ __forceinline__ void lp_load16(uint32_t w[16], const uint32_t (*rows)[kLpCols],
-                                          int base, int col) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) w[i] = rows[base + i][col];
-}
-
-// schedule words W[t0..t0+15] from the rolling window w (W[t0-16..t0-1]);
-// stores K[t0 + i] + W[t0 + i] to rows[base + i][lane]
-template <int T0>
-__device__ __forceinline__ void lp_sched16(uint32_t w[16], uint32_t (*rows)[kLpCols], int base,
-                                           int lane) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    w[i] = small_sigma1(w[(i + 14) & 15]) + w[(i + 9) & 15] + small_sigma0(w[(i + 1) & 15]) +
-           w[i];
-    rows[base + i][lane] = w[i] + kSha.K[T0 + i];
-  }
-}
-
-// schedule words W[T0..T0+N-1] (T0 >= 16) from the rolling window w, which
-// holds W[t] at w[t & 15]; stores K[t] + W[t] to rows[t - 16][lane].  With
-// PRE, the terms of W[16..30] that depend on message words 8..15 alone come
-// from pre (lp_presum), computed while the previous block was hashed.
-template <int T0, int N, bool PRE>
-__device__ __forceinline__ void lp_sched_words(uint32_t w[16], uint32_t (*rows)[kLpCols],
-                                               int lane, const uint32_t pre[16]) {
-#pragma unroll
-  for (int t = T0; t < T0 + N; ++t) {
-    uint32_t v;
-    if (PRE && (t == 16 || t == 17))
-      v = small_sigma0(w[(t - 15) & 15]) + w[t & 15] + pre[t - 16];
-    else if (PRE && t == 23)
-      v = small_sigma1(w[(t - 2) & 15]) + w[(t - 7) & 15] + pre[7] + w[t & 15];
-    else if (PRE && t >= 24 && t <= 30)
-      v = small_sigma1(w[(t - 2) & 15]) + w[(t - 7) & 15] + pre[t - 16];
-    else
-      v = small_sigma1(w[(t - 2) & 15]) + w[(t - 7) & 15] + small_sigma0(w[(t - 15) & 15]) +
-          w[t & 15];
-    w[t & 15] = v;
-    rows[t - 16][lane] = v + kSha.K[t];
-  }
-}
-
-// The parts of schedule words 16..30 of a first compression whose message
-// words 8..15 are m[0..7] (every block but the chain's first and the
-// boundary block) that do not involve words 0..7:
-//   W16 = sigma0(W1) + W0 + [sigma1(W14) + W9]     W17 likewise
-//   W23 = sigma1(W21) + W16 + W7 + [sigma0(W8)]
-//   W24..W30 = sigma1(W[t-2]) + W[t-7] + [sigma0(W[t-15]) + W[t-16]]
-__device__ __forceinline__ void lp_presum(const uint32_t m[8], uint32_t pre[16]) {
-  pre[0] = small_sigma1(m[6]) + m[1];
-  pre[1] = small_sigma1(m[7]) + m[2];
-  pre[7] = small_sigma0(m[0]);
-#pragma unroll
-  for (int i = 0; i < 7; ++i) pre[8 + i] = small_sigma0(m[1 + i]) + m[i];
-}
-
-// The first compression's schedule words W[16..63] depend on h_{j-1} and are
-// released to the rounds waves in groups, one barrier each: group g holds
-// W[kLpGroup[g] .. kLpGroup[g + 1] - 1].  A barrier costs the waves about as
-// much as the rounds lose waiting for a larger group (the schedule wave
-// makes a word a little slower than the rounds use one): three groups of 16
-// measured fastest, splits into 4 to 8 groups slower.
-constexpr int kLpGroup[] = {KVGOV_LP_GROUPS};
-constexpr int kLpGroups = (int)(sizeof(kLpGroup) / sizeof(kLpGroup[0])) - 1;
-static_assert(kLpGroup[0] == 16 && kLpGroup[kLpGroups] == 64, "groups cover W[16..63]");
-
+// Steps 4 G .. 4 G + 3; kt the lane's constants of these.
 template <int G>
-__device__ __forceinline__ void lp_sched_groups(uint32_t w[16], uint32_t (*rows)[kLpCols],
-                                                int lane, bool work, const uint32_t pre[16],
-                                                bool use_pre) {
-  if constexpr (G < kLpGroups) {
-    constexpr int S = kLpGroup[G], N = kLpGroup[G + 1] - kLpGroup[G];
-    static_assert(N > 0, "groups ascend");
-    if (work) {
-      if (S <= 30 && use_pre)  // workgroup-uniform
-        lp_sched_words<S, N, true>(w, rows, lane, pre);
-      else
-        lp_sched_words<S, N, false>(w, rows, lane, pre);
-    }
-    __syncthreads();
-    lp_sched_groups<G + 1>(w, rows, lane, work, pre, use_pre);
-  }
+__device__ __forceinline__ void lp_pair4(uint32_t w[16], uint32_t row, const uint32_t *kt) {
+  uint32_t t1, t2, t3, t4, t5, t6;
+  constexpr int b = (8 * G) & 15;  // the window's start: 0 or 8
+#define KVGOV_LP_W(I) [w##I] "+v"(w[(b + I) & 15])
+  asm volatile(KVGOV_LP_ALIGN
+               KVGOV_LP_SCHED("%[w0]", "%[w1]", "%[w9]", "%[w14]", "%[w15]", "%[k0]", "%c[o0]")
+               KVGOV_LP_SCHED("%[w2]", "%[w3]", "%[w11]", "%[w0]", "%[w1]", "%[k1]", "%c[o1]")
+               KVGOV_LP_SCHED("%[w4]", "%[w5]", "%[w13]", "%[w2]", "%[w3]", "%[k2]", "%c[o2]")
+               KVGOV_LP_SCHED("%[w6]", "%[w7]", "%[w15]", "%[w4]", "%[w5]", "%[k3]", "%c[o3]")
+               : KVGOV_LP_W(0), KVGOV_LP_W(1), KVGOV_LP_W(2), KVGOV_LP_W(3), KVGOV_LP_W(4),
+                 KVGOV_LP_W(5), KVGOV_LP_W(6), KVGOV_LP_W(7), KVGOV_LP_W(9), KVGOV_LP_W(11),
+                 KVGOV_LP_W(13), KVGOV_LP_W(14), KVGOV_LP_W(15), [t1] "=&v"(t1), [t2] "=&v"(t2),
+                 [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6)
+               : [k0] "v"(kt[0]), [k1] "v"(kt[1]), [k2] "v"(kt[2]), [k3] "v"(kt[3]),
+                 [row] "v"(row), [ol] "s"(kALanes), [o0] "i"(32 * G), [o1] "i"(32 * G + 8),
+                 [o2] "i"(32 * G + 16), [o3] "i"(32 * G + 24)
+               : "memory");
+#undef KVGOV_LP_W
 }
 
-// Rounds of the first compression from step kLpGroup[G] - C on: after the
-// barrier that releases group G, its K + W rows are loaded into kw and the
-// steps up to the next group's barrier (or to step 63) run.  kw2 receives
-// the second compression's first 16 K + W rows during the last group.
-template <int G>
-__device__ __forceinline__ void lp_round_groups(uint32_t s[4], uint32_t &z, uint32_t kw[64],
-                                                uint32_t kw2[16],
-                                                const uint32_t (*rows)[kLpCols],
-                                                const uint32_t (*rows2)[kLpCols], int col,
-                                                const LpLane &c, bool act) {
-  if constexpr (G < kLpGroups) {
-    constexpr int C = KVGOV_LP_COVER;
-    constexpr int S = kLpGroup[G], E = kLpGroup[G + 1];
-    __syncthreads();  // releases W[S..E-1]
-    if (act) {
+// What a request does in iteration i of its workgroup.
+enum LpBlock {
+  kLpPlain,     // first (IV; h || T[0..7])      second (.; T[8..15] || pad96)
+  kLpFirst,     // first (IV; T[0..15])          second (.; pad64)
+  kLpBoundary,  // first (IV; sigma || h)        second (.; T[0..15])
+  kLpPad        // first idle                    second (the boundary block's state; pad128)
+};
+
+// The tables of a request's next iteration that depend on tokens and
+// constants: raw words and K + words of the first message except h (written
+// by the rounds lanes), and K + W of all 64 rounds of the second message (all on
+// both lanes of the pair; the schedule is split by parity).
+__device__ __forceinline__ void lp_prepare(const uint32_t Tn[16], const uint32_t sig[8],
+                                           LpBlock what, LpLds &L, int buf, int col, bool odd,
+                                           const uint32_t kt[24]) {
+  uint32_t m[16], w[16];
+  lp_quad *raw = reinterpret_cast<lp_quad *>(L.msg[col]);
+  lp_quad *kwm = reinterpret_cast<lp_quad *>(L.kwm[col]);
+  // words 8..15 of the first message
+  if (what == kLpPlain || what == kLpFirst) {
+    const int o = what == kLpFirst ? 8 : 0;
 #pragma unroll
-      for (int t = S; t < E; ++t) kw[t] = rows[t - 16][col];
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (E < 64) {
-        lp_steps<E - S>(s, z, kw + S - C, kw[E - C], c);
-      } else {
-        lp_steps<C>(s, z, kw + S - C, kw[S], c);
-        lp_load16(kw2, rows2, 0, col);
-        __builtin_amdgcn_sched_barrier(0);
-        lp_steps<64 - S>(s, z, kw + S, 1u, c);
+    for (int x = 0; x < 2; ++x) {
+      lp_quad r, k;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        r[y] = o ? Tn[8 + 4 * x + y] : Tn[4 * x + y];
+        k[y] = r[y] + kSha.K[8 + 4 * x + y];
       }
+      raw[2 + x] = r;
+      kwm[x] = k;
     }
-    lp_round_groups<G + 1>(s, z, kw, kw2, rows, rows2, col, c, act);
   }
-}
-
-// Message schedule on a lane pair: with two schedule lanes per request,
-// lane p of the pair makes the words W[t], t = 16 + 2k + p, of step k, so a
-// wave makes a word of 32 requests in about 16 instructions per two words
-// instead of one lane making every word in 11.  Both lanes keep a 16-word
-// window in which lane p's logical word i at step k is W[2k + p + i],
-// stored at w[(2k + i) & 15]: the four operands of W[t] (t - 16, t - 15,
-// t - 7, t - 2: logical 0, 1, 9, 14) are then the same registers on both
-// lanes.  After the step each lane takes its partner's new word with one DPP
-// swap: lane 0 needs it as logical 15 of the next window (W[17 + 2k]), lane 1
-// as logical 13 (W[16 + 2k]); lane 1's logical 15 (W[18 + 2k], lane 0's next
-// word) is set the same way one step later, before it is first read (as
-// logical 9, four steps on).  rows[2k + p][col] receives K[t] + W[t].
-template <int K>
-__device__ __forceinline__ void lp_pair_step(uint32_t w[16], uint32_t (*rows)[kLpCols], int col,
-                                             bool odd) {
-  constexpr int i0 = (2 * K) & 15, i1 = (2 * K + 1) & 15, i9 = (2 * K + 9) & 15;
-  constexpr int i14 = (2 * K + 14) & 15, i15 = (2 * K + 15) & 15;
-  const uint32_t v = small_sigma1(w[i14]) + w[i9] + small_sigma0(w[i1]) + w[i0];
-  const uint32_t kt = odd ? kSha.K[17 + 2 * K] : kSha.K[16 + 2 * K];
-  rows[2 * K + (odd ? 1 : 0)][col] = v + kt;
-  const uint32_t pv = lp_partner(v);
-  w[i0] = v;                    // logical 14 of the next window
-  w[i1] = pv;                   // logical 15 (lane 1: replaced before it is read)
-  w[i15] = odd ? pv : w[i15];   // logical 13 on lane 1
-}
-
-// Steps K .. K + N - 1.
-template <int K, int N>
-__device__ __forceinline__ void lp_pair_run(uint32_t w[16], uint32_t (*rows)[kLpCols], int col,
-                                            bool odd) {
-  if constexpr (N > 0) {
-    lp_pair_step<K>(w, rows, col, odd);
-    lp_pair_run<K + 1, N - 1>(w, rows, col, odd);
+  if (what == kLpBoundary || what == kLpFirst) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      lp_quad r;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) r[y] = what == kLpFirst ? Tn[4 * x + y] : sig[4 * x + y];
+      raw[x] = r;
+    }
   }
-}
-
-// The window of step 0 from the message words m[0..15] (all on both lanes):
-// lane 1's logical i is W[i + 1]; its logical 15 (W[16]) comes from lane 0's
-// first step.
-__device__ __forceinline__ void lp_pair_window(const uint32_t m[16], uint32_t w[16], bool odd) {
+  // the second message
+#pragma unroll
+  for (int x = 0; x < 16; ++x) m[x] = 0;
+  if (what == kLpPlain) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) m[x] = Tn[8 + x];
+    pad96_tail(m);
+  } else if (what == kLpBoundary) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) m[x] = Tn[x];
+  } else {
+    m[0] = 0x80000000u;
+    m[15] = what == kLpFirst ? 64 * 8 : 128 * 8;
+  }
+  lp_quad *row = reinterpret_cast<lp_quad *>(L.c2[buf][col]);
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    lp_quad k;
+#pragma unroll
+    for (int y = 0; y < 4; ++y) k[y] = m[4 * x + y] + kSha.K[4 * x + y];
+    if (x == 0) {  // the feed-forward of the first compression (see above)
+      k[0] += kSha.H0[3] + kSha.H0[7];
+      k[1] += kSha.H0[2];
+      k[2] += kSha.H0[1];
+    }
+    row[x] = k;
+  }
+  // lane 1's window starts one word later; its logical 15 (W[16]) comes
+  // from lane 0's first step
 #pragma unroll
   for (int i = 0; i < 15; ++i) w[i] = odd ? m[i + 1] : m[i];
   w[15] = m[15];
+  const uint32_t out = lds_addr(L.c2[buf][col] + 16 + (odd ? 1 : 0));
+  lp_pair4<0>(w, out, kt);
+  lp_pair4<1>(w, out, kt + 4);
+  lp_pair4<2>(w, out, kt + 8);
+  lp_pair4<3>(w, out, kt + 12);
+  lp_pair4<4>(w, out, kt + 16);
+  lp_pair4<5>(w, out, kt + 20);
 }
 
-// The first compression's schedule in groups, as lp_sched_groups, on lane
-// pairs: group g's words, then the barrier that releases them.
-template <int G>
-__device__ __forceinline__ void lp_pair_groups(uint32_t w[16], uint32_t (*rows)[kLpCols], int col,
-                                               bool odd, bool work) {
-  if constexpr (G < kLpGroups) {
-    constexpr int S = kLpGroup[G], N = kLpGroup[G + 1] - kLpGroup[G];
-    static_assert(S % 2 == 0 && N % 2 == 0, "pair groups hold whole steps");
-    if (work) lp_pair_run<(S - 16) / 2, N / 2>(w, rows, col, odd);
-    __syncthreads();
-    lp_pair_groups<G + 1>(w, rows, col, odd, work);
-  }
+// The A lane's Z and third word with which two steps from (c, d) of the
+// state give it b and a: what a padding iteration starts from, see lp_pad.
+__device__ __forceinline__ uint32_t lp_a_sum(uint32_t x0, uint32_t x1, uint32_t x2) {
+  return big_sigma0(x0) + maj(x0, x1, x2);
 }
 
-// Per block and request, the three message patterns of the chain (the
-// compressions of a block, "first" and "second", plus a third for the
-// boundary block):
-//   plain        first (IV; h_{j-1} || T[0..7])   second (.; T[8..15] || pad96)
-//   first block  first (IV; T[0..15])             second (.; pad64)
-//   boundary     first (IV; sigma || h_{k-1})     second (.; T[0..15])
-//                third (.; pad128)
-// Prepared one block ahead from tokens and constants: the first message's
-// words into ha / hb except h_{j-1} (written by the rounds lanes at the end
-// of block j - 1), and K + W of all 64 rounds of the second message.
-__device__ __forceinline__ void lp_message(const uint32_t Tn[16], const uint32_t sig[8],
-                                           bool first_block, bool boundary, LpLds &L, int buf,
-                                           int lane, uint32_t m[16]) {
-  if (boundary) {
+// Before C2 of a padding iteration: the ring and Z as steps 64 and 65 of a C1
+// with the saved state P (e..h on E lanes, a..d on A lanes) as its result
+// would find them.  kw0 = C2's kw row 0.  The E lane's step 0 takes P as it
+// is.  The A lane's ring must read c - IV_2, d - IV_3, and its two steps give
+// b - IV_1 and a - IV_0 (the feed-forward comes after them): its Z, and x2
+// (which only its own next Z takes, as x3, and step 0's majority), are
+// solved for.
+__device__ __forceinline__ void lp_pad(const uint32_t P[4], uint32_t kw0, bool a_lane,
+                                       uint32_t s[4], uint32_t &z) {
+  uint32_t o[4];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) L.ha[x][lane] = sig[x];
-#pragma unroll
-    for (int x = 0; x < 16; ++x) m[x] = Tn[x];
-  } else if (first_block) {
-#pragma unroll
-    for (int x = 0; x < 8; ++x) {
-      L.ha[x][lane] = Tn[x];
-      L.hb[x][lane] = Tn[8 + x];
-    }
-    m[0] = 0x80000000u;
-#pragma unroll
-    for (int x = 1; x < 15; ++x) m[x] = 0;
-    m[15] = 64 * 8;
+  for (int x = 0; x < 4; ++x) o[x] = lp_partner(P[x]);
+  if (a_lane) {
+    const uint32_t a = P[0] - kSha.H0[0], b = P[1] - kSha.H0[1], cc = P[2] - kSha.H0[2],
+                   d = P[3] - kSha.H0[3];
+    // step 1: a = sum(b, c, d) + Z1, Z1 = ~x2 + (1 - IV_4) + e
+    const uint32_t z1 = a - lp_a_sum(b, cc, d);
+    const uint32_t x2 = ~(z1 - 1u + kSha.H0[4] - o[0]);
+    s[0] = cc;
+    s[1] = d;
+    s[2] = x2;
+    s[3] = 0;
+    z = b - lp_a_sum(cc, d, x2);
   } else {
 #pragma unroll
-    for (int x = 0; x < 8; ++x) {
-      L.hb[x][lane] = Tn[x];
-      m[x] = Tn[8 + x];
-    }
-    pad96_tail(m);
+    for (int x = 0; x < 4; ++x) s[x] = P[x];
+    z = P[3] + o[3] + kw0 - kSha.H0[3] - kSha.H0[7];
   }
-#pragma unroll
-  for (int x = 0; x < 16; ++x) L.c2[buf][x][lane] = kSha.K[x] + m[x];
-}
-
-__device__ __forceinline__ void lp_prepare(const uint32_t Tn[16], const uint32_t sig[8],
-                                           bool first_block, bool boundary, LpLds &L, int buf,
-                                           int lane) {
-  uint32_t m[16];
-  lp_message(Tn, sig, first_block, boundary, L, buf, lane, m);
-  lp_sched16<16>(m, L.c2[buf], 16, lane);
-  lp_sched16<32>(m, L.c2[buf], 32, lane);
-  lp_sched16<48>(m, L.c2[buf], 48, lane);
-}
-
-// lp_prepare on a lane pair: both lanes write the same message words (the
-// same values to the same addresses), the schedule is split by parity.
-__device__ __forceinline__ void lp_prepare_pair(const uint32_t Tn[16], const uint32_t sig[8],
-                                                bool first_block, bool boundary, LpLds &L, int buf,
-                                                int col, bool odd) {
-  uint32_t m[16], w[16];
-  lp_message(Tn, sig, first_block, boundary, L, buf, col, m);
-  lp_pair_window(m, w, odd);
-  lp_pair_run<0, 24>(w, L.c2[buf] + 16, col, odd);
-}
-
-__device__ __forceinline__ void lp_load16(uint32_t w[16], const uint32_t (*rows)[2], int base,
-                                          int col) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) w[i] = rows[base + i][col];
-}
-
-// The rounds of one compression from the initial words st (E: e..h, A:
-// a..d), K + W from 16-row groups: kw0 holds rounds 0..15 (already in
-// registers), the later groups are loaded from `rows` (64 rows) one group
-// ahead; returns st + the compression's result.
-template <typename Rows>
-__device__ __forceinline__ void lp_compress_rows(uint32_t st[4], const uint32_t kw0[16], Rows rows,
-                                                 int col, const LpLane &c, bool a_lane) {
-  uint32_t s[4], wa[16], wb[16], z;
-#pragma unroll
-  for (int x = 0; x < 4; ++x) s[x] = a_lane ? (x < 2 ? st[x + 2] : 0u) : st[x];
-  z = lp_z0(s, kw0[0], c);
-  lp_load16(wa, rows, 16, col);
-  __builtin_amdgcn_sched_barrier(0);
-  lp_head(s, z, kw0[1], kw0[2], c, st[1], st[0], a_lane);
-  lp_steps<14>(s, z, kw0 + 2, wa[0], c);   // 2..15
-  lp_load16(wb, rows, 32, col);
-  __builtin_amdgcn_sched_barrier(0);
-  lp_steps<16>(s, z, wa, wb[0], c);        // 16..31
-  lp_load16(wa, rows, 48, col);
-  __builtin_amdgcn_sched_barrier(0);
-  lp_steps<16>(s, z, wb, wa[0], c);        // 32..47
-  lp_steps<16>(s, z, wa, 1u, c);           // 48..63
-  lp_tail(s, z, c, a_lane);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) st[x] += s[x];
 }
 
 // Workgroup `group` of the lane-pair kernel: requests group * 64 + 0..63 of
-// the (ordered) batch.  Waves 0 and 1 run the rounds.  PAIR (workgroups of
-// four waves): waves 2 and 3 run the schedule with two lanes per request
-// (32 requests each), so that the first compression's words are ready before
-// the rounds take them; otherwise wave 2 runs it with one lane per request
-// (and a fourth wave, if any, only keeps the barriers).
-template <int MODE, bool PAIR>
+// the (ordered) batch.
+template <int MODE>
 __device__ __forceinline__ void lp_group(const ChainArgs &a, int32_t group, LpLds &L) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const bool sched_wave = wave >= 2;
-  const bool idle = !PAIR && wave >= 3;
-  const bool a_lane = !sched_wave && (lane & 1);
-  // the lane's parity in a schedule pair
-  const bool odd = PAIR && sched_wave && (lane & 1);
-  // the request (LDS column) of this lane within the workgroup
-  const int mine = sched_wave && !PAIR ? lane : (wave & 1) * 32 + (lane >> 1);
+  const bool odd = lane & 1;  // rounds: the A lane; schedule: the odd words' lane
+  // the request (LDS row) of this lane within the workgroup
+  const int mine = (wave & 1) * 32 + (lane >> 1);
   const int32_t base = group * kWave;
   const int32_t i = base + mine;
 
-  ChainReq q;
+  ChainReq q{};
   bool ok = false;
+  int32_t r = 0;
   if (i < a.n) {
-    const int32_t r = a.order ? a.order[i] : i;
+    r = a.order ? a.order[i] : i;
     ok = chain_setup<MODE>(a, r, q);
   }
   const int64_t nf = ok ? q.nf : 0;
-  const int64_t kb = ok ? q.kr : -1;  // boundary iteration (boundary mode), else -1
-  // Trip count and boundary iterations are decided over all 64 requests of
-  // the workgroup: the schedule wave holds them all, and a rounds lane also
-  // looks at the request of the same lane in the other rounds wave.
-  const ReqPeek own{nf, kb};
-  ReqPeek other{0, -1};
-  if (!sched_wave || PAIR) other = req_peek<MODE>(a, base + (1 - (wave & 1)) * 32 + (mine & 31));
-  int64_t J = own.nf > other.nf ? own.nf : other.nf;
+  const int64_t kb = ok && q.kr < nf ? q.kr : -1;  // the boundary block's iteration, else -1
+  // iterations: the blocks, and the boundary block's padding
+  const int64_t ni = nf + (MODE == KVGOV_BOUNDARY && kb >= 0 ? 1 : 0);
+
+  // Trip count over all 64 requests: each wave's maximum through LDS (the
+  // first words of the tables, before these are written).
+  int64_t J = ni;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     const int64_t o = __shfl_xor(J, d, kWave);
     J = o > J ? o : J;
   }
+  int64_t *trips = reinterpret_cast<int64_t *>(&L);
+  if (lane == 0) trips[wave] = J;
+  __syncthreads();
+  J = trips[0] > trips[1] ? trips[0] : trips[1];
+  __syncthreads();
+  if (J == 0) return;  // every wave of the workgroup
 
-  // constant columns; the padding block of a 128-byte message
-  uint32_t(*rows)[kLpCols] = reinterpret_cast<uint32_t(*)[kLpCols]>(&L);
-  for (int x = threadIdx.x; x < kLpRows; x += blockDim.x)
-    rows[x][kWave] = x < 16 ? 1u - kShaDev.K[x] : 1u;
-  for (int x = threadIdx.x; x < 64; x += blockDim.x) {
-    L.c3[x][0] = kPad128Dev.kw[x];
-    L.c3[x][1] = 1u;
+  // the A lanes' rows
+  for (int x = threadIdx.x; x < 12; x += blockDim.x) L.kwm[kWave][x] = 1u;
+  for (int x = threadIdx.x; x < 52; x += blockDim.x) L.c1[kWave][x] = 1u;
+  for (int x = threadIdx.x; x < 68; x += blockDim.x) {
+    const uint32_t v = x == 1 ? 1u - kSha.H0[4] : (x == 2 ? 1u - kSha.H0[3] : 1u);
+    L.c2[0][kWave][x] = v;
+    L.c2[1][kWave][x] = v;
   }
 
-  // rounds lanes: role constants
+  if (sched_wave) {
+    // ---- schedule waves, two lanes per request
+    uint32_t kt[24];  // the lane's round constants, K[16 + 2k + parity]
+#pragma unroll
+    for (int k = 0; k < 24; ++k) {
+      kt[k] = odd ? kSha.K[17 + 2 * k] : kSha.K[16 + 2 * k];
+      asm("" : "+v"(kt[k]));  // kept in a register
+    }
+    // tokens one block ahead: raw holds block `held` (lanes without blocks
+    // read a valid dummy: some request of the workgroup has a block, so the
+    // token array holds at least 16 tokens)
+    u32x4 raw[4];
+    const int32_t *tp = nf > 0 ? q.tp : a.tokens;
+    const int64_t last = nf > 0 ? nf - 1 : 0;
+    int64_t held = 0;
+    load_raw(tp, raw);
+    {
+      uint32_t T0[16];
+      swap_block(raw, T0);
+      held = last < 1 ? last : 1;
+      load_raw(tp + 16 * held, raw);
+      // h_{j0-1}: the parent digest when resuming (in the second half of a
+      // boundary block's first message), sigma for a salted root
+      const bool resume = ok && q.j0 > 0, bnd0 = MODE == KVGOV_BOUNDARY && kb == 0;
+      const bool root = ok && q.salted_root;
+      uint32_t h[8];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) h[x] = root ? q.sig[x] : 0u;
+      if (resume && nf > 0) load_digest(a.parents + (int64_t)r * 32, h);
+      if (nf > 0) {
+        lp_prepare(T0, q.sig, bnd0 ? kLpBoundary : (resume || root ? kLpPlain : kLpFirst), L, 0,
+                   mine, odd, kt);
+        if (resume || root) {
+#pragma unroll
+          for (int x = 0; x < 8; ++x) {
+            if (bnd0) {
+              L.msg[mine][8 + x] = h[x];
+              L.kwm[mine][x] = h[x] + kSha.K[8 + x];
+            } else {
+              L.msg[mine][x] = h[x];
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t row1 = lds_addr(L.c1[mine] + (odd ? 1 : 0));
+    const uint32_t *msg = L.msg[mine] + (odd ? 1 : 0);
+    uint32_t w[16];
+#pragma unroll
+    for (int x = 8; x < 15; ++x) w[x] = msg[x];
+    w[15] = L.msg[mine][15];
+    for (int64_t j = 0; j < J; ++j) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) w[x] = msg[x];
+      if (MODE == KVGOV_BOUNDARY) {  // may hold h_{j-1}, which the rounds lanes wrote
+#pragma unroll
+        for (int x = 8; x < 15; ++x) w[x] = msg[x];
+        w[15] = L.msg[mine][15];
+      }
+      lp_pair4<0>(w, row1, kt);
+      __syncthreads();
+      lp_pair4<1>(w, row1, kt + 4);
+      __syncthreads();
+      lp_pair4<2>(w, row1, kt + 8);
+      __syncthreads();
+      lp_pair4<3>(w, row1, kt + 12);
+      __syncthreads();
+      lp_pair4<4>(w, row1, kt + 16);
+      __syncthreads();
+      lp_pair4<5>(w, row1, kt + 20);
+      __syncthreads();
+      // iteration j + 1: its tokens (block `held`, unless it is a padding
+      // iteration), and the load of the block after it
+      const bool pad = MODE == KVGOV_BOUNDARY && kb >= 0 && j == kb;
+      uint32_t Tn[16];
+      swap_block(raw, Tn);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!pad) held = held < last ? held + 1 : last;
+      load_raw(tp + 16 * held, raw);
+      __builtin_amdgcn_sched_barrier(0);
+      if (j + 1 < ni) {
+        const bool bnd = MODE == KVGOV_BOUNDARY && kb >= 0 && j + 1 == kb;
+        lp_prepare(Tn, q.sig, MODE != KVGOV_BOUNDARY ? kLpPlain
+                                                     : (pad ? kLpPad : (bnd ? kLpBoundary : kLpPlain)),
+                   L, (int)((j + 1) & 1), mine, odd, kt);
+      }
+      if (MODE != KVGOV_BOUNDARY) {  // this pair's own writes
+#pragma unroll
+        for (int x = 8; x < 15; ++x) w[x] = msg[x];
+        w[15] = L.msg[mine][15];
+      }
+      __syncthreads();
+    }
+    return;
+  }
+
+  // ---- rounds waves
+  const bool a_lane = odd;
   LpLane c;
   c.r1 = a_lane ? 2 : 6;
   c.r2 = a_lane ? 13 : 11;
   c.r3 = a_lane ? 22 : 25;
   c.m = a_lane ? ~0u : 0u;
-  const int col = a_lane ? kWave : mine;
-  const int col3 = a_lane ? 1 : 0;
+  const int row = a_lane ? kWave : mine;
   const int half = a_lane ? 0 : 4;  // state words held: a..d = 0..3, e..h = 4..7
-  uint32_t iv[4];                   // the initial value's words held by the lane
+  // feed-forward of C1: added on E lanes before C2, on A lanes two steps on
+  uint32_t fe[4], fa[4];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) iv[x] = a_lane ? kSha.H0[x] : kSha.H0[4 + x];
-
-  // schedule wave: tokens one block ahead (lanes without blocks read a
-  // valid dummy block: the loop runs only if some request of the workgroup
-  // has a block, so the token array holds at least 16 tokens)
-  u32x4 nxt[4];
-  const int32_t *tp = nf > 0 ? q.tp : a.tokens;
-  const int64_t nfl = nf > 0 ? nf : 1;
-  if (sched_wave && !idle && J > 0) {
-    load_raw(tp, nxt);
-    uint32_t T0[16];
-    take_block(nxt, T0, tp, 0, nfl);
-    if (nf > 0) {
-      // h_{j0-1}: the parent digest when resuming (in the second half of a
-      // boundary block's first message), sigma for a salted root
-      const bool resume = q.j0 > 0, bnd0 = MODE == KVGOV_BOUNDARY && kb == 0;
-      if (resume || q.salted_root) {
-        uint32_t h[8];
-        if (resume)
-          load_digest(a.parents + (int64_t)(a.order ? a.order[i] : i) * 32, h);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) (bnd0 ? L.hb : L.ha)[x][mine] = resume ? h[x] : q.sig[x];
-      }
-      if (PAIR)
-        lp_prepare_pair(T0, q.sig, !resume && !q.salted_root, bnd0, L, 0, mine, odd);
-      else
-        lp_prepare(T0, q.sig, !resume && !q.salted_root, bnd0, L, 0, lane);
-    }
+  for (int x = 0; x < 4; ++x) {
+    fe[x] = a_lane ? 0u : kSha.H0[4 + x];
+    fa[x] = a_lane ? kSha.H0[x] : 0u;
   }
-  __syncthreads();
-
-  uint32_t pre[16];  // schedule lanes: partial sums of the next block's first schedule
+  // step 1 of C1: E_1 = K_0 + W_0 + (h + Sigma1(e) + Ch(e, f, g) + d) on E
+  // lanes; Z of step 1 = K_1 + W_1 + g + c
+  constexpr uint32_t e0 = kSha.H0[4], f0 = kSha.H0[5], g0 = kSha.H0[6];
+  constexpr uint32_t c_e1 = kSha.K[0] + kSha.H0[7] + kSha.H0[3] +
+                            (c_rotr(e0, 6) ^ c_rotr(e0, 11) ^ c_rotr(e0, 25)) +
+                            ((e0 & f0) ^ (~e0 & g0));
+  constexpr uint32_t c_z1 = kSha.K[1] + g0 + kSha.H0[2];
+  const uint32_t x1_0 = a_lane ? kSha.H0[2] : e0;  // x1, x2 of step 1
+  const uint32_t x2_0 = a_lane ? kSha.H0[3] : f0;
+  const uint32_t am = lds_addr(L.kwm[row]), ac1 = lds_addr(L.c1[row]);
+  const uint32_t ac2_0 = lds_addr(L.c2[0][row]), ac2_1 = lds_addr(L.c2[1][row]);
+  uint32_t sg[4];  // the lane's half of the salt (boundary mode)
 #pragma unroll
-  for (int x = 0; x < 16; ++x) pre[x] = 0;
+  for (int x = 0; x < 4; ++x) sg[x] = MODE != KVGOV_BOUNDARY ? 0u : (a_lane ? q.sig[x] : q.sig[4 + x]);
+  uint8_t *out = ok ? q.out + half * 4 : nullptr;
+  uint32_t kd[4] = {c_e1, c_z1, kSha.K[2], kSha.K[3]};  // added to the partner's words
+#pragma unroll
+  for (int x = 0; x < 4; ++x) asm("" : "+v"(kd[x]));  // in registers: one DPP add each
+
+  __syncthreads();  // the first iteration's tables
+  // st: words 0..7 of the first message (A lanes 0..3, E lanes 4..7)
+  uint32_t st[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) st[x] = L.msg[mine][half + x];
+  uint32_t hold[4] = {0, 0, 0, 0};  // the boundary block's state (boundary mode)
+  uint32_t k8[4];  // the lane's half of K[8..15] (boundary mode)
+#pragma unroll
+  for (int x = 0; x < 4; ++x) k8[x] = a_lane ? kSha.K[8 + x] : kSha.K[12 + x];
+  // C1's start from words 0..7 of its message (E lanes take a..d from the partner)
+  uint32_t kw[8], x0_1, z_1;
+  const auto start = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t o = lp_partner(st[t]) + kd[t];
+      if (t == 0) x0_1 = a_lane ? kSha.H0[1] : o;
+      if (t == 1) z_1 = o;
+      if (t >= 2) kw[t] = a_lane ? 1u : o;
+      kw[4 + t] = a_lane ? 1u : st[t] + kSha.K[4 + t];
+    }
+  };
+  start();
   for (int64_t j = 0; j < J; ++j) {
-    const bool act = j < nf;
-    const bool next = j + 1 < nf;
-    const int cb = (int)(j & 1), nb = cb ^ 1;
-    // boundary blocks take a third compression (workgroup-uniform decision)
-    bool third = false;
+    const uint32_t ac2 = (j & 1) ? ac2_1 : ac2_0;
+    uint32_t ring[4] = {x0_1, x1_0, x2_0, 0}, z = z_1, s[4], x[4], n0, n1;
+    lp_quad p[3];
+    lp_c1(ring, z, kw, kSha.H0[0], c, am, ac1, ac2, p);
+    s[0] = ring[1] + fe[0];
+    s[1] = ring[2] + fe[1];
+    s[2] = ring[3] + fe[2];
+    s[3] = ring[0] + fe[3];
     if (MODE == KVGOV_BOUNDARY) {
-      const bool mine_bnd = (j < own.nf && j == own.kr) || (j < other.nf && j == other.kr);
-      third = __any(mine_bnd);
+      const bool pad = kb >= 0 && j == kb + 1;
+      if (__any(pad)) {
+        uint32_t sp[4], zp;
+        lp_pad(hold, p[0][0], a_lane, sp, zp);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s[t] = pad ? sp[t] : s[t];
+        z = pad ? zp : z;
+      }
     }
-
-    if (!sched_wave) {
-      // ---- rounds waves.  Step i of a group takes the kw of step i + 1 (the
-      // next step's z starts early).  Each barrier comes C steps before the
-      // first word it releases is taken, so that the LDS reads after it are
-      // covered by those steps.
-      constexpr int C = KVGOV_LP_COVER;
-      uint32_t s[4], st[4], wa[16], z = 0;
-      uint32_t kw[64];
-      if (act) {
+    lp_c2(s, z, p, fa, c, ac2, x, n0, n1);
+    st[0] = (a_lane ? n1 : x[0]) + s[0];
+    st[1] = (a_lane ? n0 : x[1]) + s[1];
+    st[2] = (a_lane ? x[0] : x[2]) + s[2];
+    st[3] = (a_lane ? x[1] : x[3]) + s[3] + fa[3];
+    // h_j: words 0..7 of the next iteration's first message, or 8..15 when
+    // that is the boundary block (words 0..7 are then the salt's)
+    const bool hashed = MODE != KVGOV_BOUNDARY || j != kb;  // st is a digest
+    if (j < ni && hashed) {
+      *reinterpret_cast<u32x4 *>(out) = u32x4{bswap(st[0]), bswap(st[1]), bswap(st[2]), bswap(st[3])};
+      out += 32;
+    }
+    if (MODE == KVGOV_BOUNDARY) {
+      const bool bnd = kb >= 0 && j + 1 == kb;
+      lp_quad kw8;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          kw[t] = kSha.K[t] + L.ha[t][col];
-          kw[8 + t] = kSha.K[8 + t] + L.hb[t][col];
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x) s[x] = a_lane ? (x < 2 ? iv[x + 2] : 0u) : iv[x];
-        z = lp_z0(s, kw[0], c);
-        lp_head(s, z, kw[1], kw[2], c, iv[1], iv[0], a_lane);
-        lp_steps<6>(s, z, kw + 2, kw[8], c);  // steps 2..7
-        lp_steps<8 - C>(s, z, kw + 8, kw[16 - C], c);
+      for (int t = 0; t < 4; ++t) {
+        hold[t] = hashed ? hold[t] : st[t];
+        kw8[t] = st[t] + k8[t];
       }
-      // steps 16 - C .. 63, one barrier per schedule group
-      lp_round_groups<0>(s, z, kw, wa, L.c1b, L.c2[cb], col, c, act);
-      if (act) {
-        lp_tail(s, z, c, a_lane);
+      *reinterpret_cast<lp_quad *>(bnd ? L.kwm[mine] + half : L.kwm[kWave + 1]) = kw8;
+      *reinterpret_cast<lp_quad *>(L.msg[mine] + half + (bnd ? 8 : 0)) =
+          lp_quad{st[0], st[1], st[2], st[3]};
 #pragma unroll
-        for (int x = 0; x < 4; ++x) st[x] = iv[x] + s[x];
-        // second compression
-        lp_compress_rows(st, wa, L.c2[cb], col, c, a_lane);
-        if (MODE == KVGOV_BOUNDARY && third) {
-          // third compression (the boundary block's padding), for all lanes;
-          // only boundary requests keep its result
-          uint32_t st3[4], k3[16];
-#pragma unroll
-          for (int x = 0; x < 4; ++x) st3[x] = st[x];
-          lp_load16(k3, L.c3, 0, col3);
-          lp_compress_rows(st3, k3, L.c3, col3, c, a_lane);
-          const bool bnd = j == kb;
-#pragma unroll
-          for (int x = 0; x < 4; ++x) st[x] = bnd ? st3[x] : st[x];
-        }
-        // h_j: the next block's first message words 0..7 (plain), or 8..15
-        // (the next block is the boundary block)
-        const bool next_bnd = MODE == KVGOV_BOUNDARY && j + 1 == kb;
-        uint32_t(*hrows)[kLpCols] = next_bnd ? L.hb : L.ha;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) hrows[half + x][mine] = st[x];
-        u32x4 *dst = reinterpret_cast<u32x4 *>(q.out + j * 32 + half * 4);
-        *dst = u32x4{bswap(st[0]), bswap(st[1]), bswap(st[2]), bswap(st[3])};
-      }
-      __syncthreads();
-    } else if (PAIR) {
-      // ---- schedule waves, two lanes per request
-      uint32_t w[16];
-      if (act) {
-        uint32_t m[16];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          m[x] = L.ha[x][mine];
-          m[8 + x] = L.hb[x][mine];
-        }
-        lp_pair_window(m, w, odd);
-      }
-      lp_pair_groups<0>(w, L.c1b, mine, odd, act);
-      {
-        // block j + 1's tokens, and the load of block j + 2
-        uint32_t Tn[16];
-        const int64_t jn = j + 1 < nfl ? j + 1 : nfl - 1;
-        take_block(nxt, Tn, tp, jn, nfl);
-        if (next) {
-          const bool bnd_next = MODE == KVGOV_BOUNDARY && j + 1 == kb;
-          lp_prepare_pair(Tn, q.sig, false, bnd_next, L, nb, mine, odd);
-        }
-      }
-      __syncthreads();
+      for (int t = 0; t < 4; ++t) st[t] = bnd ? sg[t] : st[t];
     } else {
-      // ---- schedule wave (an idle wave only meets the barriers)
-      uint32_t w[16];
-      if (act && !idle) {
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          w[x] = L.ha[x][lane];
-          w[8 + x] = L.hb[x][lane];
-        }
-      }
-      // the partial sums hold for block j unless it is a chain's first
-      // block or some request's boundary block
-      lp_sched_groups<0>(w, L.c1b, lane, act && !idle, pre, j > 0 && !third);
-      if (!idle) {
-        // block j + 1's tokens, and the load of block j + 2
-        uint32_t Tn[16];
-        const int64_t jn = j + 1 < nfl ? j + 1 : nfl - 1;
-        take_block(nxt, Tn, tp, jn, nfl);
-        if (next) {
-          const bool bnd_next = MODE == KVGOV_BOUNDARY && j + 1 == kb;
-          lp_prepare(Tn, q.sig, false, bnd_next, L, nb, lane);
-          lp_presum(Tn, pre);
-        }
-      }
-      __syncthreads();
+      *reinterpret_cast<lp_quad *>(L.msg[mine] + half) = lp_quad{st[0], st[1], st[2], st[3]};
     }
+    // while the LDS writes complete
+    start();
+#pragma unroll
+    for (int t = 2; t < 8; ++t) asm volatile("" : "+v"(kw[t]));
+    __syncthreads();
   }
 }
 
-template <int MODE, bool PAIR>
+template <int MODE>
 __global__ __launch_bounds__(4 * kWave) void k_chains_lp(ChainArgs a) {
-  __shared__ LpLds L;
-  lp_group<MODE, PAIR>(a, blockIdx.x, L);
+  __shared__ __align__(16) LpLds L;
+  lp_group<MODE>(a, blockIdx.x, L);
 }
 
 // Large ordered batches: the first `lp_groups` workgroups run the lane-pair
 // path on the longest requests (the batch is ordered longest first), so
-// that the longest chains finish ~1.4x sooner; the remaining workgroups run
+// that the longest chains finish sooner; the remaining workgroups run
 // one lane per request on the rest.  Both in one launch, 256 lanes per
 // workgroup.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_chains_mixed(ChainArgs a, int32_t lp_groups) {
-  __shared__ LpLds L;
+  __shared__ __align__(16) LpLds L;
   if ((int32_t)blockIdx.x < lp_groups)
-    lp_group<MODE, true>(a, blockIdx.x, L);
+    lp_group<MODE>(a, blockIdx.x, L);
   else
     single_chain<MODE>(a, lp_groups * kWave + ((int32_t)blockIdx.x - lp_groups) * 256 +
                               (int32_t)threadIdx.x);
@@ -1407,7 +1354,7 @@ static size_t lp_lds_reserve(int per_cu) {
 }
 
 // Lane-pair workgroups per CU for a batch of n requests: the lane-pair
-// kernel shortens every chain but needs three waves per 64 requests, so it
+// kernel shortens every chain but needs four waves per 64 requests, so it
 // runs while the batch fits in one or two workgroups per CU (latency-bound
 // batches); larger batches keep every SIMD busy with the single-wave kernel
 // (0).
@@ -1654,28 +1601,17 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
   const int slots = lp_slots(n);
   std::unique_lock<std::mutex> lk;  // held while the ordered launch is enqueued
   if (slots) {
-    // lane pairs: two rounds waves and a schedule wave per 64 requests, one
-    // or two workgroups per CU; every request of the batch is resident from
-    // the start, so the order of the requests does not matter
-    // (one workgroup per CU: a fourth wave, which shares the schedule;
-    // two: three waves, the schedule on one)
+    // lane pairs: two rounds waves and two schedule waves per 64 requests,
+    // one or two workgroups per CU; every request of the batch is resident
+    // from the start, so the order of the requests does not matter
     const dim3 grid((unsigned)ceil_div(n, kWave));
     const size_t lds = lp_lds_reserve(slots);
     if (ev_start && hipEventRecord(ev_start, s) != hipSuccess) return KVGOV_E_HIP;
-    if (slots == 1) {
-      const dim3 block(4 * kWave);
-      switch (mode) {
-        case KVGOV_NONE: hipLaunchKernelGGL((k_chains_lp<KVGOV_NONE, true>), grid, block, lds, s, a); break;
-        case KVGOV_ROOT: hipLaunchKernelGGL((k_chains_lp<KVGOV_ROOT, true>), grid, block, lds, s, a); break;
-        default: hipLaunchKernelGGL((k_chains_lp<KVGOV_BOUNDARY, true>), grid, block, lds, s, a); break;
-      }
-    } else {
-      const dim3 block(kLpThreads);
-      switch (mode) {
-        case KVGOV_NONE: hipLaunchKernelGGL((k_chains_lp<KVGOV_NONE, false>), grid, block, lds, s, a); break;
-        case KVGOV_ROOT: hipLaunchKernelGGL((k_chains_lp<KVGOV_ROOT, false>), grid, block, lds, s, a); break;
-        default: hipLaunchKernelGGL((k_chains_lp<KVGOV_BOUNDARY, false>), grid, block, lds, s, a); break;
-      }
+    const dim3 block(4 * kWave);
+    switch (mode) {
+      case KVGOV_NONE: hipLaunchKernelGGL(k_chains_lp<KVGOV_NONE>, grid, block, lds, s, a); break;
+      case KVGOV_ROOT: hipLaunchKernelGGL(k_chains_lp<KVGOV_ROOT>, grid, block, lds, s, a); break;
+      default: hipLaunchKernelGGL(k_chains_lp<KVGOV_BOUNDARY>, grid, block, lds, s, a); break;
     }
   } else {
     // More than two lane-pair workgroups per CU: the batch has at least as

@@ -175,6 +175,25 @@ def test_chains_long_with_scattered_boundaries(mode):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("n_req", [1, 63, 64, 65, 129, 1092])
+def test_chains_every_boundary_block(n_req):
+    """Every boundary block of chains of 1..13 blocks, and past the last one,
+    side by side in workgroups: a request takes one iteration more than its
+    blocks for its boundary block's padding, at an iteration of its own."""
+    nf = [f for f in range(1, 14) for _ in range(f + 1)] * 11
+    k = [j for f in range(1, 14) for j in range(f + 1)] * 11
+    order = np.random.default_rng(47).permutation(len(nf))[:n_req]
+    g = np.random.default_rng(48)
+    lens = np.array(nf)[order] * 16 + g.integers(0, 16, order.size)
+    b = ragged(49, lens, P=5)
+    b.boundary_tok[:] = np.minimum(np.array(k)[order] * 16 + g.integers(0, 16, order.size), lens)
+    Kb, ids = secret(13, 5)
+    got = gpu_chains(b, K.salts(Kb, dev(ids)), W.BOUNDARY).cpu().numpy()
+    want = O.hash_chains(b.tokens, b.tok_offsets, b.principal, O.salts(Kb, ids), W.BOUNDARY,
+                         b.boundary_tok)
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("n_req", [3000, 40000])
 def test_chains_permutation_invariance(n_req):
     """A request's digests depend only on its own tokens, principal and
