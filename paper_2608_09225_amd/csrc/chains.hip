@@ -130,34 +130,44 @@ __device__ __forceinline__ void compress_rolled(uint32_t st[8], uint32_t w[16]) 
 // ---------------------------------------------------------------------------
 
 struct SaltArgs {
-  uint32_t key[16];  // K zero-padded to 64 bytes, as big-endian words
+  uint32_t inner[8], outer[8];  // states after K ^ ipad and K ^ opad
   const uint8_t *ids;
   int32_t id_len;
   int32_t P;
   uint8_t *salts;
 };
 
+typedef uint32_t u32_any __attribute__((aligned(1)));  // a dword at any byte
+
 // sigma_p = H((K ^ opad) || H((K ^ ipad) || id_p))   (RFC 2104 over SHA-256)
+// The first compression of either hash takes only K, so the states after
+// them are the caller's (two compressions on the host): a salt is then the
+// id's blocks and one more, in sequence, and a launch of one wave is
+// nothing but that sequence.  64 ids of 32 bytes: 17.9 us with all four
+// compressions here and the ids read by bytes, 9.2 us so.
 __global__ __launch_bounds__(64) void k_salts(SaltArgs a) {
   const int p = blockIdx.x * kWave + threadIdx.x;
   if (p >= a.P) return;
   const uint8_t *id = a.ids + (int64_t)p * a.id_len;
   const int L = a.id_len;
   uint32_t st[8], w[16];
-  set_iv(st);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) w[i] = a.key[i] ^ 0x36363636u;
-  compress(st, w);
+  for (int i = 0; i < 8; ++i) st[i] = a.inner[i];
   const int nblk = (L + 9 + 63) / 64;  // id, 0x80, 64-bit length
   for (int blk = 0; blk < nblk; ++blk) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
+      const int at = blk * 64 + 4 * i;
       uint32_t word = 0;
+      if (at + 4 <= L) {
+        word = bswap(*reinterpret_cast<const u32_any *>(id + at));
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int pos = blk * 64 + 4 * i + q;
-        const uint32_t byte = pos < L ? (uint32_t)id[pos] : (pos == L ? 0x80u : 0u);
-        word = (word << 8) | byte;
+        for (int q = 0; q < 4; ++q) {
+          const int pos = at + q;
+          const uint32_t byte = pos < L ? (uint32_t)id[pos] : (pos == L ? 0x80u : 0u);
+          word = (word << 8) | byte;
+        }
       }
       w[i] = word;
     }
@@ -169,12 +179,11 @@ __global__ __launch_bounds__(64) void k_salts(SaltArgs a) {
     compress(st, w);
   }
   uint32_t o[8];
-  set_iv(o);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) w[i] = a.key[i] ^ 0x5c5c5c5cu;
-  compress(o, w);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) w[i] = st[i];
+  for (int i = 0; i < 8; ++i) {
+    o[i] = a.outer[i];
+    w[i] = st[i];
+  }
   w[8] = 0x80000000u;
 #pragma unroll
   for (int i = 9; i < 15; ++i) w[i] = 0;
@@ -1493,6 +1502,31 @@ const char *kvgov_strerror(int code) {
 
 int kvgov_version(void) { return (1 << 16) | 0; }
 
+// One compression from the initial value on the host (salts: the blocks that
+// hold K alone).  w is overwritten.
+static void host_compress_iv(uint32_t out[8], uint32_t w[16]) {
+  uint32_t s[8];
+  for (int i = 0; i < 8; ++i) s[i] = kSha.H0[i];
+  for (int t = 0; t < 64; ++t) {
+    if (t >= 16) {
+      const uint32_t a = w[(t - 2) & 15], b = w[(t - 15) & 15];
+      w[t & 15] += (c_rotr(a, 17) ^ c_rotr(a, 19) ^ (a >> 10)) + w[(t - 7) & 15] +
+                   (c_rotr(b, 7) ^ c_rotr(b, 18) ^ (b >> 3));
+    }
+    const uint32_t e = s[4], a = s[0];
+    const uint32_t t1 = s[7] + (c_rotr(e, 6) ^ c_rotr(e, 11) ^ c_rotr(e, 25)) +
+                        ((e & s[5]) ^ (~e & s[6])) + kSha.K[t] + w[t & 15];
+    const uint32_t t2 = (c_rotr(a, 2) ^ c_rotr(a, 13) ^ c_rotr(a, 22)) +
+                        ((a & s[1]) ^ (a & s[2]) ^ (s[1] & s[2]));
+    for (int i = 7; i > 0; --i) s[i] = s[i - 1];
+    s[4] += t1;
+    s[0] = t1 + t2;
+  }
+  for (int i = 0; i < 8; ++i) out[i] = kSha.H0[i] + s[i];
+  volatile uint32_t *wipe = s;
+  for (int i = 0; i < 8; ++i) wipe[i] = 0;
+}
+
 int kvgov_salts(const uint8_t *K, size_t K_len, const uint8_t *principal_ids, int32_t id_len,
                 int32_t P, uint8_t *salts, void *stream) {
   if (!K || K_len == 0 || P < 0 || id_len < 0 || id_len > KVGOV_MAX_ID_BYTES)
@@ -1502,7 +1536,12 @@ int kvgov_salts(const uint8_t *K, size_t K_len, const uint8_t *principal_ids, in
   if (P > 0 && (reinterpret_cast<uintptr_t>(salts) & 3)) return KVGOV_E_INVAL;
   if (P == 0) return KVGOV_OK;
   SaltArgs a{};
-  for (size_t i = 0; i < K_len; ++i) a.key[i / 4] |= (uint32_t)K[i] << (24 - 8 * (i % 4));
+  uint32_t key[16] = {}, w[16];
+  for (size_t i = 0; i < K_len; ++i) key[i / 4] |= (uint32_t)K[i] << (24 - 8 * (i % 4));
+  for (int i = 0; i < 16; ++i) w[i] = key[i] ^ 0x36363636u;
+  host_compress_iv(a.inner, w);
+  for (int i = 0; i < 16; ++i) w[i] = key[i] ^ 0x5c5c5c5cu;
+  host_compress_iv(a.outer, w);
   a.ids = principal_ids;
   a.id_len = id_len;
   a.P = P;
@@ -1510,8 +1549,10 @@ int kvgov_salts(const uint8_t *K, size_t K_len, const uint8_t *principal_ids, in
   hipLaunchKernelGGL(k_salts, dim3((unsigned)ceil_div(P, kWave)), dim3(kWave), 0,
                      as_stream(stream), a);
   const int rc = launch_status();
-  volatile uint32_t *wipe = a.key;  // the kernel argument was copied at launch
-  for (int i = 0; i < 16; ++i) wipe[i] = 0;
+  // the kernel argument was copied at launch
+  volatile uint32_t *wipe[4] = {key, w, a.inner, a.outer};
+  for (int k = 0; k < 4; ++k)
+    for (int i = 0; i < (k < 2 ? 16 : 8); ++i) wipe[k][i] = 0;
   return rc;
 }
 
