@@ -349,11 +349,10 @@ int kvgov_cache_admit(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
  * keep reading one key per probe), in stream order.  n_kept / n_erased: host
  * out or NULL; non-NULL waits for `stream`, stores the keys kept / the
  * distinct present keys erased, and returns any latched error.
- * Scratch: 40 * (slots + 1) bytes + 2 KiB of the stream's scratch (see the
- * notes at the top).  Errors: KVGOV_E_INVAL, KVGOV_E_NOMEM,
+ * Scratch: 40 * slots bytes + slots / 256 + 10 KiB of the stream's scratch
+ * (see the notes at the top).  Errors: KVGOV_E_INVAL, KVGOV_E_NOMEM,
  * KVGOV_E_UNSUPPORTED (as above, or 2^32 - 1 calls since the last clear),
- * KVGOV_E_HIP, KVGOV_E_DEVICE; KVGOV_E_INTERNAL latched if the compaction
- * counted more keys than the table's slots (never expected).
+ * KVGOV_E_HIP, KVGOV_E_DEVICE.
  */
 int kvgov_cache_set_recency(kvgov_cache *c, int32_t on);
 int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *stream);

@@ -64,6 +64,7 @@ __global__ __launch_bounds__(256) void k_cache_fill(u32x4 *keys, unsigned long l
     }
     if (threadIdx.x == 0) {
       m->exported = 0;
+      m->erased = 0;
       m->ones_tag = 0;
       m->ones_rank = 0;
       m->status = 0;
@@ -76,6 +77,13 @@ __global__ __launch_bounds__(256) void k_cache_fill(u32x4 *keys, unsigned long l
     tags[s] = 0;
     if (rank) rank[s] = 0;
   }
+}
+
+// The depth of a key: its row within its request (clamped; only malformed
+// interior offsets put it outside [0, n_blocks)).
+__device__ __forceinline__ uint32_t row_depth(int64_t jj, int64_t n_blocks) {
+  const int64_t most = n_blocks < 0x7FFFFFFF ? n_blocks : 0x7FFFFFFF;
+  return (uint32_t)(jj < 0 ? 0 : (jj > most ? most : jj));
 }
 
 // Consecutive keys per wave chunk of k_chunk_insert.  Longer chunks mean fewer
@@ -175,9 +183,7 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
         if (r >= 1 && jj >= 0 && jj < b_r - b_p && b_p + jj >= lo)
           dup = key_eq(key, load_key(hashes + (b_p + jj) * 32));
         uint32_t code = kCodeDup;
-        // the depth of the key: its row within its request (clamped; only
-        // malformed interior offsets put it outside [0, 2^31))
-        const uint32_t depth = (uint32_t)(jj < 0 ? 0 : (jj > 0x7FFFFFFF ? 0x7FFFFFFF : jj));
+        const uint32_t depth = row_depth(jj, n_blocks);
         if (!dup) added += insert_key<ADMIT>(t, key, f, lo, hashes, epoch, &code, depth);
         if (ADMIT) codes[f] = code;
       }
@@ -204,21 +210,25 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 //     same key: the group's first lane inserts the request's first row
 //     before the others start, and if the slot's tag names an earlier row
 //     (the request that claimed the key, mostly the earliest one, since
-//     workgroups start in request order) the group compares against the
-//     rows that follow it.  Requests of one principal share the
+//     workgroups start in request order; for a key of an earlier call, the
+//     request that renewed its tag in this one) the group compares against
+//     the rows that follow it.  Requests of one principal share the
 //     root-salted prefix but are rarely adjacent.  (Lowering the tag to the
 //     earliest first row with an atomic minimum, as admission does, measured
 //     slower: 35.7 -> 36.6 us for the paper-shaped root-mode insert.)
-// On a table that tracks recency only the first comparison is made (the
-// second one's row may lie past the end of that request, at another depth,
-// and a key's rank holds its smallest depth).
+// A key's rank holds its smallest depth, so on a table that tracks recency the
+// second comparison stops at the end of that request, which a search of the
+// offsets finds (the row past it lies in another request, at another depth).
+// Without the second comparison, every request's prefix rows read and raised
+// their keys' words: 66 us for the paper-shaped root-mode batch, 37 with it
+// (46 for a second batch, whose prefix keys are of an earlier call).
 // Each request inserts the rows [blk_offsets[r], blk_offsets[r + 1]) cut to
 // the batch [blk_offsets[0], blk_offsets[n]); requests whose offsets are out
 // of order insert nothing.  With non-decreasing offsets that is every row
 // once.  Otherwise every row of the batch still lies in some request's
 // range (take the last r with blk_offsets[r] <= row), so the table receives
 // exactly the batch's keys.
-template <int G>
+template <int G, bool TRACK>
 __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *hashes,
                                                     const int64_t *blk_offsets, int32_t n,
                                                     int64_t n_blocks, uint32_t epoch) {
@@ -246,7 +256,7 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
     const int64_t n_p = r >= 1 && b_p >= lo && b_p <= b_r ? b_r - b_p : 0;
     if (b0 < b1) {
       // first row, by the group's first lane
-      int64_t g0 = -1;
+      int64_t g0 = -1, g1 = hi;  // the earlier request's rows
       if (sub == 0) {
         const int64_t jj = b0 - b_r;
         const Key key = load_key(hashes + b0 * 32);
@@ -254,21 +264,30 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
         if (!dup) {
           uint32_t code;
           unsigned long long claim = 0;
-          added += insert_key<false>(t, key, b0, lo, hashes, epoch, &code, (uint32_t)jj, &claim);
+          added += insert_key<false>(t, key, b0, lo, hashes, epoch, &code,
+                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim, true);
           const int64_t c = lo + (int64_t)(claim & 0xFFFFFFFFull) - 1;
-          if (!t.track && jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0)
+          if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0) {
             g0 = c;
+            if (TRACK) {
+              const int32_t q = find_request(blk_offsets, n, c);
+              g1 = blk_offsets[q + 1] < hi ? blk_offsets[q + 1] : hi;
+              if (blk_offsets[q] != c) g0 = -1;
+            }
+          }
         }
       }
       g0 = __shfl(g0, base, 64);
+      if (TRACK) g1 = __shfl(g1, base, 64);
       for (int64_t f = b0 + 1 + sub; f < b1; f += G) {
         const int64_t jj = f - b_r;
         const Key key = load_key(hashes + f * 32);
         bool dup = jj < n_p && key_eq(key, load_key(hashes + (b_p + jj) * 32));
-        if (!dup && g0 >= 0) dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
+        if (!dup && g0 >= 0 && (!TRACK || g0 + jj < g1)) dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
         uint32_t code;
-        const uint32_t depth = (uint32_t)(jj > 0x7FFFFFFF ? 0x7FFFFFFF : jj);
-        if (!dup) added += insert_key<false>(t, key, f, lo, hashes, epoch, &code, depth);
+        if (!dup)
+          added += insert_key<false>(t, key, f, lo, hashes, epoch, &code,
+                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth);
       }
     }
   }
@@ -449,35 +468,290 @@ __global__ __launch_bounds__(256) void k_export(TableView t, uint8_t *out, int64
 // ---------------------------------------------------------------------------
 
 // Eviction keeps every key whose recency word (newer stamp first, then
-// smaller depth) is at least a threshold chosen by a radix select over the
-// 64-bit words, 8 bits per pass.
+// smaller depth) is at least a threshold.  Only the bits that differ between
+// the table's words decide: the low bits of the stamp up to the highest that
+// differs and the same of the depth half, put together (order kept), are a
+// number of few bits: 2 calls of requests of up to 200 rows make 2 + 8.  A
+// histogram of the top kRankDigit of these bits finds the digit at which the
+// kept count crosses the budget, the next pass takes the next bits of the
+// words with that digit, and so on.  Words of 0 (keys of calls that did not
+// track) are the lowest class and take no part; their number is the table's
+// less the others.
+//
+// One launch per pass: the workgroup that adds its counts last takes the
+// decision.  (As eight passes of eight bits of the whole word, two launches
+// each, over words gathered into a dense array, the select of a 2^20-slot
+// table took 180 us of a 240 us evict; now 27 of 53.)
+constexpr int kRankDigit = 11;
+constexpr int kRankBins = 1 << kRankDigit;
+constexpr int kRankLanes = 16;  // addresses the range's atomics are spread over
+constexpr int kRankThreads = 1024;
+static_assert(kRankBins == 2 * kRankThreads, "two bins per thread in the decision");
 
 struct SelectState {
-  unsigned long long prefix;     // rank bits decided so far
-  unsigned long long threshold;  // keep rank >= threshold once done
-  long long budget;              // keys still allowed below the decided part
-  unsigned long long kept;       // keys copied out by the compaction
-  unsigned long long erased;     // keys marked by erase
-  unsigned long long n_dense;    // recency words gathered for the select
-  unsigned long long lo, hi;     // their minimum and maximum
-  int32_t level;                 // 8-bit digits decided
+  unsigned long long any[kRankLanes];   // or of the words
+  unsigned long long all[kRankLanes];   // and of the words
+  unsigned long long used[kRankLanes];  // words other than 0
+  unsigned long long prefix;            // digits decided so far
+  unsigned long long threshold;         // keep rank >= threshold once done
+  unsigned long long budget;            // keys still allowed below the decided part
+  unsigned long long ones_rank;         // the all-0xFF key's, if it is kept
+  int32_t bits;                         // bits left to decide (kRankStart: none decided yet)
   int32_t done;
+  int32_t ones_keep;
+  uint32_t arrived;                     // workgroups that have added their counts
+};
+constexpr int32_t kRankStart = 255;
+
+__global__ __launch_bounds__(256) void k_select_init(SelectState *st, unsigned int *hist,
+                                                     long long budget, int erase, CacheMeta *m) {
+  if (threadIdx.x < kRankLanes) {
+    st->any[threadIdx.x] = 0;
+    st->all[threadIdx.x] = ~0ull;
+    st->used[threadIdx.x] = 0;
+  }
+  if (threadIdx.x == 0) {
+    st->prefix = 0;
+    st->threshold = 0;  // erase: keep every key not marked
+    st->budget = (unsigned long long)budget;
+    st->ones_rank = 0;
+    st->bits = kRankStart;
+    st->done = erase;
+    st->ones_keep = 0;
+    st->arrived = 0;
+    m->erased = 0;
+  }
+  if (!erase)
+    for (int i = threadIdx.x; i < kRankBins; i += blockDim.x) hist[i] = 0;
+}
+
+__device__ __forceinline__ unsigned long long wave_or(unsigned long long v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v |= __shfl_xor(v, d, 64);
+  return v;
+}
+__device__ __forceinline__ unsigned long long wave_and(unsigned long long v) {
+  return ~wave_or(~v);
+}
+
+// The recency words' bits and number.  An empty slot's word is 0, so the tags
+// are not read.
+__global__ __launch_bounds__(256) void k_rank_range(TableView t, SelectState *st) {
+  const int64_t slots = (int64_t)t.mask + 1;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  unsigned long long any = 0, all = ~0ull, used = 0;
+  for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots; s += stride) {
+    const unsigned long long r = t.rank[s];
+    any |= r;
+    all &= r ? r : ~0ull;
+    used += r ? 1 : 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && t.meta->ones_present && t.meta->ones_rank) {
+    any |= t.meta->ones_rank;
+    all &= t.meta->ones_rank;
+    ++used;
+  }
+  __shared__ unsigned long long w[3][4];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) used += __shfl_xor(used, d, 64);
+  any = wave_or(any);
+  all = wave_and(all);
+  if ((threadIdx.x & 63) == 0) {
+    w[0][threadIdx.x >> 6] = any;
+    w[1][threadIdx.x >> 6] = all;
+    w[2][threadIdx.x >> 6] = used;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  used = w[2][0] + w[2][1] + w[2][2] + w[2][3];
+  if (!used) return;
+  const int l = blockIdx.x % kRankLanes;
+  atomicOr(&st->any[l], w[0][0] | w[0][1] | w[0][2] | w[0][3]);
+  atomicAnd(&st->all[l], w[1][0] & w[1][1] & w[1][2] & w[1][3]);
+  atomicAdd(&st->used[l], used);
+}
+
+// Which bits of the recency words differ, as the widths of the two halves.
+struct RankBits {
+  unsigned long long common;  // the bits above them, equal in every word
+  unsigned long long used;    // words other than 0
+  int cs, cd;                 // low bits of the stamp and of the depth half that decide
+  __device__ __forceinline__ unsigned long long pack(unsigned long long r) const {
+    return ((r >> 32) & ((1ull << cs) - 1)) << cd | (r & ((1ull << cd) - 1));
+  }
+  __device__ __forceinline__ unsigned long long unpack(unsigned long long c) const {
+    return common | (c >> cd) << 32 | (c & ((1ull << cd) - 1));
+  }
 };
 
-constexpr int kRankBins = 256;
-constexpr int kCompactItems = 16;  // slots per thread per block step
+__device__ __forceinline__ RankBits rank_bits(const SelectState *st) {
+  unsigned long long any = 0, all = ~0ull;
+  RankBits b;
+  b.used = 0;
+#pragma unroll
+  for (int i = 0; i < kRankLanes; ++i) {
+    any |= st->any[i];
+    all &= st->all[i];
+    b.used += st->used[i];
+  }
+  const unsigned long long vary = any & ~all;
+  const uint32_t hi = (uint32_t)(vary >> 32), lo = (uint32_t)vary;
+  b.cs = hi ? 32 - __builtin_clz(hi) : 0;
+  b.cd = lo ? 32 - __builtin_clz(lo) : 0;
+  b.common = any & ~((((1ull << b.cs) - 1) << 32) | ((1ull << b.cd) - 1));
+  return b;
+}
 
-// Exclusive prefix of v over the workgroup (256 threads) and the total; one
-// global atomic on `counter` per call reserves the workgroup's range, whose
-// start is returned in *base.  Several hundred workgroups hitting one counter
-// once per 4096 slots cost little; once per wave they serialised (~200 us
-// for a 2^20-slot table).
-__device__ __forceinline__ uint32_t block_reserve(uint32_t v, unsigned long long *counter,
-                                                  unsigned long long *base) {
+// The next digit: its histogram over the words that match the decided
+// digits, and, in the workgroup that arrives last, the digit at which the
+// kept count crosses the budget (keys with a higher digit are kept).  Leaves
+// the histogram and the arrival count cleared for the next pass.
+__global__ __launch_bounds__(kRankThreads) void k_rank_select(TableView t, SelectState *st,
+                                                              unsigned int *hist) {
+  __shared__ unsigned int h[kRankBins];
+  __shared__ unsigned long long above[kRankThreads / 64];
+  __shared__ int last;
+  if (st->done) return;
+  const int tid = threadIdx.x;
+  const RankBits rb = rank_bits(st);
+  const int left = st->bits == kRankStart ? rb.cs + rb.cd : st->bits;
+  const int width = left < kRankDigit ? left : kRankDigit;
+  const int shift = left - width;
+  const unsigned long long prefix = st->prefix, budget = st->budget;
+  const int bins = 1 << width;
+  for (int i = tid; i < bins; i += kRankThreads) h[i] = 0;
+  __syncthreads();
+  const auto count = [&](unsigned long long r) {
+    if (!r) return;
+    const unsigned long long c = rb.pack(r) >> shift;
+    if ((c >> width) == prefix) atomicAdd(&h[c & (bins - 1)], 1u);
+  };
+  const int64_t slots = (int64_t)t.mask + 1;
+  const int64_t stride = (int64_t)gridDim.x * kRankThreads;
+#pragma unroll 4
+  for (int64_t s = (int64_t)blockIdx.x * kRankThreads + tid; s < slots; s += stride)
+    count(t.rank[s]);
+  if (blockIdx.x == 0 && tid == 0 && t.meta->ones_present) count(t.meta->ones_rank);
+  __syncthreads();
+  // Each count is added by an atomic whose result is waited for, so it has
+  // been performed before the workgroup counts itself as arrived, and the last
+  // one takes the sums by atomics as well: no other memory passes between
+  // workgroups, and no cache is written back (a fence per wave made the pass
+  // take 47 us).
+  unsigned int seen = 0;
+  for (int i = tid; i < bins; i += kRankThreads)
+    if (h[i]) seen |= atomicAdd(&hist[i], h[i]);
+  asm volatile("s_waitcnt vmcnt(0)" ::"v"(seen) : "memory");
+  __syncthreads();
+  if (tid == 0) last = atomicAdd(&st->arrived, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+
+  // thread i owns bins 2i and 2i + 1; `over` = keys in higher bins
+  unsigned int c[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int b = 2 * tid + k;
+    c[k] = b < bins ? atomicExch(&hist[b], 0u) : 0u;
+  }
+  const int lane = tid & 63, wid = tid >> 6;
+  unsigned long long inc = (unsigned long long)c[0] + c[1];  // this thread and higher lanes
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long u = __shfl_down(inc, d, 64);
+    if (lane + d < 64) inc += u;
+  }
+  if (lane == 0) above[wid] = inc;
+  __syncthreads();
+  unsigned long long over = inc - c[0] - c[1];
+  for (int i = 0; i < kRankThreads / 64; ++i) over += i > wid ? above[i] : 0ull;
+  if (tid == 0) st->arrived = 0;
+  if (st->bits == kRankStart) {
+    // first pass: everything fits, or everything but the words of 0
+    unsigned long long keys = 0;
+    for (int i = 0; i < kCounterLanes; ++i) keys += t.meta->n_keys[i];
+    if (keys <= budget || rb.used <= budget) {
+      if (tid == 0) {
+        st->threshold = keys <= budget ? 0ull : 1ull;
+        st->done = 1;
+      }
+      return;
+    }
+  }
+  // the one bin with over <= budget < over + its count (a later pass's total
+  // exceeds the budget as well: its digit did not fit as a whole)
+#pragma unroll
+  for (int k = 1; k >= 0; --k) {
+    if (over <= budget && budget < over + c[k]) {
+      const unsigned long long p = (prefix << width) | (unsigned long long)(2 * tid + k);
+      st->prefix = p;
+      st->budget = budget - over;
+      st->bits = shift;
+      if (shift == 0) {  // the whole class p does not fit: keep what ranks above it
+        st->threshold = rb.unpack(p) + 1;
+        st->done = 1;
+      }
+    }
+    over += c[k];
+  }
+}
+
+// Erase: a present key's recency word becomes kErased (counted once per key).
+__global__ __launch_bounds__(256) void k_erase_mark(TableView t, const uint8_t *keys,
+                                                    int64_t n) {
+  __shared__ uint32_t lds4[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  uint32_t marked = 0;
+  if (i < n) {
+    const Key k = load_key(keys + i * 32);
+    unsigned long long *w = nullptr;
+    if (key_is_empty_pattern(k)) {
+      if (t.meta->ones_present) w = &t.meta->ones_rank;
+    } else {
+      const int64_t slot = find_slot(t, k);
+      if (slot >= 0) w = &t.rank[slot];
+    }
+    if (w && atomicExch(w, kErased) != kErased) marked = 1;
+  }
+  const uint32_t total = block_sum(marked, lds4);
+  if (threadIdx.x == 0 && total) atomicAdd(&t.meta->erased, (unsigned long long)total);
+}
+
+// The rebuild.  A workgroup takes a region of kRegion slots, copies the
+// region's kept keys and recency words to the scratch, close together from the
+// region's own place on, and empties the region's occupied slots (the others
+// are empty as they are); then every copy is inserted again.  No counter is
+// shared, and a table at load 1/4 has a quarter of its slots written.  (With
+// the copies packed over the whole table by one atomic per 4096 slots, the
+// table emptied by a launch of its own, and 256 workgroups: 50 us for 2^20
+// slots; now 26.)
+constexpr int kRegion = 1024;
+
+__global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, u32x4 *out_keys,
+                                                 unsigned long long *out_rank,
+                                                 uint32_t *region_count) {
   __shared__ uint32_t wsum[4];
-  __shared__ unsigned long long wbase;
+  const int64_t slots = (int64_t)t.mask + 1;
+  const unsigned long long thr = st->threshold;
+  const u32x4 ones = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  constexpr int kItems = kRegion / 256;
+  const int64_t b0 = (int64_t)blockIdx.x * kRegion;
+  unsigned long long r[kItems];
+  uint32_t keep = 0, have = 0;
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    const int64_t s = b0 + k * 256 + threadIdx.x;
+    r[k] = 0;
+    if (s < slots && t.tags[s] != 0) {
+      r[k] = t.rank[s];
+      have |= 1u << k;
+      if (r[k] != kErased && r[k] >= thr) keep |= 1u << k;
+    }
+  }
+  // exclusive prefix of the kept counts over the workgroup
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
+  const uint32_t mine = __popc(keep);
+  uint32_t inc = mine;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t u = __shfl_up(inc, d, 64);
@@ -486,250 +760,30 @@ __device__ __forceinline__ uint32_t block_reserve(uint32_t v, unsigned long long
   if (lane == 63) wsum[w] = inc;
   __syncthreads();
   uint32_t before = 0, total = 0;
+#pragma unroll
   for (int i = 0; i < 4; ++i) {
     before += i < w ? wsum[i] : 0u;
     total += wsum[i];
   }
-  if (threadIdx.x == 0) wbase = total ? atomicAdd(counter, (unsigned long long)total) : 0ull;
-  __syncthreads();
-  *base = wbase;
-  __syncthreads();  // wsum and wbase are reused by the next call
-  return before + inc - v;
-}
-
-// Gathers the recency words of the occupied slots (and of the all-0xFF key)
-// into a dense array: the select passes then read 8 bytes per key instead
-// of 16 per slot.
-__global__ __launch_bounds__(256) void k_gather_ranks(TableView t, SelectState *st,
-                                                      unsigned long long *dense) {
-  const int64_t slots = (int64_t)t.mask + 1;
-  const int64_t step = (int64_t)256 * kCompactItems;
-  for (int64_t b0 = (int64_t)blockIdx.x * step; b0 < slots; b0 += (int64_t)gridDim.x * step) {
-    unsigned long long r[kCompactItems];
-    uint32_t have = 0;
+  int64_t o = b0 + before + inc - mine;
 #pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-      const int64_t s = b0 + (int64_t)k * 256 + threadIdx.x;
-      r[k] = 0;
-      if (s < slots && t.tags[s] != 0) {
-        r[k] = t.rank[s];
-        have |= 1u << k;
-      }
+  for (int k = 0; k < kItems; ++k) {
+    if (!(have & (1u << k))) continue;
+    const int64_t s = b0 + k * 256 + threadIdx.x;
+    if (keep & (1u << k)) {
+      out_keys[2 * o] = t.keys[2 * s];
+      out_keys[2 * o + 1] = t.keys[2 * s + 1];
+      out_rank[o] = r[k];
+      ++o;
     }
-    unsigned long long base;
-    uint32_t at = block_reserve(__popc(have), &st->n_dense, &base);
-    unsigned long long mn = ~0ull, mx = 0;
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-      if (have & (1u << k)) {
-        dense[base + at++] = r[k];
-        mn = r[k] < mn ? r[k] : mn;
-        mx = r[k] > mx ? r[k] : mx;
-      }
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const unsigned long long a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
-      mn = a < mn ? a : mn;
-      mx = b > mx ? b : mx;
-    }
-    // a wave holding keys reports its range even when every word is 0 (keys
-    // inserted while tracking was off): the select must see that class too
-    const bool any = __ballot(have != 0) != 0;
-    if ((threadIdx.x & 63) == 0 && any) {
-      atomicMin(&st->lo, mn);
-      atomicMax(&st->hi, mx);
-    }
+    t.keys[2 * s] = ones;
+    t.keys[2 * s + 1] = ones;
+    t.tags[s] = 0;
+    t.rank[s] = 0;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && t.meta->ones_present) {
-    const unsigned long long r = t.meta->ones_rank;
-    dense[atomicAdd(&st->n_dense, 1ull)] = r;
-    atomicMin(&st->lo, r);
-    atomicMax(&st->hi, r);
-  }
-}
-
-// Starts the select below the leading digits that all gathered words share
-// (typically the high bytes of the stamp and of the depth), or ends it when
-// they form one class.
-__global__ void k_select_start(SelectState *st) {
-  if (st->n_dense == 0) {
-    st->done = 1;
-    return;
-  }
-  const unsigned long long lo = st->lo, hi = st->hi;
-  if (lo == hi) {
-    st->threshold = st->n_dense <= (unsigned long long)st->budget ? 0ull : lo + 1;
-    st->done = 1;
-    return;
-  }
-  const int level = __builtin_clzll(lo ^ hi) / 8;  // 0..7
-  st->level = level;
-  st->prefix = level ? lo >> (64 - 8 * level) : 0ull;
-}
-
-// Histogram of the next digit of the gathered words that match the decided
-// prefix, per workgroup in LDS.  Most keys of a table share the leading
-// digits, so each wave first adds its lanes that share the first active
-// lane's bin with one atomic.
-__global__ __launch_bounds__(256) void k_rank_hist(const SelectState *st,
-                                                   const unsigned long long *dense,
-                                                   unsigned int *hist) {
-  __shared__ unsigned int h[kRankBins];
-  if (st->done) return;
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int level = st->level;
-  const unsigned long long prefix = st->prefix;
-  const int shift = 56 - 8 * level;
-  const int64_t n = (int64_t)st->n_dense;
-  const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  // every lane of a wave runs the same number of rounds (ballot inside)
-  const int64_t rounds = (n + stride - 1) / stride;
-  for (int64_t k = 0; k < rounds; ++k) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x + k * stride;
-    bool valid = false;
-    int bin = 0;
-    if (i < n) {
-      const unsigned long long r = dense[i];
-      valid = level == 0 || (r >> (shift + 8)) == prefix;
-      bin = (int)((r >> shift) & 255);
-    }
-    const uint64_t act = __ballot(valid);
-    if (!act) continue;
-    const int leader = __builtin_ctzll(act);
-    const int lbin = __shfl(bin, leader, 64);
-    const uint64_t same = __ballot(valid && bin == lbin);
-    if (lane == leader) atomicAdd(&h[lbin], (unsigned int)__popcll(same));
-    if (valid && bin != lbin) atomicAdd(&h[bin], 1u);
-  }
-  __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
-}
-
-// One workgroup: the digit at which the kept count crosses the budget (keys
-// with a higher digit are kept), or the end when everything left fits.
-// Leaves the histogram cleared for the next pass.
-__global__ __launch_bounds__(256) void k_rank_select(SelectState *st, unsigned int *hist) {
-  __shared__ unsigned long long c[kRankBins];
-  __shared__ unsigned long long total;
-  const int t = threadIdx.x;
-  c[t] = hist[t];
-  hist[t] = 0;
-  const int done = st->done;
-  const long long budget = st->budget;
-  const int level = st->level;
-  const unsigned long long prefix = st->prefix;
-  __syncthreads();
-  if (done) return;
-  unsigned long long above = 0;  // keys whose digit exceeds t
-  for (int u = t + 1; u < kRankBins; ++u) above += c[u];
-  if (t == 0) total = above + c[0];
-  __syncthreads();
-  const unsigned long long B = (unsigned long long)budget;
-  if (total <= B) {
-    if (t == 0) {
-      st->threshold = level == 0 ? 0ull : prefix << (64 - 8 * level);
-      st->done = 1;
-    }
-    return;
-  }
-  if (above <= B && B < above + c[t]) {  // exactly one digit
-    const unsigned long long p = (prefix << 8) | (unsigned long long)t;
-    st->budget = budget - (long long)above;
-    st->prefix = p;
-    st->level = level + 1;
-    if (level + 1 == 8) {  // the whole class p does not fit: keep what ranks above it
-      st->threshold = p + 1;
-      st->done = 1;
-    }
-  }
-}
-
-__global__ void k_select_init(SelectState *st, unsigned int *hist, long long budget,
-                              int erase) {
-  if (threadIdx.x == 0) {
-    st->prefix = 0;
-    st->threshold = 0;  // erase: keep every key not marked
-    st->budget = budget;
-    st->kept = 0;
-    st->erased = 0;
-    st->n_dense = 0;
-    st->lo = ~0ull;
-    st->hi = 0;
-    st->level = 0;
-    st->done = erase;
-  }
-  hist[threadIdx.x] = 0;
-}
-
-// Erase: a present key's recency word becomes kErased (counted once per key).
-__global__ __launch_bounds__(256) void k_erase_mark(TableView t, const uint8_t *keys,
-                                                    int64_t n, SelectState *st) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const Key k = load_key(keys + i * 32);
-  unsigned long long *w = nullptr;
-  if (key_is_empty_pattern(k)) {
-    if (t.meta->ones_present) w = &t.meta->ones_rank;
-  } else {
-    const int64_t slot = find_slot(t, k);
-    if (slot >= 0) w = &t.rank[slot];
-  }
-  if (w && atomicExch(w, kErased) != kErased) atomicAdd(&st->erased, 1ull);
-}
-
-// Copies the kept keys and their recency to scratch (one atomic per
-// workgroup step of 4096 slots).
-__global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, u32x4 *out_keys,
-                                                 unsigned long long *out_rank, int64_t cap) {
-  const int64_t slots = (int64_t)t.mask + 1;
-  const unsigned long long thr = st->threshold;
-  const int64_t step = (int64_t)256 * kCompactItems;
-  for (int64_t b0 = (int64_t)blockIdx.x * step; b0 < slots; b0 += (int64_t)gridDim.x * step) {
-    uint32_t keep = 0;
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-      const int64_t s = b0 + (int64_t)k * 256 + threadIdx.x;
-      if (s < slots && t.tags[s] != 0) {
-        const unsigned long long r = t.rank[s];
-        if (r != kErased && r >= thr) keep |= 1u << k;
-      }
-    }
-    unsigned long long base;
-    uint32_t at = block_reserve(__popc(keep), &st->kept, &base);
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-      if (!(keep & (1u << k))) continue;
-      const int64_t s = b0 + (int64_t)k * 256 + threadIdx.x;
-      const int64_t o = (int64_t)(base + at++);
-      if (o < cap) {
-        out_keys[2 * o] = t.keys[2 * s];
-        out_keys[2 * o + 1] = t.keys[2 * s + 1];
-        out_rank[o] = t.rank[s];
-      }
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && t.meta->ones_present) {
-    const unsigned long long r = t.meta->ones_rank;
-    if (r != kErased && r >= thr) {
-      const int64_t o = (int64_t)atomicAdd(&st->kept, 1ull);
-      if (o < cap) {
-        const u32x4 ones = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-        out_keys[2 * o] = ones;
-        out_keys[2 * o + 1] = ones;
-        out_rank[o] = r;
-      }
-    }
-  }
-}
-
-// Empties the slots and the key counters for the rebuild; the latched error
-// and the export count stay.
-__global__ __launch_bounds__(256) void k_rebuild_fill(TableView t) {
-  const int64_t slots = (int64_t)t.mask + 1;
-  const u32x4 ones = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  if (threadIdx.x == 0) region_count[blockIdx.x] = total;
+  // the all-0xFF key and the counters (the latched error and the export and
+  // erase counts stay)
   if (blockIdx.x == 0) {
     CacheMeta *m = t.meta;
     for (int i = threadIdx.x; i < kCounterLanes; i += blockDim.x) {
@@ -738,17 +792,13 @@ __global__ __launch_bounds__(256) void k_rebuild_fill(TableView t) {
       m->new_keys[1][i] = 0;
     }
     if (threadIdx.x == 0) {
+      const unsigned long long q = m->ones_rank;
+      st->ones_keep = m->ones_present && q != kErased && q >= thr;
+      st->ones_rank = q;
       m->ones_tag = 0;
       m->ones_rank = 0;
       m->ones_present = 0;
     }
-  }
-  for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots;
-       s += (int64_t)gridDim.x * 256) {
-    t.keys[2 * s] = ones;
-    t.keys[2 * s + 1] = ones;
-    t.tags[s] = 0;
-    t.rank[s] = 0;
   }
 }
 
@@ -756,23 +806,21 @@ __global__ __launch_bounds__(256) void k_rebuild_fill(TableView t) {
 __global__ __launch_bounds__(256) void k_reinsert(TableView t, const SelectState *st,
                                                   const uint8_t *keys,
                                                   const unsigned long long *rank,
-                                                  uint32_t epoch, int64_t cap) {
+                                                  const uint32_t *region_count, uint32_t epoch) {
   __shared__ uint32_t lds4[4];
-  int64_t n = (int64_t)st->kept;
-  if (n > cap) {
-    // more keys counted than the copy-out had room for (never expected: a
-    // table holds at most cap keys): reinsert the copies only
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&t.meta->status, 0, KVGOV_E_INTERNAL);
-    n = cap;
-  }
+  const int64_t b0 = (int64_t)blockIdx.x * kRegion;
+  const int64_t n = b0 + region_count[blockIdx.x];
   uint32_t added = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = b0 + threadIdx.x; i < n; i += 256) {
     uint32_t code = kCodeFailed;
     added += insert_key<false>(t, load_key(keys + i * 32), i, 0, keys, epoch, &code);
-    unsigned long long *dst =
-        code == kCodeOnes ? &t.meta->ones_rank : (code < kCodeFailed ? &t.rank[code] : nullptr);
-    if (dst) *dst = rank[i];
+    if (code < kCodeFailed) t.rank[code] = rank[i];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && st->ones_keep) {
+    t.meta->ones_tag = (unsigned long long)epoch << 32 | 1ull;
+    t.meta->ones_present = 1;
+    t.meta->ones_rank = st->ones_rank;
+    ++added;
   }
   const uint32_t total = block_sum(added, lds4);
   if (threadIdx.x == 0 && total)
@@ -830,6 +878,7 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s) {
                      c->view.tags, c->rank_dirty ? c->view.rank : nullptr, c->slots,
                      c->view.meta);
   c->rank_dirty = false;
+  c->max_rows = 0;
   c->epoch.store(0);
   return launch_status();
 }
@@ -855,6 +904,15 @@ unsigned insert_grid(int64_t n_blocks) {
   return (unsigned)std::min<int64_t>(groups, (int64_t)device_cu_count() * 16);
 }
 
+// A call that tracks recency is about to be enqueued: its depths are below
+// n_blocks.
+void note_tracked(kvgov_cache *c, int64_t n_blocks) {
+  c->rank_dirty = true;
+  int64_t seen = c->max_rows.load();
+  while (seen < n_blocks && !c->max_rows.compare_exchange_weak(seen, n_blocks)) {
+  }
+}
+
 int read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s) {
   if (hipMemcpyAsync(m, c->view.meta, sizeof(CacheMeta), hipMemcpyDeviceToHost, s) !=
       hipSuccess)
@@ -864,72 +922,67 @@ int read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s) {
 }
 
 // Maintenance scratch, in the stream's scratch buffer: selection state, the
-// rank histogram and room for every key of the table (32 B key + 8 B recency
-// each).  `lk` holds the scratch registry while the call enqueues its
-// kernels; the stream runs its calls in order, so the buffer serves this
-// call until its kernels end.
+// rank histogram, the regions' counts and room for every key of the table (32
+// B key + 8 B recency each).  `lk` holds the scratch registry while the call
+// enqueues its kernels; the stream runs its calls in order, so the buffer
+// serves this call until its kernels end.
 struct MaintScratch {
   SelectState *st = nullptr;
   unsigned int *hist = nullptr;
+  uint32_t *regions = nullptr;
   u32x4 *keys = nullptr;
   unsigned long long *rank = nullptr;
-  int64_t cap = 0;
   std::unique_lock<std::mutex> lk;
 };
 
-// Workgroups of the compaction kernels: one step of 4096 slots each, at most
-// 4 per CU.
-unsigned compact_grid(int64_t slots) {
-  return (unsigned)std::max<int64_t>(
-      1, std::min<int64_t>(ceil_div(slots, 256 * kCompactItems), (int64_t)device_cu_count() * 4));
-}
+unsigned region_grid(int64_t slots) { return (unsigned)ceil_div(slots, kRegion); }
 
 int maint_alloc(kvgov_cache *c, hipStream_t s, MaintScratch &m) {
-  m.cap = c->slots + 1;
-  const size_t off_hist = 256;
-  const size_t off_keys = off_hist + kRankBins * sizeof(unsigned int);
-  const size_t off_rank = off_keys + (size_t)m.cap * 32;
-  const size_t bytes = off_rank + (size_t)m.cap * 8;
+  const size_t off_hist = 1024;
+  static_assert(sizeof(SelectState) <= 1024, "the state's part of the scratch");
+  const size_t off_regions = off_hist + kRankBins * sizeof(unsigned int);
+  const size_t off_keys = off_regions + ((size_t)region_grid(c->slots) * 4 + 255) / 256 * 256;
+  const size_t off_rank = off_keys + (size_t)c->slots * 32;
+  const size_t bytes = off_rank + (size_t)c->slots * 8;
   void *base = nullptr;
   const int rc = stream_scratch(s, bytes, &base, m.lk);
   if (rc != KVGOV_OK) return rc;
   uint8_t *b = static_cast<uint8_t *>(base);
   m.st = reinterpret_cast<SelectState *>(b);
   m.hist = reinterpret_cast<unsigned int *>(b + off_hist);
+  m.regions = reinterpret_cast<uint32_t *>(b + off_regions);
   m.keys = reinterpret_cast<u32x4 *>(b + off_keys);
   m.rank = reinterpret_cast<unsigned long long *>(b + off_rank);
   return KVGOV_OK;
 }
 
-// Copies out what ranks at or above the selected threshold, empties the
-// table and inserts the copies again; then reads one counter if asked
-// (waiting for the stream).
-int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, const unsigned long long *count,
-                    int64_t *out) {
+// Copies out what ranks at or above the selected threshold while emptying the
+// table, and inserts the copies again; then reads the table's counters if
+// asked (waiting for the stream).
+int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, CacheMeta *meta) {
   const uint32_t epoch = c->epoch.fetch_add(1) + 1;
-  int rc = epoch == 0xFFFFFFFFu ? KVGOV_E_UNSUPPORTED : KVGOV_OK;
-  if (rc == KVGOV_OK) {
-    hipLaunchKernelGGL(k_compact, dim3(compact_grid(c->slots)), dim3(256), 0, s, c->view, m.st,
-                       m.keys, m.rank, m.cap);
-    hipLaunchKernelGGL(k_rebuild_fill, dim3(grid_for(c->slots, 64)), dim3(256), 0, s, c->view);
-    hipLaunchKernelGGL(k_reinsert, dim3(grid_for(m.cap, 16)), dim3(256), 0, s, c->view, m.st,
-                       reinterpret_cast<const uint8_t *>(m.keys), m.rank, epoch, m.cap);
-    rc = launch_status();
-  }
-  unsigned long long host = 0;
-  if (rc == KVGOV_OK && out &&
-      hipMemcpyAsync(&host, count, sizeof host, hipMemcpyDeviceToHost, s) != hipSuccess)
-    rc = KVGOV_E_HIP;
-  if (m.lk.owns_lock()) m.lk.unlock();  // everything that uses the scratch is enqueued
-  if (rc == KVGOV_OK && out) {
-    if (hipStreamSynchronize(s) != hipSuccess) return KVGOV_E_HIP;
-    *out = (int64_t)host;
-    CacheMeta meta{};
-    rc = read_meta(c, &meta, s);
-    if (rc == KVGOV_OK) rc = meta.status;
+  if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
+  const dim3 grid(region_grid(c->slots)), block(256);
+  hipLaunchKernelGGL(k_compact, grid, block, 0, s, c->view, m.st, m.keys, m.rank, m.regions);
+  hipLaunchKernelGGL(k_reinsert, grid, block, 0, s, c->view, m.st,
+                     reinterpret_cast<const uint8_t *>(m.keys), m.rank, m.regions, epoch);
+  int rc = launch_status();
+  m.lk.unlock();  // everything that uses the scratch is enqueued
+  if (rc == KVGOV_OK && meta) {
+    rc = read_meta(c, meta, s);
+    if (rc == KVGOV_OK) rc = meta->status;
   }
   return rc;
 }
+
+// Keys in the table, from its counters.
+int64_t key_count(const CacheMeta &m) {
+  int64_t total = 0;
+  for (int i = 0; i < kCounterLanes; ++i) total += (int64_t)m.n_keys[i];
+  return total;
+}
+
+int bit_length(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
 
 // Keys added by insert call `epoch` (waits for the stream), and the latched
 // error.
@@ -943,34 +996,38 @@ int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s)
   return m.status;
 }
 
+template <bool TRACK>
+void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
+                int64_t n_blocks, uint32_t epoch, int g, hipStream_t s) {
+  const dim3 grid((unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * g, 256))), block(256);
+  switch (g) {
+    case 4: hipLaunchKernelGGL((k_insert_req<4, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+    case 8: hipLaunchKernelGGL((k_insert_req<8, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+    case 16: hipLaunchKernelGGL((k_insert_req<16, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+    case 32: hipLaunchKernelGGL((k_insert_req<32, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+    default: hipLaunchKernelGGL((k_insert_req<64, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+  }
+}
+
 }  // namespace
 
 int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
                              int32_t n, int64_t n_blocks, hipStream_t s, uint32_t *epoch) {
   *epoch = c->epoch.fetch_add(1) + 1;
   if (*epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;  // 2^32 - 1 inserts since clear
-  if (c->view.track) c->rank_dirty = true;
-  if (n == 0) {
-    // no request: only the batch check and the next call's counters
-    hipLaunchKernelGGL(k_insert_req<64>, dim3(1), dim3(256), 0, s, c->view, hashes, blk_offsets,
-                       n, n_blocks, *epoch);
-    return launch_status();
-  }
-  if (n_blocks > (int64_t)n * kReqInsertMaxAvg) {
+  if (c->view.track) note_tracked(c, n_blocks);
+  if (n > 0 && n_blocks > (int64_t)n * kReqInsertMaxAvg) {
     // few, long requests: a group per request would leave the chip idle
     hipLaunchKernelGGL(k_chunk_insert<false>, dim3(insert_grid(n_blocks)), dim3(256), 0, s,
                        c->view, hashes, blk_offsets, n, n_blocks, *epoch, nullptr);
     return launch_status();
   }
-  const int g = insert_group(n, n_blocks);
-  const dim3 grid((unsigned)ceil_div((int64_t)n * g, 256)), block(256);
-  switch (g) {
-    case 4: hipLaunchKernelGGL(k_insert_req<4>, grid, block, 0, s, c->view, hashes, blk_offsets, n, n_blocks, *epoch); break;
-    case 8: hipLaunchKernelGGL(k_insert_req<8>, grid, block, 0, s, c->view, hashes, blk_offsets, n, n_blocks, *epoch); break;
-    case 16: hipLaunchKernelGGL(k_insert_req<16>, grid, block, 0, s, c->view, hashes, blk_offsets, n, n_blocks, *epoch); break;
-    case 32: hipLaunchKernelGGL(k_insert_req<32>, grid, block, 0, s, c->view, hashes, blk_offsets, n, n_blocks, *epoch); break;
-    default: hipLaunchKernelGGL(k_insert_req<64>, grid, block, 0, s, c->view, hashes, blk_offsets, n, n_blocks, *epoch); break;
-  }
+  // (no request: only the batch check and the next call's counters)
+  const int g = n > 0 ? insert_group(n, n_blocks) : 64;
+  if (c->view.track)
+    insert_req<true>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, g, s);
+  else
+    insert_req<false>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, g, s);
   return launch_status();
 }
 
@@ -1113,7 +1170,7 @@ int kvgov_cache_admit(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
   uint32_t *codes = static_cast<uint32_t *>(scratch_p);
   const uint32_t epoch = c->epoch.fetch_add(1) + 1;
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
-  if (c->view.track) c->rank_dirty = true;
+  if (c->view.track) note_tracked(c, n_blocks);
   hipLaunchKernelGGL(k_chunk_insert<true>, dim3(insert_grid(n_blocks)), dim3(256), 0, s,
                      c->view, hashes, blk_offsets, n, n_blocks, epoch, codes);
   AdmitArgs a{c->view, blk_offsets, n, n_blocks, epoch, codes, hit_blocks, new_blocks};
@@ -1147,21 +1204,23 @@ int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *s
   MaintScratch m;
   rc = maint_alloc(c, s, m);
   if (rc != KVGOV_OK) return rc;
-  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kRankBins), 0, s, m.st, m.hist,
-                     (long long)max_keys, 0);
-  // the gathered words live in the key area of the scratch until the
-  // compaction overwrites it
-  unsigned long long *dense = reinterpret_cast<unsigned long long *>(m.keys);
-  hipLaunchKernelGGL(k_gather_ranks, dim3(compact_grid(c->slots)), dim3(256), 0, s, c->view,
-                     m.st, dense);
-  hipLaunchKernelGGL(k_select_start, dim3(1), dim3(1), 0, s, m.st);
-  for (int level = 0; level < 8; ++level) {
-    hipLaunchKernelGGL(k_rank_hist, dim3(grid_for(c->slots, 4)), dim3(256), 0, s, m.st, dense,
-                       m.hist);
-    hipLaunchKernelGGL(k_rank_select, dim3(1), dim3(kRankBins), 0, s, m.st, m.hist);
-  }
+  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, s, m.st, m.hist, (long long)max_keys,
+                     0, c->view.meta);
+  hipLaunchKernelGGL(k_rank_range, dim3(grid_for(ceil_div(c->slots, 8), 4)), dim3(256), 0, s,
+                     c->view, m.st);
+  // enough passes for every bit that can differ: stamps up to the clock,
+  // depths up to the largest tracked batch (a pass after the last needed one
+  // ends at once)
+  const int bits = bit_length(c->epoch.load()) + bit_length((uint64_t)c->max_rows.load());
+  const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(c->slots, kRankThreads * 8),
+                                                   device_cu_count() * 2);
+  for (int left = std::max(bits, 1); left > 0; left -= kRankDigit)
+    hipLaunchKernelGGL(k_rank_select, dim3(wgs), dim3(kRankThreads), 0, s, c->view, m.st, m.hist);
   c->rank_dirty = true;
-  return compact_rebuild(c, s, m, &m.st->kept, n_kept);
+  CacheMeta meta{};
+  rc = compact_rebuild(c, s, m, n_kept ? &meta : nullptr);
+  if (rc == KVGOV_OK && n_kept) *n_kept = key_count(meta);
+  return rc;
 }
 
 int kvgov_cache_erase(kvgov_cache *c, const uint8_t *keys, int64_t n_keys, int64_t *n_erased,
@@ -1174,12 +1233,16 @@ int kvgov_cache_erase(kvgov_cache *c, const uint8_t *keys, int64_t n_keys, int64
   MaintScratch m;
   rc = maint_alloc(c, s, m);
   if (rc != KVGOV_OK) return rc;
-  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kRankBins), 0, s, m.st, m.hist, 0ll, 1);
+  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, s, m.st, m.hist, 0ll, 1,
+                     c->view.meta);
   if (n_keys > 0)
     hipLaunchKernelGGL(k_erase_mark, dim3((unsigned)ceil_div(n_keys, 256)), dim3(256), 0, s,
-                       c->view, keys, n_keys, m.st);
+                       c->view, keys, n_keys);
   c->rank_dirty = true;
-  return compact_rebuild(c, s, m, &m.st->erased, n_erased);
+  CacheMeta meta{};
+  rc = compact_rebuild(c, s, m, n_erased ? &meta : nullptr);
+  if (rc == KVGOV_OK && n_erased) *n_erased = (int64_t)meta.erased;
+  return rc;
 }
 
 int kvgov_cache_count(kvgov_cache *c, int64_t *n_keys, void *stream) {
@@ -1189,9 +1252,7 @@ int kvgov_cache_count(kvgov_cache *c, int64_t *n_keys, void *stream) {
   CacheMeta m{};
   rc = read_meta(c, &m, as_stream(stream));
   if (rc != KVGOV_OK) return rc;
-  int64_t total = 0;
-  for (int i = 0; i < kCounterLanes; ++i) total += (int64_t)m.n_keys[i];
-  *n_keys = total;
+  *n_keys = key_count(m);
   return m.status;
 }
 

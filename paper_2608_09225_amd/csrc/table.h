@@ -20,6 +20,7 @@ struct CacheMeta {
   unsigned long long n_keys[kCounterLanes];       // keys in the table (all-0xFF key included)
   unsigned long long new_keys[2][kCounterLanes];  // keys added by insert call `epoch`, at [epoch & 1]
   unsigned long long exported;                    // keys written by the latest export
+  unsigned long long erased;                      // keys marked by the latest erase
   unsigned long long ones_tag;                    // the all-0xFF key's tag (0 = absent)
   unsigned long long ones_rank;                   // its recency rank (as `rank`)
   int32_t status;                                 // latched error (0 = none)
@@ -149,14 +150,17 @@ __device__ __forceinline__ unsigned long long recency(uint32_t epoch, uint32_t d
 // and returns the claim.  Coherent atomics are used for the claim only.
 // Returns 1 if the key was added; *code receives where the key went, and
 // *claim (if given) the key's tag as this lane found it (its own claim if it
-// added the key).  On a table that tracks recency the key (added or found)
+// added the key).  With `renew`, a key of an earlier call takes this call's tag
+// (the plain insert's first rows: a later row with the same key then learns
+// of an earlier one in this call, as it does of a new key's).  On a table that tracks recency the key (added or found)
 // is touched with (epoch, depth) unless depth is kNoDepth.
 template <bool ADMIT>
 __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &key, int64_t i,
                                                int64_t lo, const uint8_t *hashes,
                                                uint32_t epoch, uint32_t *code,
                                                uint32_t depth = kNoDepth,
-                                               unsigned long long *claim = nullptr) {
+                                               unsigned long long *claim = nullptr,
+                                               bool renew = false) {
   const unsigned long long mine = ((unsigned long long)epoch << 32) |
                                   (unsigned long long)(i - lo + 1);
   if (key_is_empty_pattern(key)) {
@@ -199,6 +203,13 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
     }
     if (key_eq(key, other)) {
       if (ADMIT && current) lower_claim(&t.tags[s], tag, mine);
+      if (renew && !current) {
+        unsigned long long expect = tag;
+        tag = __hip_atomic_compare_exchange_strong(&t.tags[s], &expect, mine, __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                  ? mine
+                  : expect;
+      }
       *code = (uint32_t)s;
       if (claim) *claim = tag;
       if (t.track && depth != kNoDepth) touch(&t.rank[s], recency(epoch, depth), false);
@@ -266,5 +277,8 @@ struct kvgov_cache {
   // recency words may be nonzero (set when a call that can write them is
   // enqueued; the next clear rewrites them)
   std::atomic<bool> rank_dirty{true};
+  // the largest row count of a tracked call since the last clear: every depth
+  // in a recency word is below it
+  std::atomic<int64_t> max_rows{0};
 };
 

@@ -289,3 +289,63 @@ def test_concurrent_maintenance_on_two_streams():
     finally:
         for c in caches:
             c.close()
+
+
+@pytest.mark.parametrize("calls,longest", [(1, 1), (1, 3000), (2, 2047), (2, 2048), (40, 70),
+                                           (300, 20000)])
+def test_evict_selects_over_any_bits(calls, longest):
+    """The select decides over the recency bits that differ, eleven per pass:
+    one class, one half only, one pass exactly full, and up to three passes
+    (9 bits of stamp and 15 of depth).  Each eviction keeps the same keys as
+    the oracle, down to one key and none, with one key held by two calls."""
+    g = np.random.default_rng(calls * 7 + longest)
+    hist, at = [], 0
+    for k in range(calls):
+        lens = np.array([longest if k == calls - 1 else int(g.integers(1, 21)), 3, 1])
+        lens = np.minimum(lens, longest)
+        bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        ids = np.arange(at, at + int(bo[-1]))
+        at += int(bo[-1]) - 1  # the last key comes again in the next call
+        rows = np.zeros((ids.size, 32), np.uint8)
+        rows[:, :8] = (ids.astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+        rows[:, 8] = 1
+        hist.append((rows, bo))
+    T = O.Table()
+    with KV.Cache(16) as c:
+        c.set_recency(True)
+        for rows, bo in hist:
+            assert c.insert(dev(rows), dev(bo)) == T.insert(rows, bo)
+        n = len(T.keys)
+        for keep in (n, n - 1, n * 2 // 3, n // 2, 100, 7, 1, 0):
+            if keep <= len(T.keys):
+                assert c.evict(keep) == T.evict(keep), keep
+                assert key_set(c.export()) == T.keys, keep
+
+
+@pytest.mark.parametrize("max_len", [1, 3, 9, 40])
+@pytest.mark.parametrize("repeat", [1, 3])
+def test_tracked_insert_of_shared_heads(max_len, repeat):
+    """Tracked batches of requests that share first keys and differ in
+    length, over keys that occur at many depths: a row may be skipped as
+    equal to an earlier request's only at the same depth, and that request
+    may end before it.  The second and third insert find every key present
+    (first keys take the new call's tag)."""
+    g = np.random.default_rng(max_len)
+    pool = [key_of(i) for i in range(60)]
+    T = O.Table()
+    with KV.Cache(12) as c:
+        c.set_recency(True)
+        for _ in range(repeat):
+            lens = g.integers(0, max_len + 1, 400)
+            bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            rows = []
+            for n in lens:
+                head = int(g.integers(0, 5))
+                rows += [pool[(head * 7 + j) % 60 if j < n * 2 // 3 + 1 else int(g.integers(60))]
+                         for j in range(n)]
+            h = arr(rows)
+            assert c.insert(dev(h), dev(bo)) == T.insert(h, bo)
+        for keep in (50, 30, 11, 4, 1):
+            if keep <= len(T.keys):
+                assert c.evict(keep) == T.evict(keep), keep
+                assert key_set(c.export()) == T.keys, keep
