@@ -1011,12 +1011,16 @@ void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_of
 
 }  // namespace
 
+bool kvgov::cache_inserts_by_request(int32_t n, int64_t n_blocks) {
+  return n == 0 || n_blocks <= (int64_t)n * kReqInsertMaxAvg;
+}
+
 int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
                              int32_t n, int64_t n_blocks, hipStream_t s, uint32_t *epoch) {
   *epoch = c->epoch.fetch_add(1) + 1;
   if (*epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;  // 2^32 - 1 inserts since clear
   if (c->view.track) note_tracked(c, n_blocks);
-  if (n > 0 && n_blocks > (int64_t)n * kReqInsertMaxAvg) {
+  if (!cache_inserts_by_request(n, n_blocks)) {
     // few, long requests: a group per request would leave the chip idle
     hipLaunchKernelGGL(k_chunk_insert<false>, dim3(insert_grid(n_blocks)), dim3(256), 0, s,
                        c->view, hashes, blk_offsets, n, n_blocks, *epoch, nullptr);

@@ -10,18 +10,31 @@
 //     the unsalted tree), stored in a block table (table.h); a node's id is
 //     its slot index;
 //   * token nodes: the prefixes of 1..15 tokens of a block below its parent
-//     block node, stored as edges (parent id, token) -> child in an edge table
-//     of 64-bit keys; a child's id is kEdgeBase + its edge slot.
+//     block node.  The first sequence to go below a block node leaves its
+//     tokens there as the node's chain (one record of up to 15 tokens, one
+//     compare-and-swap for all of its token nodes): the node of the chain's
+//     first l tokens is (block node, l).  A sequence that leaves the chain, or
+//     goes past its end, continues as edges (parent id, token) -> child in an
+//     edge table of 64-bit keys; such a child's id is kEdgeBase + its edge
+//     slot.
 // A full block leads from the node of h_{j-1} to the node of h_j (through the
-// block table: the 16th token is never an edge); a partial last block of an
-// inserted sequence ends at a token node.  Match: the first block whose digest
-// is absent gives the block depth m, and the longest walk of edges from the
-// node of h_{m-1} over the request's next tokens (at most 15) gives the rest:
-// match = 16 m + steps.  The 16th step cannot exist: it would make block m
-// present.
+// block table: the 16th token is never a token node); a partial last block
+// of an inserted sequence ends at a token node.  Match: the first block whose
+// digest is absent gives the block depth m, and the longest walk over the
+// chain and the edges below the node of h_{m-1} along the request's next
+// tokens (at most 15) gives the rest: match = 16 m + steps.  The 16th step
+// cannot exist: it would make block m present.
+//
+// Most blocks have one successor, so most token nodes are chains: 4096
+// sequences of ~34 private blocks made 2.2 M edges, each a read, a
+// compare-and-swap and a write at a random place of the edge table, one after
+// the other along a block (236 us); as 147 k chains (46 us).
 //
 // Edge insert is one 64-bit compare-and-swap per edge (the key is the whole
-// slot), so no lane ever reads a slot another lane is still writing.
+// slot), so no lane ever reads a slot another lane is still writing.  A chain
+// is claimed by a tag (call epoch, request); a lane of the same call that
+// finds it claimed reads the claimant's tokens from the call's input, as the
+// block table does with keys.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,6 +49,12 @@ constexpr uint32_t kEdgeBase = 0x80000000u;  // id of the token node in edge slo
 constexpr uint32_t kOnesNode = 0x7FFFFFFFu;  // id of the all-0xFF block key (no slot)
 constexpr uint32_t kNoNode = 0xFFFFFFFFu;
 constexpr int kMaxLog2Radix = 30;           // keeps slot ids clear of the ids above
+// Block tables up to this size keep chains: a token node of a chain has the id
+// slot * 16 + l, below 2^30.  Larger ones (whose records would take another
+// 72 bytes for each of 2^27 slots or more) have edges alone, and a block node's
+// id is its slot.
+constexpr int kMaxLog2Chains = 26;
+constexpr int kChainMax = 15;
 
 struct RadixMeta {
   unsigned long long n_edges[kCounterLanes];
@@ -46,6 +65,9 @@ struct EdgeView {
   unsigned long long *keys;
   uint64_t mask;
   RadixMeta *meta;
+  unsigned long long *chain_tags;  // per block slot: 0, or (call epoch << 32) | (request + 1);
+                                   // NULL: no chains
+  u32x4 *chains;                   // per block slot: the token count, then up to 15 tokens
 };
 
 __device__ __forceinline__ uint64_t edge_hash(unsigned long long k) {
@@ -94,14 +116,9 @@ __device__ __forceinline__ uint32_t edge_find(const EdgeView &e, uint32_t node, 
   return kNoNode;
 }
 
-// Node id of a block key (kNoNode if absent).
-__device__ __forceinline__ uint32_t block_node(const TableView &t, const Key &k) {
-  const int64_t s = find_slot(t, k);
-  return s >= 0 ? (uint32_t)s : (s == -2 ? kOnesNode : kNoNode);
-}
-
 __global__ __launch_bounds__(256) void k_edge_fill(unsigned long long *keys, int64_t slots,
-                                                   RadixMeta *m) {
+                                                   unsigned long long *chain_tags,
+                                                   int64_t block_slots, RadixMeta *m) {
   const int64_t stride = (int64_t)gridDim.x * 256;
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < kCounterLanes; i += blockDim.x) m->n_edges[i] = 0;
@@ -109,6 +126,9 @@ __global__ __launch_bounds__(256) void k_edge_fill(unsigned long long *keys, int
   }
   for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots; s += stride)
     keys[s] = kEdgeEmpty;
+  if (chain_tags)
+    for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < block_slots; s += stride)
+      chain_tags[s] = 0;
 }
 
 // Root keys into the block table (a row each; the insert protocol of
@@ -173,55 +193,197 @@ __device__ __forceinline__ bool radix_req(const RadixArgs &a, int64_t r, RadixRe
   return true;
 }
 
-// Insert: G lanes per request, one (possibly partial) block each: the edges
-// of its first min(len, 15) tokens below its parent block node.  The edges
-// of a full block j are fixed by h_j (its parent and its tokens), so only
-// the row that claimed h_j in this call's block insert walks them: a block
-// present before the call has them already, and every other row holding
-// h_j would repeat them (thousands of rows of a shared prefix would
-// otherwise contend on the same edge slots).  A partial last block has no
-// digest and always walks its edges.
-template <int G>
+// The id of block node `slot` (find_slot's value) as a parent of edges.
+__device__ __forceinline__ uint32_t node_id(const EdgeView &e, int64_t slot) {
+  if (slot == -2) return kOnesNode;
+  return e.chain_tags ? (uint32_t)slot * 16u : (uint32_t)slot;
+}
+
+// The slot that a row's key claimed with the tag `mine`, or -1 if another row
+// or an earlier call holds the key: the claim lies on the key's probe sequence,
+// before the first empty slot, so the tags alone tell, for as far as most
+// sequences go; past that (a table that is nearly full) the key is looked
+// for, which ends at the key.
+__device__ __forceinline__ int64_t claimed_slot(const TableView &t, const Key &key,
+                                                unsigned long long mine) {
+  const uint64_t home = home_slot(key, t.mask);
+  for (uint64_t p = 0; p < 8; ++p) {
+    const uint64_t s = seq_slot(home, p, t.mask);
+    const unsigned long long tag = t.tags[s];
+    if (tag == mine) return (int64_t)s;
+    if (tag == 0) return -1;
+  }
+  const int64_t slot = find_slot(t, key);
+  return slot >= 0 && t.tags[slot] == mine ? slot : -1;
+}
+
+// A block's first 15 tokens (rem tokens from p on are the request's): 0 past
+// its end.  A full block is four 16-byte loads.
+__device__ __forceinline__ void load_tokens(const int32_t *p, int64_t rem, uint32_t tok[16]) {
+  if (rem >= 16) {
+    const u32x4 *v = reinterpret_cast<const u32x4 *>(p);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const u32x4 w = v[x];
+      tok[4 * x] = w.x;
+      tok[4 * x + 1] = w.y;
+      tok[4 * x + 2] = w.z;
+      tok[4 * x + 3] = w.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kChainMax; ++i) tok[i] = i < rem ? (uint32_t)p[i] : 0u;
+  }
+}
+
+// A chain's record: the token count, then the tokens.
+__device__ __forceinline__ void load_chain(const u32x4 *rec, uint32_t c[16]) {
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const u32x4 v = rec[x];
+    c[4 * x] = v.x;
+    c[4 * x + 1] = v.y;
+    c[4 * x + 2] = v.z;
+    c[4 * x + 3] = v.w;
+  }
+}
+
+// Inserts the token nodes of one (possibly partial) block below block node
+// `slot`: record j of request r, rem tokens of the request at tp.  Returns
+// the number of token nodes added.
+__device__ __forceinline__ uint32_t insert_tokens(const RadixArgs &a, int64_t slot, int64_t r,
+                                                  int64_t j, const int32_t *tp, int64_t rem) {
+  const EdgeView &e = a.e;
+  const int steps = (int)(rem < kChainMax ? rem : kChainMax);
+  uint32_t tok[16], added = 0;
+  load_tokens(tp, rem, tok);
+  int l = 0;
+  if (e.chain_tags && slot >= 0) {
+    const unsigned long long mine =
+        ((unsigned long long)a.blk_epoch << 32) | (unsigned long long)(r + 1);
+    unsigned long long tag = 0;
+    u32x4 *rec = e.chains + slot * 4;
+    if (__hip_atomic_compare_exchange_strong(&e.chain_tags[slot], &tag, mine, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+      rec[0] = u32x4{(uint32_t)steps, tok[0], tok[1], tok[2]};
+#pragma unroll
+      for (int q = 1; q < 4; ++q)
+        rec[q] = u32x4{tok[4 * q - 1], tok[4 * q], tok[4 * q + 1], tok[4 * q + 2]};
+      return (uint32_t)steps;
+    }
+    uint32_t other[16];
+    if ((uint32_t)(tag >> 32) == a.blk_epoch) {
+      // claimed in this call: the same block of that request (whose offsets the
+      // claimant found valid; a block that it does not have, which only
+      // digests that are not its tokens' give, is an empty chain)
+      const int64_t q = (int64_t)(tag & 0xFFFFFFFFull) - 1;
+      const int64_t t0 = a.tok_offsets[q];
+      int64_t left = a.tok_offsets[q + 1] - t0 - 16 * j;
+      left = left < 0 ? 0 : left;
+      uint32_t ot[16];
+      load_tokens(a.tokens + t0 + 16 * j, left, ot);
+      other[0] = (uint32_t)(left < kChainMax ? left : kChainMax);
+#pragma unroll
+      for (int i = 0; i < kChainMax; ++i) other[1 + i] = ot[i];
+    } else {
+      load_chain(rec, other);
+    }
+    const int both = steps < (int)other[0] ? steps : (int)other[0];
+    bool same = true;
+#pragma unroll
+    for (int i = 0; i < kChainMax; ++i) {
+      same = same && i < both && tok[i] == other[1 + i];
+      l += same ? 1 : 0;
+    }
+  }
+  uint32_t node = node_id(e, slot) + (uint32_t)l;
+  for (; l < steps && node != kNoNode; ++l) node = edge_insert(e, node, tp[l], &added);
+  return added;
+}
+
+// Insert: G lanes per request, one (possibly partial) block each.  The token
+// nodes of a full block j are fixed by h_j (its parent and its tokens), so
+// only the row that claimed h_j in this call's block insert makes them: a
+// block present before the call has them already, and every other row
+// holding h_j would repeat them (thousands of rows of a shared prefix would
+// otherwise contend on the same slots).  A partial last block has no digest
+// and always makes its own.  A row that the block insert skipped, as equal to
+// the previous request's row or to the row of the request that claimed its
+// first key, claimed nothing: where that insert was by requests (BY_REQUEST)
+// the same comparisons are made here first, and only the other rows look for
+// their claim.  The parent's slot is mostly the neighbour lane's claim.
+template <int G, bool BY_REQUEST>
 __global__ __launch_bounds__(256) void k_radix_edges(RadixArgs a) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t r = gid / G;
   if (r >= a.n) return;
   const int sub = (int)(gid % G);
+  const int base = (threadIdx.x & 63) & ~(G - 1);
   RadixReq q;
-  if (!radix_req(a, r, q)) return;
+  if (!radix_req(a, r, q)) return;  // the whole group
   uint32_t added = 0;
   const int64_t nrec = (q.len + 15) >> 4;  // full blocks and a partial tail
   const int64_t lo = a.blk_offsets[0];
-  for (int64_t j = sub; j < nrec; j += G) {
-    if (j < q.nf) {
-      const int64_t f = q.b0 + j;
-      const int64_t slot = find_slot(a.t, load_key(a.hashes + f * 32));
-      if (slot >= 0) {
-        const unsigned long long tag = a.t.tags[slot];
-        if ((uint32_t)(tag >> 32) != a.blk_epoch ||
-            (int64_t)(tag & 0xFFFFFFFFull) - 1 != f - lo)
-          continue;  // not this row's block to expand
+  const unsigned long long epoch = (unsigned long long)a.blk_epoch << 32;
+  // the comparisons of the block insert (k_insert_req)
+  int64_t b_p = 0, n_p = 0, g0 = -1;
+  if (BY_REQUEST && q.nf > 0) {
+    b_p = r >= 1 ? a.blk_offsets[r - 1] : 0;
+    n_p = r >= 1 && b_p >= lo && b_p <= q.b0 ? q.b0 - b_p : 0;
+    if (sub == 0 && q.b0 >= lo) {
+      const Key key = load_key(a.hashes + q.b0 * 32);
+      if (!(n_p > 0 && key_eq(key, load_key(a.hashes + b_p * 32)))) {
+        const int64_t slot = find_slot(a.t, key);
+        const unsigned long long tag =
+            slot >= 0 ? a.t.tags[slot] : (slot == -2 ? a.t.meta->ones_tag : 0ull);
+        const int64_t c = lo + (int64_t)(tag & 0xFFFFFFFFull) - 1;
+        if ((tag >> 32) == a.blk_epoch && c >= lo && c < q.b0) g0 = c;
       }
-      // slot < 0: the all-0xFF digest (no tag: expand, edges are idempotent)
-      // or a block the full table could not take (the walk below latches)
     }
-    uint32_t node = block_node(a.t, load_key(j == 0 ? q.root : a.hashes + (q.b0 + j - 1) * 32));
-    if (node == kNoNode) {
+    g0 = __shfl(g0, base, 64);
+  }
+  int64_t before = -1;  // the claim of the row before this group's next lanes
+  for (int64_t j0 = 0; j0 < nrec; j0 += G) {
+    const int64_t j = j0 + sub;
+    const int64_t f = q.b0 + j;
+    int64_t slot = -1;  // this row's claim
+    bool work = j < nrec;
+    if (j < q.nf) {
+      const Key key = load_key(a.hashes + f * 32);
+      bool dup = false;
+      if (BY_REQUEST && f >= lo) {
+        dup = j < n_p && key_eq(key, load_key(a.hashes + (b_p + j) * 32));
+        if (!dup && g0 >= 0 && j > 0) dup = key_eq(key, load_key(a.hashes + (g0 + j) * 32));
+      }
+      if (dup) {
+        work = false;
+      } else if (!key_is_empty_pattern(key)) {
+        slot = claimed_slot(a.t, key, epoch | (unsigned long long)(f - lo + 1));
+        work = slot >= 0;
+      }
+      // the all-0xFF digest has no tag: its token nodes are made again, which
+      // changes nothing
+    }
+    int64_t parent = __shfl(slot, sub == 0 ? base : base + sub - 1, 64);
+    if (sub == 0) parent = before;
+    before = __shfl(slot, base + G - 1, 64);
+    if (!work) continue;
+    if (parent < 0)
+      parent = find_slot(a.t, load_key(j == 0 ? q.root : a.hashes + (f - 1) * 32));
+    if (parent == -1) {
       // the parent block was not inserted (a full table, latched there)
       atomicCAS(&a.e.meta->status, 0, KVGOV_E_FULL);
       continue;
     }
-    const int64_t rem = q.len - 16 * j;
-    const int steps = (int)(rem < 15 ? rem : 15);
-    const int32_t *tp = a.tokens + q.t0 + 16 * j;
-    for (int i = 0; i < steps && node != kNoNode; ++i) node = edge_insert(a.e, node, tp[i], &added);
+    added += insert_tokens(a, parent, r, j, a.tokens + q.t0 + 16 * j, q.len - 16 * j);
   }
   if (added)
     atomicAdd(&a.e.meta->n_edges[blockIdx.x % kCounterLanes], (unsigned long long)added);
 }
 
 // Match: G lanes per request find the first absent block digest m (ballot),
-// then one lane walks the edges below block node m - 1 (or the root).
+// then one lane follows the chain and the edges below block node m - 1 (or the
+// root).
 template <int G>
 __global__ __launch_bounds__(256) void k_radix_match(RadixArgs a) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -236,32 +398,48 @@ __global__ __launch_bounds__(256) void k_radix_match(RadixArgs a) {
     if (sub == 0) a.match_len[r] = 0;
     return;
   }
-  const bool ones = a.t.meta->ones_present != 0;
   int64_t m = q.nf;
+  int64_t slot = -1;    // of this lane's block
+  int64_t parent = -1;  // of the last block found
   for (int64_t j0 = 0; j0 < q.nf; j0 += G) {
     const int64_t j = j0 + sub;
-    bool miss = false;
-    if (j < q.nf) miss = !probe(a.t, load_key(a.hashes + (q.b0 + j) * 32), ones);
-    const uint64_t mk = __ballot(miss) & gmask;
+    slot = j < q.nf ? find_slot(a.t, load_key(a.hashes + (q.b0 + j) * 32)) : -1;
+    const uint64_t mk = __ballot(slot == -1) & gmask;
+    const int first = mk ? __builtin_ctzll(mk) - base : G;
+    const int64_t found = __shfl(slot, base + (first > 0 ? first - 1 : 0), 64);
+    if (first > 0) parent = found;
     if (mk) {
-      m = j0 + (__builtin_ctzll(mk) - base);
+      m = j0 + first;
       break;
     }
   }
   if (sub != 0) return;
-  uint32_t node = block_node(a.t, load_key(m == 0 ? q.root : a.hashes + (q.b0 + m - 1) * 32));
+  if (m == 0) parent = find_slot(a.t, load_key(q.root));
   int64_t steps = 0;
-  if (node != kNoNode) {
+  if (parent != -1) {
     const int64_t rem = q.len - 16 * m;
-    const int64_t lim = rem < 15 ? rem : 15;
+    const int lim = (int)(rem < kChainMax ? rem : kChainMax);
     const int32_t *tp = a.tokens + q.t0 + 16 * m;
-    while (steps < lim) {
+    bool below = true;  // the node has token nodes
+    if (a.e.chain_tags && parent >= 0) {
+      uint32_t tok[16], other[16];
+      load_tokens(tp, rem, tok);
+      load_chain(a.e.chains + parent * 4, other);
+      below = a.e.chain_tags[parent] != 0;
+      const int both = !below ? 0 : (lim < (int)other[0] ? lim : (int)other[0]);
+      bool same = true;
+#pragma unroll
+      for (int i = 0; i < kChainMax; ++i) {
+        same = same && i < both && tok[i] == other[1 + i];
+        steps += same ? 1 : 0;
+      }
+    }
+    uint32_t node = node_id(a.e, parent) + (uint32_t)steps;
+    while (below && steps < lim) {
       node = edge_find(a.e, node, tp[steps]);
       if (node == kNoNode) break;
       ++steps;
     }
-  } else if (m > 0) {
-    m = 0;  // cannot happen for a consistent table: h_{m-1} was just found
   }
   a.match_len[r] = (int32_t)(16 * m + steps);
 }
@@ -290,7 +468,7 @@ int enqueue_edge_clear(kvgov_radix *x, hipStream_t s) {
   const unsigned grid = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>(ceil_div(x->edge_slots, 256), (int64_t)device_cu_count() * 64));
   hipLaunchKernelGGL(k_edge_fill, dim3(grid), dim3(256), 0, s, x->edges.keys, x->edge_slots,
-                     x->edges.meta);
+                     x->edges.chain_tags, x->blocks->slots, x->edges.meta);
   return launch_status();
 }
 
@@ -335,6 +513,18 @@ int radix_args(kvgov_radix *x, const int32_t *tokens, int64_t n_tokens,
   return KVGOV_OK;
 }
 
+template <bool BY_REQUEST>
+void radix_edges(const RadixArgs &a, int g, hipStream_t s) {
+  const dim3 grid((unsigned)ceil_div((int64_t)a.n * g, 256)), block(256);
+  switch (g) {
+    case 4: hipLaunchKernelGGL((k_radix_edges<4, BY_REQUEST>), grid, block, 0, s, a); break;
+    case 8: hipLaunchKernelGGL((k_radix_edges<8, BY_REQUEST>), grid, block, 0, s, a); break;
+    case 16: hipLaunchKernelGGL((k_radix_edges<16, BY_REQUEST>), grid, block, 0, s, a); break;
+    case 32: hipLaunchKernelGGL((k_radix_edges<32, BY_REQUEST>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_radix_edges<64, BY_REQUEST>), grid, block, 0, s, a); break;
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -357,12 +547,17 @@ int kvgov_radix_create(int32_t log2_block_slots, int32_t log2_edge_slots, kvgov_
   }
   x->edge_slots = (int64_t)1 << log2_edge_slots;
   x->edges.mask = (uint64_t)x->edge_slots - 1;
-  void *keys = nullptr, *meta = nullptr, *zero = nullptr;
+  void *keys = nullptr, *meta = nullptr, *zero = nullptr, *ctags = nullptr, *chains = nullptr;
+  const bool chained = log2_block_slots <= kMaxLog2Chains;
   if (hipMalloc(&keys, (size_t)x->edge_slots * 8) != hipSuccess ||
-      hipMalloc(&meta, sizeof(RadixMeta)) != hipSuccess || hipMalloc(&zero, 32) != hipSuccess) {
+      hipMalloc(&meta, sizeof(RadixMeta)) != hipSuccess || hipMalloc(&zero, 32) != hipSuccess ||
+      (chained && (hipMalloc(&ctags, (size_t)x->blocks->slots * 8) != hipSuccess ||
+                   hipMalloc(&chains, (size_t)x->blocks->slots * 64) != hipSuccess))) {
     if (keys) (void)hipFree(keys);
     if (meta) (void)hipFree(meta);
     if (zero) (void)hipFree(zero);
+    if (ctags) (void)hipFree(ctags);
+    if (chains) (void)hipFree(chains);
     kvgov_cache_destroy(x->blocks);
     delete x;
     return KVGOV_E_NOMEM;
@@ -370,6 +565,8 @@ int kvgov_radix_create(int32_t log2_block_slots, int32_t log2_edge_slots, kvgov_
   x->edges.keys = static_cast<unsigned long long *>(keys);
   x->edges.meta = static_cast<RadixMeta *>(meta);
   x->zero_root = static_cast<uint8_t *>(zero);
+  x->edges.chain_tags = static_cast<unsigned long long *>(ctags);
+  x->edges.chains = static_cast<u32x4 *>(chains);
   rc = hipMemset(zero, 0, 32) == hipSuccess ? KVGOV_OK : KVGOV_E_HIP;
   if (rc == KVGOV_OK) rc = enqueue_edge_clear(x, nullptr);
   if (rc == KVGOV_OK && hipStreamSynchronize(nullptr) != hipSuccess) rc = KVGOV_E_HIP;
@@ -388,6 +585,8 @@ int kvgov_radix_destroy(kvgov_radix *x) {
   if (hipFree(x->edges.keys) != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->edges.meta) != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->zero_root) != hipSuccess) rc = KVGOV_E_HIP;
+  if (hipFree(x->edges.chain_tags) != hipSuccess) rc = KVGOV_E_HIP;
+  if (hipFree(x->edges.chains) != hipSuccess) rc = KVGOV_E_HIP;
   const int rb = kvgov_cache_destroy(x->blocks);
   if (rc == KVGOV_OK) rc = rb;
   delete x;
@@ -424,15 +623,10 @@ int kvgov_radix_insert(kvgov_radix *x, const int32_t *tokens, int64_t n_tokens,
   if (rc != KVGOV_OK) return rc;
   rc = cache_insert_rows(c, hashes, blk_offsets, n, n_blocks, s, &a.blk_epoch);
   if (rc != KVGOV_OK) return rc;
-  const int g = radix_group(n, n_blocks);
-  const dim3 grid((unsigned)ceil_div((int64_t)n * g, 256)), block(256);
-  switch (g) {
-    case 4: hipLaunchKernelGGL(k_radix_edges<4>, grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL(k_radix_edges<8>, grid, block, 0, s, a); break;
-    case 16: hipLaunchKernelGGL(k_radix_edges<16>, grid, block, 0, s, a); break;
-    case 32: hipLaunchKernelGGL(k_radix_edges<32>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_radix_edges<64>, grid, block, 0, s, a); break;
-  }
+  if (cache_inserts_by_request(n, n_blocks))
+    radix_edges<true>(a, radix_group(n, n_blocks), s);
+  else
+    radix_edges<false>(a, radix_group(n, n_blocks), s);
   return launch_status();
 }
 
@@ -472,6 +666,9 @@ int kvgov_radix_stats(kvgov_radix *x, int64_t *block_nodes, int64_t *edges, void
   *edges = e;
   rc = kvgov_cache_count(x->blocks, block_nodes, stream);
   if (rc != KVGOV_OK) return rc;
+  // token nodes of chains take no edge slot, but the index holds as many as it
+  // has edge slots for
+  if (m.status == 0 && e > x->edge_slots) return KVGOV_E_FULL;
   return m.status;
 }
 

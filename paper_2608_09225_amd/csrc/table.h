@@ -265,6 +265,9 @@ __device__ __forceinline__ int64_t find_slot(const TableView &t, const Key &key)
 int cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
                       int32_t n, int64_t n_blocks, hipStream_t s, uint32_t *epoch);
 
+// Whether that insert walks the batch by requests (k_insert_req) or in chunks.
+bool cache_inserts_by_request(int32_t n, int64_t n_blocks);
+
 }  // namespace kvgov
 
 // The table object behind kvgov_cache *.
