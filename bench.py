@@ -1345,10 +1345,10 @@ def run_workload(name: str, args, dev, K, torch):
                                  for m in modes]))
         g_i = admit_group(A.n, nA)
         itr = [recorded_traffic(k, wl.name, t) for k, t in
-               (("k_radix_roots", "radix"), (f"k_insert_req<{g_i},false>", "cache"),
+               (("k_radix_roots", "radix"), (f"k_insert_req<{g_i},false,false>", "cache"),
                 (f"k_radix_edges<{g_i}>", "radix"))]
         result["roofline_radix_insert"] = {
-            "bound": "hbm", "kernel": f"k_radix_roots + k_insert_req<{g_i},false> + k_radix_edges<{g_i}> "
+            "bound": "hbm", "kernel": f"k_radix_roots + k_insert_req<{g_i},false,false> + k_radix_edges<{g_i}> "
                                       "(kvgov_radix_insert)",
             "achieved": ins_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": ins_gbs / HBM_PEAK_GBS,
@@ -1372,11 +1372,11 @@ def run_workload(name: str, args, dev, K, torch):
     if not probe_only and not admission and not radix_cfg:
         ins_gbs = float(np.mean([phases[W.MODE_NAMES[m]]["insert"]["gbs"] for m in modes]))
         g_ins = admit_group(A.n, nA)
-        itr = recorded_traffic(f"k_insert_req<{g_ins},false>", wl.name, "cache")
+        itr = recorded_traffic(f"k_insert_req<{g_ins},false,false>", wl.name, "cache")
         ins_s = float(np.mean([phases[W.MODE_NAMES[m]]["insert"]["ms_median"]
                                for m in modes])) / 1e3
         result["roofline_insert"] = {
-            "bound": "hbm", "kernel": f"k_insert_req<{g_ins},false> (set-union insert)",
+            "bound": "hbm", "kernel": f"k_insert_req<{g_ins},false,false> (set-union insert)",
             "achieved": ins_gbs,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ins_gbs / HBM_PEAK_GBS,
             "traffic": None if itr is None else itr["bytes"],

@@ -105,10 +105,19 @@ __device__ __forceinline__ int32_t find_request(const int64_t *bo, int32_t n, in
   return a;
 }
 
+// Table sizes whose new keys are claimed without reading the tag first (see
+// k_insert_req), each in a batch of distinct keys that fills 0.4 of the table,
+// read first against claimed first: 2^17 slots 24.8 / 27.5 us, 2^18 30.0 /
+// 26.7, 2^20 57.1 / 51.2, 2^22 126 / 132, 2^23 336 / 302, 2^25 (with clear and
+// lookup) 2199 / 2156.
+__device__ __forceinline__ bool claims_first(uint64_t mask) {
+  return mask >= (1ull << 23) - 1 || (mask >= (1ull << 18) - 1 && mask <= (1ull << 20) - 1);
+}
+
 // Insert walking the batch in chunks of kInsChunk consecutive rows per wave,
-// 64 at a time: the admission's first half (ADMIT), and the plain insert of
-// batches whose requests are so long that a group per request would leave
-// the chip idle (a flat key set given as one request).  Before touching the
+// 64 at a time: for batches whose requests are so long that a group per
+// request would leave the chip idle (a flat key set given as one request), in
+// the plain insert and as the admission's first half (ADMIT).  Before touching the
 // table a key is compared with the key at the same block position of the
 // previous request (requests that share a prefix - the same principal, or
 // any principal below the boundary block - hold the same keys there): an
@@ -210,9 +219,8 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 //     same key: the group's first lane inserts the request's first row
 //     before the others start, and if the slot's tag names an earlier row
 //     (the request that claimed the key, mostly the earliest one, since
-//     workgroups start in request order; for a key of an earlier call, the
-//     request that renewed its tag in this one) the group compares against
-//     the rows that follow it.  Requests of one principal share the
+//     workgroups start in request order) the group compares against the rows
+//     that follow it.  Requests of one principal share the
 //     root-salted prefix but are rarely adjacent.  (Lowering the tag to the
 //     earliest first row with an atomic minimum, as admission does, measured
 //     slower: 35.7 -> 36.6 us for the paper-shaped root-mode insert.)
@@ -221,17 +229,38 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 // offsets finds (the row past it lies in another request, at another depth).
 // Without the second comparison, every request's prefix rows read and raised
 // their keys' words: 66 us for the paper-shaped root-mode batch, 37 with it
-// (46 for a second batch, whose prefix keys are of an earlier call).
+// (46 for a second batch, whose prefix keys are of an earlier call: a tracked
+// first row gives such a key this call's tag, so that later requests find an
+// earlier one by it.  Untracked, reading the present keys costs less than the
+// renewals: 20 against 25 us for a batch that is all present.)
+//
+// Where the first key is new in this call, a chain's later keys are new as
+// well, or of this call: these rows go to the compare-and-swap without reading
+// the tag first, where that pays (claims_first).  The plain read fetches the
+// tag's line into this XCD's cache, from which the other XCDs' claims take it
+// again (270,000 random claims of 2^20 slots: 34 us with the read, 17
+// without).  Rows that follow a key of an earlier call keep the read: they are
+// mostly present (a batch that is all present: 20 us, 34 without the read).
 // Each request inserts the rows [blk_offsets[r], blk_offsets[r + 1]) cut to
 // the batch [blk_offsets[0], blk_offsets[n]); requests whose offsets are out
 // of order insert nothing.  With non-decreasing offsets that is every row
 // once.  Otherwise every row of the batch still lies in some request's
 // range (take the last r with blk_offsets[r] <= row), so the table receives
 // exactly the batch's keys.
-template <int G, bool TRACK>
+//
+// ADMIT: claims are lowered to the earliest row, tags of earlier calls stay (a
+// key's tag says that it was there before the call), and codes[f] records
+// where row f's key went, kCodeDup for a skipped row.  Its equal lies in an
+// earlier request: the previous one, or, by the second comparison, a row
+// before this request's first (a first key claimed by a later request is
+// lowered, and that group compares with nothing).  (The chunked walk, which
+// admission took for every batch before it had the second comparison: 73 us for
+// 8192 requests of two paper-shaped batches; now 47.)
+template <int G, bool ADMIT, bool TRACK>
 __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *hashes,
                                                     const int64_t *blk_offsets, int32_t n,
-                                                    int64_t n_blocks, uint32_t epoch) {
+                                                    int64_t n_blocks, uint32_t epoch,
+                                                    uint32_t *codes) {
   __shared__ uint32_t lds4[4];
   const int64_t lo = blk_offsets[0], hi = blk_offsets[n];
   if (blockIdx.x == 0 && threadIdx.x < kCounterLanes)
@@ -257,15 +286,18 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
     if (b0 < b1) {
       // first row, by the group's first lane
       int64_t g0 = -1, g1 = hi;  // the earlier request's rows
+      int fresh = 0;             // the first key is new in this call
       if (sub == 0) {
         const int64_t jj = b0 - b_r;
         const Key key = load_key(hashes + b0 * 32);
         const bool dup = jj < n_p && key_eq(key, load_key(hashes + (b_p + jj) * 32));
+        uint32_t code = kCodeDup;
         if (!dup) {
-          uint32_t code;
           unsigned long long claim = 0;
-          added += insert_key<false>(t, key, b0, lo, hashes, epoch, &code,
-                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim, true);
+          added += insert_key<ADMIT>(t, key, b0, lo, hashes, epoch, &code,
+                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim,
+                                     TRACK && !ADMIT);
+          fresh = !TRACK && claims_first(t.mask) && (uint32_t)(claim >> 32) == epoch;
           const int64_t c = lo + (int64_t)(claim & 0xFFFFFFFFull) - 1;
           if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0) {
             g0 = c;
@@ -274,20 +306,26 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
               g1 = blk_offsets[q + 1] < hi ? blk_offsets[q + 1] : hi;
               if (blk_offsets[q] != c) g0 = -1;
             }
+            if (ADMIT && g1 > b0) g1 = b0;
           }
         }
+        if (ADMIT) codes[b0] = code;
       }
       g0 = __shfl(g0, base, 64);
-      if (TRACK) g1 = __shfl(g1, base, 64);
+      fresh = __shfl(fresh, base, 64);
+      if (TRACK || ADMIT) g1 = __shfl(g1, base, 64);
       for (int64_t f = b0 + 1 + sub; f < b1; f += G) {
         const int64_t jj = f - b_r;
         const Key key = load_key(hashes + f * 32);
         bool dup = jj < n_p && key_eq(key, load_key(hashes + (b_p + jj) * 32));
-        if (!dup && g0 >= 0 && (!TRACK || g0 + jj < g1)) dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
-        uint32_t code;
+        if (!dup && g0 >= 0 && (!(TRACK || ADMIT) || g0 + jj < g1))
+          dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
+        uint32_t code = kCodeDup;
         if (!dup)
-          added += insert_key<false>(t, key, f, lo, hashes, epoch, &code,
-                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth);
+          added += insert_key<ADMIT>(t, key, f, lo, hashes, epoch, &code,
+                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr, false,
+                                     fresh != 0);
+        if (ADMIT) codes[f] = code;
       }
     }
   }
@@ -352,7 +390,7 @@ struct AdmitArgs {
   int32_t n;
   int64_t n_blocks;
   uint32_t epoch;
-  const uint32_t *codes;  // per row, from k_chunk_insert<true>
+  const uint32_t *codes;  // per row, from the insert
   int32_t *hit_blocks;
   int32_t *new_blocks;
 };
@@ -364,7 +402,7 @@ struct AdmitArgs {
 //                      before b0 (an earlier request holds it);
 //   new for r     <=>  K's earliest row is f itself.
 // hit_blocks[r] = first row not visible (relative to b0), new_blocks[r] =
-// rows new for r.  The earliest rows are final: k_chunk_insert<true> has ended.
+// rows new for r.  The earliest rows are final: the insert has ended.
 template <int G>
 __global__ __launch_bounds__(256) void k_admit_scan(AdmitArgs a) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -376,7 +414,7 @@ __global__ __launch_bounds__(256) void k_admit_scan(AdmitArgs a) {
   const uint64_t gmask = group_mask<G>(base);
   const int64_t lo = a.blk_offsets[0], hi = a.blk_offsets[a.n];
   const int64_t b0 = a.blk_offsets[r], b1 = a.blk_offsets[r + 1];
-  // the batch check of k_chunk_insert<true> (which then wrote no codes), and this
+  // the batch check of the insert (which then wrote no codes), and this
   // request's rows inside the batch
   if (lo < 0 || hi < lo || hi > a.n_blocks || hi - lo >= 0xFFFFFFFFll || b0 < lo || b1 < b0 ||
       b1 > hi) {
@@ -400,7 +438,7 @@ __global__ __launch_bounds__(256) void k_admit_scan(AdmitArgs a) {
         seen = false;
       } else if (code != kCodeDup) {
         const unsigned long long tag =
-            code == kCodeOnes ? a.t.meta->ones_tag : a.t.tags[code];
+            code == kCodeOnes ? a.t.meta->ones_tag : a.t.tags[code & a.t.mask];
         if ((uint32_t)(tag >> 32) == a.epoch) {
           const int64_t first = lo + (int64_t)(tag & 0xFFFFFFFFull) - 1;
           seen = first < b0;
@@ -889,12 +927,15 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s) {
 // the chunked walk above it.
 constexpr int64_t kReqInsertMaxAvg = 4096;
 
-// Lanes per request of the plain insert: about one lane per two rows of
-// the average request, 4 to 64.
+// Lanes per request of the insert: about one lane per two rows of the average
+// request, 4 to 64; in a batch small enough to be resident at once, a lane per
+// row (a group then takes one round after its first row: 64 requests of 16
+// rows 13.6 -> 9.8 us).
 int insert_group(int32_t n, int64_t n_blocks) {
   const int64_t avg = n > 0 ? n_blocks / n : 0;
   int g = 4;
   while (g < 64 && (int64_t)g * 2 < avg) g <<= 1;
+  while (g < 64 && g < avg && (int64_t)n * g * 2 <= (1 << 16)) g <<= 1;
   return g;
 }
 
@@ -996,17 +1037,34 @@ int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s)
   return m.status;
 }
 
-template <bool TRACK>
+template <bool ADMIT, bool TRACK>
 void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
-                int64_t n_blocks, uint32_t epoch, int g, hipStream_t s) {
+                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+  // (no request: only the batch check and the next call's counters)
+  const int g = n > 0 ? insert_group(n, n_blocks) : 64;
   const dim3 grid((unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * g, 256))), block(256);
   switch (g) {
-    case 4: hipLaunchKernelGGL((k_insert_req<4, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
-    case 8: hipLaunchKernelGGL((k_insert_req<8, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
-    case 16: hipLaunchKernelGGL((k_insert_req<16, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
-    case 32: hipLaunchKernelGGL((k_insert_req<32, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
-    default: hipLaunchKernelGGL((k_insert_req<64, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch); break;
+    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
   }
+}
+
+// The insert of a call: by requests, or, for few, long requests, where a group
+// per request would leave the chip idle, in chunks.  codes: ADMIT only.
+template <bool ADMIT>
+int insert_batch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
+                 int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+  if (!cache_inserts_by_request(n, n_blocks))
+    hipLaunchKernelGGL(k_chunk_insert<ADMIT>, dim3(insert_grid(n_blocks)), dim3(256), 0, s, t,
+                       hashes, blk_offsets, n, n_blocks, epoch, codes);
+  else if (t.track)
+    insert_req<ADMIT, true>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+  else
+    insert_req<ADMIT, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+  return launch_status();
 }
 
 }  // namespace
@@ -1020,19 +1078,7 @@ int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_
   *epoch = c->epoch.fetch_add(1) + 1;
   if (*epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;  // 2^32 - 1 inserts since clear
   if (c->view.track) note_tracked(c, n_blocks);
-  if (!cache_inserts_by_request(n, n_blocks)) {
-    // few, long requests: a group per request would leave the chip idle
-    hipLaunchKernelGGL(k_chunk_insert<false>, dim3(insert_grid(n_blocks)), dim3(256), 0, s,
-                       c->view, hashes, blk_offsets, n, n_blocks, *epoch, nullptr);
-    return launch_status();
-  }
-  // (no request: only the batch check and the next call's counters)
-  const int g = n > 0 ? insert_group(n, n_blocks) : 64;
-  if (c->view.track)
-    insert_req<true>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, g, s);
-  else
-    insert_req<false>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, g, s);
-  return launch_status();
+  return insert_batch<false>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, nullptr, s);
 }
 
 extern "C" {
@@ -1175,8 +1221,8 @@ int kvgov_cache_admit(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
   const uint32_t epoch = c->epoch.fetch_add(1) + 1;
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
   if (c->view.track) note_tracked(c, n_blocks);
-  hipLaunchKernelGGL(k_chunk_insert<true>, dim3(insert_grid(n_blocks)), dim3(256), 0, s,
-                     c->view, hashes, blk_offsets, n, n_blocks, epoch, codes);
+  rc = insert_batch<true>(c->view, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+  if (rc != KVGOV_OK) return rc;
   AdmitArgs a{c->view, blk_offsets, n, n_blocks, epoch, codes, hit_blocks, new_blocks};
   const int g = admit_group(n, n_blocks);
   const dim3 grid((unsigned)ceil_div((int64_t)n * g, 256)), block(256);

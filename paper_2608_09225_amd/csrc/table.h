@@ -151,8 +151,10 @@ __device__ __forceinline__ unsigned long long recency(uint32_t epoch, uint32_t d
 // Returns 1 if the key was added; *code receives where the key went, and
 // *claim (if given) the key's tag as this lane found it (its own claim if it
 // added the key).  With `renew`, a key of an earlier call takes this call's tag
-// (the plain insert's first rows: a later row with the same key then learns
-// of an earlier one in this call, as it does of a new key's).  On a table that tracks recency the key (added or found)
+// (a tracked insert's first rows: a later row with the same key then learns of
+// an earlier one in this call, as it does of a new key's).  With
+// `claim_first` (the key is thought to be new) the tag is not read before the
+// compare-and-swap.  On a table that tracks recency the key (added or found)
 // is touched with (epoch, depth) unless depth is kNoDepth.
 template <bool ADMIT>
 __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &key, int64_t i,
@@ -160,7 +162,7 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
                                                uint32_t epoch, uint32_t *code,
                                                uint32_t depth = kNoDepth,
                                                unsigned long long *claim = nullptr,
-                                               bool renew = false) {
+                                               bool renew = false, bool claim_first = false) {
   const unsigned long long mine = ((unsigned long long)epoch << 32) |
                                   (unsigned long long)(i - lo + 1);
   if (key_is_empty_pattern(key)) {
@@ -179,7 +181,7 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
   const uint64_t home = home_slot(key, t.mask);
   for (uint64_t probes = 0; probes <= t.mask; ++probes) {
     const uint64_t s = seq_slot(home, probes, t.mask);
-    unsigned long long tag = t.tags[s];
+    unsigned long long tag = claim_first ? 0ull : t.tags[s];
     if (tag == 0) {
       unsigned long long expect = 0;
       if (__hip_atomic_compare_exchange_strong(&t.tags[s], &expect, mine, __ATOMIC_RELAXED,

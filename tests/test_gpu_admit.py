@@ -225,3 +225,40 @@ def test_concurrent_admission_on_two_streams():
     finally:
         for c in caches:
             c.close()
+
+
+@pytest.mark.parametrize("max_len", [2, 7, 33, 150])
+@pytest.mark.parametrize("log2_slots,track", [(12, False), (12, True), (18, False), (18, True),
+                                              (23, False)])
+def test_admit_interleaved_heads(max_len, log2_slots, track):
+    """Requests that share first keys with requests far before or after them,
+    differ in length, and hold the same keys at other depths, so that a row may
+    be skipped only as equal to a row before its request's first; admitted
+    into an empty table (first keys new in the call) and, a second time, into
+    one that holds most of the keys; table sizes on both sides of the rule
+    for claiming without reading the tag."""
+    g = np.random.default_rng(max_len * 3 + log2_slots)
+    pool = g.integers(0, 256, (max_len * 12, 32), dtype=np.uint8)
+    pool[:, 0] = 1
+    T = O.Table()
+    with K.Cache(log2_slots) as c:
+        c.set_recency(track)
+        for _ in range(2):
+            lens = g.integers(0, max_len + 1, 300)
+            bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            rows = np.empty((int(bo[-1]), 32), np.uint8)
+            for r, n in enumerate(lens):
+                head = int(g.integers(0, 6)) * 2 * max_len
+                j = np.arange(n)
+                own = g.integers(0, pool.shape[0], n)
+                rows[bo[r]:bo[r + 1]] = pool[np.where(j < n * 2 // 3 + 1, head + j, own)]
+            hits, new, n_new = c.admit(dev(rows), dev(bo))
+            wh, wn = T.admit(rows, bo)
+            assert np.array_equal(hits.cpu().numpy(), wh)
+            assert np.array_equal(new.cpu().numpy(), wn)
+            assert n_new == int(wn.sum())
+            assert key_set(c.export().cpu().numpy()) == T.keys
+        if track:
+            for keep in (len(T.keys) * 3 // 4, 11, 1):
+                assert c.evict(keep) == T.evict(keep)
+                assert key_set(c.export().cpu().numpy()) == T.keys
