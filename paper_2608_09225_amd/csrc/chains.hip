@@ -17,18 +17,13 @@
 //
 // Per block a lane issues two compressions: (IV; h_{j-1} || T_j[0..7]) and
 // (state; T_j[8..15] || padding of a 96-byte message).  Three cases leave
-// that pattern and take the "special" path, entered only when some lane of
-// the wave needs it:
+// that pattern:
 //   * the first block of an unsalted chain: a 64-byte message T_0, whose
 //     second compression is the constant padding block;
 //   * the boundary block k > 0: a 128-byte message sigma || h_{k-1} || T_k,
-//     three compressions; the first, (IV; sigma || h_{k-1}), runs as an
-//     extra step and the usual two then take (T_k) and the padding block;
-//   * the root-salted first block needs no special path: it is the usual
-//     pattern with sigma in place of h_{-1}.
-// The hot path is fully unrolled with the round constants as immediates; the
-// special path uses a rolled compression reading them from constant memory,
-// which keeps the kernel's code within the instruction cache.
+//     three compressions, which its request alone spends further iterations on;
+//   * the root-salted first block is the usual pattern with sigma in place of
+//     h_{-1}.
 //
 // Token ids are little-endian int32 (4 bytes each, no separator); SHA-256
 // words are big-endian, so each token word is byte-swapped on load.  Digests
@@ -49,7 +44,6 @@ namespace kvgov {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
-__constant__ Sha256Tables kShaDev = make_tables();
 
 // ---------------------------------------------------------------------------
 // device helpers
@@ -100,29 +94,6 @@ __device__ __forceinline__ void load_digest(const uint8_t *src, uint32_t H[8]) {
   const u32x4 a = q[0], b = q[1];
   H[0] = bswap(a.x); H[1] = bswap(a.y); H[2] = bswap(a.z); H[3] = bswap(a.w);
   H[4] = bswap(b.x); H[5] = bswap(b.y); H[6] = bswap(b.z); H[7] = bswap(b.w);
-}
-
-// Compression with the 64 rounds in 4 groups of 16 and the constants read
-// from constant memory: same result as compress(), a quarter of the code.
-__device__ __forceinline__ void compress_rolled(uint32_t st[8], uint32_t w[16]) {
-  uint32_t a = st[0], b = st[1], c = st[2], d = st[3];
-  uint32_t e = st[4], f = st[5], g = st[6], h = st[7];
-#pragma unroll 1
-  for (int grp = 0; grp < 4; ++grp) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (grp > 0) {
-        w[i] = small_sigma1(w[(i + 14) & 15]) + w[(i + 9) & 15] +
-               small_sigma0(w[(i + 1) & 15]) + w[i];
-      }
-      const uint32_t t1 = h + big_sigma1(e) + ch(e, f, g) + kShaDev.K[grp * 16 + i] + w[i];
-      const uint32_t t2 = big_sigma0(a) + maj(a, b, c);
-      h = g; g = f; f = e; e = d + t1;
-      d = c; c = b; b = a; a = t1 + t2;
-    }
-  }
-  st[0] += a; st[1] += b; st[2] += c; st[3] += d;
-  st[4] += e; st[5] += f; st[6] += g; st[7] += h;
 }
 
 // ---------------------------------------------------------------------------
@@ -498,39 +469,6 @@ __device__ __forceinline__ bool chain_setup(const ChainArgs &a, int32_t r, Chain
   return true;
 }
 
-// The special path, per lane (rolled compressions):
-//   normal  : (IV; h || T[0..7])        (state; T[8..15] || pad96)
-//   u0      : (IV; T[0..15])            (state; pad64)
-//   boundary: (IV; sigma || h) -> X,   (X; T[0..15])   (state; pad128)
-// H (h_{j-1} in, h_j out) and the block's token words T.
-__device__ __forceinline__ void special_block(uint32_t H[8], const uint32_t T[16],
-                                              const uint32_t sig[8], bool u0, bool bnd) {
-  uint32_t X[8], st[8], w[16];
-  set_iv(X);
-  if (bnd) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) { w[q] = sig[q]; w[8 + q] = H[q]; }
-    compress_rolled(X, w);
-  }
-  const bool whole = u0 || bnd;  // first compression takes all 16 token words
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    st[q] = X[q];
-    w[q] = whole ? T[q] : H[q];
-    w[8 + q] = whole ? T[8 + q] : T[q];
-  }
-  compress_rolled(st, w);
-#pragma unroll
-  for (int q = 0; q < 8; ++q) w[q] = whole ? (q == 0 ? 0x80000000u : 0u) : T[8 + q];
-  w[8] = whole ? 0u : 0x80000000u;
-#pragma unroll
-  for (int q = 9; q < 15; ++q) w[q] = 0;
-  w[15] = u0 ? 64 * 8 : (bnd ? 128 * 8 : 96 * 8);
-  compress_rolled(st, w);
-#pragma unroll
-  for (int q = 0; q < 8; ++q) H[q] = st[q];
-}
-
 // Padding words 8..15 of the second block of a 96-byte message.
 __device__ __forceinline__ void pad96_tail(uint32_t w[16]) {
   w[8] = 0x80000000u;
@@ -541,6 +479,17 @@ __device__ __forceinline__ void pad96_tail(uint32_t w[16]) {
 
 // One lane per request.  Every instruction of a compression (rounds and
 // message schedule) is issued by the lane's wave.
+//
+// An iteration is two compressions: (IV; h || T[0..7]), then (state; T[8..15]
+// || pad96).  A block of another pattern takes iterations of its own lane,
+// with one compression each (the second one's result is not used), while the
+// other lanes of the wave go on with theirs: the unsalted first block two, (IV;
+// T) and (state; pad64), the boundary block three, (IV; sigma || h), (state;
+// T) and (state; pad128).  So a request costs its wave one or two iterations
+// more, wherever its boundary is.  (In one iteration for the whole wave, a
+// wave of 64 boundaries ran three compressions in nearly every iteration:
+// 262,144 chains of 32 blocks with uniform boundaries 2.24 ms, now 0.95, and
+// 0.83 with root salts.)
 template <int MODE>
 __device__ __forceinline__ void single_chain(const ChainArgs &a, int32_t i) {
   if (i >= a.n) return;
@@ -549,46 +498,97 @@ __device__ __forceinline__ void single_chain(const ChainArgs &a, int32_t i) {
   if (!chain_setup<MODE>(a, r, q) || q.nf == 0) return;
   const int64_t nf = q.nf;
 
-  // H holds h_{j-1} as state words: the parent digest when resuming; a
+  // What the lane's next first compression is: a plain block's, or one of the
+  // others' (sigma || h; the block's tokens; padding of `bits`).
+  enum { kPlain, kSalt, kTokens, kPadding };
+  int what = kPlain;
+  uint32_t bits = 64 * 8;
+
+  // H holds h_{j-1} as state words, or, between the compressions of a block of
+  // another pattern, the state so far: the parent digest when resuming; a
   // root-salted first block (and k == 0 in boundary mode) is the usual
   // pattern with sigma in place of h_{-1}.
   uint32_t H[8];
   if (q.j0 > 0) {
     load_digest(a.parents + (int64_t)r * 32, H);
-  } else {
+  } else if (q.salted_root) {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) H[w] = q.salted_root ? q.sig[w] : 0u;
+    for (int w = 0; w < 8; ++w) H[w] = q.sig[w];
+  } else {
+    set_iv(H);
+    what = kTokens;
+  }
+  if (MODE == KVGOV_BOUNDARY && q.kr == 0) {
+    what = kSalt;
+    bits = 128 * 8;
   }
 
   u32x4 nxt[4];
   uint32_t T[16];  // tokens of block j
   load_raw(q.tp, nxt);
   take_block(nxt, T, q.tp, 0, nf);
-  const bool plain_first = !q.salted_root && q.j0 == 0;
 
-  // iteration j hashes block q.j0 + j of the chain
-  for (int64_t j = 0; j < nf; ++j) {
-    const bool u0 = plain_first && j == 0;
-    const bool bnd = (MODE == KVGOV_BOUNDARY) && j == q.kr;
-    if (MODE == KVGOV_ROOT || !__any(u0 || bnd)) {
-      // hot path: (IV; h || T[0..7]) then (state; T[8..15] || pad96)
-      uint32_t st[8], w[16];
+  // block q.j0 + j of the chain
+  for (int64_t j = 0; j < nf;) {
+    uint32_t st[8], w[16];
+    const bool other = MODE != KVGOV_ROOT && __any(what != kPlain);
+    if (!other) {
       set_iv(st);
 #pragma unroll
       for (int x = 0; x < 8; ++x) { w[x] = H[x]; w[8 + x] = T[x]; }
-      compress(st, w);
+    } else {
+      const bool iv = what == kPlain || what == kSalt;
 #pragma unroll
-      for (int x = 0; x < 8; ++x) w[x] = T[8 + x];
-      pad96_tail(w);
-      compress(st, w);
+      for (int x = 0; x < 8; ++x) {
+        st[x] = iv ? kSha.H0[x] : H[x];
+        const uint32_t lo = what == kSalt ? q.sig[x] : H[x];
+        const uint32_t hi = what == kSalt ? H[x] : T[x];
+        w[x] = what == kTokens ? T[x] : lo;
+        w[8 + x] = what == kTokens ? T[8 + x] : hi;
+        if (what == kPadding) {
+          w[x] = x == 0 ? 0x80000000u : 0u;
+          w[8 + x] = x == 7 ? bits : 0u;
+        }
+      }
+    }
+    compress(st, w);
+    if (MODE != KVGOV_ROOT) {
 #pragma unroll
       for (int x = 0; x < 8; ++x) H[x] = st[x];
-    } else {
-      special_block(H, T, q.sig, u0, bnd);
     }
-    // the next block's tokens before the digest store (see take_block)
-    take_block(nxt, T, q.tp, j + 1 < nf ? j + 1 : j, nf);
-    store_digest(q.out + j * 32, H);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) w[x] = T[8 + x];
+    pad96_tail(w);
+    compress(st, w);
+    if (!other) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) H[x] = st[x];
+      // the next block's tokens before the digest store (see take_block)
+      take_block(nxt, T, q.tp, j + 1 < nf ? j + 1 : j, nf);
+      store_digest(q.out + j * 32, H);
+      ++j;
+    } else {
+      const bool plain = what == kPlain;
+      const bool ends = plain || what == kPadding;  // the block's digest is there
+#pragma unroll
+      for (int x = 0; x < 8; ++x) H[x] = plain ? st[x] : H[x];
+      // a lane whose block goes on keeps its tokens, and loads the same again
+      uint32_t N[16];
+      swap_block(nxt, N);
+      __builtin_amdgcn_sched_barrier(0);
+      const int64_t at = ends ? j + 2 : j + 1;
+      load_raw(q.tp + 16 * (at < nf ? at : nf - 1), nxt);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int x = 0; x < 16; ++x) T[x] = ends ? N[x] : T[x];
+      if (ends) store_digest(q.out + j * 32, H);
+      j += ends ? 1 : 0;
+      what = ends ? kPlain : (what == kSalt ? kTokens : kPadding);
+    }
+    if (MODE == KVGOV_BOUNDARY && j == q.kr && what == kPlain) {
+      what = kSalt;
+      bits = 128 * 8;
+    }
   }
 }
 
@@ -1345,27 +1345,6 @@ __global__ __launch_bounds__(256) void k_chains_mixed(ChainArgs a, int32_t lp_gr
 // host side
 // ---------------------------------------------------------------------------
 
-// Dynamic LDS per chain workgroup: just over half a CU's LDS.
-static size_t chain_lds_reserve() {
-  static std::mutex mu;
-  static std::vector<size_t> per_dev;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 96 * 1024;
-  std::lock_guard<std::mutex> g(mu);
-  if ((int)per_dev.size() <= dev) per_dev.resize(dev + 1, 0);
-  if (per_dev[dev] == 0) {
-    int cu_lds = 0, blk_lds = 0;
-    if (hipDeviceGetAttribute(&cu_lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
-            hipSuccess || cu_lds <= 0)
-      cu_lds = 160 * 1024;
-    if (hipDeviceGetAttribute(&blk_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
-            hipSuccess || blk_lds <= 0)
-      blk_lds = cu_lds;
-    per_dev[dev] = std::min<size_t>((size_t)cu_lds / 2 + 4096, (size_t)blk_lds);
-  }
-  return per_dev[dev];
-}
-
 static int cu_lds_bytes() {
   int dev = 0, v = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -1694,7 +1673,7 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
     // many waves (one lane per request) as the chip has SIMDs, and it is
     // ordered longest first (counting sort of block counts).  The longest
     // requests then run on lane-pair workgroups (one eighth of the CUs), the
-    // rest one lane per request; one workgroup per CU.
+    // rest one lane per request.
     // The ordering scratch: the library's fixed array for the
     // allocation-free entry point, else the stream's own scratch.
     int32_t *buf = nullptr;
@@ -1712,8 +1691,12 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
     const int32_t lp_groups = std::max(1, device_cu_count() / 8);
     const int64_t rest = std::max<int64_t>(0, (int64_t)n - (int64_t)lp_groups * kWave);
     const dim3 grid((unsigned)(lp_groups + ceil_div(rest, 4 * kWave))), block(4 * kWave);
-    const size_t res = chain_lds_reserve();
-    const size_t lds = res > sizeof(LpLds) ? res - sizeof(LpLds) : 0;
+    // two workgroups per CU: a second wave on each SIMD issues while the first
+    // waits (250,000 chains of 32 blocks 0.695 -> 0.635 ms; one per CU was the
+    // rule while a one-lane wave beside a lane-pair one slowed its chain, which
+    // the rounds waves' priority prevents: 65,536 lognormal prompts 5.14 ->
+    // 5.01 ms)
+    const size_t lds = lp_lds_reserve(2);
     if (ev_start && hipEventRecord(ev_start, s) != hipSuccess) return KVGOV_E_HIP;
     switch (mode) {
       case KVGOV_NONE: hipLaunchKernelGGL(k_chains_mixed<KVGOV_NONE>, grid, block, lds, s, a, lp_groups); break;

@@ -175,13 +175,14 @@ def test_chains_long_with_scattered_boundaries(mode):
     assert np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("n_req", [1, 63, 64, 65, 129, 1092])
+@pytest.mark.parametrize("n_req", [1, 63, 64, 65, 129, 1092, 20000, 36000])
 def test_chains_every_boundary_block(n_req):
     """Every boundary block of chains of 1..13 blocks, and past the last one,
-    side by side in workgroups: a request takes one iteration more than its
-    blocks for its boundary block's padding, at an iteration of its own."""
-    nf = [f for f in range(1, 14) for _ in range(f + 1)] * 11
-    k = [j for f in range(1, 14) for j in range(f + 1)] * 11
+    side by side in workgroups: a request takes an iteration more than its
+    blocks for its boundary block's padding (on lane pairs; two on one lane,
+    36,000 requests), at an iteration of its own."""
+    nf = [f for f in range(1, 14) for _ in range(f + 1)] * 347
+    k = [j for f in range(1, 14) for j in range(f + 1)] * 347
     order = np.random.default_rng(47).permutation(len(nf))[:n_req]
     g = np.random.default_rng(48)
     lens = np.array(nf)[order] * 16 + g.integers(0, 16, order.size)
@@ -189,8 +190,8 @@ def test_chains_every_boundary_block(n_req):
     b.boundary_tok[:] = np.minimum(np.array(k)[order] * 16 + g.integers(0, 16, order.size), lens)
     Kb, ids = secret(13, 5)
     got = gpu_chains(b, K.salts(Kb, dev(ids)), W.BOUNDARY).cpu().numpy()
-    want = O.hash_chains(b.tokens, b.tok_offsets, b.principal, O.salts(Kb, ids), W.BOUNDARY,
-                         b.boundary_tok)
+    want = O.hash_chains_parallel(b.tokens, b.tok_offsets, b.principal, O.salts(Kb, ids),
+                                  W.BOUNDARY, b.boundary_tok)
     assert np.array_equal(got, want)
 
 
