@@ -61,10 +61,13 @@ __global__ __launch_bounds__(256) void k_cache_fill(u32x4 *keys, unsigned long l
       m->n_keys[i] = 0;
       m->new_keys[0][i] = 0;
       m->new_keys[1][i] = 0;
+      m->n_edges[i] = 0;
     }
     if (threadIdx.x == 0) {
       m->exported = 0;
       m->erased = 0;
+      m->marked = 0;
+      m->radix_status = 0;
       m->ones_tag = 0;
       m->ones_rank = 0;
       m->status = 0;
@@ -522,46 +525,27 @@ __global__ __launch_bounds__(256) void k_export(TableView t, uint8_t *out, int64
 // table took 180 us of a 240 us evict; now 27 of 53.)
 constexpr int kRankDigit = 11;
 constexpr int kRankBins = 1 << kRankDigit;
-constexpr int kRankLanes = 16;  // addresses the range's atomics are spread over
 constexpr int kRankThreads = 1024;
 static_assert(kRankBins == 2 * kRankThreads, "two bins per thread in the decision");
 
 struct SelectState {
-  unsigned long long any[kRankLanes];   // or of the words
-  unsigned long long all[kRankLanes];   // and of the words
-  unsigned long long used[kRankLanes];  // words other than 0
-  unsigned long long prefix;            // digits decided so far
-  unsigned long long threshold;         // keep rank >= threshold once done
-  unsigned long long budget;            // keys still allowed below the decided part
-  unsigned long long ones_rank;         // the all-0xFF key's, if it is kept
-  int32_t bits;                         // bits left to decide (kRankStart: none decided yet)
+  unsigned long long prefix;     // digits decided so far
+  unsigned long long threshold;  // keep rank >= threshold once done
+  unsigned long long budget;     // keys still allowed below the decided part
+  unsigned long long ones_rank;  // the all-0xFF key's, if it is kept
+  int32_t bits;                  // bits left to decide (kRankStart: none decided yet)
   int32_t done;
   int32_t ones_keep;
-  uint32_t arrived;                     // workgroups that have added their counts
+  uint32_t arrived;              // workgroups that have added their counts
 };
 constexpr int32_t kRankStart = 255;
 
-__global__ __launch_bounds__(256) void k_select_init(SelectState *st, unsigned int *hist,
-                                                     long long budget, int erase, CacheMeta *m) {
-  if (threadIdx.x < kRankLanes) {
-    st->any[threadIdx.x] = 0;
-    st->all[threadIdx.x] = ~0ull;
-    st->used[threadIdx.x] = 0;
-  }
-  if (threadIdx.x == 0) {
-    st->prefix = 0;
-    st->threshold = 0;  // erase: keep every key not marked
-    st->budget = (unsigned long long)budget;
-    st->ones_rank = 0;
-    st->bits = kRankStart;
-    st->done = erase;
-    st->ones_keep = 0;
-    st->arrived = 0;
-    m->erased = 0;
-  }
-  if (!erase)
-    for (int i = threadIdx.x; i < kRankBins; i += blockDim.x) hist[i] = 0;
-}
+// One workgroup's part of the recency words: which bits they have, and how
+// many there are.
+struct RankPart {
+  unsigned long long any, all, used;  // or, and, number of the words other than 0
+};
+constexpr int kRankParts = 512;
 
 __device__ __forceinline__ unsigned long long wave_or(unsigned long long v) {
 #pragma unroll
@@ -572,41 +556,47 @@ __device__ __forceinline__ unsigned long long wave_and(unsigned long long v) {
   return ~wave_or(~v);
 }
 
-// The recency words' bits and number.  An empty slot's word is 0, so the tags
-// are not read.
-__global__ __launch_bounds__(256) void k_rank_range(TableView t, SelectState *st) {
+// The recency words' bits and number, a part per workgroup (added up by each
+// workgroup of the select).  An empty slot's word is 0, so the tags are not
+// read.  Workgroup 0 also starts the select.
+__global__ __launch_bounds__(256) void k_rank_range(TableView t, SelectState *st, RankPart *parts,
+                                                    unsigned int *hist, long long budget) {
   const int64_t slots = (int64_t)t.mask + 1;
   const int64_t stride = (int64_t)gridDim.x * 256;
   unsigned long long any = 0, all = ~0ull, used = 0;
+#pragma unroll 8
   for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots; s += stride) {
     const unsigned long long r = t.rank[s];
     any |= r;
     all &= r ? r : ~0ull;
     used += r ? 1 : 0;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && t.meta->ones_present && t.meta->ones_rank) {
-    any |= t.meta->ones_rank;
-    all &= t.meta->ones_rank;
-    ++used;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      const unsigned long long r = t.meta->ones_present ? t.meta->ones_rank : 0ull;
+      any |= r;
+      all &= r ? r : ~0ull;
+      used += r ? 1 : 0;
+      st->prefix = 0;
+      st->threshold = 0;
+      st->budget = (unsigned long long)budget;
+      st->bits = kRankStart;
+      st->done = 0;
+      st->arrived = 0;
+    }
+    for (int i = threadIdx.x; i < kRankBins; i += 256) hist[i] = 0;
   }
-  __shared__ unsigned long long w[3][4];
+  __shared__ RankPart w[4];
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) used += __shfl_xor(used, d, 64);
   any = wave_or(any);
   all = wave_and(all);
-  if ((threadIdx.x & 63) == 0) {
-    w[0][threadIdx.x >> 6] = any;
-    w[1][threadIdx.x >> 6] = all;
-    w[2][threadIdx.x >> 6] = used;
-  }
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = RankPart{any, all, used};
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  used = w[2][0] + w[2][1] + w[2][2] + w[2][3];
-  if (!used) return;
-  const int l = blockIdx.x % kRankLanes;
-  atomicOr(&st->any[l], w[0][0] | w[0][1] | w[0][2] | w[0][3]);
-  atomicAnd(&st->all[l], w[1][0] & w[1][1] & w[1][2] & w[1][3]);
-  atomicAdd(&st->used[l], used);
+  if (threadIdx.x == 0)
+    parts[blockIdx.x] = RankPart{w[0].any | w[1].any | w[2].any | w[3].any,
+                                 w[0].all & w[1].all & w[2].all & w[3].all,
+                                 w[0].used + w[1].used + w[2].used + w[3].used};
 }
 
 // Which bits of the recency words differ, as the widths of the two halves.
@@ -622,15 +612,25 @@ struct RankBits {
   }
 };
 
-__device__ __forceinline__ RankBits rank_bits(const SelectState *st) {
+// From the parts, for every thread of a workgroup of kRankThreads.
+__device__ __forceinline__ RankBits rank_bits(const RankPart *parts, int n_parts) {
+  __shared__ RankPart w[kRankThreads / 64];
+  RankPart p{0, ~0ull, 0};
+  if ((int)threadIdx.x < n_parts) p = parts[threadIdx.x];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) p.used += __shfl_xor(p.used, d, 64);
+  p.any = wave_or(p.any);
+  p.all = wave_and(p.all);
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = p;
+  __syncthreads();
   unsigned long long any = 0, all = ~0ull;
   RankBits b;
   b.used = 0;
 #pragma unroll
-  for (int i = 0; i < kRankLanes; ++i) {
-    any |= st->any[i];
-    all &= st->all[i];
-    b.used += st->used[i];
+  for (int i = 0; i < kRankThreads / 64; ++i) {
+    any |= w[i].any;
+    all &= w[i].all;
+    b.used += w[i].used;
   }
   const unsigned long long vary = any & ~all;
   const uint32_t hi = (uint32_t)(vary >> 32), lo = (uint32_t)vary;
@@ -639,19 +639,21 @@ __device__ __forceinline__ RankBits rank_bits(const SelectState *st) {
   b.common = any & ~((((1ull << b.cs) - 1) << 32) | ((1ull << b.cd) - 1));
   return b;
 }
+static_assert(kRankParts <= kRankThreads, "a thread per part");
 
 // The next digit: its histogram over the words that match the decided
 // digits, and, in the workgroup that arrives last, the digit at which the
 // kept count crosses the budget (keys with a higher digit are kept).  Leaves
 // the histogram and the arrival count cleared for the next pass.
 __global__ __launch_bounds__(kRankThreads) void k_rank_select(TableView t, SelectState *st,
+                                                              const RankPart *parts, int n_parts,
                                                               unsigned int *hist) {
   __shared__ unsigned int h[kRankBins];
   __shared__ unsigned long long above[kRankThreads / 64];
   __shared__ int last;
   if (st->done) return;
   const int tid = threadIdx.x;
-  const RankBits rb = rank_bits(st);
+  const RankBits rb = rank_bits(parts, n_parts);
   const int left = st->bits == kRankStart ? rb.cs + rb.cd : st->bits;
   const int width = left < kRankDigit ? left : kRankDigit;
   const int shift = left - width;
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(256) void k_erase_mark(TableView t, const uint8_t *
     if (w && atomicExch(w, kErased) != kErased) marked = 1;
   }
   const uint32_t total = block_sum(marked, lds4);
-  if (threadIdx.x == 0 && total) atomicAdd(&t.meta->erased, (unsigned long long)total);
+  if (threadIdx.x == 0 && total) atomicAdd(&t.meta->marked, (unsigned long long)total);
 }
 
 // The rebuild.  A workgroup takes a region of kRegion slots, copies the
@@ -762,29 +764,30 @@ __global__ __launch_bounds__(256) void k_erase_mark(TableView t, const uint8_t *
 // shared, and a table at load 1/4 has a quarter of its slots written.  (With
 // the copies packed over the whole table by one atomic per 4096 slots, the
 // table emptied by a launch of its own, and 256 workgroups: 50 us for 2^20
-// slots; now 26.)
+// slots; now 24.)
 constexpr int kRegion = 1024;
 
-__global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, u32x4 *out_keys,
-                                                 unsigned long long *out_rank,
+__global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, int erase,
+                                                 u32x4 *out_keys, unsigned long long *out_rank,
                                                  uint32_t *region_count) {
   __shared__ uint32_t wsum[4];
   const int64_t slots = (int64_t)t.mask + 1;
-  const unsigned long long thr = st->threshold;
+  const unsigned long long thr = erase ? 0ull : st->threshold;  // erase: all but the marked
   const u32x4 ones = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
   constexpr int kItems = kRegion / 256;
   const int64_t b0 = (int64_t)blockIdx.x * kRegion;
-  unsigned long long r[kItems];
+  unsigned long long r[kItems], tag[kItems];
   uint32_t keep = 0, have = 0;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
     const int64_t s = b0 + k * 256 + threadIdx.x;
-    r[k] = 0;
-    if (s < slots && t.tags[s] != 0) {
-      r[k] = t.rank[s];
-      have |= 1u << k;
-      if (r[k] != kErased && r[k] >= thr) keep |= 1u << k;
-    }
+    tag[k] = s < slots ? t.tags[s] : 0ull;
+    r[k] = s < slots ? t.rank[s] : 0ull;
+  }
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    have |= tag[k] != 0 ? 1u << k : 0u;
+    keep |= tag[k] != 0 && r[k] != kErased && r[k] >= thr ? 1u << k : 0u;
   }
   // exclusive prefix of the kept counts over the workgroup
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -836,6 +839,8 @@ __global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, u
       m->ones_tag = 0;
       m->ones_rank = 0;
       m->ones_present = 0;
+      m->erased = m->marked;
+      m->marked = 0;
     }
   }
 }
@@ -954,13 +959,17 @@ void note_tracked(kvgov_cache *c, int64_t n_blocks) {
   }
 }
 
-int read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s) {
-  if (hipMemcpyAsync(m, c->view.meta, sizeof(CacheMeta), hipMemcpyDeviceToHost, s) !=
-      hipSuccess)
+}  // namespace
+
+int kvgov::cache_read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s, bool radix) {
+  const size_t bytes = radix ? sizeof(CacheMeta) : offsetof(CacheMeta, n_edges);
+  if (hipMemcpyAsync(m, c->view.meta, bytes, hipMemcpyDeviceToHost, s) != hipSuccess)
     return KVGOV_E_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return KVGOV_E_HIP;
   return KVGOV_OK;
 }
+
+namespace {
 
 // Maintenance scratch, in the stream's scratch buffer: selection state, the
 // rank histogram, the regions' counts and room for every key of the table (32
@@ -969,6 +978,7 @@ int read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s) {
 // serves this call until its kernels end.
 struct MaintScratch {
   SelectState *st = nullptr;
+  RankPart *parts = nullptr;
   unsigned int *hist = nullptr;
   uint32_t *regions = nullptr;
   u32x4 *keys = nullptr;
@@ -979,8 +989,9 @@ struct MaintScratch {
 unsigned region_grid(int64_t slots) { return (unsigned)ceil_div(slots, kRegion); }
 
 int maint_alloc(kvgov_cache *c, hipStream_t s, MaintScratch &m) {
-  const size_t off_hist = 1024;
-  static_assert(sizeof(SelectState) <= 1024, "the state's part of the scratch");
+  const size_t off_parts = 256;
+  static_assert(sizeof(SelectState) <= 256, "the state's part of the scratch");
+  const size_t off_hist = off_parts + kRankParts * sizeof(RankPart);
   const size_t off_regions = off_hist + kRankBins * sizeof(unsigned int);
   const size_t off_keys = off_regions + ((size_t)region_grid(c->slots) * 4 + 255) / 256 * 256;
   const size_t off_rank = off_keys + (size_t)c->slots * 32;
@@ -990,6 +1001,7 @@ int maint_alloc(kvgov_cache *c, hipStream_t s, MaintScratch &m) {
   if (rc != KVGOV_OK) return rc;
   uint8_t *b = static_cast<uint8_t *>(base);
   m.st = reinterpret_cast<SelectState *>(b);
+  m.parts = reinterpret_cast<RankPart *>(b + off_parts);
   m.hist = reinterpret_cast<unsigned int *>(b + off_hist);
   m.regions = reinterpret_cast<uint32_t *>(b + off_regions);
   m.keys = reinterpret_cast<u32x4 *>(b + off_keys);
@@ -1000,27 +1012,21 @@ int maint_alloc(kvgov_cache *c, hipStream_t s, MaintScratch &m) {
 // Copies out what ranks at or above the selected threshold while emptying the
 // table, and inserts the copies again; then reads the table's counters if
 // asked (waiting for the stream).
-int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, CacheMeta *meta) {
+int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, int erase, CacheMeta *meta) {
   const uint32_t epoch = c->epoch.fetch_add(1) + 1;
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
   const dim3 grid(region_grid(c->slots)), block(256);
-  hipLaunchKernelGGL(k_compact, grid, block, 0, s, c->view, m.st, m.keys, m.rank, m.regions);
+  hipLaunchKernelGGL(k_compact, grid, block, 0, s, c->view, m.st, erase, m.keys, m.rank,
+                     m.regions);
   hipLaunchKernelGGL(k_reinsert, grid, block, 0, s, c->view, m.st,
                      reinterpret_cast<const uint8_t *>(m.keys), m.rank, m.regions, epoch);
   int rc = launch_status();
   m.lk.unlock();  // everything that uses the scratch is enqueued
   if (rc == KVGOV_OK && meta) {
-    rc = read_meta(c, meta, s);
+    rc = cache_read_meta(c, meta, s);
     if (rc == KVGOV_OK) rc = meta->status;
   }
   return rc;
-}
-
-// Keys in the table, from its counters.
-int64_t key_count(const CacheMeta &m) {
-  int64_t total = 0;
-  for (int i = 0; i < kCounterLanes; ++i) total += (int64_t)m.n_keys[i];
-  return total;
 }
 
 int bit_length(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
@@ -1029,7 +1035,7 @@ int bit_length(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
 // error.
 int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s) {
   CacheMeta m{};
-  int rc = read_meta(c, &m, s);
+  int rc = cache_read_meta(c, &m, s);
   if (rc != KVGOV_OK) return rc;
   int64_t added = 0;
   for (int i = 0; i < kCounterLanes; ++i) added += (int64_t)m.new_keys[epoch & 1][i];
@@ -1254,10 +1260,9 @@ int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *s
   MaintScratch m;
   rc = maint_alloc(c, s, m);
   if (rc != KVGOV_OK) return rc;
-  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, s, m.st, m.hist, (long long)max_keys,
-                     0, c->view.meta);
-  hipLaunchKernelGGL(k_rank_range, dim3(grid_for(ceil_div(c->slots, 8), 4)), dim3(256), 0, s,
-                     c->view, m.st);
+  const int parts = (int)std::min<int64_t>(ceil_div(c->slots, 256 * 8), kRankParts);
+  hipLaunchKernelGGL(k_rank_range, dim3(parts), dim3(256), 0, s, c->view, m.st, m.parts, m.hist,
+                     (long long)max_keys);
   // enough passes for every bit that can differ: stamps up to the clock,
   // depths up to the largest tracked batch (a pass after the last needed one
   // ends at once)
@@ -1265,10 +1270,11 @@ int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *s
   const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(c->slots, kRankThreads * 8),
                                                    device_cu_count() * 2);
   for (int left = std::max(bits, 1); left > 0; left -= kRankDigit)
-    hipLaunchKernelGGL(k_rank_select, dim3(wgs), dim3(kRankThreads), 0, s, c->view, m.st, m.hist);
+    hipLaunchKernelGGL(k_rank_select, dim3(wgs), dim3(kRankThreads), 0, s, c->view, m.st, m.parts,
+                       parts, m.hist);
   c->rank_dirty = true;
   CacheMeta meta{};
-  rc = compact_rebuild(c, s, m, n_kept ? &meta : nullptr);
+  rc = compact_rebuild(c, s, m, 0, n_kept ? &meta : nullptr);
   if (rc == KVGOV_OK && n_kept) *n_kept = key_count(meta);
   return rc;
 }
@@ -1283,14 +1289,12 @@ int kvgov_cache_erase(kvgov_cache *c, const uint8_t *keys, int64_t n_keys, int64
   MaintScratch m;
   rc = maint_alloc(c, s, m);
   if (rc != KVGOV_OK) return rc;
-  hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, s, m.st, m.hist, 0ll, 1,
-                     c->view.meta);
   if (n_keys > 0)
     hipLaunchKernelGGL(k_erase_mark, dim3((unsigned)ceil_div(n_keys, 256)), dim3(256), 0, s,
                        c->view, keys, n_keys);
   c->rank_dirty = true;
   CacheMeta meta{};
-  rc = compact_rebuild(c, s, m, n_erased ? &meta : nullptr);
+  rc = compact_rebuild(c, s, m, 1, n_erased ? &meta : nullptr);
   if (rc == KVGOV_OK && n_erased) *n_erased = (int64_t)meta.erased;
   return rc;
 }
@@ -1300,7 +1304,7 @@ int kvgov_cache_count(kvgov_cache *c, int64_t *n_keys, void *stream) {
   int rc = check_device(c);
   if (rc != KVGOV_OK) return rc;
   CacheMeta m{};
-  rc = read_meta(c, &m, as_stream(stream));
+  rc = cache_read_meta(c, &m, as_stream(stream));
   if (rc != KVGOV_OK) return rc;
   *n_keys = key_count(m);
   return m.status;
@@ -1319,7 +1323,7 @@ int kvgov_cache_export(kvgov_cache *c, uint8_t *keys, int64_t cap, int64_t *n_ke
   rc = launch_status();
   if (rc != KVGOV_OK) return rc;
   CacheMeta m{};
-  rc = read_meta(c, &m, s);
+  rc = cache_read_meta(c, &m, s);
   if (rc != KVGOV_OK) return rc;
   *n_keys = (int64_t)m.exported;
   return (int64_t)m.exported > cap ? KVGOV_E_CAPACITY : KVGOV_OK;

@@ -56,15 +56,10 @@ constexpr int kMaxLog2Radix = 30;           // keeps slot ids clear of the ids a
 constexpr int kMaxLog2Chains = 26;
 constexpr int kChainMax = 15;
 
-struct RadixMeta {
-  unsigned long long n_edges[kCounterLanes];
-  int32_t status;
-};
-
 struct EdgeView {
   unsigned long long *keys;
   uint64_t mask;
-  RadixMeta *meta;
+  CacheMeta *meta;                 // the block table's: n_edges, radix_status
   unsigned long long *chain_tags;  // per block slot: 0, or (call epoch << 32) | (request + 1);
                                    // NULL: no chains
   u32x4 *chains;                   // per block slot: the token count, then up to 15 tokens
@@ -100,7 +95,7 @@ __device__ __forceinline__ uint32_t edge_insert(const EdgeView &e, uint32_t node
     if (cur == key) return kEdgeBase + (uint32_t)s;
     s = (s + 1) & e.mask;
   }
-  atomicCAS(&e.meta->status, 0, KVGOV_E_FULL);
+  atomicCAS(&e.meta->radix_status, 0, KVGOV_E_FULL);
   return kNoNode;
 }
 
@@ -118,12 +113,8 @@ __device__ __forceinline__ uint32_t edge_find(const EdgeView &e, uint32_t node, 
 
 __global__ __launch_bounds__(256) void k_edge_fill(unsigned long long *keys, int64_t slots,
                                                    unsigned long long *chain_tags,
-                                                   int64_t block_slots, RadixMeta *m) {
+                                                   int64_t block_slots) {
   const int64_t stride = (int64_t)gridDim.x * 256;
-  if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < kCounterLanes; i += blockDim.x) m->n_edges[i] = 0;
-    if (threadIdx.x == 0) m->status = 0;
-  }
   for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots; s += stride)
     keys[s] = kEdgeEmpty;
   if (chain_tags)
@@ -177,13 +168,13 @@ __device__ __forceinline__ bool radix_req(const RadixArgs &a, int64_t r, RadixRe
   q.nf = b1 - q.b0;
   if (q.t0 < 0 || t1 < q.t0 || t1 > a.n_tokens || q.b0 < 0 || q.nf != (q.len >> 4) ||
       b1 > a.n_blocks) {
-    atomicCAS(&a.e.meta->status, 0, KVGOV_E_OFFSETS);
+    atomicCAS(&a.e.meta->radix_status, 0, KVGOV_E_OFFSETS);
     return false;
   }
   if (a.salts) {
     const int32_t p = a.principal[r];
     if (p < 0 || p >= a.P) {
-      atomicCAS(&a.e.meta->status, 0, KVGOV_E_PRINCIPAL);
+      atomicCAS(&a.e.meta->radix_status, 0, KVGOV_E_PRINCIPAL);
       return false;
     }
     q.root = a.salts + (int64_t)p * 32;
@@ -372,7 +363,7 @@ __global__ __launch_bounds__(256) void k_radix_edges(RadixArgs a) {
       parent = find_slot(a.t, load_key(j == 0 ? q.root : a.hashes + (f - 1) * 32));
     if (parent == -1) {
       // the parent block was not inserted (a full table, latched there)
-      atomicCAS(&a.e.meta->status, 0, KVGOV_E_FULL);
+      atomicCAS(&a.e.meta->radix_status, 0, KVGOV_E_FULL);
       continue;
     }
     added += insert_tokens(a, parent, r, j, a.tokens + q.t0 + 16 * j, q.len - 16 * j);
@@ -468,7 +459,7 @@ int enqueue_edge_clear(kvgov_radix *x, hipStream_t s) {
   const unsigned grid = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>(ceil_div(x->edge_slots, 256), (int64_t)device_cu_count() * 64));
   hipLaunchKernelGGL(k_edge_fill, dim3(grid), dim3(256), 0, s, x->edges.keys, x->edge_slots,
-                     x->edges.chain_tags, x->blocks->slots, x->edges.meta);
+                     x->edges.chain_tags, x->blocks->slots);
   return launch_status();
 }
 
@@ -547,14 +538,13 @@ int kvgov_radix_create(int32_t log2_block_slots, int32_t log2_edge_slots, kvgov_
   }
   x->edge_slots = (int64_t)1 << log2_edge_slots;
   x->edges.mask = (uint64_t)x->edge_slots - 1;
-  void *keys = nullptr, *meta = nullptr, *zero = nullptr, *ctags = nullptr, *chains = nullptr;
+  void *keys = nullptr, *zero = nullptr, *ctags = nullptr, *chains = nullptr;
   const bool chained = log2_block_slots <= kMaxLog2Chains;
   if (hipMalloc(&keys, (size_t)x->edge_slots * 8) != hipSuccess ||
-      hipMalloc(&meta, sizeof(RadixMeta)) != hipSuccess || hipMalloc(&zero, 32) != hipSuccess ||
+      hipMalloc(&zero, 32) != hipSuccess ||
       (chained && (hipMalloc(&ctags, (size_t)x->blocks->slots * 8) != hipSuccess ||
                    hipMalloc(&chains, (size_t)x->blocks->slots * 64) != hipSuccess))) {
     if (keys) (void)hipFree(keys);
-    if (meta) (void)hipFree(meta);
     if (zero) (void)hipFree(zero);
     if (ctags) (void)hipFree(ctags);
     if (chains) (void)hipFree(chains);
@@ -563,7 +553,7 @@ int kvgov_radix_create(int32_t log2_block_slots, int32_t log2_edge_slots, kvgov_
     return KVGOV_E_NOMEM;
   }
   x->edges.keys = static_cast<unsigned long long *>(keys);
-  x->edges.meta = static_cast<RadixMeta *>(meta);
+  x->edges.meta = x->blocks->view.meta;
   x->zero_root = static_cast<uint8_t *>(zero);
   x->edges.chain_tags = static_cast<unsigned long long *>(ctags);
   x->edges.chains = static_cast<u32x4 *>(chains);
@@ -583,7 +573,6 @@ int kvgov_radix_destroy(kvgov_radix *x) {
   int rc = KVGOV_OK;
   if (hipDeviceSynchronize() != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->edges.keys) != hipSuccess) rc = KVGOV_E_HIP;
-  if (hipFree(x->edges.meta) != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->zero_root) != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->edges.chain_tags) != hipSuccess) rc = KVGOV_E_HIP;
   if (hipFree(x->edges.chains) != hipSuccess) rc = KVGOV_E_HIP;
@@ -656,20 +645,18 @@ int kvgov_radix_stats(kvgov_radix *x, int64_t *block_nodes, int64_t *edges, void
   if (!x || !block_nodes || !edges) return KVGOV_E_INVAL;
   int rc = radix_check(x);
   if (rc != KVGOV_OK) return rc;
-  hipStream_t s = as_stream(stream);
-  RadixMeta m{};
-  if (hipMemcpyAsync(&m, x->edges.meta, sizeof m, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return KVGOV_E_HIP;
+  CacheMeta m{};
+  rc = cache_read_meta(x->blocks, &m, as_stream(stream), true);
+  if (rc != KVGOV_OK) return rc;
   int64_t e = 0;
   for (int i = 0; i < kCounterLanes; ++i) e += (int64_t)m.n_edges[i];
   *edges = e;
-  rc = kvgov_cache_count(x->blocks, block_nodes, stream);
-  if (rc != KVGOV_OK) return rc;
+  *block_nodes = key_count(m);
+  if (m.status != 0) return m.status;
   // token nodes of chains take no edge slot, but the index holds as many as it
   // has edge slots for
-  if (m.status == 0 && e > x->edge_slots) return KVGOV_E_FULL;
-  return m.status;
+  if (m.radix_status == 0 && e > x->edge_slots) return KVGOV_E_FULL;
+  return m.radix_status;
 }
 
 }  // extern "C"

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <atomic>
+#include <cstddef>
 
 #include "common.h"
 
@@ -20,11 +21,16 @@ struct CacheMeta {
   unsigned long long n_keys[kCounterLanes];       // keys in the table (all-0xFF key included)
   unsigned long long new_keys[2][kCounterLanes];  // keys added by insert call `epoch`, at [epoch & 1]
   unsigned long long exported;                    // keys written by the latest export
-  unsigned long long erased;                      // keys marked by the latest erase
+  unsigned long long erased;                      // keys removed by the latest erase
+  unsigned long long marked;                      // keys that the erase under way has marked
   unsigned long long ones_tag;                    // the all-0xFF key's tag (0 = absent)
   unsigned long long ones_rank;                   // its recency rank (as `rank`)
   int32_t status;                                 // latched error (0 = none)
   int32_t ones_present;                           // the all-0xFF key is in the table
+  // of the radix index that the table belongs to: its token nodes and latched
+  // error (here, so that one read-back brings both tables' state)
+  unsigned long long n_edges[kCounterLanes];
+  int32_t radix_status;
 };
 
 // Recency of a key (table maintenance, when the table tracks it): one word,
@@ -259,6 +265,16 @@ __device__ __forceinline__ int64_t find_slot(const TableView &t, const Key &key)
     if (key_is_empty_pattern(slot)) return -1;
   }
   return -1;
+}
+
+// Waits for the stream and reads the table's counters, with the radix index's
+// if asked (cache.hip).
+int cache_read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s, bool radix = false);
+// Keys in the table, from its counters.
+inline int64_t key_count(const CacheMeta &m) {
+  int64_t total = 0;
+  for (int i = 0; i < kCounterLanes; ++i) total += (int64_t)m.n_keys[i];
+  return total;
 }
 
 // Enqueues the plain set-union insert of a batch's rows (cache.hip); stores
