@@ -112,7 +112,9 @@ __device__ __forceinline__ int32_t find_request(const int64_t *bo, int32_t n, in
 // k_insert_req), each in a batch of distinct keys that fills 0.4 of the table,
 // read first against claimed first: 2^17 slots 24.8 / 27.5 us, 2^18 30.0 /
 // 26.7, 2^20 57.1 / 51.2, 2^22 126 / 132, 2^23 336 / 302, 2^25 (with clear and
-// lookup) 2199 / 2156.
+// lookup) 2199 / 2156.  Past the home's bucket the tag is read again: where the
+// table is fuller, the next slots are mostly taken (0.65 of 2^20 slots: 171 us
+// with, 196 without).
 __device__ __forceinline__ bool claims_first(uint64_t mask) {
   return mask >= (1ull << 23) - 1 || (mask >= (1ull << 18) - 1 && mask <= (1ull << 20) - 1);
 }
@@ -244,6 +246,15 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 // again (270,000 random claims of 2^20 slots: 34 us with the read, 17
 // without).  Rows that follow a key of an earlier call keep the read: they are
 // mostly present (a batch that is all present: 20 us, 34 without the read).
+//
+// KEYS: these rows look at a slot's key before its tag.  A present key then
+// costs one line, not two, and a walk past other keys reads the line that holds
+// them instead of their claimants' rows.  It pays where the tags are not cached as a
+// whole, from 2^21 slots (tags first / keys first, us; P: all keys present, N:
+// none, H: half): 2^20 slots, 270,000 keys N 39 / 43; 2^21, 1.05 M P 73 / 53, N
+// 109 / 100, H 91 / 78; 2^22, 3.0 M P 230 / 171, N 333 / 297; 2^23, 5.9 M P 440
+// / 324, N 783 / 681, H 585 / 480; 2^25, 8.4 M P 384 / 240, N 785 / 738, H 631 /
+// 574.
 // Each request inserts the rows [blk_offsets[r], blk_offsets[r + 1]) cut to
 // the batch [blk_offsets[0], blk_offsets[n]); requests whose offsets are out
 // of order insert nothing.  With non-decreasing offsets that is every row
@@ -259,7 +270,7 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 // lowered, and that group compares with nothing).  (The chunked walk, which
 // admission took for every batch before it had the second comparison: 73 us for
 // 8192 requests of two paper-shaped batches; now 47.)
-template <int G, bool ADMIT, bool TRACK>
+template <int G, bool ADMIT, bool TRACK, bool KEYS>
 __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *hashes,
                                                     const int64_t *blk_offsets, int32_t n,
                                                     int64_t n_blocks, uint32_t epoch,
@@ -325,9 +336,9 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
           dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
         uint32_t code = kCodeDup;
         if (!dup)
-          added += insert_key<ADMIT>(t, key, f, lo, hashes, epoch, &code,
-                                     TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr, false,
-                                     fresh != 0);
+          added += insert_key<ADMIT, KEYS>(t, key, f, lo, hashes, epoch, &code,
+                                           TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr,
+                                           false, fresh != 0);
         if (ADMIT) codes[f] = code;
       }
     }
@@ -1043,19 +1054,32 @@ int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s)
   return m.status;
 }
 
-template <bool ADMIT, bool TRACK>
-void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
-                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+template <bool ADMIT, bool TRACK, bool KEYS>
+void insert_req_launch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets,
+                       int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
   // (no request: only the batch check and the next call's counters)
   const int g = n > 0 ? insert_group(n, n_blocks) : 64;
   const dim3 grid((unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * g, 256))), block(256);
   switch (g) {
-    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
   }
+}
+
+// Table sizes from which rows look at a slot's key before its tag (see
+// k_insert_req).
+constexpr uint64_t kKeysFirstSlots = (uint64_t)1 << 21;
+
+template <bool ADMIT, bool TRACK>
+void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
+                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+  if (!ADMIT && t.mask + 1 >= kKeysFirstSlots)
+    insert_req_launch<ADMIT, TRACK, !ADMIT>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+  else
+    insert_req_launch<ADMIT, TRACK, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
 }
 
 // The insert of a call: by requests, or, for few, long requests, where a group

@@ -109,6 +109,14 @@ __device__ __forceinline__ uint64_t seq_slot(uint64_t home, uint64_t p, uint64_t
   return ((((home >> 2) + (p >> 2)) << 2) & mask) | ((home + p) & 3);
 }
 
+// A key read while it may be written: all of it is there if no word is as in an
+// empty slot.
+__device__ __forceinline__ bool key_is_whole(const Key &k) {
+  const uint32_t ones = 0xFFFFFFFFu;
+  return k.lo.x != ones && k.lo.y != ones && k.lo.z != ones && k.lo.w != ones && k.hi.x != ones &&
+         k.hi.y != ones && k.hi.z != ones && k.hi.w != ones;
+}
+
 // Sum of v over the workgroup (256 threads), valid in thread 0.
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *lds4) {
 #pragma unroll
@@ -160,9 +168,11 @@ __device__ __forceinline__ unsigned long long recency(uint32_t epoch, uint32_t d
 // (a tracked insert's first rows: a later row with the same key then learns of
 // an earlier one in this call, as it does of a new key's).  With
 // `claim_first` (the key is thought to be new) the tag is not read before the
-// compare-and-swap.  On a table that tracks recency the key (added or found)
-// is touched with (epoch, depth) unless depth is kNoDepth.
-template <bool ADMIT>
+// compare-and-swap in the home's bucket.  KEYS (for callers that need neither
+// *code nor *claim): the slot's key is looked at before its tag, and the tag
+// only if that key is not all there.  On a table that tracks recency the key
+// (added or found) is touched with (epoch, depth) unless depth is kNoDepth.
+template <bool ADMIT, bool KEYS = false>
 __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &key, int64_t i,
                                                int64_t lo, const uint8_t *hashes,
                                                uint32_t epoch, uint32_t *code,
@@ -184,10 +194,23 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
     if (t.track && depth != kNoDepth) touch(&t.meta->ones_rank, recency(epoch, depth), won);
     return won ? 1u : 0u;
   }
+  enum class Slot { kMine, kOther, kUnclear };
+  const auto look = [&](uint64_t s) {
+    const Key there{t.keys[2 * s], t.keys[2 * s + 1]};
+    if (!key_eq(key, there)) return key_is_whole(there) ? Slot::kOther : Slot::kUnclear;
+    if (t.track && depth != kNoDepth) touch(&t.rank[s], recency(epoch, depth), false);
+    return Slot::kMine;
+  };
   const uint64_t home = home_slot(key, t.mask);
   for (uint64_t probes = 0; probes <= t.mask; ++probes) {
     const uint64_t s = seq_slot(home, probes, t.mask);
-    unsigned long long tag = claim_first ? 0ull : t.tags[s];
+    const bool at_once = claim_first && probes < (KEYS ? 1 : 4);
+    if (KEYS && !at_once) {
+      const Slot is = look(s);
+      if (is == Slot::kMine) return 0;
+      if (is == Slot::kOther) continue;
+    }
+    unsigned long long tag = at_once || KEYS ? 0ull : t.tags[s];
     if (tag == 0) {
       unsigned long long expect = 0;
       if (__hip_atomic_compare_exchange_strong(&t.tags[s], &expect, mine, __ATOMIC_RELAXED,
@@ -200,6 +223,11 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
         return 1;
       }
       tag = expect;  // somebody claimed it first: examine the claimant
+      if (KEYS && at_once) {
+        const Slot is = look(s);
+        if (is == Slot::kMine) return 0;
+        if (is == Slot::kOther) continue;
+      }
     }
     Key other;
     const bool current = (uint32_t)(tag >> 32) == epoch;

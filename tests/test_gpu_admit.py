@@ -262,3 +262,61 @@ def test_admit_interleaved_heads(max_len, log2_slots, track):
             for keep in (len(T.keys) * 3 // 4, 11, 1):
                 assert c.evict(keep) == T.evict(keep)
                 assert key_set(c.export().cpu().numpy()) == T.keys
+
+
+M64 = (1 << 64) - 1
+
+
+def i64(x):
+    """An int64 with the bits of the unsigned 64-bit x."""
+    x &= M64
+    return x - (1 << 64) if x >> 63 else x
+
+
+def shr(x, k):
+    return (x >> k) & ((1 << (64 - k)) - 1)
+
+
+def keys_with_hash(ident, x):
+    """Keys [n][32] whose third word is `ident` and whose slot hash is x (two
+    int64 tensors): the hash's last steps are inverted for the first word."""
+    y = x ^ shr(x, 29) ^ shr(x, 58)
+    y = y * i64(pow(0xBF58476D1CE4E5B9, -1, 1 << 64))
+    y = y ^ shr(y, 31) ^ shr(y, 62)
+    w1, w3 = ident * i64(0x9E3779B97F4A7C15), ~ident
+    w0 = y ^ (w1 * i64(0x9E3779B97F4A7C15)) ^ (ident * i64(0xC2B2AE3D27D4EB4F)) ^ (
+        w3 * i64(0x165667B19E3779F9))
+    return torch.stack([w0, w1, ident, w3], 1).view(torch.uint8)
+
+
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("log2_slots", [20, 21])
+def test_insert_of_crowded_slots(log2_slots, track):
+    """Inserts on both sides of the table size from which a slot's key is looked
+    at before its tag: keys that share a few home buckets (long probe
+    sequences), a third of them with words that are as in an empty slot, and
+    which many requests insert at once; into an empty table and into one that
+    holds part of them."""
+    g = np.random.default_rng(log2_slots + track)
+    home = g.integers(0, 40, 1500) * 4096 + g.integers(0, 8, 1500)
+    x = torch.from_numpy(home | (g.integers(0, 1 << 30, 1500) << 32))
+    pool = keys_with_hash(torch.arange(1500), x).numpy().copy()
+    words = pool.view(np.uint32)
+    words[np.arange(0, 1500, 3), g.integers(2, 8, 500)] = 0xFFFFFFFF
+    pool[7] = 0xFF
+    T = O.Table()
+    with K.Cache(log2_slots) as c:
+        c.set_recency(track)
+        for top in (600, 1500, 1500):
+            lens = g.integers(0, 70, 500)
+            bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            rows = pool[g.integers(0, top, int(bo[-1]))]
+            before = len(T.keys)
+            T.insert(rows, bo)
+            assert c.insert(dev(rows), dev(bo)) == len(T.keys) - before
+            assert key_set(c.export().cpu().numpy()) == T.keys
+            assert np.array_equal(c.lookup(dev(rows), dev(bo)).cpu().numpy(), lens)
+        if track:
+            for keep in (1000, 11):
+                assert c.evict(keep) == T.evict(keep)
+                assert key_set(c.export().cpu().numpy()) == T.keys
