@@ -36,8 +36,8 @@
  *     kvgov_salts returns and logs nothing.
  *   - The calls allocate no device memory except kvgov_cache_create,
  *     kvgov_radix_create, and the per-stream scratch that kvgov_hash_chains
- *     and its resume variant, kvgov_cache_admit, the maintenance calls and
- *     the offset helpers use:
+ *     and its resume variant, kvgov_cache_admit, the maintenance calls, the
+ *     offset helpers and inserts of more than 10 M rows use:
  *     one buffer per (device, stream) the library has seen, grown on demand
  *     (growth waits for that stream, then frees the old buffer) and held
  *     until the process ends.  A stream runs its work in order, so its
@@ -277,6 +277,9 @@ int kvgov_cache_slots(const kvgov_cache *c, int64_t *slots);
  *              any latched error.  NULL: nothing waits.
  * Kernel errors: KVGOV_E_OFFSETS (nothing inserted), KVGOV_E_FULL (the table
  * holds a consistent subset of the union; clear it before reuse).
+ * Scratch: calls of more than 10 M rows, for tables of a row to three slots
+ * per row, use 13 * n_blocks bytes of the stream's scratch (see the notes at
+ * the top); under capture, or where it cannot be had, they do without.
  */
 int kvgov_cache_insert(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
                        int32_t n, int64_t n_blocks, int64_t *n_new, void *stream);

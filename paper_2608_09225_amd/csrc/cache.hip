@@ -41,6 +41,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <new>
 
 #include "table.h"
@@ -212,6 +213,21 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
   }
 }
 
+// The state of an insert by regions (below).
+struct RegionState {
+  uint32_t n_rest;  // rows in the rest list
+  uint32_t bad;     // a malformed batch, or rows fewer than half of n_blocks
+  // first keys seen << 32 | of them repeated (or in the table): of the evenly
+  // spread requests, of those chosen by their key
+  unsigned long long spread, by_key;
+
+  // Does the batch go by requests?
+  __device__ bool by_request() const {
+    return bad || (spread & 0xFFFFFFFFu) * 8 > spread >> 32 ||
+           (by_key & 0xFFFFFFFFu) * 8 > by_key >> 32;
+  }
+};
+
 // Plain (set-union) insert with G lanes per request, which walk the
 // request's rows G at a time.  Two comparisons keep keys that many requests
 // share away from the table (a key skipped by either equals a row of the
@@ -274,8 +290,9 @@ template <int G, bool ADMIT, bool TRACK, bool KEYS>
 __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *hashes,
                                                     const int64_t *blk_offsets, int32_t n,
                                                     int64_t n_blocks, uint32_t epoch,
-                                                    uint32_t *codes) {
+                                                    uint32_t *codes, const RegionState *st) {
   __shared__ uint32_t lds4[4];
+  if (st && !st->by_request()) return;  // the batch goes by regions
   const int64_t lo = blk_offsets[0], hi = blk_offsets[n];
   if (blockIdx.x == 0 && threadIdx.x < kCounterLanes)
     t.meta->new_keys[(epoch + 1) & 1][threadIdx.x] = 0;  // counters of the next call
@@ -348,6 +365,330 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
     const int cl = blockIdx.x % kCounterLanes;
     atomicAdd(&t.meta->new_keys[epoch & 1][cl], (unsigned long long)total);
     atomicAdd(&t.meta->n_keys[cl], (unsigned long long)total);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// insert by regions: very large batches of new keys
+// ---------------------------------------------------------------------------
+//
+// A key inserted on its own moves, at random places, its tag's line in and out
+// and its 32 bytes, behind a compare-and-swap that waits for the line: 13.7 M
+// new keys into 2^25 slots take k_insert_req 1.59 ms.  Taken region by region
+// the tags are read once, in order, and claimed in LDS; what is moved instead
+// is one entry of 8 bytes per row, to its region's list and back, and one
+// random read of the row's key: 205 + 810 us, of which the 2.65 GB read and
+// 0.66 GB written by k_region_insert are 670 us at a copy's rate (the random
+// read fetches 128 bytes for each key's 32).
+//   k_region_clear    counters, lists and sets of this call
+//   k_region_sample   a look at the requests' first keys: where many of them are
+//                     shared, or in the table already, or the rows are fewer
+//                     than half of n_blocks, k_insert_req is the better one (it
+//                     keeps such rows off the table by comparisons, and finds
+//                     present keys with one read each) and the kernels below
+//                     end at once; otherwise k_insert_req does
+//   k_region_lists    rows to their regions' lists
+//   k_region_insert   region by region
+//   k_list_insert     by insert_key: what the lists had no room for (keys that
+//                     come many times) and rows whose probe sequence leaves
+//                     their region
+constexpr int kRegionLog2 = 14;
+constexpr int kListThreads = 1024;
+constexpr int kListItems = 16;  // rows per thread
+constexpr int kListRows = kListThreads * kListItems;
+constexpr int kMaxRegions = 4096;
+constexpr int kMaxListed = 65000;  // entries of a region: an index fits 16 bits
+constexpr int kSampleSlots = 8192;
+constexpr int kSampled = 1024;      // requests looked at, evenly spread
+constexpr int kSampledByKey = 2048;  // about as many, chosen by their first key
+
+struct RegionArgs {
+  TableView t;
+  const uint8_t *hashes;
+  const int64_t *blk_offsets;
+  int32_t n;
+  int64_t n_blocks;
+  uint32_t epoch;
+  RegionState *st;
+  uint32_t *cursor;             // per region: rows listed (may exceed cap)
+  unsigned long long *sample;   // two sets of kSampleSlots hashes
+  unsigned long long *entries;  // per region: cap entries, (print << 46) | (home within the
+                                // region << 32) | row; prints have 16 bits
+  uint32_t *rest;               // rows for k_list_insert
+  uint32_t cap;
+  uint32_t regions;
+  uint32_t key_mask;            // of the hash bits that choose a request by its first key
+};
+
+// The batch's rows, or none (an empty or malformed batch).
+__device__ __forceinline__ bool region_rows(const RegionArgs &a, int64_t &lo, int64_t &hi) {
+  lo = a.blk_offsets[0];
+  hi = a.blk_offsets[a.n];
+  return !(lo < 0 || hi < lo || hi > a.n_blocks || hi - lo >= 0xFFFFFFFFll);
+}
+
+__global__ __launch_bounds__(256) void k_region_clear(RegionArgs a) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < 2 * kSampleSlots) a.sample[i] = 0;
+  if (i < kMaxRegions) a.cursor[i] = 0;
+  if (i == 0) *a.st = RegionState{};
+}
+
+// Was x in the set before?  (A set that is full where x belongs says no.)
+__device__ __forceinline__ bool sample_twice(unsigned long long *set, uint64_t x) {
+  x |= 1;  // never an empty slot; two keys that agree in 63 bits count as one
+  uint32_t at = (uint32_t)(x >> 16) & (kSampleSlots - 1);  // not by the bits that choose
+  for (int p = 0; p < 64; ++p, at = (at + 1) & (kSampleSlots - 1)) {
+    // read first, from the caches: thousands of requests may hold one key
+    unsigned long long was = set[at];
+    if (was == 0) was = atomicCAS(&set[at], 0ull, (unsigned long long)x);
+    if (was == 0) return false;
+    if (was == x) return true;
+  }
+  return false;
+}
+
+// Two looks, for sharing of both kinds: kSampled requests evenly spread find
+// few keys that many requests share (and keys that are in the table); all
+// requests whose first key has zeros in some bits of its hash find groups of a
+// few requests anywhere in the batch, which come into this sample together.
+__global__ __launch_bounds__(kListThreads) void k_region_sample(RegionArgs a) {
+  __shared__ unsigned long long cnt[2];
+  int64_t lo, hi;
+  const bool ok = region_rows(a, lo, hi);
+  if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t r = (int64_t)blockIdx.x * kListThreads + threadIdx.x;
+  const int64_t b = r < a.n ? a.blk_offsets[r] : -1;
+  if (ok && b >= lo && b < hi) {
+    const Key key = load_key(a.hashes + b * 32);
+    const uint64_t x = slot_hash(key);
+    if (r == 0 || r * kSampled / a.n != (r - 1) * kSampled / a.n) {
+      const bool twice = sample_twice(a.sample, x) || probe(a.t, key, true);
+      atomicAdd(&cnt[0], 1ull << 32 | (twice ? 1 : 0));
+    }
+    if (((uint32_t)(x >> 40) & a.key_mask) == 0) {
+      const bool twice = sample_twice(a.sample + kSampleSlots, x);
+      atomicAdd(&cnt[1], 1ull << 32 | (twice ? 1 : 0));
+    }
+  }
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < kCounterLanes)
+      a.t.meta->new_keys[(a.epoch + 1) & 1][threadIdx.x] = 0;  // counters of the next call
+    if (threadIdx.x == 0) {
+      if (!ok) atomicCAS(&a.t.meta->status, 0, KVGOV_E_OFFSETS);
+      a.st->bad = !ok || (hi - lo) * 2 < a.n_blocks;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && cnt[0]) atomicAdd(&a.st->spread, cnt[0]);
+  if (threadIdx.x == 64 && cnt[1]) atomicAdd(&a.st->by_key, cnt[1]);
+}
+
+// A workgroup sorts its 16384 rows by region in LDS, so that a region's entries
+// leave together (written in the rows' order: 340 us instead of 205, 13.7 M
+// rows).
+__global__ __launch_bounds__(kListThreads) void k_region_lists(RegionArgs a) {
+  constexpr int kPer = kMaxRegions / kListThreads;  // regions per thread
+  // (print << 14 | home within the region) << 26 | row of the workgroup << 12 | region
+  __shared__ unsigned long long sorted[kListRows];
+  __shared__ uint32_t at[kMaxRegions];  // rows per region, then their first place
+  __shared__ uint32_t wave_sum[kListThreads / 64];
+  if (a.st->by_request()) return;
+  int64_t lo, hi;
+  if (!region_rows(a, lo, hi)) return;
+  for (int64_t base = lo + (int64_t)blockIdx.x * kListRows; base < hi;
+       base += (int64_t)gridDim.x * kListRows) {
+    const int m = (int)(hi - base < kListRows ? hi - base : kListRows);
+    for (uint32_t i = threadIdx.x; i < kMaxRegions; i += kListThreads) at[i] = 0;
+    __syncthreads();
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    uint32_t what[kListItems], where[kListItems];  // (print, home); (region << 16) | rank
+    constexpr int kBatch = 8;                      // rows in flight per thread
+#pragma unroll
+    for (int k0 = 0; k0 < kListItems; k0 += kBatch) {
+      Key key[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int r = (k0 + k) * kListThreads + threadIdx.x;
+        key[k] = load_key(a.hashes + (base + (r < m ? r : 0)) * 32);
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int r = (k0 + k) * kListThreads + threadIdx.x;
+        where[k0 + k] = kNone;
+        if (r >= m) continue;
+        if (key_is_empty_pattern(key[k])) {  // has no slot
+          a.rest[atomicAdd(&a.st->n_rest, 1u)] = (uint32_t)(base - lo) + r;
+          continue;
+        }
+        const uint64_t x = slot_hash(key[k]);
+        const uint32_t home = (uint32_t)(x & a.t.mask), g = home >> kRegionLog2;
+        what[k0 + k] = (uint32_t)(x >> 48) << kRegionLog2 | (home & ((1u << kRegionLog2) - 1));
+        where[k0 + k] = g << 16 | atomicAdd(&at[g], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t cnt[kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      cnt[i] = at[threadIdx.x * kPer + i];
+      sum += cnt[i];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t v = __shfl_up(incl, d, 64);
+      if ((int)(threadIdx.x & 63) >= d) incl += v;
+    }
+    if ((threadIdx.x & 63) == 63) wave_sum[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    uint32_t start = incl - sum, listed = 0;
+    for (int w = 0; w < kListThreads / 64; ++w) {
+      if (w < (int)(threadIdx.x >> 6)) start += wave_sum[w];
+      listed += wave_sum[w];
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      at[threadIdx.x * kPer + i] = start;
+      start += cnt[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kListItems; ++k) {
+      if (where[k] == kNone) continue;
+      const uint32_t g = where[k] >> 16, r = k * kListThreads + threadIdx.x;
+      sorted[at[g] + (where[k] & 0xFFFFu)] = (unsigned long long)what[k] << 26 | r << 12 | g;
+    }
+    __syncthreads();
+    // from a place in `sorted` to the place in the region's list
+    uint32_t got[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      got[i] = cnt[i] ? atomicAdd(&a.cursor[threadIdx.x * kPer + i], cnt[i]) : 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      at[threadIdx.x * kPer + i] = got[i] - at[threadIdx.x * kPer + i];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < listed; i += kListThreads) {
+      const unsigned long long e = sorted[i];
+      const uint32_t g = (uint32_t)e & (kMaxRegions - 1), to = at[g] + i;
+      const uint32_t row = (uint32_t)(base - lo) + ((uint32_t)(e >> 12) & (kListRows - 1));
+      if (to < a.cap)
+        a.entries[(uint64_t)g * a.cap + to] = e >> 26 << 32 | row;
+      else
+        a.rest[atomicAdd(&a.st->n_rest, 1u)] = row;
+    }
+    __syncthreads();
+  }
+}
+static_assert(kListRows == 1 << 14 && kMaxRegions == 1 << 12, "an entry's fields");
+
+// The claims need the rows' prints alone (16 bits of the hash that the home does
+// not use): keys are read only where two prints meet, or a key of an earlier
+// call.  Then the claimed slots are written in order, each key read from its
+// row, and only where the tag is still free: a call of another stream may have
+// taken it (the compare-and-swaps of neighbouring lanes share their lines: no
+// slower than stores, 810 us either way).
+__global__ __launch_bounds__(kListThreads) void k_region_insert(RegionArgs a) {
+  constexpr int kSlots = 1 << kRegionLog2;
+  constexpr uint32_t kOld = 0xFFFFFFFFu;  // a slot taken before
+  __shared__ uint32_t claim[kSlots];      // 0, or (print << 16) | (place in the list + 1)
+  __shared__ uint32_t added_sum;
+  if (a.st->by_request()) return;
+  const uint8_t *rows = a.hashes + a.blk_offsets[0] * 32;
+  if (threadIdx.x == 0) added_sum = 0;
+  uint32_t added = 0;
+  for (uint32_t g = blockIdx.x; g < a.regions; g += gridDim.x) {
+    const uint32_t cnt = a.cursor[g] < a.cap ? a.cursor[g] : a.cap;
+    if (cnt == 0) continue;
+    const uint64_t s0 = (uint64_t)g << kRegionLog2;
+#pragma unroll
+    for (int i = 0; i < kSlots / kListThreads; ++i) {
+      const int s = i * kListThreads + threadIdx.x;
+      claim[s] = a.t.tags[s0 + s] ? kOld : 0;
+    }
+    __syncthreads();
+    const unsigned long long *list = a.entries + (uint64_t)g * a.cap;
+    for (uint32_t e = threadIdx.x; e < cnt; e += kListThreads) {
+      const unsigned long long ent = list[e];
+      const uint32_t row = (uint32_t)ent, what = (uint32_t)(ent >> 32);
+      const uint32_t home = what & (kSlots - 1), print = what >> kRegionLog2;
+      for (uint32_t p = 0;; ++p) {
+        const uint32_t bucket = (home >> 2) + (p >> 2);
+        if (bucket >= kSlots / 4) {  // the sequence leaves the region
+          a.rest[atomicAdd(&a.st->n_rest, 1u)] = row;
+          break;
+        }
+        const uint32_t s = bucket << 2 | ((home + p) & 3);
+        const uint32_t was = atomicCAS(&claim[s], 0u, print << 16 | (e + 1));
+        if (was == 0) break;
+        const bool old = was == kOld;
+        if (!old && was >> 16 != print) continue;
+        const Key other = old
+                              ? Key{a.t.keys[2 * (s0 + s)], a.t.keys[2 * (s0 + s) + 1]}
+                              : load_key(rows + (uint64_t)(uint32_t)list[(was & 0xFFFFu) - 1] * 32);
+        if (key_eq(load_key(rows + (uint64_t)row * 32), other)) break;
+      }
+    }
+    __syncthreads();
+    constexpr int kBatch = 8;  // keys in flight per thread
+    for (int i0 = 0; i0 < kSlots / kListThreads; i0 += kBatch) {
+      uint32_t at[kBatch], row[kBatch];
+      Key key[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        at[i] = claim[(i0 + i) * kListThreads + threadIdx.x];
+        if (at[i] == kOld) at[i] = 0;
+        row[i] = (uint32_t)list[at[i] ? (at[i] & 0xFFFFu) - 1 : 0];
+      }
+      // (a slot that is not claimed reads the list's first row)
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) key[i] = load_key(rows + (uint64_t)row[i] * 32);
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        if (at[i] == 0) continue;
+        const uint64_t s = s0 + (i0 + i) * kListThreads + threadIdx.x;
+        const unsigned long long mine = (unsigned long long)a.epoch << 32 | (row[i] + 1);
+        if (atomicCAS(&a.t.tags[s], 0ull, mine) != 0) {
+          a.rest[atomicAdd(&a.st->n_rest, 1u)] = row[i];
+          continue;
+        }
+        a.t.keys[2 * s] = key[i].lo;
+        a.t.keys[2 * s + 1] = key[i].hi;
+        ++added;
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) added += __shfl_xor(added, d, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0 && added) atomicAdd(&added_sum, added);
+  __syncthreads();
+  if (threadIdx.x == 0 && added_sum) {
+    const int cl = blockIdx.x % kCounterLanes;
+    atomicAdd(&a.t.meta->new_keys[a.epoch & 1][cl], (unsigned long long)added_sum);
+    atomicAdd(&a.t.meta->n_keys[cl], (unsigned long long)added_sum);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_list_insert(RegionArgs a) {
+  __shared__ uint32_t lds4[4];
+  if (a.st->by_request()) return;
+  const int64_t lo = a.blk_offsets[0];
+  const uint32_t cnt = a.st->n_rest;
+  uint32_t added = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < cnt; i += (uint64_t)gridDim.x * 256) {
+    const int64_t f = lo + a.rest[i];
+    uint32_t code;
+    added += insert_key<false>(a.t, load_key(a.hashes + f * 32), f, lo, a.hashes, a.epoch, &code);
+  }
+  const uint32_t total = block_sum(added, lds4);
+  if (threadIdx.x == 0 && total) {
+    const int cl = blockIdx.x % kCounterLanes;
+    atomicAdd(&a.t.meta->new_keys[a.epoch & 1][cl], (unsigned long long)total);
+    atomicAdd(&a.t.meta->n_keys[cl], (unsigned long long)total);
   }
 }
 
@@ -1056,16 +1397,17 @@ int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s)
 
 template <bool ADMIT, bool TRACK, bool KEYS>
 void insert_req_launch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets,
-                       int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+                       int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
+                       const RegionState *st) {
   // (no request: only the batch check and the next call's counters)
   const int g = n > 0 ? insert_group(n, n_blocks) : 64;
   const dim3 grid((unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * g, 256))), block(256);
   switch (g) {
-    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
-    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes); break;
+    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
+    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
+    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
+    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
+    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
   }
 }
 
@@ -1075,11 +1417,17 @@ constexpr uint64_t kKeysFirstSlots = (uint64_t)1 << 21;
 
 template <bool ADMIT, bool TRACK>
 void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
-                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
+                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
+                const RegionState *st = nullptr) {
   if (!ADMIT && t.mask + 1 >= kKeysFirstSlots)
-    insert_req_launch<ADMIT, TRACK, !ADMIT>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+    insert_req_launch<ADMIT, TRACK, !ADMIT>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st);
   else
-    insert_req_launch<ADMIT, TRACK, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
+    insert_req_launch<ADMIT, TRACK, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st);
+}
+
+// Whether an insert may take k_insert_req (otherwise in chunks).
+bool by_requests(int32_t n, int64_t n_blocks) {
+  return n == 0 || n_blocks <= (int64_t)n * kReqInsertMaxAvg;
 }
 
 // The insert of a call: by requests, or, for few, long requests, where a group
@@ -1087,7 +1435,7 @@ void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_of
 template <bool ADMIT>
 int insert_batch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
                  int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
-  if (!cache_inserts_by_request(n, n_blocks))
+  if (!by_requests(n, n_blocks))
     hipLaunchKernelGGL(k_chunk_insert<ADMIT>, dim3(insert_grid(n_blocks)), dim3(256), 0, s, t,
                        hashes, blk_offsets, n, n_blocks, epoch, codes);
   else if (t.track)
@@ -1099,8 +1447,82 @@ int insert_batch(const TableView &t, const uint8_t *hashes, const int64_t *blk_o
 
 }  // namespace
 
-bool kvgov::cache_inserts_by_request(int32_t n, int64_t n_blocks) {
-  return n == 0 || n_blocks <= (int64_t)n * kReqInsertMaxAvg;
+namespace {
+
+// Whether a batch may go by regions (us for new keys, by regions / by requests):
+// 11.9 M rows into 2^25 slots 972 / 1044, 16.8 M 1272 / 1536, 23.7 M 1803 /
+// 2546; but 8.4 M into 2^25 735 / 738, 16.8 M into 2^26 1507 / 1574.  Where the
+// sample then finds the keys shared or present, the look and the kernels that
+// end at once cost 20 to 30 us (16.8 M present keys 570 instead of 540), which
+// is why smaller batches, whose gain is smaller, are left alone (8.4 M new keys
+// into 2^24 slots 645 / 728, shared ones 295 / 265).  A batch of more rows than
+// slots holds duplicates; the sample reads a line for each request, so
+// requests are to be 32 rows long.
+constexpr int64_t kRegionMinRows = (int64_t)10 << 20;
+
+bool by_regions(const kvgov_cache *c, int32_t n, int64_t n_blocks) {
+  return !c->view.track && n_blocks >= kRegionMinRows && n_blocks >= c->slots / 3 &&
+         n_blocks <= c->slots && (c->slots >> kRegionLog2) <= kMaxRegions && n >= kSampled &&
+         n_blocks / n >= 32 && n_blocks <= (int64_t)n * kReqInsertMaxAvg;
+}
+
+// The insert by regions, or, where its sample finds so, by requests.  False
+// if it cannot have its scratch (then nothing is enqueued).
+bool insert_regions(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
+                    int64_t n_blocks, uint32_t epoch, hipStream_t s, int *rc) {
+  // no memory may be allocated under capture
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (cap != hipStreamCaptureStatusNone) return false;
+  RegionArgs a{c->view, hashes, blk_offsets, n, n_blocks, epoch};
+  a.regions = (uint32_t)(c->slots >> kRegionLog2);
+  // room for an even spread and ten standard deviations
+  const double mean = (double)n_blocks / a.regions;
+  a.cap = std::min((uint32_t)(mean + 10.0 * std::sqrt(mean) + 64.0), (uint32_t)kMaxListed);
+  a.key_mask = 0;
+  while (n / ((int64_t)a.key_mask + 1) >= 2 * kSampledByKey) a.key_mask = a.key_mask * 2 + 1;
+  const size_t off_cursor = 256;
+  const size_t off_sample = off_cursor + sizeof(uint32_t) * kMaxRegions;
+  const size_t off_entries = off_sample + sizeof(unsigned long long) * 2 * kSampleSlots;
+  const size_t off_rest = off_entries + sizeof(unsigned long long) * a.regions * a.cap;
+  const size_t bytes = off_rest + sizeof(uint32_t) * (size_t)n_blocks;
+  std::unique_lock<std::mutex> lk;
+  void *base = nullptr;
+  // (an allocation must not end a capture that another thread has begun)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const int got = stream_scratch(s, bytes, &base, lk);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (got != KVGOV_OK) return false;
+  uint8_t *b = static_cast<uint8_t *>(base);
+  a.st = reinterpret_cast<RegionState *>(b);
+  a.cursor = reinterpret_cast<uint32_t *>(b + off_cursor);
+  a.sample = reinterpret_cast<unsigned long long *>(b + off_sample);
+  a.entries = reinterpret_cast<unsigned long long *>(b + off_entries);
+  a.rest = reinterpret_cast<uint32_t *>(b + off_rest);
+  const unsigned cus = (unsigned)device_cu_count();
+  const unsigned tiles = (unsigned)std::min<int64_t>(ceil_div(n_blocks, kListRows), cus);
+  hipLaunchKernelGGL(k_region_clear, dim3(2 * kSampleSlots / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_region_sample, dim3((unsigned)ceil_div(n, kListThreads)), dim3(kListThreads), 0, s, a);
+  hipLaunchKernelGGL(k_region_lists, dim3(tiles), dim3(kListThreads), 0, s, a);
+  hipLaunchKernelGGL(k_region_insert, dim3(std::min(a.regions, cus)), dim3(kListThreads), 0, s, a);
+  hipLaunchKernelGGL(k_list_insert, dim3(cus * 4), dim3(256), 0, s, a);
+  insert_req<false, false>(c->view, hashes, blk_offsets, n, n_blocks, epoch, nullptr, s,
+                           a.st);
+  *rc = launch_status();
+  return true;
+}
+
+}  // namespace
+
+bool kvgov::cache_inserts_by_request(const kvgov_cache *c, int32_t n, int64_t n_blocks) {
+  return by_requests(n, n_blocks) && !by_regions(c, n, n_blocks);
 }
 
 int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
@@ -1108,6 +1530,10 @@ int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_
   *epoch = c->epoch.fetch_add(1) + 1;
   if (*epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;  // 2^32 - 1 inserts since clear
   if (c->view.track) note_tracked(c, n_blocks);
+  int rc = KVGOV_OK;
+  if (by_regions(c, n, n_blocks) &&
+      insert_regions(c, hashes, blk_offsets, n, n_blocks, *epoch, s, &rc))
+    return rc;
   return insert_batch<false>(c->view, hashes, blk_offsets, n, n_blocks, *epoch, nullptr, s);
 }
 

@@ -612,7 +612,7 @@ int kvgov_radix_insert(kvgov_radix *x, const int32_t *tokens, int64_t n_tokens,
   if (rc != KVGOV_OK) return rc;
   rc = cache_insert_rows(c, hashes, blk_offsets, n, n_blocks, s, &a.blk_epoch);
   if (rc != KVGOV_OK) return rc;
-  if (cache_inserts_by_request(n, n_blocks))
+  if (cache_inserts_by_request(c, n, n_blocks))
     radix_edges<true>(a, radix_group(n, n_blocks), s);
   else
     radix_edges<false>(a, radix_group(n, n_blocks), s);

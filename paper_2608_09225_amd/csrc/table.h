@@ -312,7 +312,7 @@ int cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
                       int32_t n, int64_t n_blocks, hipStream_t s, uint32_t *epoch);
 
 // Whether that insert walks the batch by requests (k_insert_req) or in chunks.
-bool cache_inserts_by_request(int32_t n, int64_t n_blocks);
+bool cache_inserts_by_request(const kvgov_cache *c, int32_t n, int64_t n_blocks);
 
 }  // namespace kvgov
 

@@ -320,3 +320,75 @@ def test_insert_of_crowded_slots(log2_slots, track):
             for keep in (1000, 11):
                 assert c.evict(keep) == T.evict(keep)
                 assert key_set(c.export().cpu().numpy()) == T.keys
+
+
+@pytest.mark.parametrize("kind,log2_slots", [("new", 25), ("edges", 24), ("duplicates", 24),
+                                             ("shared", 24)])
+def test_insert_of_a_very_large_batch(kind, log2_slots):
+    """Batches beyond the row count from which new keys go region by region
+    (2^14 slots each): into a table that holds some of their keys; with many
+    home slots at the ends of regions, the table's last one included; with
+    keys that come twice anywhere, 2 M times (more than a region's list takes) or
+    are all ones; with first keys that eight requests share (by requests).
+    Compared with the key set known by construction; recency off."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(log2_slots + len(kind))
+
+    def rand(lo, hi, shape):
+        return torch.randint(lo, hi, shape, device="cuda", generator=g)
+
+    rows = (10 << 20) + 12345
+    lens = rand(16, 83, (rows // 32,))
+    lens[rand(0, lens.numel(), (100,))] = 0
+    ends = torch.cumsum(lens, 0)
+    n = int((ends <= rows - 7).sum())
+    bo = torch.cat([ends.new_zeros(1), ends[:n]]) + 3  # rows before and after the batch
+    lo, hi = int(bo[0]), int(bo[-1])
+    rows = hi + 5
+    x = (rand(0, 1 << 32, (rows,)) << 32) | rand(0, 1 << 32, (rows,))
+    if kind == "edges":
+        at = rand(0, rows, (rows // 100,))
+        x[at] = (x[at] & ~0x3FFF) | rand(0x3FF0, 0x4000, at.shape)
+        at = rand(0, rows, (200,))
+        x[at] = x[at] | ((1 << log2_slots) - 4)
+    keys = keys_with_hash(torch.arange(rows, device="cuda"), x)
+    source = torch.arange(rows, device="cuda")  # the row whose key each row holds
+    inner = torch.ones(rows, dtype=torch.bool, device="cuda")
+    first = bo[:-1][bo[:-1] < bo[1:]]
+    inner[first] = False  # not a request's first row
+    if kind == "duplicates":
+        source[6 << 20:8 << 20] = 12345
+        at = rand(0, rows, (rows // 5,))
+        source[at] = rand(0, rows, at.shape)
+    if kind == "shared":
+        p = first[torch.randperm(first.numel(), device="cuda", generator=g)]
+        source[p] = p[torch.arange(p.numel(), device="cuda") // 8]
+        inner[:] = True
+    source = torch.where(inner, source, torch.arange(rows, device="cuda"))
+    keys = keys[source].contiguous()
+    ones = kind == "duplicates"
+    if ones:
+        at = rand(0, rows, (1000,))
+        at = at[inner[at]]
+        keys[at] = 0xFF
+    before = torch.arange(1 << 16, device="cuda") * 97 + lo + 1
+    before = before[inner[before]]
+    if kind == "shared":
+        before = before[:0]
+    want = torch.unique(torch.cat([keys[lo:hi], keys[before]]).view(torch.int64)[:, 2])
+    had = torch.unique(keys[before].view(torch.int64)[:, 2])
+    with K.Cache(log2_slots) as c:
+        if before.numel():
+            b2 = torch.tensor([0, before.numel()], device="cuda")
+            assert c.insert(keys[before].contiguous(), b2) == had.numel()
+        assert c.insert(keys, bo) == want.numel() - had.numel()
+        assert c.count() == want.numel()
+        assert torch.equal(c.lookup(keys, bo).to(torch.int64), bo[1:] - bo[:-1])
+        assert c.insert(keys, bo) == 0
+        got = c.export().view(torch.int64)
+        got = got[torch.argsort(got[:, 2])]
+        assert torch.equal(got[:, 2], want)
+        plain = want != -1  # all ones
+        table = keys_with_hash(torch.arange(rows, device="cuda"), x).view(torch.int64)
+        assert torch.equal(got[plain], table[want[plain]])
+        assert bool((got[~plain] == -1).all())
