@@ -42,6 +42,8 @@
  *     (growth waits for that stream, then frees the old buffer) and held
  *     until the process ends.  A stream runs its work in order, so its
  *     buffer serves one call at a time and no memory passes between streams.
+ *     The cache and radix calls that wait read the table's state through 2 KiB
+ *     of pinned host memory, allocated by the first of them for the process.
  */
 #ifndef KVGOV_H
 #define KVGOV_H

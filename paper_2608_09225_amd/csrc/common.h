@@ -22,6 +22,26 @@ inline int launch_status() {
   return hipGetLastError() == hipSuccess ? KVGOV_OK : KVGOV_E_HIP;
 }
 
+// While it lives, allocations of this thread do not end a capture that another
+// thread has begun.
+class RelaxedCapture {
+ public:
+  RelaxedCapture() {
+    ok_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess;
+    if (!ok_) (void)hipGetLastError();
+  }
+  ~RelaxedCapture() {
+    if (ok_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  RelaxedCapture(const RelaxedCapture &) = delete;
+  RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+  bool ok() const { return ok_; }
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+  bool ok_ = false;
+};
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 constexpr int kWave = 64;

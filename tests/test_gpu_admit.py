@@ -1,6 +1,9 @@
 """GPU parity of the admission call (lookup-then-insert in request order)
 against the oracle's ``Table.admit``; hit counts, new-block counts, n_new and
 the exported key set are compared exactly."""
+import threading
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -262,6 +265,25 @@ def test_admit_interleaved_heads(max_len, log2_slots, track):
             for keep in (len(T.keys) * 3 // 4, 11, 1):
                 assert c.evict(keep) == T.evict(keep)
                 assert key_set(c.export().cpu().numpy()) == T.keys
+
+
+def test_more_threads_read_the_state_than_it_has_blocks():
+    """Twelve threads, each on a stream of its own, wait for one table's state at
+    the same time: the blocks of pinned memory serve eight, the others copy."""
+    g = np.random.default_rng(11)
+    rows = g.integers(0, 256, (5000, 32), dtype=np.uint8)
+    start = threading.Barrier(12)
+    with K.Cache(14) as c:
+        c.insert(dev(rows), dev(np.array([0, 5000], np.int64)))
+        torch.cuda.synchronize()
+
+        def read(_):
+            stream = torch.cuda.Stream()
+            start.wait(30)
+            return {c.count(stream=stream) for _ in range(50)}
+
+        with ThreadPoolExecutor(12) as pool:
+            assert list(pool.map(read, range(12))) == [{5000}] * 12
 
 
 M64 = (1 << 64) - 1
