@@ -258,16 +258,21 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
   return 0;
 }
 
-// Is `key` in the table?  Reads the key array only, one slot at a time (the
-// slots after the first are mostly in its line, so their loads hit the cache).
+// Is `key` in the table?  Reads the key array only, two slots at a time: the
+// second is in the first's line for three keys of four, and a key that is not
+// the first's, or absent, waits once less (lookups of 1 M short probes in 2^24
+// slots 426 -> 420 us; of 65536 requests in 2^25 slots 372 -> 365).
 __device__ __forceinline__ bool probe(const TableView &t, const Key &key, bool ones_present) {
   if (key_is_empty_pattern(key)) return ones_present;
   const uint64_t home = home_slot(key, t.mask);
-  for (uint64_t p = 0; p <= t.mask; ++p) {
-    const uint64_t s = seq_slot(home, p, t.mask);
+  for (uint64_t p = 0; p <= t.mask; p += 2) {
+    const uint64_t s = seq_slot(home, p, t.mask), s1 = seq_slot(home, p + 1, t.mask);
     const Key slot{t.keys[2 * s], t.keys[2 * s + 1]};
+    const Key next{t.keys[2 * s1], t.keys[2 * s1 + 1]};
     if (key_eq(slot, key)) return true;
     if (key_is_empty_pattern(slot)) return false;
+    if (key_eq(next, key)) return true;
+    if (key_is_empty_pattern(next)) return false;
   }
   return false;
 }
