@@ -53,11 +53,33 @@ namespace kvgov {
 // kernels
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_cache_fill(u32x4 *keys, unsigned long long *tags,
-                                                    unsigned long long *rank, int64_t slots,
-                                                    CacheMeta *m) {
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  const u32x4 ones = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+// Arrays of a clear, in 16-byte units (a table has at least 16 slots): those of
+// the table, and of the radix index that it belongs to.
+struct FillArgs {
+  u32x4 *ones[2];
+  int64_t n_ones[2];
+  u32x4 *zeros[3];
+  int64_t n_zeros[3];
+  CacheMeta *m;
+};
+
+// Bound by its writes.  Consecutive lanes write consecutive 16 bytes, four
+// stores each: a clear of 2^20 slots 8.5 us and of 2^25 234 (a lane per slot,
+// whose key is two stores of every other 16 bytes: 10.0 and 235; eight
+// workgroups per CU that walk the arrays: 8.4 and 266).
+__device__ __forceinline__ void fill(u32x4 *p, int64_t n, uint32_t v) {
+  const u32x4 q = u32x4{v, v, v, v};
+  const int64_t stride = (int64_t)gridDim.x * 1024;
+  int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  for (; i + 768 < n; i += stride)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) p[i + 256 * k] = q;
+  for (int k = 0; k < 4; ++k)
+    if (i + 256 * k < n) p[i + 256 * k] = q;
+}
+
+__global__ __launch_bounds__(256) void k_cache_fill(FillArgs a) {
+  CacheMeta *m = a.m;
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < kCounterLanes; i += blockDim.x) {
       m->n_keys[i] = 0;
@@ -76,12 +98,12 @@ __global__ __launch_bounds__(256) void k_cache_fill(u32x4 *keys, unsigned long l
       m->ones_present = 0;
     }
   }
-  for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < slots; s += stride) {
-    keys[2 * s] = ones;
-    keys[2 * s + 1] = ones;
-    tags[s] = 0;
-    if (rank) rank[s] = 0;
-  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (a.n_ones[i]) fill(a.ones[i], a.n_ones[i], 0xFFFFFFFFu);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (a.n_zeros[i]) fill(a.zeros[i], a.n_zeros[i], 0u);
 }
 
 // The depth of a key: its row within its request (clamped; only malformed
@@ -1269,10 +1291,23 @@ unsigned grid_for(int64_t work, int per_cu) {
 // since they were last cleared (a tracked insert or admission, an eviction,
 // an erasure): on a table that never tracks, a clear writes 40 of its 48
 // bytes per slot.
-int enqueue_clear(kvgov_cache *c, hipStream_t s) {
-  hipLaunchKernelGGL(k_cache_fill, dim3(grid_for(c->slots, 64)), dim3(256), 0, s, c->view.keys,
-                     c->view.tags, c->rank_dirty ? c->view.rank : nullptr, c->slots,
-                     c->view.meta);
+int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMore{}) {
+  FillArgs a{};
+  a.m = c->view.meta;
+  a.ones[0] = c->view.keys;
+  a.n_ones[0] = c->slots * 2;
+  a.zeros[0] = reinterpret_cast<u32x4 *>(c->view.tags);
+  a.n_zeros[0] = c->slots / 2;
+  if (c->rank_dirty) {
+    a.zeros[1] = reinterpret_cast<u32x4 *>(c->view.rank);
+    a.n_zeros[1] = c->slots / 2;
+  }
+  a.ones[1] = more.ones;
+  a.n_ones[1] = more.n_ones;
+  a.zeros[2] = more.zeros;
+  a.n_zeros[2] = more.n_zeros;
+  hipLaunchKernelGGL(k_cache_fill, dim3(grid_for((a.n_ones[0] + a.n_ones[1]) / 4, 1024)), dim3(256),
+                     0, s, a);
   c->rank_dirty = false;
   c->max_rows = 0;
   c->epoch.store(0);
@@ -1313,6 +1348,10 @@ void note_tracked(kvgov_cache *c, int64_t n_blocks) {
 }
 
 }  // namespace
+
+int kvgov::cache_clear_with(kvgov_cache *c, hipStream_t s, const ClearMore &more) {
+  return enqueue_clear(c, s, more);
+}
 
 // The table's state to the host: a kernel writes it to pinned memory.  A copy of
 // these some hundred bytes into the caller's memory goes through the runtime's

@@ -310,6 +310,18 @@ inline int64_t key_count(const CacheMeta &m) {
   return total;
 }
 
+// What a clear writes besides the table, in 16-byte units (the radix index's
+// token nodes and chain tags).
+struct ClearMore {
+  u32x4 *ones = nullptr;
+  int64_t n_ones = 0;
+  u32x4 *zeros = nullptr;
+  int64_t n_zeros = 0;
+};
+
+// Enqueues a clear of the table and of `more`, in one launch.
+int cache_clear_with(kvgov_cache *c, hipStream_t s, const ClearMore &more);
+
 // Enqueues the plain set-union insert of a batch's rows (cache.hip); stores
 // the call's epoch, whose tags mark the slots the call claimed, each with
 // the row that claimed it.
