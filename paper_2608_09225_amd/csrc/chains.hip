@@ -279,6 +279,9 @@ __global__ __launch_bounds__(kScanThreads) void k_blk_write(const int64_t *tok_o
 
 constexpr int kOrderBuckets = 4096;  // block counts >= 4095 share the top bucket
 
+// int32 of scratch that the order of n requests takes
+constexpr int64_t order_scratch_ints(int64_t n) { return (int64_t)kOrderBuckets + 64 + n; }
+
 // bucket of request r: the blocks it hashes, from the block offsets (any
 // values are safe here; the chain kernels validate them)
 __device__ __forceinline__ int order_bucket(const int64_t *blk_offsets, int32_t r) {
@@ -312,11 +315,16 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_hist(const int64_t *blk
     if (h[i]) atomicAdd(&hist[i], h[i]);
 }
 
-// one workgroup: start[b] = number of requests in buckets above b (descending order)
-__global__ __launch_bounds__(256) void k_order_scan(int32_t *hist) {
+// one workgroup: start[b] = number of requests in buckets above b (descending
+// order), and *even = the request at place `lp_requests` is as long as the
+// longest, within a 32nd
+__global__ __launch_bounds__(256) void k_order_scan(int32_t *hist, int32_t lp_requests,
+                                                    int32_t *even) {
   __shared__ int32_t sums[256];
+  __shared__ int32_t longest, next;
   constexpr int per = kOrderBuckets / 256;
   const int t = threadIdx.x;
+  if (t == 0) longest = next = -1;
   // thread t owns buckets kOrderBuckets-1-t*per down to kOrderBuckets-(t+1)*per,
   // so the highest buckets go to thread 0
   int32_t local = 0;
@@ -330,8 +338,13 @@ __global__ __launch_bounds__(256) void k_order_scan(int32_t *hist) {
     const int b = kOrderBuckets - 1 - (t * per + i);
     const int32_t cnt = hist[b];
     hist[b] = before;
+    if (cnt > 0 && before == 0) longest = b;
+    if (before <= lp_requests && lp_requests < before + cnt) next = b;
     before += cnt;
   }
+  __syncthreads();
+  if (t == 0)
+    *even = longest < kOrderBuckets - 1 && next >= 0 && next >= longest - longest / 32;
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(const int64_t *blk_offsets,
@@ -393,6 +406,7 @@ struct ChainArgs {
   uint8_t *hashes;
   int64_t n_blocks;
   const int32_t *order;  // NULL: request i on lane i
+  const int32_t *even;   // with an order: no few requests are the longest
   int32_t *status;
   // chain extension: request r resumes at block start[r] from the parent
   // digest parents[r] (NULL: every chain starts at block 0)
@@ -1331,9 +1345,17 @@ __global__ __launch_bounds__(4 * kWave) void k_chains_lp(ChainArgs a) {
 // that the longest chains finish sooner; the remaining workgroups run
 // one lane per request on the rest.  Both in one launch, 256 lanes per
 // workgroup.
+// Where the rest's first request is as long as the longest, the lane pairs shorten
+// nothing that the batch waits for, and take CUs that the rest would fill:
+// then one lane per request for all of them (65,536 chains of 32 blocks 262 ->
+// 206 us, 131,072 433 -> 382).  The s_nop puts the loops where they were before
+// this test came: their place within 32 bytes moves 65,536 lognormal prompts
+// by one per cent (5,050 or 5,100 us).
 template <int MODE>
 __global__ __launch_bounds__(256) void k_chains_mixed(ChainArgs a, int32_t lp_groups) {
   __shared__ __align__(16) LpLds L;
+  asm volatile("s_nop 0");
+  if (*a.even) lp_groups = 0;
   if ((int32_t)blockIdx.x < lp_groups)
     lp_group<MODE>(a, blockIdx.x, L);
   else
@@ -1431,12 +1453,12 @@ int stream_scratch(hipStream_t s, size_t bytes, void **ptr, std::unique_lock<std
 }
 
 // Scratch of the allocation-free hashing entry point: the longest-first
-// order of a batch (histogram, then the order), kOrderBuckets + n int32 for
+// order of a batch (histogram, then the order), order_scratch_ints(n) int32 for
 // n up to KVGOV_NOALLOC_MAX_REQUESTS.  One copy per device, held until the
 // process ends; host code reaches it only through the address that
 // hipGetSymbolAddress returns on that device (the array's name is a host
 // stand-in, not a device address).
-constexpr int64_t kNoAllocScratchInts = (int64_t)kOrderBuckets + KVGOV_NOALLOC_MAX_REQUESTS;
+constexpr int64_t kNoAllocScratchInts = order_scratch_ints(KVGOV_NOALLOC_MAX_REQUESTS);
 static __device__ __align__(256) int32_t scratch[kNoAllocScratchInts];
 
 // Device address of `scratch` on the current device, looked up once per
@@ -1590,17 +1612,18 @@ int kvgov_resume_offsets(const int64_t *tok_offsets, const int32_t *start_block,
 }
 
 // Longest-first order of a batch's requests (counting sort of their block
-// counts) in `buf`: kOrderBuckets + n int32 (the histogram, then the
-// order).  Returns the order.
-static const int32_t *order_requests(const int64_t *blk_offsets, int32_t n, int32_t *buf,
-                                     int32_t *status, hipStream_t s) {
+// counts) in `buf`: order_scratch_ints(n) int32 (the histogram, whether the
+// longest lp_requests are like the rest, then the order).  Returns the order.
+static const int32_t *order_requests(const int64_t *blk_offsets, int32_t n, int32_t lp_requests,
+                                     int32_t *buf, int32_t *status, hipStream_t s) {
   int32_t *hist = buf;
-  int32_t *order = buf + kOrderBuckets;
+  int32_t *order = buf + order_scratch_ints(0);
   hipLaunchKernelGGL(k_fill_i32, dim3(kOrderBuckets / 256), dim3(256), 0, s, hist,
                      (int64_t)kOrderBuckets, 0);
   const dim3 tiles((unsigned)ceil_div(n, kOrderTile));
   hipLaunchKernelGGL(k_order_hist, tiles, dim3(kOrderThreads), 0, s, blk_offsets, n, hist);
-  hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(256), 0, s, hist);
+  hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(256), 0, s, hist, lp_requests,
+                     buf + kOrderBuckets);
   hipLaunchKernelGGL(k_order_scatter, tiles, dim3(kOrderThreads), 0, s, blk_offsets, n, hist,
                      order, status);
   return order;
@@ -1681,14 +1704,15 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
       buf = noalloc_scratch();
       if (!buf) return KVGOV_E_HIP;
     } else {
-      const size_t bytes = sizeof(int32_t) * ((size_t)kOrderBuckets + (size_t)n);
+      const size_t bytes = sizeof(int32_t) * (size_t)order_scratch_ints(n);
       void *p = nullptr;
       const int src = stream_scratch(s, bytes, &p, lk);
       if (src != KVGOV_OK) return src;
       buf = static_cast<int32_t *>(p);
     }
-    a.order = order_requests(blk_offsets, n, buf, status, s);
     const int32_t lp_groups = std::max(1, device_cu_count() / 8);
+    a.order = order_requests(blk_offsets, n, lp_groups * kWave, buf, status, s);
+    a.even = buf + kOrderBuckets;
     const int64_t rest = std::max<int64_t>(0, (int64_t)n - (int64_t)lp_groups * kWave);
     const dim3 grid((unsigned)(lp_groups + ceil_div(rest, 4 * kWave))), block(4 * kWave);
     // two workgroups per CU: a second wave on each SIMD issues while the first

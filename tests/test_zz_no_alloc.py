@@ -69,3 +69,45 @@ def test_noalloc_rejects_batches_above_the_limit():
         K.hash_chains_noalloc(toks, offs, None, None, W.NONE, None, blk_offsets=offs, out=out,
                               status=K.new_status())
     assert e.value.code == c["KVGOV_E_TOO_LARGE"]
+
+
+@pytest.mark.parametrize("mode", [W.NONE, W.ROOT, W.BOUNDARY])
+@pytest.mark.parametrize("kind", ["even", "nearly even", "some longer", "one longer"])
+def test_ordered_batches_of_like_lengths(kind, mode):
+    """Ordered batches (more requests than the lane-pair path takes) whose
+    lengths leave the longest requests to the other lanes, and the nearest ones that do
+    not, against the same requests hashed in slices of the lane-pair path's
+    size, by both entry points."""
+    g = np.random.default_rng(5)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 256 * cus - 100
+    longest = cus // 8 * 64  # requests that the lane pairs would take
+    lens = np.full(n, 33 * 16 + 7, np.int64)
+    if kind == "nearly even":
+        lens -= 16 * (g.random(n) < 0.5)
+    if kind == "some longer":
+        lens[g.permutation(n)[:longest]] += 64
+    if kind == "one longer":
+        lens[n // 3] += 5 * 16
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    toks = g.integers(0, W.VOCAB, int(offs[-1]), dtype=np.int32)
+    prin = g.integers(0, 37, n).astype(np.int32)
+    bt = np.floor(g.random(n) * (lens + 1)).astype(np.int32)
+    ids = dev(g.integers(0, 256, (37, 32), dtype=np.uint8))
+    salts = K.salts(g.integers(0, 256, 32, dtype=np.uint8).tobytes(), ids)
+    b = W.Batch(toks, offs, prin, bt)
+    x = [dev(b.tokens), dev(b.tok_offsets), dev(b.principal), salts, mode, dev(b.boundary_tok)]
+    bo = dev(b.blk_offsets())
+    got = K.hash_chains(*x, blk_offsets=bo)
+    step = 64 * cus
+    for r in range(0, n, step):
+        e = min(r + step, n)
+        s = W.Batch(toks[offs[r]:offs[e]], offs[r:e + 1] - offs[r], prin[r:e], bt[r:e])
+        want = K.hash_chains(dev(s.tokens), dev(s.tok_offsets), dev(s.principal), salts, mode,
+                             dev(s.boundary_tok), blk_offsets=dev(s.blk_offsets()))
+        assert torch.equal(got[int(bo[r]):int(bo[e])], want), (kind, mode, r)
+    out = torch.full_like(got, 0xAB)
+    status = K.new_status()
+    K.hash_chains_noalloc(*x, blk_offsets=bo, out=out, status=status)
+    K.check_status(status, "kvgov_hash_chains_noalloc")
+    assert torch.equal(out, got)
