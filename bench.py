@@ -260,13 +260,35 @@ def admit_bytes(n_req: int, rows: int, n_new: int) -> int:
 
 
 def admit_group(n: int, rows: int) -> int:
-    """Lanes per request of the admission scan, the plain insert and the radix
-    edge walk (the library's rule)."""
+    """Lanes per request of the admission scan and the radix edge walk (the
+    library's rule)."""
     avg = rows // n if n else 0
     g = 4
     while g < 64 and g * 2 < avg:
         g <<= 1
     return g
+
+
+def insert_kernels(n: int, rows: int, log2_slots: int, admit: bool = False,
+                   track: bool = False) -> list:
+    """Kernels of an insert or admission of new keys (the library's rules)."""
+    slots = 1 << log2_slots
+    if (not admit and not track and rows >= 10 << 20 and slots // 3 <= rows <= slots and
+            n >= 1024 and rows // n >= 32):
+        return ["k_region_clear", "k_region_sample", "k_region_lists", "k_region_insert",
+                "k_list_insert"]
+    g = admit_group(n, rows)
+    avg = rows // n if n else 0
+    while g < 64 and g < avg and n * g * 2 <= 1 << 16:
+        g <<= 1
+    flags = (admit, track, not admit and log2_slots >= 21)
+    return [f"k_insert_req<{g},{','.join(str(f).lower() for f in flags)}>"]
+
+
+def total_traffic(kernels) -> dict:
+    """Sum of the kernels' records, (name, workload, group) each, or None."""
+    rows = [recorded_traffic(*k) for k in kernels]
+    return None if None in rows else {k: sum(r[k] for r in rows) for k in rows[0]}
 
 
 def lookup_lanes(n: int, n_blocks: int) -> int:
@@ -1136,13 +1158,14 @@ def run_workload(name: str, args, dev, K, torch):
             LOOKUP_BYTES_PER_BLOCK for m in modes},
     }
     if admission:
-        atr = [recorded_traffic(k, wl.name, "cache")
-               for k in ("k_chunk_insert<true>", f"k_admit_scan<{admit_group(X.n, nX)}>")]
+        k_adm = [*insert_kernels(X.n, nX, wl.log2_slots, admit=True),
+                 f"k_admit_scan<{admit_group(X.n, nX)}>"]
+        atr = total_traffic([(k, wl.name, "cache") for k in k_adm])
         roof_lookup = {
-            "bound": "hbm", "kernel": "k_chunk_insert<true> + k_admit_scan (kvgov_cache_admit)",
+            "bound": "hbm", "kernel": " + ".join(k_adm) + " (kvgov_cache_admit)",
             "achieved": look_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": look_gbs / HBM_PEAK_GBS,
-            "traffic": None if None in atr else sum(t["bytes"] for t in atr),
+            "traffic": None if atr is None else atr["bytes"],
             "bytes_per_launch": {W.MODE_NAMES[m]: b for m, b in look_bytes.items()},
             "launch_ms": {W.MODE_NAMES[m]: t * 1e3 for m, t in look_mean.items()},
             "bytes_note": f"{INSERT_BYTES_NEW} B per new key, {INSERT_BYTES_PRESENT} B per "
@@ -1343,16 +1366,16 @@ def run_workload(name: str, args, dev, K, torch):
     if radix_cfg:
         ins_gbs = float(np.mean([phases[W.MODE_NAMES[m]]["radix_insert"]["gbs"]
                                  for m in modes]))
-        g_i = admit_group(A.n, nA)
-        itr = [recorded_traffic(k, wl.name, t) for k, t in
-               (("k_radix_roots", "radix"), (f"k_insert_req<{g_i},false,false>", "cache"),
-                (f"k_radix_edges<{g_i}>", "radix"))]
+        k_i = insert_kernels(A.n, nA, wl.log2_slots)
+        k_e = f"k_radix_edges<{admit_group(A.n, nA)},true>"
+        itr = total_traffic([("k_radix_roots", wl.name, "radix")] +
+                            [(k, wl.name, "cache") for k in k_i] + [(k_e, wl.name, "radix")])
         result["roofline_radix_insert"] = {
-            "bound": "hbm", "kernel": f"k_radix_roots + k_insert_req<{g_i},false,false> + k_radix_edges<{g_i}> "
-                                      "(kvgov_radix_insert)",
+            "bound": "hbm",
+            "kernel": " + ".join(["k_radix_roots", *k_i, k_e]) + " (kvgov_radix_insert)",
             "achieved": ins_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": ins_gbs / HBM_PEAK_GBS,
-            "traffic": None if None in itr else sum(t["bytes"] for t in itr),
+            "traffic": None if itr is None else itr["bytes"],
             "bytes_note": f"the block insert's {INSERT_BYTES_NEW}/{INSERT_BYTES_PRESENT} B per "
                           f"new/present key, {RADIX_INSERT_BYTES_RECORD} B per record (parent "
                           f"key), {RADIX_INSERT_BYTES_EDGE} B per edge walked",
@@ -1360,8 +1383,8 @@ def run_workload(name: str, args, dev, K, torch):
     if maint_cfg:
         eg = float(np.mean([phases[W.MODE_NAMES[m]]["evict"]["gbs"] for m in modes]))
         result["roofline_evict"] = {
-            "bound": "hbm", "kernel": "k_rank_hist/k_rank_select x 8 + k_compact + "
-                                      "k_rebuild_fill + k_reinsert (kvgov_cache_evict)",
+            "bound": "hbm", "kernel": "k_rank_range + k_rank_select (11 bits each) + k_compact + "
+                                      "k_reinsert (kvgov_cache_evict)",
             "achieved": eg, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": eg / HBM_PEAK_GBS,
             "traffic": None,
             "bytes_note": f"{EVICT_BYTES_PER_SLOT} B per slot, {MAINT_BYTES_PER_KEPT} B per kept "
@@ -1371,12 +1394,12 @@ def run_workload(name: str, args, dev, K, torch):
         }
     if not probe_only and not admission and not radix_cfg:
         ins_gbs = float(np.mean([phases[W.MODE_NAMES[m]]["insert"]["gbs"] for m in modes]))
-        g_ins = admit_group(A.n, nA)
-        itr = recorded_traffic(f"k_insert_req<{g_ins},false,false>", wl.name, "cache")
+        k_ins = insert_kernels(A.n, nA, wl.log2_slots, track=maint_cfg)
+        itr = total_traffic([(k, wl.name, "cache") for k in k_ins])
         ins_s = float(np.mean([phases[W.MODE_NAMES[m]]["insert"]["ms_median"]
                                for m in modes])) / 1e3
         result["roofline_insert"] = {
-            "bound": "hbm", "kernel": f"k_insert_req<{g_ins},false,false> (set-union insert)",
+            "bound": "hbm", "kernel": " + ".join(k_ins) + " (set-union insert)",
             "achieved": ins_gbs,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ins_gbs / HBM_PEAK_GBS,
             "traffic": None if itr is None else itr["bytes"],

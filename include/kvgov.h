@@ -147,7 +147,7 @@ int kvgov_block_offsets(const int64_t *tok_offsets, int32_t n, int32_t block_siz
  *              error (KVGOV_E_OFFSETS / _PRINCIPAL / _BOUNDARY) there and skip
  *              the offending request.
  * Scratch: batches of more than two 64-request lane-pair workgroups per CU
- * (n > 128 * CUs) are ordered longest first using 4 * (4096 + n) bytes of
+ * (n > 128 * CUs) are ordered longest first using 4 * (4160 + n) bytes of
  * the stream's scratch (see the notes at the top).
  * Errors: KVGOV_E_INVAL, KVGOV_E_UNSUPPORTED, KVGOV_E_NOMEM, KVGOV_E_HIP;
  * KVGOV_E_INTERNAL latched in `status` if the ordering scratch held an
@@ -167,7 +167,7 @@ int kvgov_hash_chains(const int32_t *tokens, int64_t n_tokens,
  * hipMalloc).  Same arguments, results and errors as kvgov_hash_chains; it
  * calls no hipMalloc, hipFree or allocating library routine.  The ordering
  * scratch of large batches is a fixed array inside the library, one per
- * device (4 * (4096 + KVGOV_NOALLOC_MAX_REQUESTS) bytes, about 8 MiB, held
+ * device (4 * (4160 + KVGOV_NOALLOC_MAX_REQUESTS) bytes, about 8 MiB, held
  * until the process ends; its address is looked up on the first call on
  * each device).  Every call on a device shares that device's array, so
  * calls that overlap on one device (on different streams, or from several
