@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
 //
 // A key inserted on its own moves, at random places, its tag's line in and out
 // and its 32 bytes, behind a compare-and-swap that waits for the line: 13.7 M
-// new keys into 2^25 slots take k_insert_req 1.59 ms.  Taken region by region
+// new keys into 2^25 slots take k_insert_req 1.47 ms.  Taken region by region
 // the tags are read once, in order, and claimed in LDS; what is moved instead
 // is one entry of 8 bytes per row, to its region's list and back, and one
 // random read of the row's key: 205 + 810 us, of which the 2.65 GB read and
