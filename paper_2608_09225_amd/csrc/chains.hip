@@ -296,7 +296,10 @@ __device__ __forceinline__ int order_bucket(const int64_t *blk_offsets, int32_t 
 // 1.25M-request batch).  Workgroups of four waves find room on a busy chip
 // (other streams' kernels in flight) far sooner than workgroups of sixteen.
 constexpr int kOrderThreads = 256;
-constexpr int kOrderPerThread = 16;
+// (16 requests per thread, half as many workgroups: histogram and scatter 8.6 +
+// 9.7 us for 250,000 requests of one length, with 8 5.9 + 7.3; four per thread are no
+// better and add global atomics.  1.25 M requests of many lengths: the same.)
+constexpr int kOrderPerThread = 8;
 constexpr int64_t kOrderTile = (int64_t)kOrderThreads * kOrderPerThread;
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_hist(const int64_t *blk_offsets,
