@@ -175,3 +175,42 @@ def test_radix_rejects_boundary_mode_and_bad_offsets():
         with pytest.raises(K.KvgovError) as e:
             r.x.stats()
         assert e.value.code == c["KVGOV_E_OFFSETS"]
+
+
+def test_radix_of_a_very_large_batch():
+    """A batch beyond the row count from which new block keys go region by
+    region, in one call, against the same sequences inserted in four: the same
+    nodes, and the same match of every sequence cut at a random token.  Every
+    twentieth sequence shares a head with another."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    n = 16384
+    lens = torch.randint(16 * 500, 16 * 900, (n,), device="cuda", generator=g)
+    offs = torch.cat([lens.new_zeros(1), torch.cumsum(lens, 0)])
+    toks = torch.randint(0, 32000, (int(offs[-1]),), dtype=torch.int32, device="cuda", generator=g)
+    at, length = offs.tolist(), lens.tolist()
+    for r in range(0, n, 20):
+        q = (r * 7 + 3) % n
+        m = min(length[r], length[q]) * 2 // 3
+        toks[at[r]:at[r] + m] = toks[at[q]:at[q] + m].clone()
+
+    def args(t, o):
+        blk = torch.cat([o.new_zeros(1), torch.cumsum((o[1:] - o[:-1]) // 16, 0)])
+        return (t, o, None, None, W.NONE, K.hash_chains(t, o, None, None, W.NONE), blk)
+
+    whole = args(toks, offs)
+    assert whole[5].shape[0] >= (1 << 25) // 3
+    cut = toks.clone()
+    leave = offs[:-1] + (torch.rand(n, device="cuda", generator=g) * lens).long()
+    cut[leave] += 40000
+    with K.Radix(25, 28) as x, K.Radix(25, 28) as y:
+        x.insert(*whole)
+        for a in range(0, n, n // 4):
+            o = offs[a:a + n // 4 + 1]
+            y.insert(*args(toks[int(o[0]):int(o[-1])].contiguous(), (o - o[0]).contiguous()))
+        assert x.stats() == y.stats()
+        assert torch.equal(x.match(*whole).long(), lens)
+        probe = args(cut, offs)
+        got = x.match(*probe)
+        assert torch.equal(got, y.match(*probe))
+        assert bool((got.long() >= leave - offs[:-1]).all())
