@@ -280,7 +280,7 @@ int kvgov_cache_slots(const kvgov_cache *c, int64_t *slots);
  * Kernel errors: KVGOV_E_OFFSETS (nothing inserted), KVGOV_E_FULL (the table
  * holds a consistent subset of the union; clear it before reuse).
  * Scratch: calls of more than 10 M rows, for tables of a row to three slots
- * per row, use 13 * n_blocks bytes of the stream's scratch (see the notes at
+ * per row, use 14 * n_blocks bytes of the stream's scratch (see the notes at
  * the top); under capture, or where it cannot be had, they do without.
  */
 int kvgov_cache_insert(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
