@@ -918,11 +918,17 @@ __device__ __forceinline__ void lp_c2(uint32_t s[4], uint32_t z, const lp_quad p
 // later, before it is first read (as logical 9, four steps on).
 // Word 2k of the row at LDS address `row` (already offset by p) receives
 // K[t] + W[t]; kt = the lane's K.  Four steps are one asm statement of
-// eight-byte instructions only (see KVGOV_LP_ALIGN): 14 per step, and no
-// wait state before the DPP read (two instructions after the write).
-#define KVGOV_LP_SCHED(W0, W1, W9, W14, W15, KT, OFF)                               \
+// eight-byte instructions only (see KVGOV_LP_ALIGN): 13 per step and a write for
+// two, with no wait state before a DPP read (two instructions after the write of
+// what it reads): the first step's exchange is put between the second step's
+// first instructions.  The rounds waves wait for the schedule at every group
+// once a group takes it longer than eight steps take them, and then each barrier
+// costs them some 70 cycles, however short the wait: 0.510 ms for the 4096
+// chains above with a write per step, 0.468 so.
+#define KVGOV_LP_SUM(W0, W1, W9, W14, KT, T, MID)                                   \
   "v_alignbit_b32 %[t1], " W1 ", " W1 ", 7\n\t"                                    \
   "v_alignbit_b32 %[t2], " W1 ", " W1 ", 18\n\t"                                   \
+  MID                                                                              \
   "v_lshrrev_b32_e64 %[t3], 3, " W1 "\n\t"                                         \
   "v_alignbit_b32 %[t4], " W14 ", " W14 ", 17\n\t"                                 \
   "v_bitop3_b32 %[t1], %[t1], %[t2], %[t3] bitop3:0x96\n\t"                        \
@@ -931,34 +937,46 @@ __device__ __forceinline__ void lp_c2(uint32_t s[4], uint32_t z, const lp_quad p
   "v_add3_u32 " W0 ", %[t1], " W0 ", " W9 "\n\t"                                   \
   "v_bitop3_b32 %[t4], %[t4], %[t5], %[t6] bitop3:0x96\n\t"                        \
   "v_add_u32_e64 " W0 ", " W0 ", %[t4]\n\t"                                        \
-  "v_add_u32_e64 %[t1], " W0 ", " KT "\n\t"                                        \
-  "ds_write_b32 %[row], %[t1] offset:" OFF "\n\t"                                  \
-  "v_mov_b32_dpp " W1 ", " W0 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t" \
-  "v_cndmask_b32_e64 " W15 ", " W15 ", " W1 ", %[ol]\n\t"
-// w[i0] <- the new word (logical 14 of the next window), w[i1] <- the
+  "v_add_u32_e64 " T ", " W0 ", " KT "\n\t"
+// w[i0] holds the new word (logical 14 of the next window); w[i1] <- the
 // partner's (logical 15; on lane 1 replaced before it is read), w[i15] on
 // lane 1 <- the partner's (logical 13)
+#define KVGOV_LP_SWAP(W0, W1, W15)                                                  \
+  "v_mov_b32_dpp " W1 ", " W0 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t" \
+  "v_cndmask_b32_e64 " W15 ", " W15 ", " W1 ", %[ol]\n\t"
+#define KVGOV_LP_SCHED2(W0, W1, W2, W3, W9, W11, W14, W15, KA, KB, OA, OB)          \
+  KVGOV_LP_SUM(W0, W1, W9, W14, KA, "%[t7]", "")                                   \
+  KVGOV_LP_SUM(W2, W3, W11, W0, KB, "%[t1]", KVGOV_LP_SWAP(W0, W1, W15))           \
+  "ds_write2_b32 %[row], %[t7], %[t1] offset0:" OA " offset1:" OB "\n\t"           \
+  KVGOV_LP_SWAP(W2, W3, W1)
 
 // Steps 4 G .. 4 G + 3; kt the lane's constants of these.
 template <int G>
 __device__ __forceinline__ void lp_pair4(uint32_t w[16], uint32_t row, const uint32_t *kt) {
-  uint32_t t1, t2, t3, t4, t5, t6;
+  uint32_t t1, t2, t3, t4, t5, t6, t7;
   constexpr int b = (8 * G) & 15;  // the window's start: 0 or 8
 #define KVGOV_LP_W(I) [w##I] "+v"(w[(b + I) & 15])
   asm volatile(KVGOV_LP_ALIGN
-               KVGOV_LP_SCHED("%[w0]", "%[w1]", "%[w9]", "%[w14]", "%[w15]", "%[k0]", "%c[o0]")
-               KVGOV_LP_SCHED("%[w2]", "%[w3]", "%[w11]", "%[w0]", "%[w1]", "%[k1]", "%c[o1]")
-               KVGOV_LP_SCHED("%[w4]", "%[w5]", "%[w13]", "%[w2]", "%[w3]", "%[k2]", "%c[o2]")
-               KVGOV_LP_SCHED("%[w6]", "%[w7]", "%[w15]", "%[w4]", "%[w5]", "%[k3]", "%c[o3]")
+               KVGOV_LP_SCHED2("%[w0]", "%[w1]", "%[w2]", "%[w3]", "%[w9]", "%[w11]", "%[w14]",
+                               "%[w15]", "%[k0]", "%[k1]", "%c[o0]", "%c[o1]")
+               KVGOV_LP_SCHED2("%[w4]", "%[w5]", "%[w6]", "%[w7]", "%[w13]", "%[w15]", "%[w2]",
+                               "%[w3]", "%[k2]", "%[k3]", "%c[o2]", "%c[o3]")
                : KVGOV_LP_W(0), KVGOV_LP_W(1), KVGOV_LP_W(2), KVGOV_LP_W(3), KVGOV_LP_W(4),
                  KVGOV_LP_W(5), KVGOV_LP_W(6), KVGOV_LP_W(7), KVGOV_LP_W(9), KVGOV_LP_W(11),
                  KVGOV_LP_W(13), KVGOV_LP_W(14), KVGOV_LP_W(15), [t1] "=&v"(t1), [t2] "=&v"(t2),
-                 [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6)
+                 [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7)
                : [k0] "v"(kt[0]), [k1] "v"(kt[1]), [k2] "v"(kt[2]), [k3] "v"(kt[3]),
-                 [row] "v"(row), [ol] "s"(kALanes), [o0] "i"(32 * G), [o1] "i"(32 * G + 8),
-                 [o2] "i"(32 * G + 16), [o3] "i"(32 * G + 24)
+                 [row] "v"(row), [ol] "s"(kALanes), [o0] "i"(8 * G), [o1] "i"(8 * G + 2),
+                 [o2] "i"(8 * G + 4), [o3] "i"(8 * G + 6)
                : "memory");
 #undef KVGOV_LP_W
+}
+
+// The schedule waves' barrier.  The compiler waits for the LDS accesses that it
+// knows; lp_pair4's writes are inside asm, so their wait is here.
+__device__ __forceinline__ void lp_sched_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
 }
 
 // What a request does in iteration i of its workgroup.
@@ -1180,7 +1198,7 @@ __device__ __forceinline__ void lp_group(const ChainArgs &a, int32_t group, LpLd
         }
       }
     }
-    __syncthreads();
+    lp_sched_barrier();
     const uint32_t row1 = lds_addr(L.c1[mine] + (odd ? 1 : 0));
     const uint32_t *msg = L.msg[mine] + (odd ? 1 : 0);
     uint32_t w[16];
@@ -1196,17 +1214,17 @@ __device__ __forceinline__ void lp_group(const ChainArgs &a, int32_t group, LpLd
         w[15] = L.msg[mine][15];
       }
       lp_pair4<0>(w, row1, kt);
-      __syncthreads();
+      lp_sched_barrier();
       lp_pair4<1>(w, row1, kt + 4);
-      __syncthreads();
+      lp_sched_barrier();
       lp_pair4<2>(w, row1, kt + 8);
-      __syncthreads();
+      lp_sched_barrier();
       lp_pair4<3>(w, row1, kt + 12);
-      __syncthreads();
+      lp_sched_barrier();
       lp_pair4<4>(w, row1, kt + 16);
-      __syncthreads();
+      lp_sched_barrier();
       lp_pair4<5>(w, row1, kt + 20);
-      __syncthreads();
+      lp_sched_barrier();
       // iteration j + 1: its tokens (block `held`, unless it is a padding
       // iteration), and the load of the block after it
       const bool pad = MODE == KVGOV_BOUNDARY && kb >= 0 && j == kb;
@@ -1227,7 +1245,7 @@ __device__ __forceinline__ void lp_group(const ChainArgs &a, int32_t group, LpLd
         for (int x = 8; x < 15; ++x) w[x] = msg[x];
         w[15] = L.msg[mine][15];
       }
-      __syncthreads();
+      lp_sched_barrier();
     }
     return;
   }
