@@ -61,7 +61,7 @@ __device__ __forceinline__ Key load_key(const uint8_t *p) {
   return Key{q[0], q[1]};
 }
 
-__device__ __forceinline__ bool key_eq(const Key &a, const Key &b) {
+__host__ __device__ __forceinline__ bool key_eq(const Key &a, const Key &b) {
   const uint32_t d = (a.lo.x ^ b.lo.x) | (a.lo.y ^ b.lo.y) | (a.lo.z ^ b.lo.z) |
                      (a.lo.w ^ b.lo.w) | (a.hi.x ^ b.hi.x) | (a.hi.y ^ b.hi.y) |
                      (a.hi.z ^ b.hi.z) | (a.hi.w ^ b.hi.w);
@@ -111,10 +111,20 @@ __device__ __forceinline__ uint64_t seq_slot(uint64_t home, uint64_t p, uint64_t
 
 // A key read while it may be written: all of it is there if no word is as in an
 // empty slot.
-__device__ __forceinline__ bool key_is_whole(const Key &k) {
+__host__ __device__ __forceinline__ bool key_is_whole(const Key &k) {
   const uint32_t ones = 0xFFFFFFFFu;
   return k.lo.x != ones && k.lo.y != ones && k.lo.z != ones && k.lo.w != ones && k.hi.x != ones &&
          k.hi.y != ones && k.hi.z != ones && k.hi.w != ones;
+}
+
+// What a slot holds for a lane that looks for `key`, from a read of the slot's
+// key that another lane may be writing.  A part of a key can equal a key with
+// all-ones words where the rest is missing, so only a whole one is compared: the
+// others, keys with such a word among them, are left to the tag.
+enum class Slot { kMine, kOther, kUnclear };
+__host__ __device__ __forceinline__ Slot slot_holds(const Key &key, const Key &there) {
+  if (!key_is_whole(there)) return Slot::kUnclear;
+  return key_eq(key, there) ? Slot::kMine : Slot::kOther;
 }
 
 // Sum of v over the workgroup (256 threads), valid in thread 0.
@@ -170,7 +180,7 @@ __device__ __forceinline__ unsigned long long recency(uint32_t epoch, uint32_t d
 // `claim_first` (the key is thought to be new) the tag is not read before the
 // compare-and-swap in the home's bucket.  KEYS (for callers that need neither
 // *code nor *claim): the slot's key is looked at before its tag, and the tag
-// only if that key is not all there.  On a table that tracks recency the key
+// only if that key is not all there (slot_holds).  On a table that tracks recency the key
 // (added or found) is touched with (epoch, depth) unless depth is kNoDepth.
 template <bool ADMIT, bool KEYS = false>
 __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &key, int64_t i,
@@ -194,12 +204,11 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
     if (t.track && depth != kNoDepth) touch(&t.meta->ones_rank, recency(epoch, depth), won);
     return won ? 1u : 0u;
   }
-  enum class Slot { kMine, kOther, kUnclear };
   const auto look = [&](uint64_t s) {
-    const Key there{t.keys[2 * s], t.keys[2 * s + 1]};
-    if (!key_eq(key, there)) return key_is_whole(there) ? Slot::kOther : Slot::kUnclear;
-    if (t.track && depth != kNoDepth) touch(&t.rank[s], recency(epoch, depth), false);
-    return Slot::kMine;
+    const Slot is = slot_holds(key, Key{t.keys[2 * s], t.keys[2 * s + 1]});
+    if (is == Slot::kMine && t.track && depth != kNoDepth)
+      touch(&t.rank[s], recency(epoch, depth), false);
+    return is;
   };
   const uint64_t home = home_slot(key, t.mask);
   for (uint64_t probes = 0; probes <= t.mask; ++probes) {

@@ -344,6 +344,68 @@ def test_insert_of_crowded_slots(log2_slots, track):
                 assert key_set(c.export().cpu().numpy()) == T.keys
 
 
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("half", ["second", "some words"])
+def test_insert_of_keys_that_halves_of_others_equal(half, track):
+    """Pairs of keys with one home slot, of which one equals what a read of the
+    other can show while it is being written (all ones in the second half, or in
+    some words), held at the same depth by many short requests of one batch, in
+    a table whose slots are looked at key first."""
+    log2_slots, n = 21, 4000
+    g = np.random.default_rng(len(half) + track)
+    one = g.integers(0, 1 << 32, (n, 8), dtype=np.uint32)
+    if half == "second":
+        one[:, 4:] = 0xFFFFFFFF
+    else:
+        one[np.arange(n), g.integers(0, 8, n)] = 0xFFFFFFFF
+        one[np.arange(n), g.integers(0, 8, n)] = 0xFFFFFFFF
+    # its partner: the same words but for those of all ones, of which one 64-bit
+    # word is solved for (the first such) so that the homes agree
+    other = np.where(one == 0xFFFFFFFF, g.integers(0, 0xFFFFFFFF, (n, 8), dtype=np.uint32), one)
+    mul = [1, 0x9E3779B97F4A7C15, 0xC2B2AE3D27D4EB4F, 0x165667B19E3779F9]
+
+    def parts(k):
+        q = torch.from_numpy(k.view(np.int64))
+        return [q[:, i] * i64(mul[i]) for i in range(4)]
+
+    def home_of(p):
+        y = p[0] ^ p[1] ^ p[2] ^ p[3]
+        y = (y ^ shr(y, 31)) * i64(0xBF58476D1CE4E5B9)
+        return (y ^ shr(y, 29)) & ((1 << log2_slots) - 1)
+
+    if half == "second":
+        at = home_of(parts(one)) | torch.from_numpy(g.integers(0, 1 << 40, n) << log2_slots)
+        y = at ^ shr(at, 29) ^ shr(at, 58)
+        y = y * i64(pow(0xBF58476D1CE4E5B9, -1, 1 << 64))
+        p = parts(other)
+        w3 = (y ^ shr(y, 31) ^ shr(y, 62) ^ p[0] ^ p[1] ^ p[2]) * i64(pow(mul[3], -1, 1 << 64))
+        other.view(np.int64)[:, 3] = w3.numpy()
+        assert torch.equal(home_of(parts(one)), home_of(parts(other)))
+    pair = np.stack([one, other], 1).view(np.uint8).reshape(n, 2, 32)
+    head = g.integers(0, 256, (1, 32), dtype=np.uint8)
+    rows, lens = [], []
+    for r in range(0, 3 * n, 3):  # three requests, of four pairs each
+        for swap in (0, 1, 0):
+            i = (r // 3 + np.arange(4) * 5) % n
+            rows += [head, pair[i, (np.arange(4) + swap) % 2]]
+            lens.append(5)
+    rows = np.concatenate(rows)
+    bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    T = O.Table()
+    T.insert(rows, bo)
+    for _ in range(3):
+        with K.Cache(log2_slots) as c:
+            c.set_recency(track)
+            assert c.insert(dev(rows), dev(bo)) == len(T.keys)
+            assert key_set(c.export().cpu().numpy()) == T.keys
+            assert np.array_equal(c.lookup(dev(rows), dev(bo)).cpu().numpy(), lens)
+            if track:
+                assert c.evict(len(T.keys) // 2) == T.evict(len(T.keys) // 2)
+                assert key_set(c.export().cpu().numpy()) == T.keys
+                T = O.Table()
+                T.insert(rows, bo)
+
+
 @pytest.mark.parametrize("kind,log2_slots", [("new", 25), ("edges", 24), ("duplicates", 24),
                                              ("shared", 24)])
 def test_insert_of_a_very_large_batch(kind, log2_slots):
