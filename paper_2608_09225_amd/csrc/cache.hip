@@ -1287,6 +1287,21 @@ unsigned grid_for(int64_t work, int per_cu) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(work, 256), cap));
 }
 
+template <class T>
+void raise_to(std::atomic<T> &most, T v) {
+  T seen = most.load();
+  while (seen < v && !most.compare_exchange_weak(seen, v)) {
+  }
+}
+
+// Is the stream being captured, as far as is known?
+bool is_capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // The recency words are rewritten only if something may have written them
 // since they were last cleared (a tracked insert or admission, an eviction,
 // an erasure): on a table that never tracks, a clear writes 40 of its 48
@@ -1309,8 +1324,7 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
   hipLaunchKernelGGL(k_cache_fill, dim3(grid_for((a.n_ones[0] + a.n_ones[1]) / 4, 1024)), dim3(256),
                      0, s, a);
   c->rank_dirty = false;
-  c->max_rows = 0;
-  c->epoch.store(0);
+  raise_to(c->top_epoch, c->epoch.exchange(0));
   return launch_status();
 }
 
@@ -1342,9 +1356,7 @@ unsigned insert_grid(int64_t n_blocks) {
 // n_blocks.
 void note_tracked(kvgov_cache *c, int64_t n_blocks) {
   c->rank_dirty = true;
-  int64_t seen = c->max_rows.load();
-  while (seen < n_blocks && !c->max_rows.compare_exchange_weak(seen, n_blocks)) {
-  }
+  raise_to(c->max_rows, n_blocks);
 }
 
 }  // namespace
@@ -1562,13 +1574,7 @@ bool by_regions(const kvgov_cache *c, int32_t n, int64_t n_blocks) {
 // if it cannot have its scratch (then nothing is enqueued).
 bool insert_regions(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
                     int64_t n_blocks, uint32_t epoch, hipStream_t s, int *rc) {
-  // no memory may be allocated under capture
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (cap != hipStreamCaptureStatusNone) return false;
+  if (is_capturing(s)) return false;  // no memory may be allocated then
   RegionArgs a{c->view, hashes, blk_offsets, n, n_blocks, epoch};
   a.regions = (uint32_t)(c->slots >> kRegionLog2);
   // room for an even spread and ten standard deviations
@@ -1800,8 +1806,10 @@ int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *s
                      (long long)max_keys);
   // enough passes for every bit that can differ: stamps up to the clock,
   // depths up to the largest tracked batch (a pass after the last needed one
-  // ends at once)
-  const int bits = bit_length(c->epoch.load()) + bit_length((uint64_t)c->max_rows.load());
+  // ends at once); a captured eviction runs on tables of any later calls
+  const int bits = is_capturing(s) ? 64
+                                   : bit_length(std::max(c->epoch.load(), c->top_epoch.load())) +
+                                         bit_length((uint64_t)c->max_rows.load());
   const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(c->slots, kRankThreads * 8),
                                                    device_cu_count() * 2);
   for (int left = std::max(bits, 1); left > 0; left -= kRankDigit)

@@ -352,8 +352,11 @@ struct kvgov_cache {
   // recency words may be nonzero (set when a call that can write them is
   // enqueued; the next clear rewrites them)
   std::atomic<bool> rank_dirty{true};
-  // the largest row count of a tracked call since the last clear: every depth
-  // in a recency word is below it
+  // the largest epoch of a call before the last clear, and the largest row count
+  // of a tracked call: no recency word has a higher stamp than this or `epoch`,
+  // nor a depth above the row count.  (A clear does not lower them: a captured
+  // insert keeps the stamp that it was captured with.)
+  std::atomic<uint32_t> top_epoch{0};
   std::atomic<int64_t> max_rows{0};
 };
 

@@ -349,3 +349,51 @@ def test_tracked_insert_of_shared_heads(max_len, repeat):
             if keep <= len(T.keys):
                 assert c.evict(keep) == T.evict(keep), keep
                 assert key_set(c.export()) == T.keys, keep
+
+
+def test_evict_with_captured_calls():
+    """A captured insert keeps the stamp that it was captured with, also when its
+    graph runs after a clear; a captured eviction runs on tables with more calls
+    and longer requests than there were at its capture.  Each keeps what the
+    oracle keeps."""
+    def rows_of(lens, at):
+        bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        rows = np.zeros((int(bo[-1]), 32), np.uint8)
+        ids = np.arange(at, at + rows.shape[0]).astype(np.uint64)
+        rows[:, :8] = (ids * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+        rows[:, 8] = 1
+        return rows, bo
+
+    side = torch.cuda.Stream()
+    with KV.Cache(14) as c, torch.cuda.stream(side):
+        c.set_recency(True)
+        for k in range(70):
+            c.insert(*map(dev, rows_of([1], 100000 + k)))
+        assert c.evict(1) == 1  # and its scratch is there
+        h, bo = rows_of([3000, 1000, 1], 0)
+        dh, dbo = dev(h), dev(bo)
+        insert, evict = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+        side.synchronize()
+        with torch.cuda.graph(insert, stream=side):
+            c.insert(dh, dbo, sync=False)
+        with torch.cuda.graph(evict, stream=side):
+            c.evict(2500, sync=False)
+        for keep in (2500, 4001, 1):
+            c.clear()
+            T = O.Table()
+            insert.replay()
+            T.insert(h, bo)
+            assert c.evict(keep) == T.evict(keep)
+            assert key_set(c.export()) == T.keys
+        for calls in (1, 40, 300):
+            c.clear()
+            T = O.Table()
+            for k in range(calls):
+                batch = rows_of([3500 if k == 0 else 30], 10000 * (k + 1))
+                c.insert(*map(dev, batch), sync=False)
+                T.insert(*batch)
+            evict.replay()
+            want = T.evict(2500)
+            assert c.count() == want
+            assert key_set(c.export()) == T.keys
+        side.synchronize()

@@ -1,0 +1,129 @@
+"""The host half of the calls without a GPU: the library in a process whose HIP
+runtime is a stand-in that records launches and allocations and runs nothing,
+so that what a call enqueues can be compared with what the device will need."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2608_09225_amd import kvgov as K
+
+pytestmark = pytest.mark.skipif(not os.path.exists(K.LIB_PATH), reason="libkvgov.so not built")
+
+RUNTIME = r"""
+#include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+static std::map<const void *, std::string> names;
+static std::string launched;
+static int capturing = 0;
+static size_t fail_bytes = 0;
+extern "C" {
+void *__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipRegisterFunction(void *, const void *host, char *, const char *name, unsigned, void *,
+                           void *, void *, void *, int *) { names[host] = name; }
+void __hipRegisterVar(void *, void *, char *, char *, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void *) {}
+struct Dim { uint32_t x, y, z; };
+static Dim grid_, block_; static size_t shmem_; static void *stream_;
+int __hipPushCallConfiguration(Dim g, Dim b, size_t s, void *st) {
+  grid_ = g; block_ = b; shmem_ = s; stream_ = st; return 0; }
+int __hipPopCallConfiguration(Dim *g, Dim *b, size_t *s, void **st) {
+  *g = grid_; *b = block_; *s = shmem_; *st = stream_; return 0; }
+int hipLaunchKernel(const void *f, Dim, Dim, void **, size_t, void *) {
+  launched += names[f] + "\n"; return 0; }
+int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
+int hipDeviceSynchronize() { return 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipFree(void *p) { free(p); return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipGetLastError() { return 0; }
+int hipGetSymbolAddress(void **, const void *) { return 1; }
+int hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); return 0; }
+int hipMalloc(void **p, size_t n) {
+  if (fail_bytes && n >= fail_bytes) return 2;
+  *p = malloc(64); return 0; }
+int hipMemcpyAsync(void *d, const void *, size_t n, int, void *) { memset(d, 0, n); return 0; }
+int hipMemset(void *, int, size_t) { return 0; }
+int hipStreamIsCapturing(void *, int *s) { *s = capturing; return 0; }
+int hipStreamSynchronize(void *) { return 0; }
+int hipThreadExchangeStreamCaptureMode(int *) { return 0; }
+void test_capture(int on) { capturing = on; }
+void test_fail_from(size_t bytes) { fail_bytes = bytes; }
+const char *test_launched() { static std::string s; s = launched; launched.clear(); return s.c_str(); }
+}
+"""
+
+PRELUDE = """
+import ctypes, json, re
+hip = ctypes.CDLL({hip!r}, mode=ctypes.RTLD_GLOBAL)
+hip.test_launched.restype = ctypes.c_char_p
+lib = ctypes.CDLL({lib!r})
+i32, i64, vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+fake = vp(0x1000)  # device memory: never touched here
+def launched():
+    return re.findall(r"(k_\\w+?)(?:I[LN]|E)", hip.test_launched().decode())
+def cache(log2_slots, track=1):
+    h = vp()
+    assert lib.kvgov_cache_create(i32(log2_slots), ctypes.byref(h)) == 0
+    assert lib.kvgov_cache_set_recency(h, i32(track)) == 0
+    return h
+def insert(h, n, n_blocks):
+    assert lib.kvgov_cache_insert(h, fake, fake, i32(n), i64(n_blocks), None, None) == 0
+def clear(h):
+    assert lib.kvgov_cache_clear(h, None) == 0
+def evict(h):
+    launched()
+    assert lib.kvgov_cache_evict(h, i64(10), None, None) == 0
+    return launched()
+launched()
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launches")
+    src, out = d / "hip.cpp", d / "libhip_stand_in.so"
+    src.write_text(RUNTIME)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", str(out), str(src)], check=True)
+
+    def go(body):
+        script = PRELUDE.format(hip=str(out), lib=K.LIB_PATH) + body
+        r = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return go
+
+
+def passes(bits):
+    return max(1, -(-bits // 11))  # bits that one pass of the select decides
+
+
+def test_evict_decides_every_bit_that_can_differ(run):
+    """An eviction's passes cover the stamps and depths that any call so far has
+    been given, captured ones that run after a clear included; a captured
+    eviction covers whole words."""
+    got = run("""
+out = {}
+h = cache(16)
+out["empty"] = evict(h).count("k_rank_select")
+for _ in range(4000):
+    insert(h, 3, 20)
+insert(h, 3, 5000)
+out["filled"] = evict(h).count("k_rank_select")
+clear(h)  # a graph captured before may insert with the stamps of before
+out["cleared"] = evict(h).count("k_rank_select")
+hip.test_capture(1)
+out["captured"] = evict(h).count("k_rank_select")
+print(json.dumps(out))
+""")
+    need = passes((4001).bit_length() + (5000).bit_length())
+    assert got["empty"] == 1
+    assert got["filled"] == need
+    assert got["cleared"] >= need
+    assert got["captured"] == passes(64)
