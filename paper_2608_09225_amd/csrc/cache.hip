@@ -1305,7 +1305,9 @@ bool is_capturing(hipStream_t s) {
 // The recency words are rewritten only if something may have written them
 // since they were last cleared (a tracked insert or admission, an eviction,
 // an erasure): on a table that never tracks, a clear writes 40 of its 48
-// bytes per slot.
+// bytes per slot.  A captured clear empties nothing yet and runs on a table of
+// any later state: it writes the words as well, and the clock goes on (an insert
+// before its first run is not to meet its own epoch in an older tag).
 int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMore{}) {
   FillArgs a{};
   a.m = c->view.meta;
@@ -1313,7 +1315,8 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
   a.n_ones[0] = c->slots * 2;
   a.zeros[0] = reinterpret_cast<u32x4 *>(c->view.tags);
   a.n_zeros[0] = c->slots / 2;
-  if (c->rank_dirty) {
+  const bool captured = is_capturing(s);
+  if (captured || c->rank_dirty) {
     a.zeros[1] = reinterpret_cast<u32x4 *>(c->view.rank);
     a.n_zeros[1] = c->slots / 2;
   }
@@ -1323,8 +1326,10 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
   a.n_zeros[2] = more.n_zeros;
   hipLaunchKernelGGL(k_cache_fill, dim3(grid_for((a.n_ones[0] + a.n_ones[1]) / 4, 1024)), dim3(256),
                      0, s, a);
-  c->rank_dirty = false;
-  raise_to(c->top_epoch, c->epoch.exchange(0));
+  if (!captured) {
+    c->rank_dirty = false;
+    raise_to(c->top_epoch, c->epoch.exchange(0));
+  }
   return launch_status();
 }
 

@@ -397,3 +397,45 @@ def test_evict_with_captured_calls():
             assert c.count() == want
             assert key_set(c.export()) == T.keys
         side.synchronize()
+
+
+def test_evict_after_captured_clears():
+    """A graph of a clear and a tracked insert, captured on an empty table: after
+    each run an eviction finds the recency of that run's keys alone."""
+    def rows_of(lens, at):
+        rows = np.zeros((sum(lens), 32), np.uint8)
+        ids = np.arange(at, at + rows.shape[0]).astype(np.uint64)
+        rows[:, :8] = (ids * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+        rows[:, 8] = 1
+        return rows
+
+    lens = [200, 900, 37, 500]
+    bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    side = torch.cuda.Stream()
+    with KV.Cache(12) as c, torch.cuda.stream(side):
+        c.set_recency(True)
+        assert c.evict(0) == 0  # its scratch is there
+        c.clear()
+        buf, dbo = dev(rows_of(lens, 0)), dev(bo)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            c.clear()
+            c.insert(buf, dbo, sync=False)
+        for run, keep in enumerate((700, 100, 1600, 1)):
+            rows = rows_of(lens, 5000 * run)
+            buf.copy_(torch.from_numpy(rows))
+            graph.replay()
+            T = O.Table()
+            T.insert(rows, bo)
+            assert c.evict(keep) == T.evict(keep)
+            assert key_set(c.export()) == T.keys
+        extra = rows_of([50], 10 ** 6)  # eager, after the graph's: ranks above it
+        graph.replay()
+        T = O.Table()
+        T.insert(rows, bo)
+        c.insert(dev(extra), dev(np.array([0, 50], np.int64)))
+        T.insert(extra, np.array([0, 50]))
+        assert c.evict(60) == T.evict(60)
+        assert key_set(c.export()) == T.keys
+        side.synchronize()

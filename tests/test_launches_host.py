@@ -34,8 +34,12 @@ int __hipPushCallConfiguration(Dim g, Dim b, size_t s, void *st) {
   grid_ = g; block_ = b; shmem_ = s; stream_ = st; return 0; }
 int __hipPopCallConfiguration(Dim *g, Dim *b, size_t *s, void **st) {
   *g = grid_; *b = block_; *s = shmem_; *st = stream_; return 0; }
-int hipLaunchKernel(const void *f, Dim, Dim, void **, size_t, void *) {
-  launched += names[f] + "\n"; return 0; }
+// of a clear, also whether it writes the recency words (the second array of its zeros)
+int hipLaunchKernel(const void *f, Dim, Dim, void **args, size_t, void *) {
+  launched += names[f] + "\n";
+  if (names[f].find("k_cache_fill") != std::string::npos && ((int64_t *)args[0])[8])
+    launched += "k_recencyE\n";
+  return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipDeviceSynchronize() { return 0; }
 int hipEventRecord(void *, void *) { return 0; }
@@ -127,3 +131,27 @@ print(json.dumps(out))
     assert got["filled"] == need
     assert got["cleared"] >= need
     assert got["captured"] == passes(64)
+
+
+def test_captured_clear_leaves_the_host_state(run):
+    """A clear that is being captured has emptied nothing: the next insert takes a
+    new epoch, and every run of the graph writes the recency words, whatever the
+    table held at the capture."""
+    got = run("""
+out = {}
+h = cache(16)
+clear(h); launched()
+clear(h); out["unused"] = launched()
+for _ in range(1000):
+    insert(h, 3, 20)
+out["passes"] = evict(h).count("k_rank_select")
+clear(h); out["used"] = launched()
+hip.test_capture(1)
+clear(h); out["captured"] = launched()
+insert(h, 3, 20); launched()
+hip.test_capture(0)
+clear(h); out["after"] = launched()
+print(json.dumps(out))
+""")
+    assert got["unused"] == ["k_cache_fill"]
+    assert got["used"] == got["captured"] == got["after"] == ["k_cache_fill", "k_recency"]
