@@ -381,7 +381,8 @@ int kvgov_cache_erase(kvgov_cache *c, const uint8_t *keys, int64_t n_keys, int64
  * block).
  *
  * create: block table of 2^log2_block_slots slots (48 B each, and 72 B for
- * the tokens below it up to 2^26 slots) and edge table of 2^log2_edge_slots
+ * the tokens below it up to 2^26 slots, where there is memory for that) and edge
+ * table of 2^log2_edge_slots
  * slots (8 B each; up to 15 edges per distinct block, fewer where sequences
  * share token prefixes), both in [4, 30], on the current device (which must
  * be current for every later call: KVGOV_E_DEVICE otherwise).  Errors:

@@ -49,10 +49,10 @@ constexpr uint32_t kEdgeBase = 0x80000000u;  // id of the token node in edge slo
 constexpr uint32_t kOnesNode = 0x7FFFFFFFu;  // id of the all-0xFF block key (no slot)
 constexpr uint32_t kNoNode = 0xFFFFFFFFu;
 constexpr int kMaxLog2Radix = 30;           // keeps slot ids clear of the ids above
-// Block tables up to this size keep chains: a token node of a chain has the id
-// slot * 16 + l, below 2^30.  Larger ones (whose records would take another
-// 72 bytes for each of 2^27 slots or more) have edges alone, and a block node's
-// id is its slot.
+// Block tables up to this size keep chains, if there is memory for them: a token
+// node of a chain has the id slot * 16 + l, below 2^30.  Larger ones (whose records
+// would take another 72 bytes for each of 2^27 slots or more) have edges alone,
+// and a block node's id is its slot.
 constexpr int kMaxLog2Chains = 26;
 constexpr int kChainMax = 15;
 
@@ -535,18 +535,20 @@ int kvgov_radix_create(int32_t log2_block_slots, int32_t log2_edge_slots, kvgov_
   x->edge_slots = (int64_t)1 << log2_edge_slots;
   x->edges.mask = (uint64_t)x->edge_slots - 1;
   void *keys = nullptr, *zero = nullptr, *ctags = nullptr, *chains = nullptr;
-  const bool chained = log2_block_slots <= kMaxLog2Chains;
   if (hipMalloc(&keys, (size_t)x->edge_slots * 8) != hipSuccess ||
-      hipMalloc(&zero, 32) != hipSuccess ||
-      (chained && (hipMalloc(&ctags, (size_t)x->blocks->slots * 8) != hipSuccess ||
-                   hipMalloc(&chains, (size_t)x->blocks->slots * 64) != hipSuccess))) {
+      hipMalloc(&zero, 32) != hipSuccess) {
     if (keys) (void)hipFree(keys);
-    if (zero) (void)hipFree(zero);
-    if (ctags) (void)hipFree(ctags);
-    if (chains) (void)hipFree(chains);
     kvgov_cache_destroy(x->blocks);
     delete x;
     return KVGOV_E_NOMEM;
+  }
+  // where there is no memory for chains, edges alone
+  if (log2_block_slots <= kMaxLog2Chains &&
+      (hipMalloc(&ctags, (size_t)x->blocks->slots * 8) != hipSuccess ||
+       hipMalloc(&chains, (size_t)x->blocks->slots * 64) != hipSuccess)) {
+    (void)hipGetLastError();  // not left for the next launch check
+    if (ctags) (void)hipFree(ctags);
+    ctags = chains = nullptr;
   }
   x->edges.keys = static_cast<unsigned long long *>(keys);
   x->edges.meta = x->blocks->view.meta;

@@ -155,3 +155,24 @@ print(json.dumps(out))
 """)
     assert got["unused"] == ["k_cache_fill"]
     assert got["used"] == got["captured"] == got["after"] == ["k_cache_fill", "k_recency"]
+
+
+def test_radix_create_without_memory_for_chains(run):
+    """An index whose tables can be had is created, with or without the records
+    of chains; one whose tables cannot be had is refused."""
+    got = run("""
+def create(fail_from):
+    hip.test_fail_from(ctypes.c_size_t(fail_from))
+    x = vp()
+    rc = lib.kvgov_radix_create(i32(20), i32(18), ctypes.byref(x))
+    hip.test_fail_from(ctypes.c_size_t(0))
+    if rc == 0:
+        assert lib.kvgov_radix_insert(x, fake, i64(40), fake, i32(2), None, None, i32(0), i32(0),
+                                      fake, fake, i64(2), None) == 0
+        assert lib.kvgov_radix_clear(x, None) == 0
+        assert lib.kvgov_radix_destroy(x) == 0
+    return rc
+print(json.dumps([create(n) for n in (0, 64 << 20, 8 << 20, 2 << 20)]))
+""")
+    c = K.header_constants()
+    assert got == [0, 0, c["KVGOV_E_NOMEM"], c["KVGOV_E_NOMEM"]]
