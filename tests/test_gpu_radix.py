@@ -214,3 +214,33 @@ def test_radix_of_a_very_large_batch():
         got = x.match(*probe)
         assert torch.equal(got, y.match(*probe))
         assert bool((got.long() >= leave - offs[:-1]).all())
+
+
+@pytest.mark.parametrize("mode", [W.NONE, W.ROOT])
+def test_radix_of_edges_alone(mode):
+    """A block table of 2^27 slots keeps no records of chains: every token node is
+    an edge.  Sequences that share heads, end inside a block or go on from where
+    another ended, in three calls; queries cut or changed at any token.  The same
+    sequences in a small index (with chains) give the same nodes and matches."""
+    g = np.random.default_rng(19 + mode)
+    seqs = [g.integers(0, 40, int(L)).astype(np.int32) for L in g.integers(0, 90, 60)]
+    for i in range(0, 60, 2):
+        q = seqs[int(g.integers(60))]
+        seqs[i] = np.r_[q[:int(g.integers(0, len(q) + 1))], seqs[i][:int(g.integers(0, 40))]]
+    prin = g.integers(0, 5, 60)
+    prin[1::3] = prin[0]
+    with Run(mode, log2_blocks=27, log2_edges=16) as r, Run(mode, log2_edges=16) as small:
+        assert r.Kb == small.Kb
+        for a in range(0, 60, 20):
+            b = flat(seqs[a:a + 20], prin[a:a + 20])
+            r.insert(b)
+            small.insert(b)
+            qs, qp = [], []
+            for i, s in enumerate(seqs):
+                d = int(g.integers(0, len(s) + 1))
+                qs += [s[:d], np.r_[s[:d], 77, s[d:]].astype(np.int32), s]
+                qp += [prin[i]] * 3
+            assert np.array_equal(r.check(flat(qs, qp)), small.check(flat(qs, qp)))
+            assert r.x.stats() == small.x.stats()
+        r.x.clear()
+        assert r.x.stats() == (0, 0)
