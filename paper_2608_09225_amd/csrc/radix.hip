@@ -241,10 +241,13 @@ __device__ __forceinline__ uint32_t insert_tokens(const RadixArgs &a, int64_t sl
   if (e.chain_tags && slot >= 0) {
     const unsigned long long mine =
         ((unsigned long long)a.blk_epoch << 32) | (unsigned long long)(r + 1);
-    unsigned long long tag = 0;
+    // read first: thousands of sequences may leave one node (65,536 sequences of
+    // 24 tokens below the unsalted root: 871 us without the read, 165 with)
+    unsigned long long tag = e.chain_tags[slot];
     u32x4 *rec = e.chains + slot * 4;
-    if (__hip_atomic_compare_exchange_strong(&e.chain_tags[slot], &tag, mine, __ATOMIC_RELAXED,
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+    if (tag == 0 && __hip_atomic_compare_exchange_strong(&e.chain_tags[slot], &tag, mine,
+                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)) {
       rec[0] = u32x4{(uint32_t)steps, tok[0], tok[1], tok[2]};
 #pragma unroll
       for (int q = 1; q < 4; ++q)
