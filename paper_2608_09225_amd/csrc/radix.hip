@@ -399,8 +399,8 @@ __global__ __launch_bounds__(256) void k_radix_match(RadixArgs a) {
   if (sub != 0) return;
   if (m == 0) parent = find_slot(a.t, load_key(q.root));
   int64_t steps = 0;
-  if (parent != -1) {
-    const int64_t rem = q.len - 16 * m;
+  const int64_t rem = q.len - 16 * m;  // 0: a whole number of blocks, all found
+  if (parent != -1 && rem > 0) {
     const int lim = (int)(rem < kChainMax ? rem : kChainMax);
     const int32_t *tp = a.tokens + q.t0 + 16 * m;
     bool below = true;  // the node has token nodes
