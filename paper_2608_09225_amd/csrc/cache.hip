@@ -251,6 +251,11 @@ struct RegionState {
   }
 };
 
+// Rows of a request that its group of G lanes admits; the others are the walkers'
+// (at least 64: of 64 consecutive rows, those past these are one request's).
+template <int G>
+constexpr int64_t kHeadRows = G < 16 ? 64 : 4 * G;
+
 // Plain (set-union) insert with G lanes per request, which walk the
 // request's rows G at a time.  Two comparisons keep keys that many requests
 // share away from the table (a key skipped by either equals a row of the
@@ -308,12 +313,95 @@ struct RegionState {
 // before this request's first (a first key claimed by a later request is
 // lowered, and that group compares with nothing).  (The chunked walk, which
 // admission took for every batch before it had the second comparison: 73 us for
-// 8192 requests of two paper-shaped batches; now 47.)
+// 8192 requests of two paper-shaped batches; now 47.)  A group admits the first
+// kHeadRows of its request; the workgroups from `walkers` on take the batch in
+// chunks and admit the rows past them (admit_tails).  Without these a long
+// request was a chain of rounds of one wave while the chip idled: 4096 lognormal
+// prompts of up to 2048 blocks 276 us, now 120; 16 requests of 2048 rows 187 / 65;
+// 64, of which one has 8192 rows, 376 / 124 (by chunks alone 110, 64 and 125).
+// Where no request is that long they cost 0 to 4 us (4096 requests of 166 rows 44 /
+// 48, by chunks alone 62).
+//
+// admit_tails: a wave looks for its four windows' requests side by side, and a
+// window that holds rows past a head holds them of the request of its first row
+// alone (heads are as long as a window).  That request's first key mostly has its
+// tag by then; where not, the second comparison is left out.
+template <int G, bool TRACK>
+__device__ __forceinline__ uint32_t admit_tails(const TableView &t, const uint8_t *hashes,
+                                                const int64_t *blk_offsets, int32_t n,
+                                                int64_t n_blocks, uint32_t epoch, uint32_t *codes,
+                                                int64_t lo, int64_t hi, uint32_t walkers) {
+  const int lane = threadIdx.x & 63;
+  const int64_t waves = (int64_t)(gridDim.x - walkers) * 4;
+  const int64_t wave = (int64_t)(blockIdx.x - walkers) * 4 + (threadIdx.x >> 6);
+  constexpr int kWindow = 64, kPart = kWave * kWindow / kInsChunk;  // lanes per window's search
+  uint32_t added = 0;
+  int32_t known = -1;
+  int64_t b_p = 0, n_p = 0, g0 = -1, g1 = 0;  // of request `known` (see k_insert_req)
+  bool fresh = false;
+  for (int64_t f0 = lo + wave * kInsChunk; f0 < hi; f0 += waves * kInsChunk) {
+    // the windows' first rows' requests (find_request), side by side
+    const int64_t w0 = f0 + (int64_t)(lane / kPart) * kWindow;
+    int32_t a = 0;
+    for (int32_t len = n, step; len > 1; len = step) {
+      step = (len + kPart - 1) / kPart;
+      const int64_t at = a + (int64_t)(lane % kPart) * step;
+      const uint64_t le = __ballot(at < n && blk_offsets[at < n ? at : 0] <= w0) >>
+                          (lane / kPart * kPart) & ((1u << kPart) - 1);
+      a += (31 - __builtin_clz((uint32_t)le | 1u)) * step;
+    }
+    // and their rows past the head, if any (out of order: its group's)
+    const int64_t wb = blk_offsets[a], we = blk_offsets[a + 1];
+    const int64_t w1 = wb + kHeadRows<G> > w0 ? wb + kHeadRows<G> : w0;
+    const int64_t w2 = we < w0 + kWindow ? we : w0 + kWindow;
+    for (uint64_t todo = __ballot(wb >= lo && we <= hi && w1 < w2 && lane % kPart == 0); todo;
+         todo &= todo - 1) {
+      const int from = __builtin_ctzll(todo);
+      const int32_t r = __shfl(a, from, 64);
+      const int64_t b_r = __shfl(wb, from, 64), fb = __shfl(w0, from, 64);
+      const int64_t first = __shfl(w1, from, 64), end = __shfl(w2, from, 64);
+      if (r != known) {
+        known = r;
+        b_p = r >= 1 ? blk_offsets[r - 1] : 0;
+        n_p = r >= 1 && b_p >= lo && b_p <= b_r ? b_r - b_p : 0;
+        const Key head = load_key(hashes + b_r * 32);
+        const int64_t slot = find_slot(t, head);
+        const unsigned long long tag =
+            slot >= 0 ? t.tags[slot] : (slot == -2 ? t.meta->ones_tag : 0ull);
+        const bool now = (uint32_t)(tag >> 32) == epoch;
+        const int64_t c = lo + (int64_t)(tag & 0xFFFFFFFFull) - 1;
+        fresh = !TRACK && now && claims_first(t.mask);
+        g0 = now && c >= lo && c < b_r ? c : -1;
+        g1 = b_r;
+        if (TRACK && g0 >= 0) {
+          const int32_t q = find_request(blk_offsets, n, g0);
+          if (blk_offsets[q] != g0) g0 = -1;
+          if (blk_offsets[q + 1] < g1) g1 = blk_offsets[q + 1];
+        }
+      }
+      const int64_t f = fb + lane;
+      if (f >= first && f < end) {
+        const int64_t jj = f - b_r;
+        const Key key = load_key(hashes + f * 32);
+        bool dup = jj < n_p && key_eq(key, load_key(hashes + (b_p + jj) * 32));
+        if (!dup && g0 >= 0 && g0 + jj < g1) dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
+        uint32_t code = kCodeDup;
+        if (!dup)
+          added += insert_key<true>(t, key, f, lo, hashes, epoch, &code,
+                                    TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr, false, fresh);
+        codes[f] = code;
+      }
+    }
+  }
+  return added;
+}
+
 template <int G, bool ADMIT, bool TRACK, bool KEYS>
 __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *hashes,
                                                     const int64_t *blk_offsets, int32_t n,
                                                     int64_t n_blocks, uint32_t epoch,
-                                                    uint32_t *codes, const RegionState *st) {
+                                                    uint32_t *codes, uint32_t walkers,
+                                                    const RegionState *st) {
   __shared__ uint32_t lds4[4];
   if (st && !st->by_request()) return;  // the batch goes by regions
   const int64_t lo = blk_offsets[0], hi = blk_offsets[n];
@@ -331,10 +419,15 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
   uint32_t added = 0;
   // groups never straddle r < n (256 % G == 0); the block sum below needs
   // every thread, so out-of-range groups only skip the work
-  if (r < n) {
+  if (ADMIT && blockIdx.x >= walkers) {
+    added = admit_tails<G, TRACK>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, lo, hi,
+                                  walkers);
+  } else if (r < n) {
     const int64_t b_r = blk_offsets[r], b_e = blk_offsets[r + 1];
     const int64_t b_p = r >= 1 ? blk_offsets[r - 1] : 0;
-    const int64_t b0 = b_r > lo ? b_r : lo, b1 = b_e < hi ? b_e : hi;
+    const int64_t b0 = b_r > lo ? b_r : lo;
+    int64_t b1 = b_e < hi ? b_e : hi;
+    if (ADMIT && b_r >= lo && b_e <= hi && b0 + kHeadRows<G> < b1) b1 = b0 + kHeadRows<G>;
     // the previous request's rows, when its range is in order and in the batch
     const int64_t n_p = r >= 1 && b_p >= lo && b_p <= b_r ? b_r - b_p : 0;
     if (b0 < b1) {
@@ -1504,19 +1597,27 @@ int read_new_keys(kvgov_cache *c, uint32_t epoch, int64_t *n_new, hipStream_t s)
   return m.status;
 }
 
+template <int G, bool ADMIT, bool TRACK, bool KEYS>
+void insert_req_group(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets,
+                      int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
+                      const RegionState *st) {
+  const unsigned groups = (unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * G, 256));
+  const unsigned walkers = ADMIT && n_blocks > kHeadRows<G> ? insert_grid(n_blocks) : 0;
+  hipLaunchKernelGGL((k_insert_req<G, ADMIT, TRACK, KEYS>), dim3(groups + walkers), dim3(256), 0, s,
+                     t, hashes, blk_offsets, n, n_blocks, epoch, codes, groups, st);
+}
+
 template <bool ADMIT, bool TRACK, bool KEYS>
 void insert_req_launch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets,
                        int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
                        const RegionState *st) {
   // (no request: only the batch check and the next call's counters)
-  const int g = n > 0 ? insert_group(n, n_blocks) : 64;
-  const dim3 grid((unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * g, 256))), block(256);
-  switch (g) {
-    case 4: hipLaunchKernelGGL((k_insert_req<4, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
-    case 8: hipLaunchKernelGGL((k_insert_req<8, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
-    case 16: hipLaunchKernelGGL((k_insert_req<16, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
-    case 32: hipLaunchKernelGGL((k_insert_req<32, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
-    default: hipLaunchKernelGGL((k_insert_req<64, ADMIT, TRACK, KEYS>), grid, block, 0, s, t, hashes, blk_offsets, n, n_blocks, epoch, codes, st); break;
+  switch (n > 0 ? insert_group(n, n_blocks) : 64) {
+    case 4: insert_req_group<4, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
+    case 8: insert_req_group<8, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
+    case 16: insert_req_group<16, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
+    case 32: insert_req_group<32, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
+    default: insert_req_group<64, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
   }
 }
 

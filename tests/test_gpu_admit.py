@@ -267,6 +267,47 @@ def test_admit_interleaved_heads(max_len, log2_slots, track):
                 assert key_set(c.export().cpu().numpy()) == T.keys
 
 
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("n,longest,many", [(40, 1100, 0.8), (400, 600, 0.3), (3000, 300, 0.03),
+                                            (20000, 130, 0.004), (1, 700, 1.0), (2, 257, 1.0)])
+def test_admit_of_requests_longer_than_their_heads(n, longest, many, track):
+    """Batches in which some requests are longer than what their group admits
+    (64 rows and up, by the average length), of lengths around those bounds, next to
+    empty and short ones; requests share heads that go past the bound, with
+    neighbours and others, and hold keys at other depths; rows before and after
+    the batch.  Admitted into an empty table and into one that holds most keys."""
+    g = np.random.default_rng(n + longest)
+    edges = np.array([63, 64, 65, 127, 128, 129, 191, 192, 255, 256, 257, 319, 320, longest])
+    pool = g.integers(0, 256, (6 * longest, 32), dtype=np.uint8)
+    T = O.Table()
+    with K.Cache(18) as c:
+        c.set_recency(track)
+        for _ in range(2):
+            lens = g.integers(0, 6, n)
+            long_ = g.random(n) < many
+            lens[long_] = np.minimum(longest, g.choice(edges, long_.sum()) + g.integers(-1, 2))
+            bo = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64) + 3
+            rows = g.integers(0, 256, (int(bo[-1]) + 5, 32), dtype=np.uint8)
+            head = g.integers(0, 3, n)
+            head[1::7] = head[:-1][::7][:head[1::7].size]  # neighbours
+            for r in np.nonzero(lens > 0)[0]:
+                same = min(int(lens[r]), int(g.integers(1, longest + 1)))
+                rows[bo[r]:bo[r] + same] = pool[head[r] * longest:head[r] * longest + same]
+                if g.random() < 0.1:  # keys of another head, elsewhere in the request
+                    rows[bo[r] + int(g.integers(lens[r]))] = pool[int(g.integers(pool.shape[0]))]
+            hits, new, n_new = c.admit(dev(rows), dev(bo))
+            wh, wn = T.admit(rows, bo)
+            assert np.array_equal(hits.cpu().numpy(), wh)
+            assert np.array_equal(new.cpu().numpy(), wn)
+            assert n_new == int(wn.sum())
+            assert key_set(c.export().cpu().numpy()) == T.keys
+        if track:
+            for keep in (len(T.keys) * 3 // 4, 150, 1):
+                if keep <= len(T.keys):
+                    assert c.evict(keep) == T.evict(keep)
+                    assert key_set(c.export().cpu().numpy()) == T.keys
+
+
 def test_more_threads_read_the_state_than_it_has_blocks():
     """Twelve threads, each on a stream of its own, wait for one table's state at
     the same time: the blocks of pinned memory serve eight, the others copy."""
