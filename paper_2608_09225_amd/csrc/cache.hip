@@ -289,7 +289,9 @@ constexpr int64_t kHeadRows = G < 16 ? 64 : 4 * G;
 // tag's line into this XCD's cache, from which the other XCDs' claims take it
 // again (270,000 random claims of 2^20 slots: 34 us with the read, 17
 // without).  Rows that follow a key of an earlier call keep the read: they are
-// mostly present (a batch that is all present: 20 us, 34 without the read).
+// mostly present (a batch that is all present: 20 us, 34 without the read).  So do
+// a group's next rows once one was found (keys that are no chain's, 8 copies of
+// each: 2^20 slots 48 us without this, 41 with, 2^23 214 and 162).
 //
 // KEYS: these rows look at a slot's key before its tag.  A present key then
 // costs one line, not two, and a walk past other keys reads the line that holds
@@ -468,11 +470,16 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
         if (!dup && g0 >= 0 && (!(TRACK || ADMIT) || g0 + jj < g1))
           dup = key_eq(key, load_key(hashes + (g0 + jj) * 32));
         uint32_t code = kCodeDup;
-        if (!dup)
-          added += insert_key<ADMIT, KEYS>(t, key, f, lo, hashes, epoch, &code,
-                                           TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr,
-                                           false, fresh != 0);
+        uint32_t got = 1;
+        if (!dup) {
+          got = insert_key<ADMIT, KEYS>(t, key, f, lo, hashes, epoch, &code,
+                                        TRACK ? row_depth(jj, n_blocks) : kNoDepth, nullptr, false,
+                                        fresh != 0);
+          added += got;
+        }
         if (ADMIT) codes[f] = code;
+        // a row that was there: no chain, or one that goes on as another's
+        if (!TRACK && (__ballot(got == 0) & group_mask<G>(base))) fresh = 0;
       }
     }
   }
