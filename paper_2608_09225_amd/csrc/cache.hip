@@ -240,14 +240,25 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
 struct RegionState {
   uint32_t n_rest;  // rows in the rest list
   uint32_t bad;     // a malformed batch, or rows fewer than half of n_blocks
-  // first keys seen << 32 | of them repeated (or in the table): of the evenly
-  // spread requests, of those chosen by their key
-  unsigned long long spread, by_key;
+  // keys seen << 32 | of them repeated (or in the table), see k_region_sample: first
+  // keys of evenly spread requests, and those chosen by the key; then rows
+  unsigned long long spread, by_key, rows_spread, rows_by_key;
+  // of the spread rows, those repeated alone
+  unsigned long long rows_hot;
 
   // Does the batch go by requests?
   __device__ bool by_request() const {
-    return bad || (spread & 0xFFFFFFFFu) * 8 > spread >> 32 ||
-           (by_key & 0xFFFFFFFFu) * 8 > by_key >> 32;
+    return bad || heads_repeat() || rows_repeat();
+  }
+  // Are first keys repeated, or in the table?
+  __device__ bool heads_repeat() const { return repeats(spread, 8) || repeats(by_key, 8); }
+  // Are other rows?
+  __device__ bool rows_repeat() const { return repeats(rows_spread, 8) || repeats(rows_by_key, 160); }
+  // Do few keys make up much of the batch?
+  __device__ bool hot() const { return repeats(rows_hot, 8); }
+  // one in `part` at least?
+  static __device__ bool repeats(unsigned long long seen, uint32_t part) {
+    return (seen & 0xFFFFFFFFu) * part > seen >> 32;
   }
 };
 
@@ -405,7 +416,9 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
                                                     uint32_t *codes, uint32_t walkers,
                                                     const RegionState *st) {
   __shared__ uint32_t lds4[4];
-  if (st && !st->by_request()) return;  // the batch goes by regions
+  // a batch that may go by regions: does it, or is it the other launch's?
+  if (st && (!st->by_request() || st->hot() == KEYS)) return;
+  const bool repeats = st && !st->heads_repeat() && st->rows_repeat();  // no chains
   const int64_t lo = blk_offsets[0], hi = blk_offsets[n];
   if (blockIdx.x == 0 && threadIdx.x < kCounterLanes)
     t.meta->new_keys[(epoch + 1) & 1][threadIdx.x] = 0;  // counters of the next call
@@ -446,7 +459,7 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
           added += insert_key<ADMIT>(t, key, b0, lo, hashes, epoch, &code,
                                      TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim,
                                      TRACK && !ADMIT);
-          fresh = !TRACK && claims_first(t.mask) && (uint32_t)(claim >> 32) == epoch;
+          fresh = !TRACK && !repeats && claims_first(t.mask) && (uint32_t)(claim >> 32) == epoch;
           const int64_t c = lo + (int64_t)(claim & 0xFFFFFFFFull) - 1;
           if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0) {
             g0 = c;
@@ -504,12 +517,13 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
 // 0.66 GB written by k_region_insert are 670 us at a copy's rate (the random
 // read fetches 128 bytes for each key's 32).
 //   k_region_clear    counters, lists and sets of this call
-//   k_region_sample   a look at the requests' first keys: where many of them are
-//                     shared, or in the table already, or the rows are fewer
-//                     than half of n_blocks, k_insert_req is the better one (it
-//                     keeps such rows off the table by comparisons, and finds
-//                     present keys with one read each) and the kernels below
-//                     end at once; otherwise k_insert_req does
+//   k_region_sample   a look at the requests' first keys and at some rows: where
+//                     many of them are shared, or in the table already, or the
+//                     rows are fewer than half of n_blocks, k_insert_req is the
+//                     better one (it keeps such rows off the table by
+//                     comparisons, and finds present keys with one read each)
+//                     and the kernels below end at once; otherwise k_insert_req
+//                     does
 //   k_region_lists    rows to their regions' lists
 //   k_region_insert   region by region
 //   k_list_insert     by insert_key: what the lists had no room for (keys that
@@ -524,6 +538,8 @@ constexpr int kMaxListed = 65000;  // entries of a region: an index fits 16 bits
 constexpr int kSampleSlots = 8192;
 constexpr int kSampled = 1024;      // requests looked at, evenly spread
 constexpr int kSampledByKey = 2048;  // about as many, chosen by their first key
+constexpr int kSampleRows = 64;      // one row of so many
+constexpr int kSampleSets = 4;
 
 struct RegionArgs {
   TableView t;
@@ -534,13 +550,13 @@ struct RegionArgs {
   uint32_t epoch;
   RegionState *st;
   uint32_t *cursor;             // per region: rows listed (may exceed cap)
-  unsigned long long *sample;   // two sets of kSampleSlots hashes
+  unsigned long long *sample;   // kSampleSets sets of kSampleSlots hashes
   unsigned long long *entries;  // per region: cap entries, (print << 46) | (home within the
                                 // region << 32) | row; prints have 16 bits
   uint32_t *rest;               // rows for k_list_insert
   uint32_t cap;
   uint32_t regions;
-  uint32_t key_mask;            // of the hash bits that choose a request by its first key
+  uint32_t key_mask, row_mask;  // of the hash bits that choose a request by its first key, a row by its
 };
 
 // The batch's rows, or none (an empty or malformed batch).
@@ -552,7 +568,7 @@ __device__ __forceinline__ bool region_rows(const RegionArgs &a, int64_t &lo, in
 
 __global__ __launch_bounds__(256) void k_region_clear(RegionArgs a) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i < 2 * kSampleSlots) a.sample[i] = 0;
+  if (i < kSampleSets * kSampleSlots) a.sample[i] = 0;
   if (i < kMaxRegions) a.cursor[i] = 0;
   if (i == 0) *a.st = RegionState{};
 }
@@ -575,25 +591,58 @@ __device__ __forceinline__ bool sample_twice(unsigned long long *set, uint64_t x
 // few keys that many requests share (and keys that are in the table); all
 // requests whose first key has zeros in some bits of its hash find groups of a
 // few requests anywhere in the batch, which come into this sample together.
+//
+// Digests of a chain are shared from the first on or not at all, other keys may
+// differ in the first row alone.  So a row of every kSampleRows is looked at in
+// the same two ways.  Of a key's copies the second look sees one in 64: where
+// all keys come twice, repeats are one in 128 of what it sees, and about there the
+// two ways meet (14.7 M rows into 2^25 slots, by regions / by requests: two
+// copies 1040 / 925 us, 16 870 / 490, 1024 1370 / 320, one key in all rows but the
+// first 2960 / 195; all new 1140 / 1490).  A batch that then goes by requests
+// claims no slot without a read, and where few keys make up much of it, tags are
+// read before keys: a slot's key that an XCD's cache holds as it was before it was
+// written sends every later copy to the compare-and-swap (1000 keys 890 us, 360
+// by tags).
+__device__ __forceinline__ void sample_look(const RegionArgs &a, unsigned long long *sets,
+                                            const Key &key, bool spread, uint32_t mask,
+                                            unsigned long long *cnt, unsigned long long *hot) {
+  const uint64_t x = slot_hash(key);
+  if (spread) {
+    const bool twice = sample_twice(sets, x), there = twice || probe(a.t, key, true);
+    atomicAdd(&cnt[0], 1ull << 32 | (there ? 1 : 0));
+    if (hot) atomicAdd(hot, 1ull << 32 | (twice ? 1 : 0));
+  }
+  if (((uint32_t)(x >> 40) & mask) == 0) {
+    const bool twice = sample_twice(sets + kSampleSlots, x);
+    atomicAdd(&cnt[1], 1ull << 32 | (twice ? 1 : 0));
+  }
+}
+
+// Is i, of n, one of kSampled that are evenly spread?
+__device__ __forceinline__ bool is_spread(int64_t i, int64_t n) {
+  return i == 0 || i * kSampled / n != (i - 1) * kSampled / n;
+}
+
 __global__ __launch_bounds__(kListThreads) void k_region_sample(RegionArgs a) {
-  __shared__ unsigned long long cnt[2];
+  __shared__ unsigned long long cnt[kSampleSets + 1];
   int64_t lo, hi;
   const bool ok = region_rows(a, lo, hi);
-  if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+  if (threadIdx.x < kSampleSets + 1) cnt[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t r = (int64_t)blockIdx.x * kListThreads + threadIdx.x;
-  const int64_t b = r < a.n ? a.blk_offsets[r] : -1;
-  if (ok && b >= lo && b < hi) {
-    const Key key = load_key(a.hashes + b * 32);
-    const uint64_t x = slot_hash(key);
-    if (r == 0 || r * kSampled / a.n != (r - 1) * kSampled / a.n) {
-      const bool twice = sample_twice(a.sample, x) || probe(a.t, key, true);
-      atomicAdd(&cnt[0], 1ull << 32 | (twice ? 1 : 0));
-    }
-    if (((uint32_t)(x >> 40) & a.key_mask) == 0) {
-      const bool twice = sample_twice(a.sample + kSampleSlots, x);
-      atomicAdd(&cnt[1], 1ull << 32 | (twice ? 1 : 0));
-    }
+  const int64_t i = (int64_t)blockIdx.x * kListThreads + threadIdx.x;
+  const int64_t b = i < a.n ? a.blk_offsets[i] : -1;
+  if (ok && b >= lo && b < hi)
+    sample_look(a, a.sample, load_key(a.hashes + b * 32), is_spread(i, a.n), a.key_mask, cnt,
+                nullptr);
+  // (scattered, as copies may be any number of rows apart, and a row of each
+  // stretch that a plain multiple would choose never meets some of them)
+  const int64_t looks = (hi - lo) / kSampleRows;
+  if (ok && i < looks) {
+    uint32_t x = (uint32_t)i * 0x9E3779B1u;
+    x = (x ^ x >> 15) * 0x85EBCA77u;
+    const int64_t f = lo + i * kSampleRows + (x ^ x >> 13) % kSampleRows;
+    sample_look(a, a.sample + 2 * kSampleSlots, load_key(a.hashes + f * 32), is_spread(i, looks),
+                a.row_mask, cnt + 2, cnt + kSampleSets);
   }
   if (blockIdx.x == 0) {
     if (threadIdx.x < kCounterLanes)
@@ -604,8 +653,11 @@ __global__ __launch_bounds__(kListThreads) void k_region_sample(RegionArgs a) {
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0 && cnt[0]) atomicAdd(&a.st->spread, cnt[0]);
-  if (threadIdx.x == 64 && cnt[1]) atomicAdd(&a.st->by_key, cnt[1]);
+  unsigned long long *sums[kSampleSets + 1] = {&a.st->spread, &a.st->by_key, &a.st->rows_spread,
+                                               &a.st->rows_by_key, &a.st->rows_hot};
+#pragma unroll
+  for (int k = 0; k < kSampleSets + 1; ++k)
+    if (threadIdx.x == 64 * k && cnt[k]) atomicAdd(sums[k], cnt[k]);
 }
 
 // A workgroup sorts its 16384 rows by region in LDS, so that a region's entries
@@ -1634,12 +1686,11 @@ constexpr uint64_t kKeysFirstSlots = (uint64_t)1 << 21;
 
 template <bool ADMIT, bool TRACK>
 void insert_req(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
-                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
-                const RegionState *st = nullptr) {
+                int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
   if (!ADMIT && t.mask + 1 >= kKeysFirstSlots)
-    insert_req_launch<ADMIT, TRACK, !ADMIT>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st);
+    insert_req_launch<ADMIT, TRACK, !ADMIT>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, nullptr);
   else
-    insert_req_launch<ADMIT, TRACK, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st);
+    insert_req_launch<ADMIT, TRACK, false>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, nullptr);
 }
 
 // Whether an insert may take k_insert_req (otherwise in chunks).
@@ -1695,9 +1746,12 @@ bool insert_regions(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_of
   a.cap = std::min((uint32_t)(mean + 10.0 * std::sqrt(mean) + 64.0), (uint32_t)kMaxListed);
   a.key_mask = 0;
   while (n / ((int64_t)a.key_mask + 1) >= 2 * kSampledByKey) a.key_mask = a.key_mask * 2 + 1;
+  const int64_t looks = n_blocks / kSampleRows;
+  a.row_mask = 0;
+  while (looks / ((int64_t)a.row_mask + 1) >= 2 * kSampledByKey) a.row_mask = a.row_mask * 2 + 1;
   const size_t off_cursor = 256;
   const size_t off_sample = off_cursor + sizeof(uint32_t) * kMaxRegions;
-  const size_t off_entries = off_sample + sizeof(unsigned long long) * 2 * kSampleSlots;
+  const size_t off_entries = off_sample + sizeof(unsigned long long) * kSampleSets * kSampleSlots;
   const size_t off_rest = off_entries + sizeof(unsigned long long) * a.regions * a.cap;
   const size_t bytes = off_rest + sizeof(uint32_t) * (size_t)n_blocks;
   std::unique_lock<std::mutex> lk;
@@ -1712,13 +1766,16 @@ bool insert_regions(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_of
   a.rest = reinterpret_cast<uint32_t *>(b + off_rest);
   const unsigned cus = (unsigned)device_cu_count();
   const unsigned tiles = (unsigned)std::min<int64_t>(ceil_div(n_blocks, kListRows), cus);
-  hipLaunchKernelGGL(k_region_clear, dim3(2 * kSampleSlots / 256), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_region_sample, dim3((unsigned)ceil_div(n, kListThreads)), dim3(kListThreads), 0, s, a);
+  hipLaunchKernelGGL(k_region_clear, dim3(kSampleSets * kSampleSlots / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_region_sample, dim3((unsigned)ceil_div(std::max<int64_t>(n, looks), kListThreads)),
+                     dim3(kListThreads), 0, s, a);
   hipLaunchKernelGGL(k_region_lists, dim3(tiles), dim3(kListThreads), 0, s, a);
   hipLaunchKernelGGL(k_region_insert, dim3(std::min(a.regions, cus)), dim3(kListThreads), 0, s, a);
   hipLaunchKernelGGL(k_list_insert, dim3(cus * 4), dim3(256), 0, s, a);
-  insert_req<false, false>(c->view, hashes, blk_offsets, n, n_blocks, epoch, nullptr, s,
-                           a.st);
+  insert_req_launch<false, false, true>(c->view, hashes, blk_offsets, n, n_blocks, epoch, nullptr, s,
+                                        a.st);
+  insert_req_launch<false, false, false>(c->view, hashes, blk_offsets, n, n_blocks, epoch, nullptr, s,
+                                         a.st);
   *rc = launch_status();
   return true;
 }

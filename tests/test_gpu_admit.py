@@ -447,22 +447,25 @@ def test_insert_of_keys_that_halves_of_others_equal(half, track):
                 T.insert(rows, bo)
 
 
-@pytest.mark.parametrize("kind,log2_slots", [("new", 25), ("edges", 24), ("duplicates", 24),
-                                             ("shared", 24)])
+@pytest.mark.parametrize("kind,log2_slots", [("new", 25), ("new", 26), ("edges", 24),
+                                             ("some duplicates", 24), ("duplicates", 24),
+                                             ("copies", 24), ("few keys", 24), ("shared", 24)])
 def test_insert_of_a_very_large_batch(kind, log2_slots):
     """Batches beyond the row count from which new keys go region by region
-    (2^14 slots each): into a table that holds some of their keys; with many
-    home slots at the ends of regions, the table's last one included; with
-    keys that come twice anywhere, 2 M times (more than a region's list takes) or
-    are all ones; with first keys that eight requests share (by requests).
-    Compared with the key set known by construction; recency off."""
+    (2^14 slots each, 4096 of them at 2^26 slots): into a table that holds some of
+    their keys; with many home slots at the ends of regions, the table's last one
+    included; with keys that come twice anywhere, 500,000 times (more than a
+    region's list takes) or are all ones.  And batches whose sample sends them by
+    requests: one key in a fifth of the rows, eight copies of every key, a
+    thousand keys in all, first keys that eight requests share.  Compared with the
+    key set known by construction; recency off."""
     g = torch.Generator(device="cuda")
     g.manual_seed(log2_slots + len(kind))
 
     def rand(lo, hi, shape):
         return torch.randint(lo, hi, shape, device="cuda", generator=g)
 
-    rows = (10 << 20) + 12345
+    rows = max(10 << 20, (1 << log2_slots) // 3) + 12345
     lens = rand(16, 83, (rows // 32,))
     lens[rand(0, lens.numel(), (100,))] = 0
     ends = torch.cumsum(lens, 0)
@@ -470,6 +473,8 @@ def test_insert_of_a_very_large_batch(kind, log2_slots):
     bo = torch.cat([ends.new_zeros(1), ends[:n]]) + 3  # rows before and after the batch
     lo, hi = int(bo[0]), int(bo[-1])
     rows = hi + 5
+    assert max(10 << 20, (1 << log2_slots) // 3) <= rows <= 1 << log2_slots
+    assert n >= 1024 and rows // n >= 32  # what a batch by regions has
     x = (rand(0, 1 << 32, (rows,)) << 32) | rand(0, 1 << 32, (rows,))
     if kind == "edges":
         at = rand(0, rows, (rows // 100,))
@@ -481,17 +486,22 @@ def test_insert_of_a_very_large_batch(kind, log2_slots):
     inner = torch.ones(rows, dtype=torch.bool, device="cuda")
     first = bo[:-1][bo[:-1] < bo[1:]]
     inner[first] = False  # not a request's first row
-    if kind == "duplicates":
-        source[6 << 20:8 << 20] = 12345
-        at = rand(0, rows, (rows // 5,))
+    if kind in ("some duplicates", "duplicates"):
+        source[6 << 20:(6 << 20) + (500000 if kind == "some duplicates" else 2 << 20)] = 12345
+        at = rand(0, rows, (rows // (8 if kind == "some duplicates" else 5),))
         source[at] = rand(0, rows, at.shape)
+    if kind in ("copies", "few keys"):
+        source = lo + rand(0, rows // 8 if kind == "copies" else 1000, (rows,))
     if kind == "shared":
         p = first[torch.randperm(first.numel(), device="cuda", generator=g)]
         source[p] = p[torch.arange(p.numel(), device="cuda") // 8]
         inner[:] = True
     source = torch.where(inner, source, torch.arange(rows, device="cuda"))
+    repeated = 1 - torch.unique(source[lo:hi]).numel() / (hi - lo)
+    if kind != "shared":  # (there the first keys tell)
+        assert repeated < 0.2 if kind in ("new", "edges", "some duplicates") else repeated > 0.25
     keys = keys[source].contiguous()
-    ones = kind == "duplicates"
+    ones = kind in ("some duplicates", "duplicates")
     if ones:
         at = rand(0, rows, (1000,))
         at = at[inner[at]]
