@@ -1459,7 +1459,9 @@ bool is_capturing(hipStream_t s) {
 // an erasure): on a table that never tracks, a clear writes 40 of its 48
 // bytes per slot.  A captured clear empties nothing yet and runs on a table of
 // any later state: it writes the words as well, and the clock goes on (an insert
-// before its first run is not to meet its own epoch in an older tag).
+// before its first run is not to meet its own epoch in an older tag).  So does
+// the clock of a table that captured calls stamp: the rows of a later call with the
+// same epoch would be taken for the graph's own.
 int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMore{}) {
   FillArgs a{};
   a.m = c->view.meta;
@@ -1468,7 +1470,7 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
   a.zeros[0] = reinterpret_cast<u32x4 *>(c->view.tags);
   a.n_zeros[0] = c->slots / 2;
   const bool captured = is_capturing(s);
-  if (captured || c->rank_dirty) {
+  if (captured || c->rank_dirty || c->in_graph) {
     a.zeros[1] = reinterpret_cast<u32x4 *>(c->view.rank);
     a.n_zeros[1] = c->slots / 2;
   }
@@ -1480,7 +1482,7 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
                      0, s, a);
   if (!captured) {
     c->rank_dirty = false;
-    raise_to(c->top_epoch, c->epoch.exchange(0));
+    if (!c->in_graph) raise_to(c->top_epoch, c->epoch.exchange(0));
   }
   return launch_status();
 }
@@ -1517,6 +1519,11 @@ void note_tracked(kvgov_cache *c, int64_t n_blocks) {
 }
 
 }  // namespace
+
+uint32_t kvgov::next_epoch(kvgov_cache *c, hipStream_t s) {
+  if (is_capturing(s)) c->in_graph = true;
+  return c->epoch.fetch_add(1) + 1;
+}
 
 int kvgov::cache_clear_with(kvgov_cache *c, hipStream_t s, const ClearMore &more) {
   return enqueue_clear(c, s, more);
@@ -1626,7 +1633,7 @@ int maint_alloc(kvgov_cache *c, hipStream_t s, MaintScratch &m) {
 // table, and inserts the copies again; then reads the table's counters if
 // asked (waiting for the stream).
 int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, int erase, CacheMeta *meta) {
-  const uint32_t epoch = c->epoch.fetch_add(1) + 1;
+  const uint32_t epoch = next_epoch(c, s);
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
   const dim3 grid(region_grid(c->slots)), block(256);
   hipLaunchKernelGGL(k_compact, grid, block, 0, s, c->view, m.st, erase, m.keys, m.rank,
@@ -1788,7 +1795,7 @@ bool kvgov::cache_inserts_by_request(const kvgov_cache *c, int32_t n, int64_t n_
 
 int kvgov::cache_insert_rows(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_offsets,
                              int32_t n, int64_t n_blocks, hipStream_t s, uint32_t *epoch) {
-  *epoch = c->epoch.fetch_add(1) + 1;
+  *epoch = next_epoch(c, s);
   if (*epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;  // 2^32 - 1 inserts since clear
   if (c->view.track) note_tracked(c, n_blocks);
   int rc = KVGOV_OK;
@@ -1935,7 +1942,7 @@ int kvgov_cache_admit(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
                       lk);
   if (rc != KVGOV_OK) return rc;
   uint32_t *codes = static_cast<uint32_t *>(scratch_p);
-  const uint32_t epoch = c->epoch.fetch_add(1) + 1;
+  const uint32_t epoch = next_epoch(c, s);
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
   if (c->view.track) note_tracked(c, n_blocks);
   rc = insert_batch<true>(c->view, hashes, blk_offsets, n, n_blocks, epoch, codes, s);

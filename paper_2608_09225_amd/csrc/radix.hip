@@ -601,7 +601,7 @@ int kvgov_radix_insert(kvgov_radix *x, const int32_t *tokens, int64_t n_tokens,
   hipStream_t s = as_stream(stream);
   // roots, then the full blocks' digests, then the edges below them
   kvgov_cache *c = x->blocks;
-  const uint32_t epoch = c->epoch.fetch_add(1) + 1;
+  const uint32_t epoch = next_epoch(c, s);
   if (epoch == 0xFFFFFFFFu) return KVGOV_E_UNSUPPORTED;
   const uint8_t *roots = mode == KVGOV_ROOT ? salts : x->zero_root;
   const int64_t n_roots = mode == KVGOV_ROOT ? P : 1;

@@ -309,6 +309,10 @@ __device__ __forceinline__ int64_t find_slot(const TableView &t, const Key &key)
   return -1;
 }
 
+// The epoch of a call that is about to be enqueued on s (0xFFFFFFFF: there are no
+// more).
+uint32_t next_epoch(kvgov_cache *c, hipStream_t s);
+
 // Waits for the stream and reads the table's counters, with the radix index's
 // if asked (cache.hip).
 int cache_read_meta(kvgov_cache *c, CacheMeta *m, hipStream_t s, bool radix = false);
@@ -358,5 +362,8 @@ struct kvgov_cache {
   // insert keeps the stamp that it was captured with.)
   std::atomic<uint32_t> top_epoch{0};
   std::atomic<int64_t> max_rows{0};
+  // a call that stamps keys has been captured: its graph may run at any time,
+  // with the epoch of its capture, and write recency words
+  std::atomic<bool> in_graph{false};
 };
 

@@ -439,3 +439,49 @@ def test_evict_after_captured_clears():
         assert c.evict(60) == T.evict(60)
         assert key_set(c.export()) == T.keys
         side.synchronize()
+
+
+def test_clears_between_a_graphs_runs():
+    """A captured tracked insert that runs between other calls of its table: a
+    clear after it empties its keys' recency as well, and calls after a clear do
+    not get its epoch (their keys' tags would name its rows)."""
+    def rows_of(lens, at):
+        rows = np.zeros((sum(lens), 32), np.uint8)
+        ids = np.arange(at, at + rows.shape[0]).astype(np.uint64)
+        rows[:, :8] = (ids * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+        rows[:, 8] = 1
+        return rows, np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+
+    side = torch.cuda.Stream()
+    with KV.Cache(13) as c, torch.cuda.stream(side):
+        c.set_recency(True)
+        assert c.evict(0) == 0  # its scratch is there
+        for k in range(5):
+            c.insert(*map(dev, rows_of([3], 10 ** 6 + 10 * k)))
+        h, bo = rows_of([900, 400, 1], 0)
+        dh, dbo = dev(h), dev(bo)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            c.insert(dh, dbo, sync=False)
+        for run in range(3):
+            c.clear()
+            graph.replay()
+            c.clear()
+            T = O.Table()
+            for k in range(10):  # past the clock of the capture
+                batch = rows_of([150, 60], 20000 + 1000 * k)
+                assert c.insert(*map(dev, batch)) == T.insert(*batch)
+            graph.replay()
+            T.insert(h, bo)
+            assert c.count() == len(T.keys)
+            assert key_set(c.export()) == T.keys
+            c.clear()
+            T = O.Table()
+            for k in range(2):
+                batch = rows_of([500, 100], 40000 + 1000 * k)
+                c.insert(*map(dev, batch))
+                T.insert(*batch)
+            assert c.evict(700) == T.evict(700)
+            assert key_set(c.export()) == T.keys
+        side.synchronize()

@@ -22,6 +22,15 @@ static std::map<const void *, std::string> names;
 static std::string launched;
 static int capturing = 0;
 static size_t fail_bytes = 0;
+// the epochs that kernels are launched with
+static std::string epochs;
+static void note_epoch(const std::string &k, void **args) {
+  const char *by[] = {"k_insert_req", "k_chunk_insert", "k_reinsert", "k_radix_roots"};
+  const int at[] = {5, 5, 5, 3};
+  for (int i = 0; i < 4; ++i)
+    if (k.find(by[i]) != std::string::npos)
+      epochs += std::to_string(*(const uint32_t *)args[at[i]]) + " ";
+}
 extern "C" {
 void *__hipRegisterFatBinary(const void *) { static void *h; return &h; }
 void __hipRegisterFunction(void *, const void *host, char *, const char *name, unsigned, void *,
@@ -39,6 +48,7 @@ int hipLaunchKernel(const void *f, Dim, Dim, void **args, size_t, void *) {
   launched += names[f] + "\n";
   if (names[f].find("k_cache_fill") != std::string::npos && ((int64_t *)args[0])[8])
     launched += "k_recencyE\n";
+  note_epoch(names[f], args);
   return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipDeviceSynchronize() { return 0; }
@@ -57,6 +67,7 @@ int hipStreamIsCapturing(void *, int *s) { *s = capturing; return 0; }
 int hipStreamSynchronize(void *) { return 0; }
 int hipThreadExchangeStreamCaptureMode(int *) { return 0; }
 void test_capture(int on) { capturing = on; }
+const char *test_epochs() { static std::string s; s = epochs; epochs.clear(); return s.c_str(); }
 void test_fail_from(size_t bytes) { fail_bytes = bytes; }
 const char *test_launched() { static std::string s; s = launched; launched.clear(); return s.c_str(); }
 }
@@ -66,11 +77,14 @@ PRELUDE = """
 import ctypes, json, re
 hip = ctypes.CDLL({hip!r}, mode=ctypes.RTLD_GLOBAL)
 hip.test_launched.restype = ctypes.c_char_p
+hip.test_epochs.restype = ctypes.c_char_p
 lib = ctypes.CDLL({lib!r})
 i32, i64, vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
 fake = vp(0x1000)  # device memory: never touched here
 def launched():
     return re.findall(r"(k_\\w+?)(?:I[LN]|E)", hip.test_launched().decode())
+def epochs():
+    return [int(e) for e in hip.test_epochs().split()]
 def cache(log2_slots, track=1):
     h = vp()
     assert lib.kvgov_cache_create(i32(log2_slots), ctypes.byref(h)) == 0
@@ -155,6 +169,48 @@ print(json.dumps(out))
 """)
     assert got["unused"] == ["k_cache_fill"]
     assert got["used"] == got["captured"] == got["after"] == ["k_cache_fill", "k_recency"]
+
+
+@pytest.mark.parametrize("call", ["insert", "admit", "evict", "radix"])
+def test_clears_of_a_table_that_a_graph_stamps(run, call):
+    """Once a call that stamps keys has been captured its graph may run between
+    any two calls: every clear writes the recency words, and no later call of the
+    table gets the graph's epoch."""
+    got = run("""
+def radix_insert(x):
+    assert lib.kvgov_radix_insert(x, fake, i64(40), fake, i32(2), None, None, i32(0), i32(0),
+                                  fake, fake, i64(2), None) == 0
+def admit(h):
+    assert lib.kvgov_cache_admit(h, fake, fake, i32(3), i64(20), fake, fake, None, None) == 0
+call = {call!r}
+if call == "radix":
+    h = vp()
+    assert lib.kvgov_radix_create(i32(10), i32(10), ctypes.byref(h)) == 0
+    stamp, wipe = radix_insert, lambda h: lib.kvgov_radix_clear(h, None)
+else:
+    h, wipe = cache(16), lambda h: lib.kvgov_cache_clear(h, None)
+    stamp = {{"insert": lambda h: insert(h, 3, 20), "admit": admit, "evict": evict}}[call]
+stamp(h); wipe(h); launched(); hip.test_epochs()
+wipe(h)
+out = {{"before": launched()}}
+stamp(h); out["first"] = epochs()
+wipe(h); stamp(h); out["again"] = epochs()
+hip.test_capture(1)
+stamp(h); out["graph"] = epochs()
+hip.test_capture(0)
+out["clears"] = []
+for _ in range(3):
+    wipe(h); launched()
+    wipe(h); out["clears"].append(launched())
+    for _ in range(5):
+        stamp(h)
+out["later"] = epochs()
+print(json.dumps(out))
+""".format(call=call))
+    assert got["before"] == ["k_cache_fill"]
+    assert got["first"] == got["again"]  # a clear starts the clock again
+    assert got["clears"] == [["k_cache_fill", "k_recency"]] * 3
+    assert not set(got["graph"]) & set(got["later"])
 
 
 def test_radix_create_without_memory_for_chains(run):
