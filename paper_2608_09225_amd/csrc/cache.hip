@@ -292,7 +292,9 @@ constexpr int64_t kHeadRows = G < 16 ? 64 : 4 * G;
 // (46 for a second batch, whose prefix keys are of an earlier call: a tracked
 // first row gives such a key this call's tag, so that later requests find an
 // earlier one by it.  Untracked, reading the present keys costs less than the
-// renewals: 20 against 25 us for a batch that is all present.)
+// renewals: 20 against 25 us for a batch that is all present.  So it does for
+// requests of up to 8 rows: 20,000 requests of 8 rows, 3 of them one of 500 heads,
+// present, 29 us and with renewals 32, of 16 rows, 6 of them heads, 41 and 40.)
 //
 // Where the first key is new in this call, a chain's later keys are new as
 // well, or of this call: these rows go to the compare-and-swap without reading
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
           unsigned long long claim = 0;
           added += insert_key<ADMIT>(t, key, b0, lo, hashes, epoch, &code,
                                      TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim,
-                                     TRACK && !ADMIT);
+                                     TRACK && !ADMIT && b1 - b0 > 8);
           fresh = !TRACK && !repeats && claims_first(t.mask) && (uint32_t)(claim >> 32) == epoch;
           const int64_t c = lo + (int64_t)(claim & 0xFFFFFFFFull) - 1;
           if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0) {
