@@ -308,6 +308,43 @@ def test_admit_of_requests_longer_than_their_heads(n, longest, many, track):
                     assert key_set(c.export().cpu().numpy()) == T.keys
 
 
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("n,lens,heads", [(20000, [1, 2, 5, 6, 9, 10, 13], 9), (140000, [1, 5, 6], 40),
+                                          (600, [64, 65, 66, 128, 129, 130, 193], 3),
+                                          (9000, [65, 129, 130], 7)])
+def test_admit_rounds_in_turn(n, lens, heads, track):
+    """Requests whose rows fill their group's rounds, miss that by one or go past it
+    by one, in batches of few and of many groups (whose rounds go in turns, or
+    not): shared heads, and keys that come twice in one request, in different
+    rounds.  Admitted into an empty table and into one that holds some of the keys."""
+    g = np.random.default_rng(n + lens[-1])
+    with K.Cache(21) as c:
+        c.set_recency(track)
+        T = O.Table()
+        for call in range(2):
+            ls = g.choice(lens, n)
+            bo = np.concatenate([[0], np.cumsum(ls)]).astype(np.int64)
+            at = np.arange(bo[-1]) - np.repeat(bo[:-1], ls)
+            ids = np.repeat(g.integers(0, heads, n), ls) * 1000 + at
+            own = g.random(bo[-1]) < 0.15
+            ids[own] = 10 ** 6 + call + g.integers(0, 50000, own.sum())
+            twice = np.nonzero(ls > 1)[0][::3]
+            ids[bo[twice + 1] - 1] = ids[bo[twice]]
+            rows = np.zeros((len(ids), 32), np.uint8)
+            rows[:, :8] = (ids.astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+            rows[:, 8] = 1
+            hits, new, n_new = c.admit(dev(rows), dev(bo))
+            wh, wn = T.admit(rows, bo)
+            assert np.array_equal(hits.cpu().numpy(), wh)
+            assert np.array_equal(new.cpu().numpy(), wn)
+            assert n_new == int(wn.sum())
+            assert key_set(c.export().cpu().numpy()) == T.keys
+        if track:
+            for keep in (len(T.keys) * 2 // 3, 50, 1):
+                assert c.evict(keep) == T.evict(keep)
+                assert key_set(c.export().cpu().numpy()) == T.keys
+
+
 def test_more_threads_read_the_state_than_it_has_blocks():
     """Twelve threads, each on a stream of its own, wait for one table's state at
     the same time: the blocks of pinned memory serve eight, the others copy."""
