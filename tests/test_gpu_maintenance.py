@@ -485,3 +485,34 @@ def test_clears_between_a_graphs_runs():
             assert c.evict(700) == T.evict(700)
             assert key_set(c.export()) == T.keys
         side.synchronize()
+
+
+@pytest.mark.parametrize("log2_slots,load", [(4, 0.9), (9, 0.95), (10, 0.95), (11, 0.95), (16, 0.9),
+                                             (20, 0.8), (21, 0.8)])
+def test_erase_from_crowded_tables(log2_slots, load):
+    """Regions in which nearly every slot holds a key, in tables smaller and larger
+    than a region and on both sides of the size from which a lane reinserts
+    several keys: a few keys are erased, then most, and the exported keys and the
+    counts are those that remain."""
+    n = int((1 << log2_slots) * load)
+    ids = np.arange(n, dtype=np.uint64)
+    rows = np.zeros((n, 32), np.uint8)
+    rows[:, :8] = (ids * np.uint64(0x9E3779B97F4A7C15)).view(np.uint8).reshape(-1, 8)
+    rows[:, 8] = 1
+    rows[0] = 0xFF
+
+    def sorted_rows(a):
+        return np.sort(np.ascontiguousarray(a).view("V32").ravel().view("S32"))
+
+    keys = dev(rows)
+    with KV.Cache(log2_slots) as c:
+        c.insert(keys, dev(np.array([0, n // 3, n], np.int64)))
+        left = np.ones(n, bool)
+        for step in (41, 3, 2):
+            gone = np.arange(step // 2, n, step)
+            assert c.erase(keys[torch.from_numpy(gone).cuda()].contiguous()) == int(left[gone].sum())
+            left[gone] = False
+            assert c.count() == int(left.sum())
+            assert np.array_equal(sorted_rows(c.export().cpu().numpy()), sorted_rows(rows[left]))
+            hits = c.lookup(keys, dev(np.arange(n + 1, dtype=np.int64)))
+            assert np.array_equal(hits.cpu().numpy(), left.astype(np.int32))
