@@ -425,9 +425,8 @@ struct ChainArgs {
   // digest parents[r] (NULL: every chain starts at block 0)
   const int32_t *start;
   const uint8_t *parents;
-  // lane-pair workgroups from this one on are the second ones on their CUs
-  // (0: one per CU)
-  int32_t turn_from;
+  // workgroups from this one on are the second ones on their CUs (0: one per CU)
+  int32_t second_from;
 };
 
 // Per-request set-up shared by both chain kernels.  Returns false (after
@@ -518,9 +517,9 @@ __device__ __forceinline__ void pad96_tail(uint32_t w[16]) {
 // 262,144 chains of 32 blocks with uniform boundaries 2.24 ms, now 0.95, and
 // 0.83 with root salts.)
 template <int MODE>
-__device__ __forceinline__ void single_chain(const ChainArgs &a, int32_t i) {
+__device__ __forceinline__ void single_chain(const ChainArgs &a, int64_t i) {
   if (i >= a.n) return;
-  const int32_t r = a.order ? a.order[i] : i;
+  const int32_t r = a.order ? a.order[i] : (int32_t)i;
   ChainReq q;
   if (!chain_setup<MODE>(a, r, q) || q.nf == 0) return;
   const int64_t nf = q.nf;
@@ -1108,7 +1107,7 @@ __device__ __forceinline__ void lp_group(const ChainArgs &a, int32_t group, LpLd
   // that the first one's took, so that its waves 0 and 1 would meet a rounds
   // and a schedule wave; turned by three, its rounds waves meet the schedule
   // waves of the first (32,768 chains of 128 blocks: 0.633 -> 0.611 ms).
-  const int turn = a.turn_from > 0 && group >= a.turn_from ? 3 : 0;
+  const int turn = a.second_from > 0 && group >= a.second_from ? 3 : 0;
   const int wave = __builtin_amdgcn_readfirstlane((int)((threadIdx.x / kWave + turn) & 3));
   const bool sched_wave = wave >= 2;
   const bool odd = lane & 1;  // rounds: the A lane; schedule: the odd words' lane
@@ -1382,16 +1381,24 @@ __global__ __launch_bounds__(4 * kWave) void k_chains_lp(ChainArgs a) {
 // 206 us, 131,072 433 -> 382).  The s_nop puts the loops where they were before
 // this test came: their place within 32 bytes moves 65,536 lognormal prompts
 // by one per cent (5,050 or 5,100 us).
+//
+// Two workgroups share a CU, the second of them 256 (second_from) after the first.
+// These second ones take their places in reverse, so that the CU with the longest
+// first requests gets the shortest second ones; places past the batch's end have
+// nothing to do.  (131,072 chains of up to 80 blocks 587 -> 444 us, 250,000
+// lognormal ones 1,136 -> 1,075; with one workgroup per CU, the next one to whichever
+// CU was free, 511 and 1,074.)
 template <int MODE>
 __global__ __launch_bounds__(256) void k_chains_mixed(ChainArgs a, int32_t lp_groups) {
   __shared__ __align__(16) LpLds L;
   asm volatile("s_nop 0");
   if (*a.even) lp_groups = 0;
-  if ((int32_t)blockIdx.x < lp_groups)
-    lp_group<MODE>(a, blockIdx.x, L);
+  int32_t place = blockIdx.x;
+  if (place >= a.second_from && place < 2 * a.second_from) place = 3 * a.second_from - 1 - place;
+  if (place < lp_groups)
+    lp_group<MODE>(a, place, L);
   else
-    single_chain<MODE>(a, lp_groups * kWave + ((int32_t)blockIdx.x - lp_groups) * 256 +
-                              (int32_t)threadIdx.x);
+    single_chain<MODE>(a, (int64_t)lp_groups * kWave + (int64_t)(place - lp_groups) * 256 + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1716,7 +1723,7 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
     const size_t lds = lp_lds_reserve(slots);
     if (ev_start && hipEventRecord(ev_start, s) != hipSuccess) return KVGOV_E_HIP;
     const dim3 block(4 * kWave);
-    a.turn_from = slots == 2 ? device_cu_count() : 0;
+    a.second_from = slots == 2 ? device_cu_count() : 0;
     switch (mode) {
       case KVGOV_NONE: hipLaunchKernelGGL(k_chains_lp<KVGOV_NONE>, grid, block, lds, s, a); break;
       case KVGOV_ROOT: hipLaunchKernelGGL(k_chains_lp<KVGOV_ROOT>, grid, block, lds, s, a); break;
@@ -1745,7 +1752,10 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
     a.order = order_requests(blk_offsets, n, lp_groups * kWave, buf, status, s);
     a.even = buf + kOrderBuckets;
     const int64_t rest = std::max<int64_t>(0, (int64_t)n - (int64_t)lp_groups * kWave);
-    const dim3 grid((unsigned)(lp_groups + ceil_div(rest, 4 * kWave))), block(4 * kWave);
+    a.second_from = device_cu_count();
+    int64_t groups = lp_groups + ceil_div(rest, 4 * kWave);
+    if (groups > a.second_from) groups = std::max(groups, (int64_t)2 * a.second_from);
+    const dim3 grid((unsigned)groups), block(4 * kWave);
     // two workgroups per CU: a second wave on each SIMD issues while the first
     // waits (250,000 chains of 32 blocks 0.695 -> 0.635 ms; one per CU was the
     // rule while a one-lane wave beside a lane-pair one slowed its chain, which

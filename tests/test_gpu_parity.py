@@ -152,6 +152,20 @@ def test_chains_many_waves_and_ordering(mode):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("mode", [W.NONE, W.ROOT, W.BOUNDARY])
+@pytest.mark.parametrize("n_req", [32769, 59000, 90001, 131000, 140000, 200001])
+def test_chains_in_places_of_an_ordered_batch(n_req, mode):
+    """Ordered batches of fewer workgroups than CUs, of up to two per CU and of more:
+    each request's digests, in whatever place its workgroup came."""
+    g = np.random.default_rng(n_req + mode)
+    b = ragged(n_req, g.integers(0, 70, n_req), P=9)
+    Kb, ids = secret(3, 9)
+    got = gpu_chains(b, K.salts(Kb, dev(ids)), mode).cpu().numpy()
+    want = O.hash_chains_parallel(b.tokens, b.tok_offsets, b.principal, O.salts(Kb, ids), mode,
+                                  b.boundary_tok)
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("mode", [W.ROOT, W.BOUNDARY])
 def test_chains_long_with_scattered_boundaries(mode):
     """Long chains (94..200 blocks) whose boundaries fall on different blocks
