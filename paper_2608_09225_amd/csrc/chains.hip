@@ -1378,23 +1378,23 @@ __global__ __launch_bounds__(4 * kWave) void k_chains_lp(ChainArgs a) {
 // Where the rest's first request is as long as the longest, the lane pairs shorten
 // nothing that the batch waits for, and take CUs that the rest would fill:
 // then one lane per request for all of them (65,536 chains of 32 blocks 262 ->
-// 206 us, 131,072 433 -> 382).  The s_nop puts the loops where they were before
-// this test came: their place within 32 bytes moves 65,536 lognormal prompts
-// by one per cent (5,050 or 5,100 us).
+// 206 us, 131,072 433 -> 382).
 //
 // Two workgroups share a CU, the second of them 256 (second_from) after the first.
 // These second ones take their places in reverse, so that the CU with the longest
 // first requests gets the shortest second ones; places past the batch's end have
 // nothing to do.  (131,072 chains of up to 80 blocks 587 -> 444 us, 250,000
 // lognormal ones 1,136 -> 1,075; with one workgroup per CU, the next one to whichever
-// CU was free, 511 and 1,074.)
+// CU was free, 511 and 1,074.  Where the second ones are no more than the lane-pair
+// workgroups, whose waves go first, they stay beside these: 65,536 lognormal prompts
+// 5,120 us, in reverse 5,160.)
 template <int MODE>
 __global__ __launch_bounds__(256) void k_chains_mixed(ChainArgs a, int32_t lp_groups) {
   __shared__ __align__(16) LpLds L;
-  asm volatile("s_nop 0");
   if (*a.even) lp_groups = 0;
   int32_t place = blockIdx.x;
-  if (place >= a.second_from && place < 2 * a.second_from) place = 3 * a.second_from - 1 - place;
+  if (a.second_from > 0 && place >= a.second_from && place < 2 * a.second_from)
+    place = 3 * a.second_from - 1 - place;
   if (place < lp_groups)
     lp_group<MODE>(a, place, L);
   else
@@ -1752,9 +1752,12 @@ static int hash_chains_impl(const int32_t *tokens, int64_t n_tokens, const int64
     a.order = order_requests(blk_offsets, n, lp_groups * kWave, buf, status, s);
     a.even = buf + kOrderBuckets;
     const int64_t rest = std::max<int64_t>(0, (int64_t)n - (int64_t)lp_groups * kWave);
-    a.second_from = device_cu_count();
     int64_t groups = lp_groups + ceil_div(rest, 4 * kWave);
-    if (groups > a.second_from) groups = std::max(groups, (int64_t)2 * a.second_from);
+    const int32_t cus = device_cu_count();
+    if (groups > cus + lp_groups) {  // second ones beside more than the lane pairs
+      a.second_from = cus;
+      groups = std::max(groups, (int64_t)2 * cus);
+    }
     const dim3 grid((unsigned)groups), block(4 * kWave);
     // two workgroups per CU: a second wave on each SIMD issues while the first
     // waits (250,000 chains of 32 blocks 0.695 -> 0.635 ms; one per CU was the
