@@ -1258,7 +1258,7 @@ def run_workload(name: str, args, dev, K, torch):
             "longest_chain_blocks": int(cntX.max()),
             "parallelism_ceiling": min(1.0, waves / (CUS * SIMDS_PER_CU)),
             "parallelism_ceiling_note": "ceil(requests / 64) / 1024 SIMDs: waves at one lane "
-                                        "per request (the lane-pair kernel runs three waves "
+                                        "per request (the lane-pair kernel runs four waves "
                                         "per 64 requests)",
             "concurrent_modes_achieved": concurrent,
             "concurrent_modes_frac": concurrent / INT_PEAK_TOPS,

@@ -42,8 +42,14 @@
  *     (growth waits for that stream, then frees the old buffer) and held
  *     until the process ends.  A stream runs its work in order, so its
  *     buffer serves one call at a time and no memory passes between streams.
- *     The cache and radix calls that wait read the table's state through 2 KiB
- *     of pinned host memory, allocated by the first of them for the process.
+ *     The cache and radix calls that wait read the table's state through 17 KiB
+ *     of pinned host memory (room for eight of them at a time), allocated by the
+ *     first of them for the process.
+ *   - HIP graphs: calls that wait cannot be captured, nor can a call whose
+ *     stream's scratch has yet to grow.  A captured insert, admission, radix
+ *     insert, eviction or erasure keeps the clock's value at its capture for
+ *     every run: clear the table, in the graph or outside, before its graph runs
+ *     on it again.
  */
 #ifndef KVGOV_H
 #define KVGOV_H
@@ -350,11 +356,11 @@ int kvgov_cache_admit(kvgov_cache *c, const uint8_t *hashes, const int64_t *blk_
  * erase: removes exactly the given keys (device, uint8 [n_keys][32]; keys not
  * in T are ignored), tracking or not.
  *
- * Both rebuild the table from the keys they keep (no tombstones: lookups
- * keep reading one key per probe), in stream order.  n_kept / n_erased: host
+ * Both rebuild the table from the keys they keep (no tombstones: a lookup
+ * still ends at the first empty slot of a key's sequence), in stream order.  n_kept / n_erased: host
  * out or NULL; non-NULL waits for `stream`, stores the keys kept / the
  * distinct present keys erased, and returns any latched error.
- * Scratch: 40 * slots bytes + slots / 256 + 10 KiB of the stream's scratch
+ * Scratch: 40 * slots bytes + slots / 256 + 21 KiB of the stream's scratch
  * (see the notes at the top).  Errors: KVGOV_E_INVAL, KVGOV_E_NOMEM,
  * KVGOV_E_UNSUPPORTED (as above, or 2^32 - 1 calls since the last clear),
  * KVGOV_E_HIP, KVGOV_E_DEVICE.

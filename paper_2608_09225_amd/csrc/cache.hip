@@ -7,9 +7,9 @@
 //
 // Layout (HBM):
 //   keys [slots][32 B]  the stored keys; an empty slot holds 32 bytes 0xFF.
-//                       Lookups read only this array: a probe is one 32-byte
-//                       read, and a probe sequence runs through the four
-//                       slots of its 128-byte line before it leaves it.
+//                       Lookups read only this array, two slots (64 bytes of
+//                       one line) at a time, and a probe sequence runs through
+//                       the four slots of its 128-byte line before it leaves it.
 //   tags [slots] u64    0 = empty, else (epoch << 32) | (claimant + 1): the
 //                       insert call that claimed the slot and the index of the
 //                       claiming key within that call's input.
@@ -133,11 +133,16 @@ __device__ __forceinline__ int32_t find_request(const int64_t *bo, int32_t n, in
 }
 
 // Table sizes whose new keys are claimed without reading the tag first (see
-// k_insert_req), each in a batch of distinct keys that fills 0.4 of the table,
-// read first against claimed first: 2^17 slots 24.8 / 27.5 us, 2^18 30.0 /
-// 26.7, 2^20 57.1 / 51.2, 2^22 126 / 132, 2^23 336 / 302, 2^25 (with clear and
-// lookup) 2199 / 2156.  Past the home's bucket the tag is read again: where the
-// table is fuller, the next slots are mostly taken (0.65 of 2^20 slots: 171 us
+// k_insert_req): where that gains by more than the spread at loads of 0.4 and 0.65.
+// Batches of distinct keys that fill 0.4 of the table, read first / claimed first,
+// us (from 2^21 slots with keys before tags): 2^18 slots 38.9 / 34.5, 2^19 50.4 /
+// 45.2, 2^20 63.6 / 54.9, 2^21 80.9 / 78.3, 2^22 122 / 128, 2^23 338 / 308, 2^24
+// 614 / 573; that fill 0.65: 2^20 140 / 132, 2^21 179 / 185, 2^22 240 / 258, 2^23
+// 615 / 609.  Below 2^18 slots it gains by 2 to 3 us (2^17 37.7 / 34.3) and is
+// not used.  Batches whose keys are there claim nothing, but their walk is slower
+// with the claims' code in it: 2^20 40 / 41, 2^23 111 / 122, 2^24 236 / 257.  Past
+// the home's bucket (with keys first, past the home) the slot is read again: where
+// the table is fuller, the next slots are mostly taken (0.65 of 2^20 slots: 171 us
 // with, 196 without).
 __device__ __forceinline__ bool claims_first(uint64_t mask) {
   return mask >= (1ull << 23) - 1 || (mask >= (1ull << 18) - 1 && mask <= (1ull << 20) - 1);
@@ -331,7 +336,7 @@ constexpr int64_t kHeadRows = G < 16 ? 64 : 4 * G;
 // before this request's first (a first key claimed by a later request is
 // lowered, and that group compares with nothing).  (The chunked walk, which
 // admission took for every batch before it had the second comparison: 73 us for
-// 8192 requests of two paper-shaped batches; now 47.)  A group admits the first
+// 8192 requests of two paper-shaped batches; now 46.)  A group admits the first
 // kHeadRows of its request; the workgroups from `walkers` on take the batch in
 // chunks and admit the rows past them (admit_tails).  Without these a long
 // request was a chain of rounds of one wave while the chip idled: 4096 lognormal
@@ -533,7 +538,7 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
 // new keys into 2^25 slots take k_insert_req 1.47 ms.  Taken region by region
 // the tags are read once, in order, and claimed in LDS; what is moved instead
 // is one entry of 8 bytes per row, to its region's list and back, and one
-// random read of the row's key: 205 + 810 us, of which the 2.65 GB read and
+// random read of the row's key: 200 + 820 us, of which the 2.65 GB read and
 // 0.66 GB written by k_region_insert are 670 us at a copy's rate (the random
 // read fetches 128 bytes for each key's 32).
 //   k_region_clear    counters, lists and sets of this call
@@ -1759,12 +1764,13 @@ int insert_batch(const TableView &t, const uint8_t *hashes, const int64_t *blk_o
 namespace {
 
 // Whether a batch may go by regions (us for new keys, by regions / by requests):
-// 11.9 M rows into 2^25 slots 972 / 1044, 16.8 M 1272 / 1536, 23.7 M 1803 /
-// 2546; but 8.4 M into 2^25 735 / 738, 16.8 M into 2^26 1507 / 1574.  Where the
-// sample then finds the keys shared or present, the look and the kernels that
-// end at once cost 20 to 30 us (16.8 M present keys 570 instead of 540), which
-// is why smaller batches, whose gain is smaller, are left alone (8.4 M new keys
-// into 2^24 slots 645 / 728, shared ones 295 / 265).  A batch of more rows than
+// 11.9 M rows into 2^25 slots 991 / 1064, 16.8 M 1293 / 1570, 23.7 M 1793 / 2652;
+// but 8.4 M into 2^25 757 / 748, 16.8 M into 2^26 1529 / 1582.  Where the sample
+// then finds the keys shared or present, the look and the kernels that end at
+// once cost 30 to 45 us, 100 in a table that is 0.7 full (present keys: 16.8 M 617
+// instead of 573, 23.7 M 1263 instead of 1165; shared ones 16.8 M 555 instead of
+// 522), which is why smaller batches, whose gain is smaller, are left alone (8.4 M
+// new keys into 2^24 slots 670 / 758, shared ones 309 / 279).  A batch of more rows than
 // slots holds duplicates; the sample reads a line for each request, so
 // requests are to be 32 rows long.
 constexpr int64_t kRegionMinRows = (int64_t)10 << 20;

@@ -267,10 +267,10 @@ __device__ __forceinline__ uint32_t insert_key(const TableView &t, const Key &ke
   return 0;
 }
 
-// Is `key` in the table?  Reads the key array only, two slots at a time: the
-// second is in the first's line for three keys of four, and a key that is not
-// the first's, or absent, waits once less (lookups of 1 M short probes in 2^24
-// slots 426 -> 420 us; of 65536 requests in 2^25 slots 372 -> 365).
+// Is `key` in the table?  Reads the key array only, two slots at a time: both are
+// in one line (a step stays in its bucket), and a key that is not the first's, or
+// absent, waits once less (lookups of 1 M short probes in 2^24 slots 426 -> 420
+// us; of 65536 requests in 2^25 slots 372 -> 365).
 __device__ __forceinline__ bool probe(const TableView &t, const Key &key, bool ones_present) {
   if (key_is_empty_pattern(key)) return ones_present;
   const uint64_t home = home_slot(key, t.mask);
