@@ -1521,7 +1521,10 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
                      0, s, a);
   if (!captured) {
     c->rank_dirty = false;
-    if (!c->in_graph) raise_to(c->top_epoch, c->epoch.exchange(0));
+    if (!c->in_graph) {
+      c->epoch = 0;
+      c->max_rows = 0;
+    }
   }
   return launch_status();
 }
@@ -2025,7 +2028,7 @@ int kvgov_cache_evict(kvgov_cache *c, int64_t max_keys, int64_t *n_kept, void *s
   // depths up to the largest tracked batch (a pass after the last needed one
   // ends at once); a captured eviction runs on tables of any later calls
   const int bits = is_capturing(s) ? 64
-                                   : bit_length(std::max(c->epoch.load(), c->top_epoch.load())) +
+                                   : bit_length(c->epoch.load()) +
                                          bit_length((uint64_t)c->max_rows.load());
   const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(c->slots, kRankThreads * 8),
                                                    device_cu_count() * 2);

@@ -356,14 +356,12 @@ struct kvgov_cache {
   // recency words may be nonzero (set when a call that can write them is
   // enqueued; the next clear rewrites them)
   std::atomic<bool> rank_dirty{true};
-  // the largest epoch of a call before the last clear, and the largest row count
-  // of a tracked call: no recency word has a higher stamp than this or `epoch`,
-  // nor a depth above the row count.  (A clear does not lower them: a captured
-  // insert keeps the stamp that it was captured with.)
-  std::atomic<uint32_t> top_epoch{0};
+  // the largest row count of a tracked call since the last clear: no recency word
+  // has a depth above it, nor a stamp above `epoch`
   std::atomic<int64_t> max_rows{0};
   // a call that stamps keys has been captured: its graph may run at any time,
-  // with the epoch of its capture, and write recency words
+  // with the epoch of its capture, and write recency words, so that a clear
+  // lowers neither `epoch` nor max_rows any more
   std::atomic<bool> in_graph{false};
 };
 

@@ -134,14 +134,21 @@ for _ in range(4000):
     insert(h, 3, 20)
 insert(h, 3, 5000)
 out["filled"] = evict(h).count("k_rank_select")
-clear(h)  # a graph captured before may insert with the stamps of before
+clear(h)
+out["unused"] = evict(h).count("k_rank_select")
+for _ in range(4000):
+    insert(h, 3, 20)
+hip.test_capture(1)
+insert(h, 3, 5000)
+hip.test_capture(0)
+clear(h)  # the graph may insert with the stamp of its capture
 out["cleared"] = evict(h).count("k_rank_select")
 hip.test_capture(1)
 out["captured"] = evict(h).count("k_rank_select")
 print(json.dumps(out))
 """)
     need = passes((4001).bit_length() + (5000).bit_length())
-    assert got["empty"] == 1
+    assert got["empty"] == got["unused"] == 1
     assert got["filled"] == need
     assert got["cleared"] >= need
     assert got["captured"] == passes(64)
