@@ -1399,12 +1399,14 @@ __global__ __launch_bounds__(256) void k_compact(TableView t, SelectState *st, i
 
 // Inserts the kept keys again (all distinct) and restores their recency: a
 // workgroup per region.  Bound by chains of waits, the longest probe sequence of
-// each wave; in tables of up to kReinsertAtOnce slots a lane has one key at most
-// (1024 threads), in larger ones, which have regions enough to fill the chip, 256
-// threads go on to the region's next keys.  Erase of one key, a lane per key / 256
-// threads: 2^12 slots at load 0.8 90 / 140 us, 2^16 105 / 166, 2^20 240 / 322, at
-// load 0.3 55 / 55; 2^22 767 / 708, at 0.3 163 / 153.
-constexpr int64_t kReinsertAtOnce = 1 << 20;
+// each wave: in small tables a lane has one key at most, in large ones, which have
+// regions enough to fill the chip, fewer threads go on to the region's next keys.
+// Erase of one key with 256 / 512 / 1024 threads, us: 2^12 slots at load 0.8 140
+// / - / 86, 2^16 166 / - / 104, 2^20 326 / 257 / 239, 2^22 708 / - / 767; at load
+// 0.3 2^20 55 / 52 / 55, 2^22 153 / - / 163; at 0.02 2^20 26 / 26 / 28.
+static int reinsert_threads(int64_t slots) {
+  return slots <= 1 << 18 ? kRegion : slots <= 1 << 20 ? kRegion / 2 : kRegion / 4;
+}
 
 __global__ __launch_bounds__(kRegion) void k_reinsert(TableView t, const SelectState *st,
                                                       const uint8_t *keys,
@@ -1680,7 +1682,7 @@ int compact_rebuild(kvgov_cache *c, hipStream_t s, MaintScratch &m, int erase, C
   const dim3 grid(region_grid(c->slots)), block(256);
   hipLaunchKernelGGL(k_compact, grid, block, 0, s, c->view, m.st, erase, m.keys, m.rank,
                      m.regions);
-  hipLaunchKernelGGL(k_reinsert, grid, dim3(c->slots <= kReinsertAtOnce ? kRegion : 256), 0, s, c->view, m.st,
+  hipLaunchKernelGGL(k_reinsert, grid, dim3(reinsert_threads(c->slots)), 0, s, c->view, m.st,
                      reinterpret_cast<const uint8_t *>(m.keys), m.rank, m.regions, epoch);
   int rc = launch_status();
   m.lk.unlock();  // everything that uses the scratch is enqueued

@@ -487,12 +487,11 @@ def test_clears_between_a_graphs_runs():
         side.synchronize()
 
 
-@pytest.mark.parametrize("log2_slots,load", [(4, 0.9), (9, 0.95), (10, 0.95), (11, 0.95), (16, 0.9),
+@pytest.mark.parametrize("log2_slots,load", [(4, 0.9), (9, 0.95), (10, 0.95), (11, 0.95), (18, 0.9),
                                              (20, 0.8), (21, 0.8)])
 def test_erase_from_crowded_tables(log2_slots, load):
     """Regions in which nearly every slot holds a key, in tables smaller and larger
-    than a region and on both sides of the size from which a lane reinserts
-    several keys: a few keys are erased, then most, and the exported keys and the
+    than a region and of the sizes whose regions take 1024, 512 and 256 lanes: a few keys are erased, then most, and the exported keys and the
     counts are those that remain."""
     n = int((1 << log2_slots) * load)
     ids = np.arange(n, dtype=np.uint64)
