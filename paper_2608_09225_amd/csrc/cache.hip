@@ -1206,7 +1206,8 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_select(TableView t, Selec
   if (st->done) return;
   const int tid = threadIdx.x;
   const RankBits rb = rank_bits(parts, n_parts);
-  const int left = st->bits == kRankStart ? rb.cs + rb.cd : st->bits;
+  const bool first = st->bits == kRankStart;
+  const int left = first ? rb.cs + rb.cd : st->bits;
   const int width = left < kRankDigit ? left : kRankDigit;
   const int shift = left - width;
   const unsigned long long prefix = st->prefix, budget = st->budget;
@@ -1258,7 +1259,7 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_select(TableView t, Selec
   unsigned long long over = inc - c[0] - c[1];
   for (int i = 0; i < kRankThreads / 64; ++i) over += i > wid ? above[i] : 0ull;
   if (tid == 0) st->arrived = 0;
-  if (st->bits == kRankStart) {
+  if (first) {
     // first pass: everything fits, or everything but the words of 0
     unsigned long long keys = 0;
     for (int i = 0; i < kCounterLanes; ++i) keys += t.meta->n_keys[i];
@@ -1500,9 +1501,9 @@ bool is_capturing(hipStream_t s) {
 // an erasure): on a table that never tracks, a clear writes 40 of its 48
 // bytes per slot.  A captured clear empties nothing yet and runs on a table of
 // any later state: it writes the words as well, and the clock goes on (an insert
-// before its first run is not to meet its own epoch in an older tag).  So does
-// the clock of a table that captured calls stamp: the rows of a later call with the
-// same epoch would be taken for the graph's own.
+// before its first run is not to meet its own epoch in an older tag).  Of a table
+// that captured calls stamp, a clear sets the clock back to the last of these: the
+// rows of a later call with the same epoch would be taken for the graph's own.
 int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMore{}) {
   FillArgs a{};
   a.m = c->view.meta;
@@ -1511,7 +1512,7 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
   a.zeros[0] = reinterpret_cast<u32x4 *>(c->view.tags);
   a.n_zeros[0] = c->slots / 2;
   const bool captured = is_capturing(s);
-  if (captured || c->rank_dirty || c->in_graph) {
+  if (captured || c->rank_dirty || c->graph_epoch) {
     a.zeros[1] = reinterpret_cast<u32x4 *>(c->view.rank);
     a.n_zeros[1] = c->slots / 2;
   }
@@ -1523,10 +1524,8 @@ int enqueue_clear(kvgov_cache *c, hipStream_t s, const ClearMore &more = ClearMo
                      0, s, a);
   if (!captured) {
     c->rank_dirty = false;
-    if (!c->in_graph) {
-      c->epoch = 0;
-      c->max_rows = 0;
-    }
+    c->epoch = c->graph_epoch.load();
+    if (!c->graph_epoch) c->max_rows = 0;
   }
   return launch_status();
 }
@@ -1565,8 +1564,9 @@ void note_tracked(kvgov_cache *c, int64_t n_blocks) {
 }  // namespace
 
 uint32_t kvgov::next_epoch(kvgov_cache *c, hipStream_t s) {
-  if (is_capturing(s)) c->in_graph = true;
-  return c->epoch.fetch_add(1) + 1;
+  const uint32_t epoch = c->epoch.fetch_add(1) + 1;
+  if (is_capturing(s)) raise_to(c->graph_epoch, epoch);
+  return epoch;
 }
 
 int kvgov::cache_clear_with(kvgov_cache *c, hipStream_t s, const ClearMore &more) {

@@ -359,9 +359,9 @@ struct kvgov_cache {
   // the largest row count of a tracked call since the last clear: no recency word
   // has a depth above it, nor a stamp above `epoch`
   std::atomic<int64_t> max_rows{0};
-  // a call that stamps keys has been captured: its graph may run at any time,
-  // with the epoch of its capture, and write recency words, so that a clear
-  // lowers neither `epoch` nor max_rows any more
-  std::atomic<bool> in_graph{false};
+  // the largest epoch of a call that has been captured (0: none): its graph may
+  // run at any time, with the epoch of its capture, and write recency words, so
+  // that a clear sets `epoch` back no further and leaves max_rows
+  std::atomic<uint32_t> graph_epoch{0};
 };
 

@@ -181,8 +181,8 @@ print(json.dumps(out))
 @pytest.mark.parametrize("call", ["insert", "admit", "evict", "radix"])
 def test_clears_of_a_table_that_a_graph_stamps(run, call):
     """Once a call that stamps keys has been captured its graph may run between
-    any two calls: every clear writes the recency words, and no later call of the
-    table gets the graph's epoch."""
+    any two calls: every clear writes the recency words and sets the clock back, and
+    no later call of the table gets the graph's epoch."""
     got = run("""
 def radix_insert(x):
     assert lib.kvgov_radix_insert(x, fake, i64(40), fake, i32(2), None, None, i32(0), i32(0),
@@ -218,6 +218,7 @@ print(json.dumps(out))
     assert got["first"] == got["again"]  # a clear starts the clock again
     assert got["clears"] == [["k_cache_fill", "k_recency"]] * 3
     assert not set(got["graph"]) & set(got["later"])
+    assert len(set(got["later"])) == len(got["later"]) // 3  # and each clear starts it again
 
 
 def test_radix_create_without_memory_for_chains(run):
