@@ -77,7 +77,7 @@ def test_lds_accesses_are_waited_for_before_barriers(source):
 
 
 def test_late_barriers_are_found():
-    """The checker itself, on code written for it."""
+    """The walk itself, on code written for it."""
     wait, bar = "s_waitcnt lgkmcnt(0)", "s_barrier"
     assert late_barriers(["ds_write_b32 v0, v1", bar, "s_endpgm"]) == [1]
     assert late_barriers(["ds_write_b32 v0, v1", wait, bar, "s_endpgm"]) == []
