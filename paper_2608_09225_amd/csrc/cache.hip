@@ -117,7 +117,8 @@ __device__ __forceinline__ uint32_t row_depth(int64_t jj, int64_t n_blocks) {
 // waves in flight at once, so that the copies of a key that many requests
 // hold (a principal's shared prefix) reach its slot over a longer span and
 // most of them find it claimed by a plain read instead of racing for it
-// with compare-and-swaps on one address (measured: 256 beats 64, 128, 512).
+// with compare-and-swaps on one address (measured: 256 beats 64, 128, 512; an
+// admission of few rows takes shorter ones, see admit_chunk).
 constexpr int kInsChunk = 256;
 
 // The largest r in [0, n) with bo[r] <= f (bo non-decreasing in a valid
@@ -148,10 +149,11 @@ __device__ __forceinline__ bool claims_first(uint64_t mask) {
   return mask >= (1ull << 23) - 1 || (mask >= (1ull << 18) - 1 && mask <= (1ull << 20) - 1);
 }
 
-// Insert walking the batch in chunks of kInsChunk consecutive rows per wave,
-// 64 at a time: for batches whose requests are so long that a group per
+// Insert walking the batch in chunks of `chunk` (a multiple of 64) consecutive rows
+// per wave, 64 at a time: for batches whose requests are so long that a group per
 // request would leave the chip idle (a flat key set given as one request), in
-// the plain insert and as the admission's first half (ADMIT).  Before touching the
+// the plain insert and as the admission's first half (ADMIT), which takes it for
+// many short requests as well.  Before touching the
 // table a key is compared with the key at the same block position of the
 // previous request (requests that share a prefix - the same principal, or
 // any principal below the boundary block - hold the same keys there): an
@@ -174,7 +176,7 @@ template <bool ADMIT>
 __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t *hashes,
                                                       const int64_t *blk_offsets, int32_t n,
                                                       int64_t n_blocks, uint32_t epoch,
-                                                      uint32_t *codes) {
+                                                      uint32_t *codes, int chunk) {
   __shared__ uint32_t lds4[4];
   const int64_t lo = blk_offsets[0], hi = blk_offsets[n];
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
@@ -188,8 +190,8 @@ __global__ __launch_bounds__(256) void k_chunk_insert(TableView t, const uint8_t
   const int64_t waves = (int64_t)gridDim.x * 4;
   const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   uint32_t added = 0;
-  for (int64_t f0 = lo + wave * kInsChunk; f0 < hi; f0 += waves * kInsChunk) {
-    const int64_t f1 = f0 + kInsChunk < hi ? f0 + kInsChunk : hi;
+  for (int64_t f0 = lo + wave * chunk; f0 < hi; f0 += waves * chunk) {
+    const int64_t f1 = f0 + chunk < hi ? f0 + chunk : hi;
     int32_t rc = find_request(blk_offsets, n, f0);
     for (int64_t fb = f0; fb < f1; fb += 64) {
       // win[l] = start of request rc - 1 + l (clamped to [0, n])
@@ -1539,18 +1541,22 @@ constexpr int64_t kReqInsertMaxAvg = 4096;
 // Lanes per request of the insert: about one lane per two rows of the average
 // request, 4 to 64; in a batch small enough to be resident at once, a lane per
 // row (a group then takes one round after its first row: 64 requests of 16
-// rows 13.6 -> 9.8 us).
+// rows 13.6 -> 9.8 us).  An admission's groups take what lanes the chip has, for the
+// requests that are longer than the average (lognormal lengths of 6 rows on average:
+// 300 requests 44 -> 34 us, 20,000 91 -> 57; equal ones the same either way).
+template <bool ADMIT>
 int insert_group(int32_t n, int64_t n_blocks) {
   const int64_t avg = n > 0 ? n_blocks / n : 0;
   int g = 4;
   while (g < 64 && (int64_t)g * 2 < avg) g <<= 1;
   while (g < 64 && g < avg && (int64_t)n * g * 2 <= (1 << 16)) g <<= 1;
+  while (ADMIT && g < 64 && (int64_t)n * g * 2 <= (1 << 19)) g <<= 1;
   return g;
 }
 
-// k_chunk_insert: waves of 4 x kInsChunk keys, at most 16 workgroups per CU.
-unsigned insert_grid(int64_t n_blocks) {
-  const int64_t groups = ceil_div(std::max<int64_t>(n_blocks, 1), (int64_t)kInsChunk * 4);
+// k_chunk_insert: workgroups of 4 chunks, at most 16 per CU.
+unsigned insert_grid(int64_t n_blocks, int chunk) {
+  const int64_t groups = ceil_div(std::max<int64_t>(n_blocks, 1), (int64_t)chunk * 4);
   return (unsigned)std::min<int64_t>(groups, (int64_t)device_cu_count() * 16);
 }
 
@@ -1712,7 +1718,7 @@ void insert_req_group(const TableView &t, const uint8_t *hashes, const int64_t *
                       int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
                       const RegionState *st) {
   const unsigned groups = (unsigned)std::max<int64_t>(1, ceil_div((int64_t)n * G, 256));
-  const unsigned walkers = ADMIT && n_blocks > kHeadRows<G> ? insert_grid(n_blocks) : 0;
+  const unsigned walkers = ADMIT && n_blocks > kHeadRows<G> ? insert_grid(n_blocks, kInsChunk) : 0;
   hipLaunchKernelGGL((k_insert_req<G, ADMIT, TRACK, KEYS>), dim3(groups + walkers), dim3(256), 0, s,
                      t, hashes, blk_offsets, n, n_blocks, epoch, codes, groups, st);
 }
@@ -1722,7 +1728,7 @@ void insert_req_launch(const TableView &t, const uint8_t *hashes, const int64_t 
                        int32_t n, int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s,
                        const RegionState *st) {
   // (no request: only the batch check and the next call's counters)
-  switch (n > 0 ? insert_group(n, n_blocks) : 64) {
+  switch (n > 0 ? insert_group<ADMIT>(n, n_blocks) : 64) {
     case 4: insert_req_group<4, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
     case 8: insert_req_group<8, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
     case 16: insert_req_group<16, ADMIT, TRACK, KEYS>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s, st); break;
@@ -1749,14 +1755,37 @@ bool by_requests(int32_t n, int64_t n_blocks) {
   return n == 0 || n_blocks <= (int64_t)n * kReqInsertMaxAvg;
 }
 
-// The insert of a call: by requests, or, for few, long requests, where a group
-// per request would leave the chip idle, in chunks.  codes: ADMIT only.
+// Admissions of more and shorter requests than these go in chunks.  A group waits
+// for the rounds of its wave's longest request; few requests get lanes enough for
+// these (insert_group), of many most lanes would have no row.  Lognormal lengths, us
+// by requests / in chunks: 200,000 of 6 on average 164 / 127, of 12 328 / 305, 1 M
+// of 3 424 / 350, of 6 795 / 637; 2 M of one row, one in a hundred of 64, 756 / 491,
+// all there 641 / 297.
+// Equal ones are about the same either way (200,000 of 4 96 / 103, of 8 164 / 163,
+// 500,000 of one 31 / 47); longer ones can share heads that are not the previous
+// request's, which groups compare and chunks do not (200,000 of 16, half of them of
+// 64 heads, 235 / 278).
+constexpr int64_t kChunkAdmitAvg = 16;
+constexpr int32_t kChunkAdmitMin = 1 << 16;
+
+// Rows per wave of these: fewer rows than fill the chip take one or two rounds
+// (100,000 of one row 21 us, 32 in chunks of 256; 200,000 of 2 71 / 76), but half of
+// 3 M rows of 64 heads 290 / 277 (see kInsChunk).
+int admit_chunk(int64_t n_blocks) {
+  return n_blocks <= 1 << 18 ? kInsChunk / 4 : n_blocks <= 1 << 20 ? kInsChunk / 2 : kInsChunk;
+}
+
+// The insert of a call: by requests, or in chunks: few, long requests, where a group
+// per request would leave the chip idle, and an admission's many short ones.  codes:
+// ADMIT only.
 template <bool ADMIT>
 int insert_batch(const TableView &t, const uint8_t *hashes, const int64_t *blk_offsets, int32_t n,
                  int64_t n_blocks, uint32_t epoch, uint32_t *codes, hipStream_t s) {
-  if (!by_requests(n, n_blocks))
-    hipLaunchKernelGGL(k_chunk_insert<ADMIT>, dim3(insert_grid(n_blocks)), dim3(256), 0, s, t,
-                       hashes, blk_offsets, n, n_blocks, epoch, codes);
+  const bool many = ADMIT && n > kChunkAdmitMin && n_blocks < n * kChunkAdmitAvg;
+  const int chunk = many ? admit_chunk(n_blocks) : kInsChunk;
+  if (many || !by_requests(n, n_blocks))
+    hipLaunchKernelGGL(k_chunk_insert<ADMIT>, dim3(insert_grid(n_blocks, chunk)), dim3(256), 0, s,
+                       t, hashes, blk_offsets, n, n_blocks, epoch, codes, chunk);
   else if (t.track)
     insert_req<ADMIT, true>(t, hashes, blk_offsets, n, n_blocks, epoch, codes, s);
   else

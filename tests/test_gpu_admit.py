@@ -311,11 +311,14 @@ def test_admit_of_requests_longer_than_their_heads(n, longest, many, track):
 @pytest.mark.parametrize("track", [False, True])
 @pytest.mark.parametrize("n,lens,heads", [(20000, [1, 2, 5, 6, 9, 10, 13], 9), (140000, [1, 5, 6], 40),
                                           (600, [64, 65, 66, 128, 129, 130, 193], 3),
-                                          (9000, [65, 129, 130], 7)])
+                                          (9000, [65, 129, 130], 7), (65536, [1, 2, 5], 20),
+                                          (65537, [1, 2], 20), (65600, [0, 1, 64], 50),
+                                          (300000, [0, 3, 8], 300)])
 def test_admit_rounds_in_turn(n, lens, heads, track):
     """Requests whose rows fill their group's rounds, miss that by one or go past it
     by one, in batches of few and of many groups (whose rounds go in turns, or
-    not): shared heads, and keys that come twice in one request, in different
+    not), and of so many short requests that they go in chunks of 64, 128 and 256
+    rows: shared heads, and keys that come twice in one request, in different
     rounds.  Admitted into an empty table and into one that holds some of the keys."""
     g = np.random.default_rng(n + lens[-1])
     with K.Cache(21) as c:
