@@ -228,6 +228,23 @@ __device__ __forceinline__ void load_chain(const u32x4 *rec, uint32_t c[16]) {
   }
 }
 
+// How many of the first n tokens agree.  (Compared as they come: two blocks of 16
+// words held at once left five waves per SIMD of eight, and the walks along edges
+// that follow wait for memory.)
+__device__ __forceinline__ int same_tokens(const int32_t *p, const int32_t *q, int n) {
+  int l = 0;
+  for (; l + 4 <= n; l += 4) {
+    const u32x4 v = *reinterpret_cast<const u32x4 *>(p + l);
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(q + l);
+    if (v.x != w.x) return l;
+    if (v.y != w.y) return l + 1;
+    if (v.z != w.z) return l + 2;
+    if (v.w != w.w) return l + 3;
+  }
+  while (l < n && p[l] == q[l]) ++l;
+  return l;
+}
+
 // Inserts the token nodes of one (possibly partial) block below block node
 // `slot`: record j of request r, rem tokens of the request at tp.  Returns
 // the number of token nodes added.
@@ -235,8 +252,7 @@ __device__ __forceinline__ uint32_t insert_tokens(const RadixArgs &a, int64_t sl
                                                   int64_t j, const int32_t *tp, int64_t rem) {
   const EdgeView &e = a.e;
   const int steps = (int)(rem < kChainMax ? rem : kChainMax);
-  uint32_t tok[16], added = 0;
-  load_tokens(tp, rem, tok);
+  uint32_t added = 0;
   int l = 0;
   if (e.chain_tags && slot >= 0) {
     const unsigned long long mine =
@@ -248,36 +264,29 @@ __device__ __forceinline__ uint32_t insert_tokens(const RadixArgs &a, int64_t sl
     if (tag == 0 && __hip_atomic_compare_exchange_strong(&e.chain_tags[slot], &tag, mine,
                                                          __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT)) {
+      uint32_t tok[16];
+      load_tokens(tp, rem, tok);
       rec[0] = u32x4{(uint32_t)steps, tok[0], tok[1], tok[2]};
 #pragma unroll
       for (int q = 1; q < 4; ++q)
         rec[q] = u32x4{tok[4 * q - 1], tok[4 * q], tok[4 * q + 1], tok[4 * q + 2]};
       return (uint32_t)steps;
     }
-    uint32_t other[16];
+    // the chain's tokens: claimed in this call, those of the same block of that
+    // request (whose offsets the claimant found valid; a block that it does not
+    // have, which only digests that are not its tokens' give, is an empty chain)
+    const int32_t *chain = reinterpret_cast<const int32_t *>(rec) + 1;
+    int64_t count;
     if ((uint32_t)(tag >> 32) == a.blk_epoch) {
-      // claimed in this call: the same block of that request (whose offsets the
-      // claimant found valid; a block that it does not have, which only
-      // digests that are not its tokens' give, is an empty chain)
       const int64_t q = (int64_t)(tag & 0xFFFFFFFFull) - 1;
       const int64_t t0 = a.tok_offsets[q];
-      int64_t left = a.tok_offsets[q + 1] - t0 - 16 * j;
-      left = left < 0 ? 0 : left;
-      uint32_t ot[16];
-      load_tokens(a.tokens + t0 + 16 * j, left, ot);
-      other[0] = (uint32_t)(left < kChainMax ? left : kChainMax);
-#pragma unroll
-      for (int i = 0; i < kChainMax; ++i) other[1 + i] = ot[i];
+      count = a.tok_offsets[q + 1] - t0 - 16 * j;
+      chain = a.tokens + t0 + 16 * j;
     } else {
-      load_chain(rec, other);
+      count = chain[-1];
     }
-    const int both = steps < (int)other[0] ? steps : (int)other[0];
-    bool same = true;
-#pragma unroll
-    for (int i = 0; i < kChainMax; ++i) {
-      same = same && i < both && tok[i] == other[1 + i];
-      l += same ? 1 : 0;
-    }
+    const int both = count < steps ? (int)(count < 0 ? 0 : count) : steps;
+    l = same_tokens(tp, chain, both);
   }
   uint32_t node = node_id(e, slot) + (uint32_t)l;
   for (; l < steps && node != kNoNode; ++l) node = edge_insert(e, node, tp[l], &added);
