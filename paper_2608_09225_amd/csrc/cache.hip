@@ -302,9 +302,13 @@ constexpr int64_t kHeadRows = G < 16 ? 64 : 4 * G;
 // (46 for a second batch, whose prefix keys are of an earlier call: a tracked
 // first row gives such a key this call's tag, so that later requests find an
 // earlier one by it.  Untracked, reading the present keys costs less than the
-// renewals: 20 against 25 us for a batch that is all present.  So it does for
-// requests of up to 8 rows: 20,000 requests of 8 rows, 3 of them one of 500 heads,
-// present, 29 us and with renewals 32, of 16 rows, 6 of them heads, 41 and 40.)
+// renewals: 20 against 25 us for a batch that is all present.)  Short requests save
+// less by it than the search and the renewal cost, and their waves wait for those of
+// the longer ones: on a table that tracks recency it is left out for requests of up
+// to 8 rows and in batches of fewer than 16 on average (20,000 requests of 8 rows, 3
+// of them one of 500 heads, present, 29 us and with it 32, of 16 rows, 6 of them
+// heads, 41 and 40; 1 M lognormal ones of 3 on average, half of them 64 heads, 348
+// and 435, present 213 and 276).
 //
 // Where the first key is new in this call, a chain's later keys are new as
 // well, or of this call: these rows go to the compare-and-swap without reading
@@ -470,6 +474,8 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
       // first row, by the group's first lane
       int64_t g0 = -1, g1 = hi;  // the earlier request's rows
       int fresh = 0;             // the first key is new in this call
+      // the second comparison is made
+      const bool seek = !TRACK || (b1 - b0 > 8 && n_blocks >= (int64_t)n * 16);
       if (sub == 0) {
         const int64_t jj = b0 - b_r;
         const Key key = load_key(hashes + b0 * 32);
@@ -479,10 +485,11 @@ __global__ __launch_bounds__(256) void k_insert_req(TableView t, const uint8_t *
           unsigned long long claim = 0;
           added += insert_key<ADMIT>(t, key, b0, lo, hashes, epoch, &code,
                                      TRACK ? row_depth(jj, n_blocks) : kNoDepth, &claim,
-                                     TRACK && !ADMIT && b1 - b0 > 8);
+                                     TRACK && !ADMIT && seek);
           fresh = !TRACK && !repeats && claims_first(t.mask) && (uint32_t)(claim >> 32) == epoch;
           const int64_t c = lo + (int64_t)(claim & 0xFFFFFFFFull) - 1;
-          if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0) {
+          if (jj == 0 && (uint32_t)(claim >> 32) == epoch && c >= lo && c < b0 &&
+              seek) {
             g0 = c;
             if (TRACK) {
               const int32_t q = find_request(blk_offsets, n, c);
